@@ -1,9 +1,14 @@
-"""ctypes binding of include/fff.h.  Argument marshalling only.
+"""Binding of include/fff.h.  Argument marshalling only.
 
 The C ABI takes plain pointers plus (T, D, O, dtype) and cannot see the extents of the arrays
 behind them; this layer can, so it checks every tensor's shape and dtype against the
 Definition's sizes (2^depth - 1 node rows, 2^depth leaves of leaf_width neurons, D inputs,
-O outputs) on the host, before any pointer reaches the library."""
+O outputs) on the host, before any pointer reaches the library.
+
+The four forward entry points go through a native module first (csrc/fff_torch.cpp), which makes
+the same checks and the call in well under a microsecond; a call it does not recognise as ordinary
+comes back unmade (-1) and takes the checks below, which say what is wrong with it.  Everything
+else is ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -85,6 +90,21 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_native_module = None
+
+
+def _native():
+    """The native half of the binding (built with the library, loaded after it)."""
+    global _native_module
+    if _native_module is None:
+        lib()
+        if not os.path.exists(_build.TORCH_LIB):
+            _build.build_library(force=True)
+        from . import _fff_torch
+        _native_module = _fff_torch
+    return _native_module
+
+
 def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -160,7 +180,13 @@ def fff_forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, dept
                      out, leaf_idx=None, stream=None, static_scratch=False) -> None:
     """Forward_I for x [T, D] -> out [T, O] (and leaf_idx [T] int32 if given).  static_scratch=True
     calls fff_forward_hard_static, the variant that allocates nothing."""
+    rc = (_native_module or _native()).forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth,
+                                                    leaf_width, act, out, leaf_idx, stream, static_scratch)
+    if rc == 0:
+        return
     where = "fff_forward_hard_static" if static_scratch else "fff_forward_hard"
+    if rc > 0:
+        raise FffError(rc, where)
     T, D = _rows(where, "x", x)
     _, O = _rows(where, "out", out)
     if _in_range(depth, leaf_width):
@@ -230,7 +256,13 @@ def fff_leaf_forward(x, leaf_w1, leaf_b1, leaf_w2, leaf_b2, leaf_idx, depth, lea
 
 def fff_moe_top1_forward(x, gate_w, gate_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, log2_experts, leaf_width, act,
                          out, expert_idx=None, stream=None) -> None:
+    rc = (_native_module or _native()).moe_top1_forward(x, gate_w, gate_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2,
+                                                        log2_experts, leaf_width, act, out, expert_idx, stream)
+    if rc == 0:
+        return
     where = "fff_moe_top1_forward"
+    if rc > 0:
+        raise FffError(rc, where)
     T, D = _rows(where, "x", x)
     _, O = _rows(where, "out", out)
     if _in_range(log2_experts, leaf_width):
@@ -249,8 +281,14 @@ def fff_forward_soft(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, dept
                      mix=None, entropy=None, stream=None) -> None:
     """Forward_T: the soft mixture over all leaves.  mix [T, 2^depth] and entropy [2^depth - 1] are
     optional float32 device outputs."""
-    import torch
+    rc = (_native_module or _native()).forward_soft(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth,
+                                                    leaf_width, act, out, mix, entropy, stream)
+    if rc == 0:
+        return
     where = "fff_forward_soft"
+    if rc > 0:
+        raise FffError(rc, where)
+    import torch
     T, D = _rows(where, "x", x)
     _, O = _rows(where, "out", out)
     if _in_range(depth, leaf_width):
@@ -276,7 +314,14 @@ def fff_forward_block(x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, n
     """Forward_I with nodes of `node_size` hidden neurons as a pre-norm residual layer:
     out = FFF(LayerNorm(x)) (+ x when `residual`); ln_gamma = ln_beta = None skips the
     normalisation.  out may be x itself."""
+    rc = (_native_module or _native()).forward_block(x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2,
+                                                     leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, node_size, leaf_width,
+                                                     act, residual, out, leaf_idx, stream)
+    if rc == 0:
+        return
     where = "fff_forward_block"
+    if rc > 0:
+        raise FffError(rc, where)
     T, D = _rows(where, "x", x)
     _, O = _rows(where, "out", out)
     if _in_range(depth, leaf_width, node_size):

@@ -1,4 +1,5 @@
-"""Builds libfff_hip.so (the C-ABI library) and the bench-only probe library for gfx950 with hipcc, in-tree."""
+"""Builds libfff_hip.so (the C-ABI library), the native half of the torch binding and the bench-only probe
+library for gfx950 with hipcc, in-tree."""
 from __future__ import annotations
 
 import concurrent.futures
@@ -6,17 +7,20 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfff_hip.so")
+TORCH_LIB = os.path.join(HERE, "_fff_torch.so")             # the ordinary calls of binding.py (fff_torch.cpp)
 PROBE_LIB = os.path.join(HERE, "libfff_bench_probes.so")   # measuring sticks of bench.py, not the product
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["fff_api.hip", "fff_walk.hip", "fff_bucket.hip", "fff_leaf.hip", "fff_leaf_tiles.hip", "fff_leaf_slices.hip",
            "fff_token_block.hip", "fff_moe_gate.hip", "fff_soft.hip", "fff_block.hip"]
 PROBE_SOURCES = ["bench_probes.hip"]
+TORCH_SOURCE = "fff_torch.cpp"
 HEADERS = ["fff_device.h", "fff_internal.h", "fff_mfma_tile.h", os.path.join("..", "..", "include", "fff.h")]
 
 # packed fp32 VALU forms are switched off on purpose: some of them have given wrong results on
@@ -84,9 +88,27 @@ def packed_fp32_is_off() -> None:
     _flag_checked = True
 
 
+def _object(src: str) -> str:
+    return os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
+
+
+def _torch_dirs() -> tuple:
+    """(include directories, library directory) of the installed torch."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    return [inc, os.path.join(inc, "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]], os.path.join(root, "lib")
+
+
 def _compile(src: str) -> str:
-    obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
-    cmd = [_hipcc()] + HIPCC_FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+    obj = _object(src)
+    if src == TORCH_SOURCE:     # host code only
+        import torch
+        cmd = [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+               "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I/opt/rocm/include"] + \
+              [f for d in _torch_dirs()[0] for f in ("-isystem", d)] + ["-c", os.path.join(CSRC, src), "-o", obj]
+    else:
+        cmd = [_hipcc()] + HIPCC_FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if HOST_PASS_NOTE not in l)
     if r.returncode != 0:
@@ -97,17 +119,18 @@ def _compile(src: str) -> str:
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(PROBE_LIB):
+    libs = (LIB, PROBE_LIB, TORCH_LIB)
+    if not all(os.path.exists(f) for f in libs):
         return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(PROBE_LIB))
-    deps = [os.path.join(CSRC, s) for s in SOURCES + PROBE_SOURCES] + \
+    t = min(os.path.getmtime(f) for f in libs)
+    deps = [os.path.join(CSRC, s) for s in SOURCES + PROBE_SOURCES + [TORCH_SOURCE]] + \
            [os.path.normpath(os.path.join(CSRC, h)) for h in HEADERS]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
-def _link(objs, lib: str) -> None:
+def _link(objs, lib: str, flags=()) -> None:
     tmp = lib + ".tmp%d" % os.getpid()
-    r = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs,
+    r = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs + list(flags),
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
@@ -115,7 +138,7 @@ def _link(objs, lib: str) -> None:
 
 
 def _object_is_current(src: str) -> bool:
-    obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
+    obj = _object(src)
     if not os.path.exists(obj):
         return False
     t = os.path.getmtime(obj)
@@ -123,7 +146,7 @@ def _object_is_current(src: str) -> bool:
     return all(os.path.getmtime(d) <= t for d in deps)
 
 
-def build_library(force: bool = True, jobs: int = 4) -> str:
+def build_library(force: bool = True, jobs: int = 8) -> str:
     """Compile every kernel source for gfx950 and link the shared libraries.  force=False compiles
     only the sources that changed since their object file was made (or nothing, if the libraries
     are newer than every source)."""
@@ -131,12 +154,16 @@ def build_library(force: bool = True, jobs: int = 4) -> str:
         return LIB
     packed_fp32_is_off()
     os.makedirs(OBJ_DIR, exist_ok=True)
-    todo = [s for s in SOURCES + PROBE_SOURCES if force or not _object_is_current(s)]
+    todo = [s for s in [TORCH_SOURCE] + SOURCES + PROBE_SOURCES if force or not _object_is_current(s)]
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
         list(ex.map(_compile, todo))
-    objs = [os.path.join(OBJ_DIR, s.replace(".hip", ".o")) for s in SOURCES + PROBE_SOURCES]
-    _link(objs[:len(SOURCES)], LIB)
-    _link(objs[len(SOURCES):], PROBE_LIB)
+    _link([_object(s) for s in SOURCES], LIB)
+    _link([_object(s) for s in PROBE_SOURCES], PROBE_LIB)
+    # the torch libraries are found in the process (binding.py imports torch first), libfff_hip.so next to it
+    torch_lib = _torch_dirs()[1]
+    _link([_object(TORCH_SOURCE)], TORCH_LIB,
+          ["-L" + HERE, "-lfff_hip", "-L" + torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath,$ORIGIN"])
     return LIB
 
 

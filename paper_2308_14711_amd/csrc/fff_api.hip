@@ -3,8 +3,6 @@
 // (Algorithm 1): descent -> bucketing -> leaf networks with fused output rows.
 #include <hip/hip_runtime.h>
 
-#include <cstdarg>
-#include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -25,7 +23,11 @@ namespace fff {
 namespace {
 
 thread_local std::string g_last_error;
-std::string g_last_launch;   // kernels of the last forward call (process-wide, like the "last_*" options)
+// kernels of the last forward call (process-wide, like the "last_*" options), put into text by fff_last_launch
+constexpr int kMaxNotes = 8;
+LaunchNote g_notes[kMaxNotes];
+int g_n_notes = 0;
+std::string g_last_launch;
 
 // One workspace per device: the library's own block (grown on demand), or the caller's
 // (fff_set_workspace), which takes precedence while it is set.
@@ -116,7 +118,7 @@ Layout layout_for(int64_t T, int depth, int64_t extra_words = 0) {
 // launch checks below report this call's errors only.
 void begin_device_call() {
     g_last_error.clear();
-    g_last_launch.clear();
+    g_n_notes = 0;
     (void)hipGetLastError();
 }
 
@@ -533,14 +535,9 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
 
 }  // namespace
 
-void note_launch(const char* fmt, ...) {
-    char buf[256];
-    va_list ap;
-    va_start(ap, fmt);
-    std::vsnprintf(buf, sizeof buf, fmt, ap);
-    va_end(ap);
-    if (!g_last_launch.empty()) g_last_launch += " + ";
-    g_last_launch += buf;
+LaunchNote& next_launch_note() {
+    const int i = g_n_notes < kMaxNotes ? g_n_notes++ : kMaxNotes - 1;
+    return g_notes[i];
 }
 
 }  // namespace fff
@@ -922,7 +919,24 @@ const char* fff_status_string(int status) {
 
 const char* fff_last_device_error(void) { return g_last_error.c_str(); }
 
-const char* fff_last_launch(void) { return g_last_launch.c_str(); }
+const char* fff_last_launch(void) {
+    std::string text;
+    for (int i = 0; i < g_n_notes; ++i) {
+        if (i) text += " + ";
+        int arg = 0;
+        for (const char* c = g_notes[i].fmt; *c; ++c) {
+            if (c[0] != '%') {
+                text += *c;
+            } else if (*++c == 's') {
+                text += (const char*)g_notes[i].args[arg++];
+            } else {
+                text += std::to_string((long long)g_notes[i].args[arg++]);
+            }
+        }
+    }
+    g_last_launch.swap(text);
+    return g_last_launch.c_str();
+}
 
 int fff_version(void) { return 300; }
 

@@ -47,7 +47,19 @@ bool vec_ok(const void* p, int64_t row_elems, bool bf16);
 // Every launch function names the kernel it starts, with the tile parameters that select the
 // instantiation ("walk_kernel<bf16,16,6,4,512,fused,tight>"); a forward call's names, joined by
 // " + ", are what fff_last_launch returns.
-void note_launch(const char* fmt, ...) __attribute__((format(printf, 1, 2)));
+// The note is kept as it is handed over and put into text only when asked for (formatting it cost a
+// fifth of the host time of a small call): `fmt` and every %s argument must be string literals,
+// the others are printed with %d.
+struct LaunchNote {
+    static constexpr int kMaxArgs = 10;
+    const char* fmt;
+    intptr_t args[kMaxArgs];
+};
+LaunchNote& next_launch_note();
+template <class... A> inline void note_launch(const char* fmt, A... args) {
+    static_assert(sizeof...(A) <= LaunchNote::kMaxArgs, "");
+    next_launch_note() = LaunchNote{fmt, {(intptr_t)args...}};
+}
 
 // Per-block leaf counts, the hand-over from the descent to the bucketing stage: block b of the
 // descent owns tokens [b * share, (b + 1) * share) and leaves M[b][leaf] = how many of them reach
