@@ -647,20 +647,23 @@ int fff_moe_top1_forward(const void* x, const void* gate_w, const void* gate_b, 
     hipStream_t s = (hipStream_t)stream;
     Workspace ws;
     Layout lay;
-    if ((rc = get_workspace(T, log2_experts, &ws, &lay, s, 2 * T * moe_gate_blocks(G))) != FFF_OK) return rc;
+    if ((rc = get_workspace(T, log2_experts, &ws, &lay, s, moe_gate_words(T, G))) != FFF_OK) return rc;
     int32_t* ei = expert_idx ? expert_idx : ws.leaf_idx;
     stage_mark(s);
-    hipError_t e = launch_moe_gate(x, gate_w, gate_b, T, D, G, ws.extra, ei, s);
+    GateCandidates gate;
+    hipError_t e = launch_moe_gate(x, gate_w, gate_b, T, D, G, ws.extra, &gate, s);
     if (e != hipSuccess) return set_device_error(e, "gating kernel launch");
-    stage_mark(s);
     // the experts are leaves: small batches one block per token, larger ones bucketed
     if (g_opt.path != kPathStaged && token_shape_ok(p) && T <= 6 * g_opt.token_max_T) {
         g_opt.last_path = kPathToken;
-        e = launch_token_block(p, nullptr, s, ei);
+        stage_mark(s);
+        e = launch_token_block(p, expert_idx, s, nullptr, &gate);
         for (int k = 0; k < 3; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
     g_opt.last_path = kPathStaged;
+    if ((e = launch_moe_pick(gate, T, ei, s)) != hipSuccess) return set_device_error(e, "gating kernel launch");
+    stage_mark(s);
     return run_leaf_stage(p, ei, ws, s, true);
 }
 
@@ -733,7 +736,7 @@ size_t fff_workspace_bytes(int64_t T, int depth) {
 size_t fff_workspace_bytes_moe(int64_t T, int log2_experts) {
     if (T < 0 || T > kMaxTokens || log2_experts < 0 || log2_experts > FFF_MAX_DEPTH) return 0;
     const int64_t G = (int64_t)1 << log2_experts;
-    return (size_t)layout_for(T, log2_experts, 2 * T * moe_gate_blocks(G)).total * sizeof(int32_t);
+    return (size_t)layout_for(T, log2_experts, moe_gate_words(T, G)).total * sizeof(int32_t);
 }
 
 size_t fff_workspace_bytes_soft(int64_t T, int64_t O, int depth, int leaf_width) {
@@ -832,8 +835,8 @@ static int64_t* option_slot(const char* name) {
 //                    the fold kernel whenever the descent has left counts
 //   "fail_workspace_growth" n = the next n growths of the library's own workspace fail as if the device
 //                    were out of memory (FFF_ERR_WORKSPACE; the call after them allocates again)
-//   "soft_small_tiles" 1 = fff_forward_soft uses the 64 x 128 MFMA tile for every contraction (default:
-//                    the 128 x 256 tile where batch and width fill it)
+//   "soft_small_tiles" fff_forward_soft: 1 = the 64 x 128 MFMA tile for every contraction, 2 = the
+//                    small-batch kernels (slices of K) wherever they fit, 0 = by estimated time
 //   "walk_plain_x"   the descent reads token rows 1 = without the streaming hint, 2 = with it,
 //                    0 = without it while the batch fits half the last-level cache
 static int64_t* debug_slot(const char* name) {

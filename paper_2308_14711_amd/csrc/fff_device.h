@@ -147,4 +147,35 @@ __device__ __forceinline__ int64_t xcd_contiguous_block() {
 __device__ __forceinline__ int lds_rot(int row) { return ((row >> 1) & 1) + 4 * ((row >> 2) & 1); }
 __device__ __forceinline__ int tile_swz(int row, int piece) { return 8 * row + ((piece + lds_rot(row)) & 7); }
 
+// (v, i) <- the better of (v, i) and (v2, i2): larger value, then lower index
+__device__ __forceinline__ void better(float& v, int32_t& i, float v2, int32_t i2) {
+    const bool take = v2 > v || (v2 == v && i2 < i);
+    v = take ? v2 : v;
+    i = take ? i2 : i;
+}
+
+template <int N> __device__ __forceinline__ int32_t row_rotate_i(int32_t i) {
+    return __builtin_amdgcn_update_dpp(0, i, 0x120 + N, 0xf, 0xf, false);
+}
+
+template <int N> __device__ __forceinline__ void row_step(float& v, int32_t& i) {
+    const float v2 = row_rotate<N>(v);
+    const int32_t i2 = __builtin_amdgcn_update_dpp(0, i, 0x120 + N, 0xf, 0xf, false);
+    better(v, i, v2, i2);
+}
+
+// Index of the best of n candidates, found by a whole wave (lanes stride over them).
+__device__ __forceinline__ int32_t best_candidate(const float* __restrict__ val, const int32_t* __restrict__ idx, int n) {
+    float v = -__builtin_inff();
+    int32_t i = 0x7fffffff;
+    for (int b = threadIdx.x & (kWave - 1); b < n; b += kWave) better(v, i, val[b], idx[b]);
+    row_step<8>(v, i);
+    row_step<4>(v, i);
+    row_step<2>(v, i);
+    row_step<1>(v, i);
+#pragma unroll
+    for (int d = 16; d < kWave; d <<= 1) better(v, i, __shfl_xor(v, d, kWave), __shfl_xor(i, d, kWave));
+    return i;
+}
+
 }  // namespace fff

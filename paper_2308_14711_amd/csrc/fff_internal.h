@@ -160,18 +160,28 @@ hipError_t launch_leaf_tiles(const Problem& p, const int32_t* slot_leaf, const i
 // latency of the dependent loads rather than for throughput; needs token_shape_ok(p).
 constexpr size_t kTokenMaxLds = 144 * 1024;
 constexpr int64_t kTokenMaxBlocks = 8192;
-// given_leaf (optional): the leaf of every token; then only the leaf networks run (the node
-// weights are not read, token_shape_ok's condition on them does not apply).
+// given_leaf (optional): the leaf of every token, or gate: the candidates to pick it from (the pick goes to
+// leaf_idx); then only the leaf networks run (the node weights are not read, token_shape_ok's
+// condition on them does not apply).
+struct GateCandidates;
 bool token_shape_ok(const Problem& p);
 hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s,
-                              const int32_t* given_leaf = nullptr);
+                              const int32_t* given_leaf = nullptr, const GateCandidates* gate = nullptr);
 
-// Gating of a mixture of experts with one engaged expert (fff_moe_gate.hip): expert_idx[t] =
-// argmax_e gate_w[e] . x[t] (+ gate_b[e]).  cand: scratch of 2 * T * moe_gate_blocks(n_experts) words.
-int64_t moe_gate_blocks(int64_t n_experts);
+// Gating of a mixture of experts with one engaged expert (fff_moe_gate.hip).  launch_moe_gate leaves, per
+// token, the best (logit, expert) of every block of experts in `cand` (moe_gate_words(T, n_experts)
+// words); the token-block launch picks among them itself, launch_moe_pick writes expert_idx[t] =
+// argmax_e gate_w[e] . x[t] (+ gate_b[e]) for the other routes.
+struct GateCandidates {
+    const float* val = nullptr;      // [T][n]
+    const int32_t* idx = nullptr;
+    int n = 0;
+};
+int64_t moe_gate_words(int64_t T, int64_t n_experts);
 bool moe_gate_shape_ok(const void* x, const void* gate_w, int64_t D, bool bf16);
 hipError_t launch_moe_gate(const void* x, const void* gate_w, const void* gate_b, int64_t T, int64_t D,
-                           int64_t n_experts, int32_t* cand, int32_t* expert_idx, hipStream_t s);
+                           int64_t n_experts, int32_t* cand, GateCandidates* out, hipStream_t s);
+hipError_t launch_moe_pick(const GateCandidates& c, int64_t T, int32_t* expert_idx, hipStream_t s);
 
 // Forward_T (fff_soft.hip): the soft mixture over all leaves on the matrix cores.  scratch holds
 // soft_scratch_words(p) 32-bit words; mix [T, 2^depth] and entropy [2^depth - 1] (fp32) are optional outputs.
@@ -199,5 +209,22 @@ hipError_t launch_forward_block(const Problem& p, const void* gamma, const void*
 
 // Whole forward pass in one launch, one token per lane group (any shape).
 hipError_t launch_fused_generic(const Problem& p, int32_t* leaf_idx, hipStream_t s);
+
+// Contractions [T, K] x [K, N]: blocks of 16 mt x 16 nt results, and estimates of the time in us with a
+// block's waves on slices of K (mfma_wave_slice) and with 64 x 128 tiles, fitted to kernel times over
+// T = 64 .. 8192, N = 15 .. 2048, K = 80 .. 3504 (within about 25 %).  own: the soft pass's hidden
+// launch that multiplies its own mixture weights.
+inline int64_t small_blocks(int64_t T, int64_t N, int mt, int nt) {
+    return ((T + 16 * mt - 1) / (16 * mt)) * ((N + 16 * nt - 1) / (16 * nt));
+}
+inline double small_cost(double T, double N, double K, bool own = false) {
+    return 4 + T / 32 * N / 64 * (0.0076 + (own ? 0.005 : 0) + 1.9e-5 * K);
+}
+inline double tile_cost(int64_t T, int64_t N, double K) {
+    const double blocks = (double)((T + 63) / 64 * ((N + 127) / 128));
+    return 10.5 + 0.0067 * K + (blocks > 256 ? (blocks - 256) * (2e-3 + 2.8e-5 * K) : 0);
+}
+// Grids that cover three quarters of the 256 compute units keep the larger of the small tiles.
+constexpr int64_t kSmallEnoughBlocks = 192;
 
 }  // namespace fff

@@ -343,4 +343,71 @@ __device__ __forceinline__ void big_tile_store_bf16(BigTileLds& lds, const f32x4
     big_tile_flush(lds, C, ldc, M, N, m0, n0);
 }
 
+// ---- contractions too small for tiles: a wave per slice of K --------------------------------------
+//
+// A batch of a few hundred tokens is a few dozen of the tiles above, and a tile is one block's chain
+// of K / 64 memory round trips (64 tokens of 3504 features: 55 of them, 20 us a contraction with
+// most of the chip idle).  Here the waves of a block split K instead: each takes its slice's operands
+// straight from memory in the instruction's own layout (lane (j, kg) holds piece kg of row j: four
+// lanes on 64 consecutive bytes), kUnroll steps of 32 requested together, and the waves' partial
+// tiles meet in LDS.  A slice of 96 (K = 768 over eight waves) is a single round trip.
+//
+// acc[mt][nt] of lane (j, kg): row 16 mt + j of A against the four consecutive rows 16 nt + 4 kg + q
+// of B (the B rows are the instruction's first operand).  Rows are clamped to the last one (the
+// caller drops their results); pieces past the slice's end count as zeros on both sides.
+template <int MT, int NT, int kUnroll>
+__device__ __forceinline__ void mfma_wave_slice(const uint16_t* __restrict__ A, int64_t lda, int64_t M, int64_t m0,
+                                                const uint16_t* __restrict__ B, int64_t ldb, int64_t N, int64_t n0,
+                                                int k_begin, int k_end, f32x4_t (&acc)[MT][NT]) {
+    const int lane = threadIdx.x & 63, j = lane & 15, kg = lane >> 4;
+    const uint16_t *pa[MT], *pb[NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int64_t r = m0 + 16 * mt + j;
+        pa[mt] = A + (r < M ? r : M - 1) * lda;
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int64_t r = n0 + 16 * nt + j;
+        pb[nt] = B + (r < N ? r : N - 1) * ldb;
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = k_begin; k0 < k_end; k0 += 32 * kUnroll) {
+        uint4 qa[kUnroll][MT], qb[kUnroll][NT];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int k = k0 + 32 * u + 8 * kg, kc = k < k_end ? k : k_begin;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) qa[u][mt] = *(const uint4*)(pa[mt] + kc);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) qb[u][nt] = *(const uint4*)(pb[nt] + kc);
+        }
+        __builtin_amdgcn_sched_barrier(0);          // every load is requested before the first is waited for
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const bool in = k0 + 32 * u + 8 * kg < k_end;
+            bf16x8_t fa[MT], fb[NT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) fa[mt] = __builtin_bit_cast(bf16x8_t, keep_if(in, qa[u][mt]));
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) fb[nt] = __builtin_bit_cast(bf16x8_t, keep_if(in, qb[u][nt]));
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[nt], fa[mt], acc[mt][nt], 0, 0, 0);
+        }
+    }
+}
+
+// Slice s of K cut into n slices of whole steps of 32.
+__device__ __forceinline__ void k_slice(int K, int n, int s, int* begin, int* end) {
+    const int per = ((K + 31) / 32 + n - 1) / n * 32;
+    *begin = s * per < K ? s * per : K;
+    *end = (s + 1) * per < K ? (s + 1) * per : K;
+}
+
 }  // namespace fff

@@ -11,7 +11,9 @@
 // holds 4 x 2 accumulator tiles of v_mfma_f32_16x16x32_bf16.  The logits never reach memory: a
 // wave reduces its 32 experts per token with DPP row steps, the waves meet in LDS, and the block
 // writes one (value, index) candidate per token; a second small kernel picks the best candidate
-// per token over the expert blocks.  The token tiles of one expert block run back to back on one
+// per token over the expert blocks (where the experts run one block per token, that launch picks by
+// itself).  A batch of few such tiles goes to moe_gate_small_kernel instead, whose waves split K.
+// The token tiles of one expert block run back to back on one
 // XCD, so the gating matrix streams from HBM once while the (small) token rows stay cached.
 #include "fff_device.h"
 #include "fff_internal.h"
@@ -33,23 +35,6 @@ struct GateArgs {
     int D, n_eblocks;
     int64_t n_ttiles;
 };
-
-// (v, i) <- the better of (v, i) and (v2, i2): larger value, then lower index
-__device__ __forceinline__ void better(float& v, int32_t& i, float v2, int32_t i2) {
-    const bool take = v2 > v || (v2 == v && i2 < i);
-    v = take ? v2 : v;
-    i = take ? i2 : i;
-}
-
-template <int N> __device__ __forceinline__ int32_t row_rotate_i(int32_t i) {
-    return __builtin_amdgcn_update_dpp(0, i, 0x120 + N, 0xf, 0xf, false);
-}
-
-template <int N> __device__ __forceinline__ void row_step(float& v, int32_t& i) {
-    const float v2 = row_rotate<N>(v);
-    const int32_t i2 = __builtin_amdgcn_update_dpp(0, i, 0x120 + N, 0xf, 0xf, false);
-    better(v, i, v2, i2);
-}
 
 __global__ __launch_bounds__(256) void moe_gate_kernel(const GateArgs a) {
     __shared__ TileLds tile;
@@ -120,6 +105,57 @@ __global__ __launch_bounds__(256) void moe_gate_kernel(const GateArgs a) {
     }
 }
 
+// Few tiles (256 tokens against 2048 experts are 64 of them: 11.9 us, a chain of 12 steps on a quarter
+// of the chip): 16 MT x 16 NT logits a block, eight slices of K, one memory round trip for 768-wide rows.
+template <int MT, int NT>
+__global__ __launch_bounds__(512) void moe_gate_small_kernel(const GateArgs a) {
+    __shared__ f32x4_t part[8][MT * NT][kWave];
+    __shared__ float part_v[MT * NT][16];
+    __shared__ int32_t part_i[MT * NT][16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int eb = blockIdx.x % a.n_eblocks;
+    const int64_t t0 = (int64_t)(blockIdx.x / a.n_eblocks) * (16 * MT), e0 = (int64_t)eb * (16 * NT);
+    int k_begin, k_end;
+    k_slice(a.D, 8, wv, &k_begin, &k_end);
+    f32x4_t acc[MT][NT];
+    mfma_wave_slice<MT, NT, MT * NT == 8 ? 3 : 6>(a.x, a.D, a.T, t0, a.gate_w, a.D, a.G, e0, k_begin, k_end, acc);
+#pragma unroll
+    for (int i = 0; i < MT * NT; ++i) part[wv][i][lane] = acc[i / NT][i % NT];
+    __syncthreads();
+    const float ninf = -__builtin_inff();
+    if (wv < MT * NT) {
+        f32x4_t g = part[0][wv][lane];
+#pragma unroll
+        for (int s = 1; s < 8; ++s) g += part[s][wv][lane];
+        float v = ninf;
+        int32_t i = 0x7fffffff;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t e = e0 + 16 * (wv % NT) + 4 * (lane >> 4) + q;
+            if (e >= a.G) continue;
+            const float l = g[q] + (a.gate_b ? bf16_to_f32(a.gate_b[e]) : 0.0f);
+            better(v, i, l != l ? ninf : l, (int32_t)e);           // a NaN logit never wins
+        }
+        better(v, i, __shfl_xor(v, 16, kWave), __shfl_xor(i, 16, kWave));
+        better(v, i, __shfl_xor(v, 32, kWave), __shfl_xor(i, 32, kWave));
+        if (lane < 16) {
+            part_v[wv][lane] = v;
+            part_i[wv][lane] = i;
+        }
+    }
+    __syncthreads();
+    const int64_t t = t0 + tid;
+    if (tid < 16 * MT && t < a.T) {
+        const int first = tid / 16 * NT, j = tid & 15;
+        float v = part_v[first][j];
+        int32_t i = part_i[first][j];
+#pragma unroll
+        for (int nt = 1; nt < NT; ++nt) better(v, i, part_v[first + nt][j], part_i[first + nt][j]);
+        a.cand_val[t * a.n_eblocks + eb] = v;
+        a.cand_idx[t * a.n_eblocks + eb] = i;
+    }
+}
+
 // one wave per token: the best candidate over the expert blocks (lanes stride over the blocks)
 __global__ __launch_bounds__(256) void moe_pick_kernel(const float* __restrict__ cand_val,
                                                        const int32_t* __restrict__ cand_idx, int64_t T,
@@ -127,49 +163,70 @@ __global__ __launch_bounds__(256) void moe_pick_kernel(const float* __restrict__
     const int lane = threadIdx.x & 63;
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
-    float v = -__builtin_inff();
-    int32_t i = 0x7fffffff;
-    for (int b = lane; b < n_eblocks; b += kWave) better(v, i, cand_val[t * n_eblocks + b], cand_idx[t * n_eblocks + b]);
-    row_step<8>(v, i);
-    row_step<4>(v, i);
-    row_step<2>(v, i);
-    row_step<1>(v, i);
-#pragma unroll
-    for (int d = 16; d < kWave; d <<= 1) better(v, i, __shfl_xor(v, d, kWave), __shfl_xor(i, d, kWave));
+    const int32_t i = best_candidate(cand_val + t * n_eblocks, cand_idx + t * n_eblocks, n_eblocks);
     if (lane == 0) expert_idx[t] = i;
 }
 
 }  // namespace
 
-int64_t moe_gate_blocks(int64_t n_experts) { return (n_experts + kGateExperts - 1) / kGateExperts; }
+// Columns (experts) of a block: the 64 x 128 tile once a few hundred of them are there, else the largest
+// small tile whose grid covers the chip.  (The crossover lies where the small tiles' time, 27 ns a block for 768-wide
+// rows, passes the chain of 12 chunk steps of the large one.)
+constexpr int64_t kGateSmallMaxBlocks = 448;
+static int gate_columns(int64_t T, int64_t G) {
+    if (small_blocks(T, G, 2, 4) > kGateSmallMaxBlocks) return kGateExperts;
+    if (small_blocks(T, G, 2, 4) >= kSmallEnoughBlocks) return 64;
+    return small_blocks(T, G, 1, 2) >= kSmallEnoughBlocks ? 32 : 16;
+}
+static int64_t gate_blocks(int64_t T, int64_t G) {
+    const int64_t c = gate_columns(T, G);
+    return (G + c - 1) / c;
+}
+// The small tiles' candidates (at most 448 blocks of 32 x 64: 32 * 448 pairs) fit a constant, so that the
+// words never shrink as T grows: a workspace reserved for a batch serves every smaller one.
+int64_t moe_gate_words(int64_t T, int64_t n_experts) {
+    const int64_t large = 2 * T * ((n_experts + kGateExperts - 1) / kGateExperts);
+    return large > 2 * 32 * kGateSmallMaxBlocks ? large : 2 * 32 * kGateSmallMaxBlocks;
+}
 
 // bf16, D a multiple of 8, rows 16-byte aligned
 bool moe_gate_shape_ok(const void* x, const void* gate_w, int64_t D, bool bf16) {
     return bf16 && vec_ok(x, D, true) && vec_ok(gate_w, D, true) && D < ((int64_t)1 << 30);
 }
 
-// cand: scratch of 2 * T * moe_gate_blocks(G) 32-bit words
 hipError_t launch_moe_gate(const void* x, const void* gate_w, const void* gate_b, int64_t T, int64_t D,
-                           int64_t n_experts, int32_t* cand, int32_t* expert_idx, hipStream_t s) {
+                           int64_t n_experts, int32_t* cand, GateCandidates* out, hipStream_t s) {
     if (T == 0) return hipSuccess;
     GateArgs a;
     a.x = (const uint16_t*)x;
     a.gate_w = (const uint16_t*)gate_w;
     a.gate_b = (const uint16_t*)gate_b;
-    a.n_eblocks = (int)moe_gate_blocks(n_experts);
+    a.n_eblocks = (int)gate_blocks(T, n_experts);
     a.cand_val = (float*)cand;
     a.cand_idx = cand + T * a.n_eblocks;
     a.T = T;
     a.G = n_experts;
     a.D = (int)D;
     a.n_ttiles = (T + kGateTokens - 1) / kGateTokens;
-    const int64_t blocks = (a.n_ttiles * a.n_eblocks + kXcds - 1) / kXcds * kXcds;
-    note_launch("moe_gate_kernel + moe_pick_kernel");
-    moe_gate_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    moe_pick_kernel<<<dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s>>>(a.cand_val, a.cand_idx, T, a.n_eblocks,
-                                                                           expert_idx);
+    *out = GateCandidates{a.cand_val, a.cand_idx, a.n_eblocks};
+    const int columns = gate_columns(T, n_experts);
+    if (columns == kGateExperts) {
+        const int64_t blocks = (a.n_ttiles * a.n_eblocks + kXcds - 1) / kXcds * kXcds;
+        note_launch("moe_gate_kernel");
+        moe_gate_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(a);
+    } else {
+        note_launch("moe_gate_small_kernel<%d>", columns);
+        const dim3 grid((unsigned)(small_blocks(T, n_experts, columns == 64 ? 2 : 1, columns / 16)));
+        if (columns == 64) moe_gate_small_kernel<2, 4><<<grid, dim3(512), 0, s>>>(a);
+        else if (columns == 32) moe_gate_small_kernel<1, 2><<<grid, dim3(512), 0, s>>>(a);
+        else moe_gate_small_kernel<1, 1><<<grid, dim3(512), 0, s>>>(a);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_moe_pick(const GateCandidates& c, int64_t T, int32_t* expert_idx, hipStream_t s) {
+    note_launch("moe_pick_kernel");
+    moe_pick_kernel<<<dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s>>>(c.val, c.idx, T, c.n, expert_idx);
     return hipGetLastError();
 }
 

@@ -18,7 +18,7 @@
 #include "fff_mfma_tile.h"
 
 namespace fff {
-int64_t g_soft_small_tiles = 0;     // experiment switch: 1 = the 64 x 128 tile for every contraction
+int64_t g_soft_small_tiles = 0;     // experiment switch: 1 = the 64 x 128 tile for every contraction, 2 = the small-batch kernels
 namespace {
 
 struct SoftArgs {
@@ -239,7 +239,9 @@ __global__ __launch_bounds__(256, 2) void soft_nodes_big_kernel(const SoftArgs a
 // of node n over the tile's rows in row order into part[row tile][n].
 __device__ __forceinline__ int score_slot(int r, int n) { return 256 * r + (n ^ (4 * (r & 15))); }
 
-__global__ __launch_bounds__(256, 2) void soft_nodes_mix_kernel(const SoftArgs a, float* __restrict__ ent_part) {
+// (kRows: rows of x per block; 16 is the version for batches that leave a chip of 128-row tiles idle)
+template <int kRows> __global__ void soft_nodes_mix_kernel(const SoftArgs a, float* __restrict__ ent_part);
+template <> __global__ __launch_bounds__(256, 2) void soft_nodes_mix_kernel<kBigM>(const SoftArgs a, float* __restrict__ ent_part) {
     __shared__ BigTileLds tile;
     int64_t t0, n0;
     if (!big_tile_of_block(1, a.T, t0, n0)) return;
@@ -261,6 +263,14 @@ __global__ __launch_bounds__(256, 2) void soft_nodes_mix_kernel(const SoftArgs a
     float* const S = (float*)&tile;                     // [64][256] scores of one half of the tile's rows
     const int per_log = NL >= 256 ? 2 : NL >= 128 ? 1 : 0;   // leaves per lane: 4, 2 or 1
     const bool mix_vec = (reinterpret_cast<uintptr_t>(a.mix) & 15u) == 0;
+    // a lane takes `per` consecutive leaves (4 for 256 leaves): their paths share all but the last
+    // log2(per) levels, so the shared factors are multiplied once, root first, and the product
+    // then splits level by level -- every leaf still sees its factors in root-to-leaf order.  Four rows
+    // at a time, every score of theirs requested before the first is used: one row after the other the
+    // wave waits out an LDS read per level (a tile's epilogue took 40 us so, 128 rows over four waves).
+    constexpr int kMixRows = 4, kMaxShared = 6;                        // (at most 256 leaves)
+    const int shared = a.depth - per_log, first = lane << per_log;
+    const int below = ((1 << shared) - 1) + lane;                      // the lane's node under the shared levels
     float ent = 0.0f;
     for (int h = 0; h < 2; ++h) {
         if (wm == h) {
@@ -271,63 +281,68 @@ __global__ __launch_bounds__(256, 2) void soft_nodes_mix_kernel(const SoftArgs a
                     *(f32x4_t*)(S + score_slot(16 * mt + j, 128 * wn + 16 * nt + 4 * kg)) = acc[mt][nt];
         }
         __syncthreads();
-        for (int rr = 0; rr < 16; ++rr) {
-            const int r = 16 * wv + rr;
-            const int64_t t = t0 + 64 * h + r;
-            if (t >= a.T) break;
-            const float* Sr = S + 256 * r;
-            const int sw = 4 * (r & 15);
-            // a lane takes `per` consecutive leaves (4 for 256 leaves): their paths share all but the last
-            // log2(per) levels, so the shared factors are multiplied once, root first, and the product
-            // then splits level by level -- every leaf still sees its factors in root-to-leaf order
-            const int first = lane << per_log;
-            if (first < NL) {
+        for (int rr = 0; rr < 16 && t0 + 64 * h + 16 * wv + rr < a.T; rr += kMixRows) {
+            float cs[kMaxShared][kMixRows], c1[kMixRows], c2[kMixRows], c3[kMixRows];
+            const auto score = [&](int i, int n) { return S[score_slot(16 * wv + rr + i, n)]; };
+            if (first >= NL) continue;
+#pragma unroll
+            for (int lvl = 0; lvl < kMaxShared; ++lvl) {
+                const int l = lvl < shared ? lvl : 0, n = ((1 << l) - 1) + (first >> (a.depth - l));
+#pragma unroll
+                for (int i = 0; i < kMixRows; ++i) cs[lvl][i] = score(i, n);
+            }
+#pragma unroll
+            for (int i = 0; i < kMixRows; ++i) {
+                c1[i] = score(i, per_log > 0 ? below : 0);
+                c2[i] = score(i, per_log > 1 ? 2 * below + 1 : 0);
+                c3[i] = score(i, per_log > 1 ? 2 * below + 2 : 0);
+            }
+#pragma unroll
+            for (int i = 0; i < kMixRows; ++i) {
+                const int64_t t = t0 + 64 * h + 16 * wv + rr + i;
+                if (t >= a.T) break;
                 float m[4];
                 m[0] = 1.0f;
-                const int shared = a.depth - per_log;
-                for (int lvl = 0; lvl < shared; ++lvl) {
-                    const int pos = first >> (a.depth - lvl);
-                    const int bit = (first >> (a.depth - 1 - lvl)) & 1;
-                    const float cs = Sr[(((1 << lvl) - 1) + pos) ^ sw];
-                    m[0] *= bit ? cs : 1.0f - cs;
+#pragma unroll
+                for (int lvl = 0; lvl < kMaxShared; ++lvl) {
+                    const int l = lvl < shared ? lvl : 0;
+                    const float f = (first >> (a.depth - 1 - l)) & 1 ? cs[lvl][i] : 1.0f - cs[lvl][i];
+                    m[0] = lvl < shared ? m[0] * f : m[0];
                 }
+                float* mp = a.mix + t * a.NL + first;
+                uint16_t* hp = a.hid + t * a.K2 + a.NL * a.L + first;
                 if (per_log == 2) {
-                    const int n6 = ((1 << shared) - 1) + lane;                 // the lane's node on level depth - 2
-                    const float c6 = Sr[n6 ^ sw];
-                    const float c70 = Sr[(2 * n6 + 1) ^ sw], c71 = Sr[(2 * n6 + 2) ^ sw];
-                    const float lo = m[0] * (1.0f - c6), hi = m[0] * c6;
-                    m[0] = lo * (1.0f - c70); m[1] = lo * c70; m[2] = hi * (1.0f - c71); m[3] = hi * c71;
+                    const float lo = m[0] * (1.0f - c1[i]), hi = m[0] * c1[i];
+                    m[0] = lo * (1.0f - c2[i]); m[1] = lo * c2[i]; m[2] = hi * (1.0f - c3[i]); m[3] = hi * c3[i];
                     // one 16-byte store (a caller's mixture matrix may start anywhere: checked) and one 8-byte store
                     // (the hidden matrix is the library's, K2 a multiple of 8)
-                    float* mp = a.mix + t * a.NL + first;
                     if (mix_vec) {
                         __builtin_nontemporal_store(f32x4_t{m[0], m[1], m[2], m[3]}, (f32x4_t*)mp);     // written once, read by a later launch
                     } else {
                         mp[0] = m[0]; mp[1] = m[1]; mp[2] = m[2]; mp[3] = m[3];
                     }
-                    {
-                        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-                        const u32x2_t packed = {(uint32_t)f32_to_bf16(m[0]) | ((uint32_t)f32_to_bf16(m[1]) << 16),
-                                                (uint32_t)f32_to_bf16(m[2]) | ((uint32_t)f32_to_bf16(m[3]) << 16)};
-                        __builtin_nontemporal_store(packed, (u32x2_t*)(a.hid + t * a.K2 + a.NL * a.L + first));
-                    }
+                    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+                    const u32x2_t packed = {pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3])};
+                    __builtin_nontemporal_store(packed, (u32x2_t*)hp);
                 } else if (per_log == 1) {
-                    const float c7 = Sr[(((1 << shared) - 1) + lane) ^ sw];
-                    m[1] = m[0] * c7; m[0] = m[0] * (1.0f - c7);
-                    float* mp = a.mix + t * a.NL + first;
+                    m[1] = m[0] * c1[i]; m[0] = m[0] * (1.0f - c1[i]);
                     mp[0] = m[0]; mp[1] = m[1];
-                    uint16_t* hp = a.hid + t * a.K2 + a.NL * a.L + first;
                     hp[0] = f32_to_bf16(m[0]); hp[1] = f32_to_bf16(m[1]);
                 } else {
-                    a.mix[t * a.NL + first] = m[0];
-                    a.hid[t * a.K2 + a.NL * a.L + first] = f32_to_bf16(m[0]);
+                    mp[0] = m[0];
+                    hp[0] = f32_to_bf16(m[0]);
                 }
+                for (int64_t k = a.NL * (a.L + 1) + lane; k < a.K2; k += NL < kWave ? NL : kWave) a.hid[t * a.K2 + k] = 0;
             }
-            for (int64_t k = a.NL * (a.L + 1) + lane; k < a.K2; k += kWave) a.hid[t * a.K2 + k] = 0;
         }
         if (ent_part != nullptr && tid < NN) {
-            for (int r = 0; r < 64 && t0 + 64 * h + r < a.T; ++r)
-                ent += bernoulli_entropy(S[score_slot(r, tid)]);
+            for (int r0 = 0; r0 < 64; r0 += 8) {
+                float c[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) c[i] = S[score_slot(r0 + i, tid)];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) ent += t0 + 64 * h + r0 + i < a.T ? bernoulli_entropy(c[i]) : 0.0f;
+            }
         }
         __syncthreads();
     }
@@ -446,17 +461,17 @@ __global__ __launch_bounds__(256) void soft_out_kernel(const SoftArgs a) {
 // order of additions (so the result does not depend on scheduling): a block sums kEntTokens
 // tokens for every node (thread = node, so the reads run along a row of scores), then one block
 // per node adds the partial sums (strided over its threads, then a fixed tree).
-constexpr int kEntTokens = 32;
+constexpr int kEntTokens = 32, kEntPartTokens = 16;     // (tokens of the smallest partial sum of any launch)
 
 __global__ __launch_bounds__(256) void soft_entropy_part_kernel(const float* __restrict__ choice, int64_t T, int64_t NN,
                                                                 int64_t pitch, float* __restrict__ part) {
     const int64_t t0 = (int64_t)blockIdx.x * kEntTokens;
-    const int64_t t1 = t0 + kEntTokens < T ? t0 + kEntTokens : T;
     for (int64_t n = threadIdx.x; n < NN; n += 256) {
-        float s = 0.0f;
-        for (int64_t t = t0; t < t1; ++t) {
-            s += bernoulli_entropy(choice[t * pitch + n]);
-        }
+        float c[kEntTokens], s = 0.0f;
+#pragma unroll
+        for (int r = 0; r < kEntTokens; ++r) c[r] = choice[(t0 + r < T ? t0 + r : T - 1) * pitch + n];   // all in flight at once
+#pragma unroll
+        for (int r = 0; r < kEntTokens; ++r) s += t0 + r < T ? bernoulli_entropy(c[r]) : 0.0f;
         part[(int64_t)blockIdx.x * NN + n] = s;
     }
 }
@@ -475,6 +490,322 @@ __global__ __launch_bounds__(256) void soft_entropy_sum_kernel(const float* __re
     }
     if (threadIdx.x == 0) entropy[n] = red[0] / (float)T;
 }
+
+// ---- small batches ---------------------------------------------------------------------------------
+//
+// The same pass in three launches for batches that cannot fill the chip with tiles: every block's
+// waves split K among them (mfma_wave_slice), a hidden block multiplies the mixture weights of its own
+// leaves out of the scores, W2 is read where it stands instead of being transposed first, and the
+// entropies' sums ride in the second and third launch.  As tiles these batches took five to seven
+// launches, each a chain of K / 64 memory round trips.
+//
+// What bounds a block is how much one compute unit can have in flight (about 80 lines of 128 bytes:
+// 10-15 bytes a clock for rows that come from beyond the L2), so tiles shrink until the grid covers the
+// chip: 32 x 64, else 16 x 32, else 16 x 16 (64 tokens, K = 3504, 256 columns: 18 us with 32 x 64).
+constexpr int kSmallMaxDepth = 9;
+struct SmallTile {
+    int64_t t0, n0;
+};
+template <int MT, int NT> __device__ __forceinline__ SmallTile small_tile(int64_t N) {
+    const int64_t ncb = (N + 16 * NT - 1) / (16 * NT);
+    return SmallTile{(int64_t)(blockIdx.x / ncb) * (16 * MT), (int64_t)(blockIdx.x % ncb) * (16 * NT)};
+}
+// The block's tile of A B^T: wave w (of the first MT NT) returns, summed over the eight slices in
+// order, tile (w / NT, w % NT) with the lane layout of mfma_wave_slice.
+template <int MT, int NT>
+__device__ __forceinline__ f32x4_t small_contract(const uint16_t* A, int64_t M, const uint16_t* B, int64_t N, int K,
+                                                  const SmallTile& at, f32x4_t (&part)[8][MT * NT][kWave]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int k_begin, k_end;
+    k_slice(K, 8, wv, &k_begin, &k_end);
+    f32x4_t acc[MT][NT];
+    mfma_wave_slice<MT, NT, MT * NT == 8 ? 3 : 6>(A, K, M, at.t0, B, K, N, at.n0, k_begin, k_end, acc);
+#pragma unroll
+    for (int i = 0; i < MT * NT; ++i) part[wv][i][lane] = acc[i / NT][i % NT];
+    __syncthreads();
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (wv < MT * NT) {
+        v = part[0][wv][lane];
+#pragma unroll
+        for (int s = 1; s < 8; ++s) v += part[s][wv][lane];
+    }
+    return v;
+}
+
+// nodes: choice scores
+template <int MT, int NT>
+__global__ __launch_bounds__(512) void soft_small_nodes_kernel(const SoftArgs a) {
+    __shared__ f32x4_t part[8][MT * NT][kWave];
+    const SmallTile at = small_tile<MT, NT>(a.NN);
+    const f32x4_t v = small_contract<MT, NT>(a.x, a.T, a.node_w, a.NN, a.D, at, part);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t t = at.t0 + 16 * (wv / NT) + (lane & 15), n = at.n0 + 16 * (wv % NT) + 4 * (lane >> 4);
+    if (wv >= MT * NT || t >= a.T) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (n + q < a.NN) a.choice[t * a.NL + n + q] = 1.0f / (1.0f + __expf(-(v[q] + bf16_to_f32(a.node_b[n + q]))));
+}
+
+// weight of a leaf from a row of scores, root first
+__device__ __forceinline__ float leaf_weight(const float* __restrict__ c, int depth, int leaf) {
+    float cs[kSmallMaxDepth];
+#pragma unroll
+    for (int lvl = 0; lvl < kSmallMaxDepth; ++lvl) {          // all requested before the first is used
+        const int l = lvl < depth ? lvl : 0;
+        cs[lvl] = c[((1 << l) - 1) + (leaf >> (depth - l))];
+    }
+    float m = 1.0f;
+#pragma unroll
+    for (int lvl = 0; lvl < kSmallMaxDepth; ++lvl)
+        if (lvl < depth) m *= (leaf >> (depth - 1 - lvl)) & 1 ? cs[lvl] : 1.0f - cs[lvl];
+    return m;
+}
+
+// hidden, and the mixture weights of the leaves whose first neuron is in the block's columns; the
+// blocks past the tiles' leave partial entropy sums of 16 tokens each
+// (kOwn false: an earlier launch has left the weights in a.mix and the sums where they belong)
+template <int MT, int NT, bool kOwn>
+__global__ __launch_bounds__(512) void soft_small_hidden_kernel(const SoftArgs a, int64_t tile_blocks, float* __restrict__ mix_out,
+                                                                float* __restrict__ ent_part) {
+    __shared__ f32x4_t part[8][MT * NT][kWave];
+    __shared__ float weight[16 * MT * 16 * NT];               // [token][leaf of the tile's columns]
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (kOwn && blockIdx.x >= tile_blocks) {
+        const int64_t b = blockIdx.x - tile_blocks, t0 = 16 * b;
+        for (int64_t n = tid; n < a.NN; n += 512) {
+            float c[16], s = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[r] = a.choice[(t0 + r < a.T ? t0 + r : a.T - 1) * a.NL + n];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s += t0 + r < a.T ? bernoulli_entropy(c[r]) : 0.0f;
+            ent_part[b * a.NN + n] = s;
+        }
+        return;
+    }
+    const int NH = (int)(a.NL * a.L);
+    const SmallTile at = small_tile<MT, NT>(NH);
+    const int n0 = (int)at.n0, last = n0 + 16 * NT < NH ? n0 + 16 * NT - 1 : NH - 1;
+    const int leaf_lo = n0 / a.L, n_leaf = last / a.L - leaf_lo + 1;      // at most 16 NT leaves
+    for (int i = tid; i < 16 * MT * n_leaf; i += 512) {
+        const int r = i / n_leaf, leaf = leaf_lo + i % n_leaf;
+        const int64_t t = at.t0 + r;
+        if (t >= a.T) continue;
+        const float m = kOwn ? leaf_weight(a.choice + t * a.NL, a.depth, leaf) : a.mix[t * a.NL + leaf];
+        weight[i] = m;
+        if (kOwn && leaf * a.L >= n0) {
+            if (mix_out) mix_out[t * a.NL + leaf] = m;
+            a.hid[t * a.K2 + NH + leaf] = f32_to_bf16(m);
+            if (leaf == 0)
+                for (int64_t k = NH + a.NL; k < a.K2; ++k) a.hid[t * a.K2 + k] = 0;
+        }
+    }
+    const f32x4_t v = small_contract<MT, NT>(a.x, a.T, a.w1, NH, a.D, at, part);   // (its barrier covers weight[] too)
+    const int r = 16 * (wv / NT) + (lane & 15), n = n0 + 16 * (wv % NT) + 4 * (lane >> 4);
+    const int64_t t = at.t0 + r;
+    if (wv >= MT * NT || t >= a.T || n >= NH) return;
+    uint16_t h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t nq = (uint32_t)(n + q < NH ? n + q : NH - 1);
+        h[q] = f32_to_bf16(activate_bulk(v[q] + bf16_to_f32(a.b1[nq]), a.act) * weight[r * n_leaf + (int)(nq / (uint32_t)a.L) - leaf_lo]);
+    }
+    uint16_t* dst = a.hid + t * a.K2 + n;
+    if (n + 4 <= NH) {
+        *(uint2*)dst = make_uint2(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16);
+    } else {
+        for (int q = 0; n + q < NH; ++q) dst[q] = h[q];
+    }
+}
+
+// nodes + mixture weights + partial entropy sums: 16 tokens against all nodes (up to 255).  16 waves:
+// 64 nodes a wave, the rest of them splitting K; then a wave per token multiplies the paths.
+constexpr size_t kSmallPartBytes = 16 * 4 * kWave * sizeof(f32x4_t);
+__host__ __device__ inline int small_node_groups(int64_t NN) { return NN <= 64 ? 1 : NN <= 128 ? 2 : 4; }
+inline size_t small_nodes_lds(int64_t NN) { return kSmallPartBytes + 16 * (64 * small_node_groups(NN) + 4) * sizeof(float); }
+
+template <> __global__ __launch_bounds__(1024) void soft_nodes_mix_kernel<16>(const SoftArgs a, float* __restrict__ ent_part) {
+    extern __shared__ f32x4_t small_lds[];
+    f32x4_t* const part = small_lds;                                   // [wave][4][64]
+    float* const S = (float*)(small_lds + 16 * 4 * kWave);             // [16][pitch] scores
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int NN = (int)a.NN, NL = (int)a.NL;
+    const int groups = small_node_groups(NN), ks = 16 / groups, pitch = 64 * groups + 4;
+    const int64_t t0 = (int64_t)blockIdx.x * 16;
+    {
+        int k_begin, k_end;
+        k_slice(a.D, ks, wv % ks, &k_begin, &k_end);
+        f32x4_t acc[1][4];
+        mfma_wave_slice<1, 4, 4>(a.x, a.D, a.T, t0, a.node_w, a.D, NN, 64 * (wv / ks), k_begin, k_end, acc);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) part[(wv * 4 + nt) * kWave + lane] = acc[0][nt];
+    }
+    __syncthreads();
+    for (int e = tid; e < groups * 256; e += 1024) {
+        const int cg = e >> 8, at = e & 255, l = at & 63;
+        f32x4_t v = part[cg * ks * 256 + at];
+        for (int s = 1; s < ks; ++s) v += part[(cg * ks + s) * 256 + at];
+        const int n = 64 * cg + 16 * (at >> 6) + 4 * (l >> 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[q] = 1.0f / (1.0f + __expf(-(v[q] + (n + q < NN ? bf16_to_f32(a.node_b[n + q]) : 0.0f))));
+        *(f32x4_t*)(S + (l & 15) * pitch + n) = v;
+    }
+    __syncthreads();
+    const int64_t t = t0 + wv;
+    if (t < a.T) {
+        const float* c = S + wv * pitch;
+        uint16_t* hrow = a.hid + t * a.K2 + a.NL * a.L;
+        for (int leaf = lane; leaf < NL; leaf += kWave) {
+            float m = 1.0f;
+            for (int lvl = 0; lvl < a.depth; ++lvl) {
+                const float cs = c[((1 << lvl) - 1) + (leaf >> (a.depth - lvl))];
+                m *= (leaf >> (a.depth - 1 - lvl)) & 1 ? cs : 1.0f - cs;
+            }
+            a.mix[t * a.NL + leaf] = m;
+            hrow[leaf] = f32_to_bf16(m);
+        }
+        for (int k = NL + lane; k < (int)(a.K2 - a.NL * a.L); k += kWave) hrow[k] = 0;
+    }
+    if (ent_part != nullptr && tid < NN) {
+        float ent = 0.0f;
+        for (int r = 0; r < 16 && t0 + r < a.T; ++r) ent += bernoulli_entropy(S[r * pitch + tid]);
+        ent_part[(int64_t)blockIdx.x * NN + tid] = ent;
+    }
+}
+
+// Element c of eight rows of bf16 values (`words` 32-bit words of each) as one MFMA operand piece.
+template <int kWords>
+__device__ __forceinline__ uint4 transpose_piece(const uint32_t (&r)[8][kWords], int c) {
+    const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
+    const int w = c >> 1;
+    return make_uint4(__builtin_amdgcn_perm(r[1][w], r[0][w], sel), __builtin_amdgcn_perm(r[3][w], r[2][w], sel),
+                      __builtin_amdgcn_perm(r[5][w], r[4][w], sel), __builtin_amdgcn_perm(r[7][w], r[6][w], sel));
+}
+
+// out: 16 MT tokens x 16 C outputs a block, eight slices of K2.  W2 and b2 rows run along the outputs
+// while the instruction wants K contiguous: a lane loads outputs C j .. C j + C - 1 of its eight K
+// rows and turns them around in registers, so that column j of the c-th instruction stands for output
+// o0 + C j + c.  The blocks past the outputs' add up the entropies, a wave per node.
+template <int MT, int C>
+__global__ __launch_bounds__(512) void soft_small_out_kernel(const SoftArgs a, int64_t out_blocks,
+                                                             const float* __restrict__ ent_part, int64_t n_parts,
+                                                             float* __restrict__ entropy) {
+    extern __shared__ f32x4_t small_lds[];                    // [8][MT C][64]
+    constexpr int kWords = C / 2;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, j = lane & 15, kg = lane >> 4;
+    if (blockIdx.x >= out_blocks) {
+        const int64_t n = (blockIdx.x - out_blocks) * 8 + wv;
+        if (n >= a.NN) return;
+        float s = 0.0f;
+        for (int64_t b = lane; b < n_parts; b += kWave) s += ent_part[b * a.NN + n];
+        s = group_sum<64>(s);
+        if (lane == 0) entropy[n] = s / (float)a.T;
+        return;
+    }
+    const SmallTile at = small_tile<MT, C>(a.O);
+    const int64_t t0 = at.t0, o0 = at.n0;
+    const bool vec = a.O % C == 0 && ((reinterpret_cast<uintptr_t>(a.w2) | reinterpret_cast<uintptr_t>(a.b2) |
+                                       reinterpret_cast<uintptr_t>(a.out)) & (2 * C - 1)) == 0;
+    const int NH = (int)(a.NL * a.L), NB = NH + (int)a.NL;       // rows of W2, rows of W2 and b2
+    int k_begin, k_end;
+    k_slice((int)a.K2, 8, wv, &k_begin, &k_end);
+    f32x4_t acc[MT][C];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[mt][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const uint16_t* ph[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int64_t t = t0 + 16 * mt + j;
+        ph[mt] = a.hid + (t < a.T ? t : a.T - 1) * a.K2;
+    }
+    const int64_t o = o0 + C * j;
+    const int64_t oc = o + C <= a.O ? o : (vec ? a.O - C : 0);   // results past the last output are dropped
+    constexpr int kUnroll = C == 8 ? 2 : 4;
+    for (int k0 = k_begin; k0 < k_end; k0 += 32 * kUnroll) {
+        uint4 qa[kUnroll][MT];
+        uint32_t qw[kUnroll][8][kWords];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int k = k0 + 32 * u + 8 * kg, kc = k < k_end ? k : k_begin;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) qa[u][mt] = *(const uint4*)(ph[mt] + kc);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = kc + i < NB ? kc + i : NB - 1;
+                const uint16_t* w = row < NH ? a.w2 + (int64_t)row * a.O : a.b2 + (int64_t)(row - NH) * a.O;
+                if (vec && C == 8) {
+                    const uint4 v = *(const uint4*)(w + oc);
+                    qw[u][i][0] = v.x; qw[u][i][1] = v.y; qw[u][i][2 % kWords] = v.z; qw[u][i][3 % kWords] = v.w;
+                } else if (vec) {
+                    const uint2 v = *(const uint2*)(w + oc);
+                    qw[u][i][0] = v.x; qw[u][i][1] = v.y;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < kWords; ++c)
+                        qw[u][i][c] = w[o + 2 * c < a.O ? o + 2 * c : a.O - 1] |
+                                      (uint32_t)w[o + 2 * c + 1 < a.O ? o + 2 * c + 1 : a.O - 1] << 16;
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int k = k0 + 32 * u + 8 * kg;
+            const bool in = k < k_end;
+            bf16x8_t fa[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) fa[mt] = __builtin_bit_cast(bf16x8_t, keep_if(in, qa[u][mt]));
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int w = 0; w < kWords; ++w) qw[u][i][w] = in && k + i < NB ? qw[u][i][w] : 0u;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const bf16x8_t fb = __builtin_bit_cast(bf16x8_t, transpose_piece<kWords>(qw[u], c));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa[mt], acc[mt][c], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MT * C; ++i) small_lds[(wv * MT * C + i) * kWave + lane] = acc[i / C][i % C];
+    __syncthreads();
+    // thread (mt, lane, q): C consecutive outputs o0 + C (4 kg + q) + c of token 16 mt + j
+    if (tid >= MT * 256) return;
+    const float* const pf = (const float*)small_lds;
+    const int mt = tid >> 8, l = (tid >> 2) & 63, q = tid & 3;
+    float y[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        y[c] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) y[c] += pf[((s * MT * C + mt * C + c) * kWave + l) * 4 + q];
+    }
+    const int64_t t = t0 + 16 * mt + (l & 15), oy = o0 + C * (4 * (l >> 4) + q);
+    if (t >= a.T || oy >= a.O) return;
+    uint16_t* dst = a.out + t * a.O + oy;
+    if (vec) {
+        uint32_t w[kWords];
+#pragma unroll
+        for (int c = 0; c < kWords; ++c) w[c] = pack_bf16x2(y[2 * c], y[2 * c + 1]);
+        if (C == 8) *(uint4*)dst = make_uint4(w[0], w[1], w[2 % kWords], w[3 % kWords]);
+        else *(uint2*)dst = make_uint2(w[0], w[1]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (oy + c < a.O) dst[c] = f32_to_bf16(y[c]);
+    }
+}
+
+double small_out_cost(int64_t T, int64_t O, double K) { return 4 + (double)((small_blocks(T, O, 2, 8) + 255) / 256) * (3 + 0.006 * K); }
+double big_cost(int64_t T, int64_t N, double K) {
+    const int64_t blocks = (T + kBigM - 1) / kBigM * ((N + kBigN - 1) / kBigN);
+    return (16 + 0.017 * K) * (blocks <= 256 ? 1.0 : 1.5 * (double)((blocks + 511) / 512));
+}
+constexpr double kLaunchCost = 3;          // a launch of its own: host time, ramp and drain
 
 }  // namespace
 
@@ -495,7 +826,7 @@ int64_t soft_scratch_words(const Problem& p) {
     const int64_t NL = (int64_t)1 << p.depth, NN = NL - 1, K2 = soft_k2(p);
     auto up = [](int64_t w) { return (w + 63) / 64 * 64; };
     return up(p.T * NL) + up(p.T * NL) + up((p.T * K2 + 1) / 2) + up((p.O * K2 + 1) / 2) +
-           up((p.T + kEntTokens - 1) / kEntTokens * (NN > 0 ? NN : 1));
+           up((p.T + kEntPartTokens - 1) / kEntPartTokens * (NN > 0 ? NN : 1));
 }
 
 // mix (optional, [T, 2^d] fp32) and entropy (optional, [2^d - 1] fp32) are caller buffers
@@ -531,69 +862,153 @@ hipError_t launch_forward_soft(const Problem& p, int32_t* scratch, float* mix_ou
     a.w2x = (uint16_t*)w;
     w += up((p.O * a.K2 + 1) / 2);
     float* ent_part = (float*)w;
-    const int64_t mb = (p.T + kTileM - 1) / kTileM;
+    const DeviceInfo di = device_info();
     hipError_t e;
-    // the large tile where the batch and the width fill it (a batch of at least 16 row tiles, a full tile
-    // of columns)
-    const bool big = !g_soft_small_tiles && p.T >= 16 * kBigM;
-    const bool big_nodes = big && a.NN >= kBigN - 1;
-    const bool big_hidden = big && a.NL * a.L >= kBigN, big_out = big && p.O >= kBigN;
-    // nodes, mixture weights and entropy sums in one launch where all nodes fit one column tile
-    const bool fused_nodes = big && a.NN > 0 && a.NN < kBigN;
     const bool want_entropy = entropy_out && a.NN > 0;
-    if (fused_nodes)
-        note_launch("soft_nodes_mix_kernel + soft_hidden%s_kernel + soft_w2x_kernel + soft_out%s_kernel%s",
-                    big_hidden ? "_big" : "", big_out ? "_big" : "", want_entropy ? " + soft_entropy_sum_kernel" : "");
-    else
-        note_launch("%s%ssoft_mix%s_kernel + soft_hidden%s_kernel + soft_w2x_kernel + soft_out%s_kernel%s",
-                    a.NN > 0 ? (big_nodes ? "soft_nodes_big_kernel" : "soft_nodes_kernel") : "", a.NN > 0 ? " + " : "",
-                    a.NL <= kMixMaxLeaves ? "_rows" : "", big_hidden ? "_big" : "", big_out ? "_big" : "",
-                    want_entropy ? " + soft_entropy_part_kernel + soft_entropy_sum_kernel" : "");
-    if (fused_nodes) {
-        soft_nodes_mix_kernel<<<dim3(big_grid(p.T, 1)), dim3(256), 0, s>>>(a, want_entropy ? ent_part : nullptr);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else {
-        if (a.NN > 0) {
-            if (big_nodes)
-                soft_nodes_big_kernel<<<dim3(big_grid(p.T, (a.NN + kBigN - 1) / kBigN)), dim3(256), 0, s>>>(a);
-            else
-                soft_nodes_kernel<<<dim3((unsigned)(mb * ((a.NN + kTileN - 1) / kTileN))), dim3(256), 0, s>>>(a);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int64_t NH = a.NL * a.L, K2 = a.K2;
+    const auto grid = [](int64_t blocks) { return dim3((unsigned)blocks); };
+
+    // ---- which kernel makes each contraction.  The 128 x 256 tile where batch and width fill it, the
+    // 64 x 128 tile in between, slices of K over a block's waves where tiles leave the chip idle.
+    enum Kind { kSmall, kTile, kBig };
+    const auto pick = [&](double small, double tile, double big, bool big_ok) {
+        if (g_soft_small_tiles == 1) return kTile;
+        if (g_soft_small_tiles == 2) return kSmall;
+        if (small <= tile && (small <= big || !big_ok)) return kSmall;
+        return big_ok && big < tile ? kBig : kTile;
+    };
+    const bool big_rows = p.T >= 16 * kBigM;
+    // up to 2047 tokens the scores go to memory and a small hidden launch multiplies its own mixture
+    // weights; from there on, up to 255 nodes, one launch makes scores, weights and entropy sums
+    const bool own_ok = a.NN >= 1 && a.depth <= kSmallMaxDepth && !big_rows && g_soft_small_tiles != 1;
+    const bool fused_nodes = big_rows && a.NN >= 1 && a.NN < kBigN;
+    const Kind hidden = pick(small_cost(p.T, NH, a.D, own_ok),
+                             tile_cost(p.T, NH, a.D) + (own_ok ? 2 * kLaunchCost : 0),
+                             big_cost(p.T, NH, a.D), big_rows && NH >= kBigN);
+    const Kind out = pick(small_out_cost(p.T, p.O, K2), tile_cost(p.T, p.O, K2) + kLaunchCost, big_cost(p.T, p.O, K2) + kLaunchCost,
+                          big_rows && p.O >= kBigN);
+    const bool own_weights = own_ok && hidden == kSmall;
+    const int groups = small_node_groups(a.NN);
+    const double fused16_cost = (double)((p.T + 4095) / 4096) * (7 + 0.0019 * a.D + (groups - 1) * (2 + 0.0025 * a.D));
+    const bool rows16 = fused_nodes && (g_soft_small_tiles == 2 || fused16_cost < 8 + big_cost(p.T, 1, a.D));
+
+    // ---- nodes, mixture weights, entropy sums
+    int64_t ent_parts = 0;                   // rows of partial sums somebody has left in ent_part
+    if (fused_nodes && rows16) {
+        static bool raised[64];              // the limit on dynamic LDS, once per device
+        if (!raised[di.dev]) {
+            e = hipFuncSetAttribute((const void*)soft_nodes_mix_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)small_nodes_lds(kBigN - 1));
+            if (e != hipSuccess) return e;
+            raised[di.dev] = true;
         }
+        note_launch("soft_nodes_mix_kernel<16>");
+        ent_parts = (p.T + 15) / 16;
+        soft_nodes_mix_kernel<16><<<grid(ent_parts), dim3(1024), small_nodes_lds(a.NN), s>>>(a, want_entropy ? ent_part : nullptr);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else if (fused_nodes) {
+        note_launch("soft_nodes_mix_kernel<128>");
+        ent_parts = (p.T + kBigM - 1) / kBigM;
+        soft_nodes_mix_kernel<kBigM><<<dim3(big_grid(p.T, 1)), dim3(256), 0, s>>>(a, want_entropy ? ent_part : nullptr);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else if (a.NN > 0) {
+        const Kind nodes = pick(a.depth <= kSmallMaxDepth ? small_cost(p.T, a.NN, a.D, false) : 1e30, tile_cost(p.T, a.NN, a.D),
+                                big_cost(p.T, a.NN, a.D), big_rows && a.NN >= kBigN - 1);
+        constexpr int64_t enough = kSmallEnoughBlocks;
+        if (nodes == kBig) {
+            note_launch("soft_nodes_big_kernel");
+            soft_nodes_big_kernel<<<dim3(big_grid(p.T, (a.NN + kBigN - 1) / kBigN)), dim3(256), 0, s>>>(a);
+        } else if (nodes == kTile) {
+            note_launch("soft_nodes_kernel");
+            soft_nodes_kernel<<<grid((p.T + kTileM - 1) / kTileM * ((a.NN + kTileN - 1) / kTileN)), dim3(256), 0, s>>>(a);
+        } else {
+            note_launch("soft_small_nodes_kernel");
+            if (small_blocks(p.T, a.NN, 2, 4) >= enough)
+                soft_small_nodes_kernel<2, 4><<<grid(small_blocks(p.T, a.NN, 2, 4)), dim3(512), 0, s>>>(a);
+            else if (small_blocks(p.T, a.NN, 1, 2) >= enough)
+                soft_small_nodes_kernel<1, 2><<<grid(small_blocks(p.T, a.NN, 1, 2)), dim3(512), 0, s>>>(a);
+            else
+                soft_small_nodes_kernel<1, 1><<<grid(small_blocks(p.T, a.NN, 1, 1)), dim3(512), 0, s>>>(a);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (!fused_nodes && !own_weights) {
         if (a.NL <= kMixMaxLeaves) {
+            note_launch("soft_mix_rows_kernel");
             const int waves = a.NL > 1024 ? 2 : 4;
             int64_t blocks = (p.T + waves - 1) / waves;
-            const int64_t cap = (int64_t)device_info().cus * 8;
+            const int64_t cap = (int64_t)di.cus * 8;
             if (blocks > cap) blocks = cap;
             const size_t lds_bytes = sizeof(float) * 3 * waves * (size_t)a.NL;      // at most 48 KB
             soft_mix_rows_kernel<<<dim3((unsigned)blocks), dim3(64 * waves), lds_bytes, s>>>(a);
         } else {
+            note_launch("soft_mix_kernel");
             soft_mix_kernel<<<dim3((unsigned)((p.T * a.NL + 255) / 256)), dim3(256), 0, s>>>(a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (big_hidden && a.act != 0)
-        soft_hidden_big_kernel<true><<<dim3(big_grid(p.T, (a.NL * a.L + kBigN - 1) / kBigN)), dim3(256), 0, s>>>(a);
-    else if (big_hidden)
-        soft_hidden_big_kernel<false><<<dim3(big_grid(p.T, (a.NL * a.L + kBigN - 1) / kBigN)), dim3(256), 0, s>>>(a);
-    else
-        soft_hidden_kernel<<<dim3((unsigned)(mb * ((a.NL * a.L + kTileN - 1) / kTileN))), dim3(256), 0, s>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    soft_w2x_kernel<<<dim3((unsigned)(((a.K2 + 31) / 32) * ((p.O + 31) / 32))), dim3(256), 0, s>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (big_out)
-        soft_out_big_kernel<<<dim3(big_grid(p.T, (p.O + kBigN - 1) / kBigN)), dim3(256), 0, s>>>(a);
-    else
-        soft_out_kernel<<<dim3((unsigned)(mb * ((p.O + kTileN - 1) / kTileN))), dim3(256), 0, s>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (want_entropy) {
-        int64_t n_parts = (p.T + kBigM - 1) / kBigM;        // the fused launch leaves one partial sum per row tile
-        if (!fused_nodes) {
-            n_parts = (p.T + kEntTokens - 1) / kEntTokens;
-            soft_entropy_part_kernel<<<dim3((unsigned)n_parts), dim3(256), 0, s>>>(a.choice, p.T, a.NN, a.NL, ent_part);
+        if (want_entropy) {
+            note_launch("soft_entropy_part_kernel");
+            ent_parts = (p.T + kEntTokens - 1) / kEntTokens;
+            soft_entropy_part_kernel<<<grid(ent_parts), dim3(256), 0, s>>>(a.choice, p.T, a.NN, a.NL, ent_part);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        soft_entropy_sum_kernel<<<dim3((unsigned)a.NN), dim3(256), 0, s>>>(ent_part, n_parts, p.T, a.NN, entropy_out);
+    }
+
+    // ---- hidden
+    if (hidden == kBig) {
+        note_launch("soft_hidden_big_kernel");
+        const dim3 g(big_grid(p.T, (NH + kBigN - 1) / kBigN));
+        if (a.act != 0) soft_hidden_big_kernel<true><<<g, dim3(256), 0, s>>>(a);
+        else soft_hidden_big_kernel<false><<<g, dim3(256), 0, s>>>(a);
+    } else if (hidden == kTile) {
+        note_launch("soft_hidden_kernel");
+        soft_hidden_kernel<<<grid((p.T + kTileM - 1) / kTileM * ((NH + kTileN - 1) / kTileN)), dim3(256), 0, s>>>(a);
+    } else {
+        note_launch("soft_small_hidden_kernel");
+        const int64_t enough = kSmallEnoughBlocks, parts = own_weights && want_entropy ? (p.T + 15) / 16 : 0;
+        if (parts) ent_parts = parts;
+        const auto launch = [&](auto own_kern, auto given_kern, int mt, int nt) {
+            const int64_t blocks = small_blocks(p.T, NH, mt, nt);
+            if (own_weights) own_kern<<<grid(blocks + parts), dim3(512), 0, s>>>(a, blocks, mix_out, ent_part);
+            else given_kern<<<grid(blocks), dim3(512), 0, s>>>(a, blocks, nullptr, nullptr);
+        };
+        if (small_blocks(p.T, NH, 2, 4) >= enough) launch(soft_small_hidden_kernel<2, 4, true>, soft_small_hidden_kernel<2, 4, false>, 2, 4);
+        else if (small_blocks(p.T, NH, 1, 2) >= enough) launch(soft_small_hidden_kernel<1, 2, true>, soft_small_hidden_kernel<1, 2, false>, 1, 2);
+        else launch(soft_small_hidden_kernel<1, 1, true>, soft_small_hidden_kernel<1, 1, false>, 1, 1);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+
+    // ---- out
+    if (out == kSmall) {
+        static bool raised[64];
+        if (!raised[di.dev]) {
+            e = hipFuncSetAttribute((const void*)soft_small_out_kernel<2, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void*)soft_small_out_kernel<1, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+            if (e != hipSuccess) return e;
+            raised[di.dev] = true;
+        }
+        note_launch("soft_small_out_kernel");
+        const int64_t enough = kSmallEnoughBlocks, ent_blocks = want_entropy ? (a.NN + 7) / 8 : 0;
+        const auto launch = [&](auto kern, int mt, int c) {
+            const int64_t blocks = small_blocks(p.T, p.O, mt, c);
+            kern<<<grid(blocks + ent_blocks), dim3(512), (size_t)8 * mt * c * kWave * sizeof(f32x4_t), s>>>(a, blocks, ent_part, ent_parts,
+                                                                                                            entropy_out);
+        };
+        if (small_blocks(p.T, p.O, 2, 8) >= enough) launch(soft_small_out_kernel<2, 8>, 2, 8);
+        else if (small_blocks(p.T, p.O, 1, 8) >= enough) launch(soft_small_out_kernel<1, 8>, 1, 8);
+        else launch(soft_small_out_kernel<1, 4>, 1, 4);
+        return hipGetLastError();
+    }
+    note_launch(out == kBig ? "soft_w2x_kernel + soft_out_big_kernel" : "soft_w2x_kernel + soft_out_kernel");
+    soft_w2x_kernel<<<dim3((unsigned)(((K2 + 31) / 32) * ((p.O + 31) / 32))), dim3(256), 0, s>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (out == kBig) soft_out_big_kernel<<<dim3(big_grid(p.T, (p.O + kBigN - 1) / kBigN)), dim3(256), 0, s>>>(a);
+    else soft_out_kernel<<<grid((p.T + kTileM - 1) / kTileM * ((p.O + kTileN - 1) / kTileN)), dim3(256), 0, s>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (want_entropy) {
+        note_launch("soft_entropy_sum_kernel");
+        soft_entropy_sum_kernel<<<dim3((unsigned)a.NN), dim3(256), 0, s>>>(ent_part, ent_parts, p.T, a.NN, entropy_out);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

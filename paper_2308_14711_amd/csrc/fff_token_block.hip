@@ -32,8 +32,10 @@ struct TokenArgs {
     void* out;
     int32_t* leaf_idx;
     const int32_t* given_leaf;   // non-null: the leaf of every token is given, nothing is descended
+    GateCandidates gate;         // gate.n > 0: the leaf is the best candidate (mixture of experts)
     int64_t T, O;
     int depth, nvec, ovec, L, act;
+    bool descend;                // neither is given
 };
 
 template <bool BF16> __device__ __forceinline__ void widen(const uint4& v, float* f);
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kTokenBlock) void token_block_kernel(TokenArgs a) {
 
         // ---- descent by wave 0: S levels per round trip (Algorithm 1: logit >= 0 takes the right child)
         int64_t n = 0;   // position within the current level
-        for (int m = 0; wv == 0 && !a.given_leaf && m < a.depth; m += S) {
+        for (int m = 0; wv == 0 && a.descend && m < a.depth; m += S) {
             const int s = a.depth - m < S ? a.depth - m : S;
             const int64_t root = (((int64_t)1 << m) - 1 + n) + 1;   // heap row of the subtree's root, plus one
             uint4 rows[kSub][NV];
@@ -141,6 +143,7 @@ __global__ __launch_bounds__(kTokenBlock) void token_block_kernel(TokenArgs a) {
             }
             n = (n << s) + j;
         }
+        if (wv == 0 && a.gate.n > 0) n = best_candidate(a.gate.val + t * a.gate.n, a.gate.idx + t * a.gate.n, a.gate.n);
         if (threadIdx.x == 0) {
             if (a.given_leaf) n = a.given_leaf[t];
             lds_leaf[0] = (int)n;
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(kTokenBlock) void token_block_kernel(TokenArgs a) {
 }
 
 template <bool BF16, int NV, int S, bool OUTVEC>
-hipError_t run_token(const Problem& p, int32_t* leaf_idx, const int32_t* given_leaf, hipStream_t s) {
+hipError_t run_token(const Problem& p, int32_t* leaf_idx, const int32_t* given_leaf, const GateCandidates* gate, hipStream_t s) {
     constexpr int kPer = Elem<BF16>::kPerVec;
     TokenArgs a;
     a.x = (const uint4*)p.x;
@@ -258,6 +261,8 @@ hipError_t run_token(const Problem& p, int32_t* leaf_idx, const int32_t* given_l
     a.out = p.out;
     a.leaf_idx = leaf_idx;
     a.given_leaf = given_leaf;
+    a.gate = gate ? *gate : GateCandidates{};
+    a.descend = !given_leaf && !gate;
     a.T = p.T;
     a.O = p.O;
     a.depth = p.depth;
@@ -285,15 +290,15 @@ hipError_t run_token(const Problem& p, int32_t* leaf_idx, const int32_t* given_l
 }
 
 template <bool BF16, bool OUTVEC>
-hipError_t dispatch_token(const Problem& p, int32_t* leaf_idx, const int32_t* given_leaf, hipStream_t s) {
+hipError_t dispatch_token(const Problem& p, int32_t* leaf_idx, const int32_t* given_leaf, const GateCandidates* gate, hipStream_t s) {
     constexpr int kPer = Elem<BF16>::kPerVec;
     int64_t vecs = p.D / kPer;
     if (OUTVEC && p.O / kPer > vecs) vecs = p.O / kPer;
     // (vectors per lane, levels per round trip): 2^S - 1 rows of NV vectors stay under 32 registers x 4
-    if (vecs <= 64) return run_token<BF16, 1, 3, OUTVEC>(p, leaf_idx, given_leaf, s);
-    if (vecs <= 128) return run_token<BF16, 2, 3, OUTVEC>(p, leaf_idx, given_leaf, s);
-    if (vecs <= 256) return run_token<BF16, 4, 3, OUTVEC>(p, leaf_idx, given_leaf, s);
-    return run_token<BF16, 8, 2, OUTVEC>(p, leaf_idx, given_leaf, s);
+    if (vecs <= 64) return run_token<BF16, 1, 3, OUTVEC>(p, leaf_idx, given_leaf, gate, s);
+    if (vecs <= 128) return run_token<BF16, 2, 3, OUTVEC>(p, leaf_idx, given_leaf, gate, s);
+    if (vecs <= 256) return run_token<BF16, 4, 3, OUTVEC>(p, leaf_idx, given_leaf, gate, s);
+    return run_token<BF16, 8, 2, OUTVEC>(p, leaf_idx, given_leaf, gate, s);
 }
 
 bool token_out_vec(const Problem& p) {
@@ -312,13 +317,14 @@ bool token_shape_ok(const Problem& p) {
     return token_out_vec(p) || 16 + (size_t)p.L * sizeof(float) <= kTokenMaxLds;
 }
 
-hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s, const int32_t* given_leaf) {
+hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s, const int32_t* given_leaf,
+                              const GateCandidates* gate) {
     const bool ov = token_out_vec(p);
     if (p.bf16)
-        return ov ? dispatch_token<true, true>(p, leaf_idx, given_leaf, s)
-                  : dispatch_token<true, false>(p, leaf_idx, given_leaf, s);
-    return ov ? dispatch_token<false, true>(p, leaf_idx, given_leaf, s)
-              : dispatch_token<false, false>(p, leaf_idx, given_leaf, s);
+        return ov ? dispatch_token<true, true>(p, leaf_idx, given_leaf, gate, s)
+                  : dispatch_token<true, false>(p, leaf_idx, given_leaf, gate, s);
+    return ov ? dispatch_token<false, true>(p, leaf_idx, given_leaf, gate, s)
+              : dispatch_token<false, false>(p, leaf_idx, given_leaf, gate, s);
 }
 
 }  // namespace fff

@@ -21,6 +21,11 @@ CASES = [
     ("bucketed",       5000, 256, 128, 6,  4,  True),
     ("bucketed_wide",  9000, 768, 768, 3,  32, False),
     ("many_experts",   129,  96,  24,  12, 1,  True),
+    # the gating's small tiles (16, 32 and 64 experts a block) at their edges
+    ("small_16",       17,   72,  24,  5,  3,  True),
+    ("small_32",       200,  264, 64,  9,  2,  False),
+    ("small_64",       255,  520, 64,  11, 1,  True),
+    ("one_token_moe",  1,    8,   8,   3,  1,  False),
     # the end point of the paper's sweep (section "Inference speed comparison": 768-wide, experts of 32
     # neurons, batch 256, up to 2^15 experts), at full size
     ("sweep_end",      256,  768, 768, 15, 32, True),

@@ -194,3 +194,28 @@ def test_forward_soft_without_optional_outputs_and_after_hardening():
     h = out_to_f64(hard)
     gap = np.abs(got[decided] - h[decided]).max(axis=1) / np.maximum(np.abs(h[decided]).max(axis=1), 1e-30)
     assert gap.max() <= TOL[W.DTYPE_BF16]
+
+
+SMALL_BATCH = [
+    # name,            T,    D,    O,   depth, L, act: the small-batch kernels at their edges
+    ("one_row",        1,    8,    8,   1, 1,  W.ACT_RELU),      # one slice of K, two leaves
+    ("odd_out",        33,   96,   30,  3, 5,  W.ACT_GELU),      # output rows that are no whole vectors
+    ("o_mod_4",        50,   72,   28,  4, 3,  W.ACT_RELU),
+    ("k_past_slices",  17,   1032, 136, 8, 2,  W.ACT_GELU),      # 255 nodes, K two steps past eight slices
+    ("nine_levels",    65,   264,  72,  9, 1,  W.ACT_RELU),      # 511 nodes
+    ("wide_tiles",     1999, 64,   520, 5, 16, W.ACT_GELU),      # 32 x 64 tiles, ragged rows
+    ("rows_16",        2051, 80,   64,  7, 2,  W.ACT_GELU),      # 16-row nodes + mixture launch
+    ("tiles",          1500, 768,  64,  7, 8,  W.ACT_GELU),      # 64 x 128 hidden tile on a batch below 2048
+]
+
+
+@pytest.mark.parametrize("tiles", [0, 1, 2], ids=["auto", "tiles", "small"])
+@pytest.mark.parametrize("case", SMALL_BATCH, ids=[c[0] for c in SMALL_BATCH])
+def test_forward_soft_small_batch_kernels(case, tiles):
+    import paper_2308_14711_amd as F
+    F.fff_debug_option("soft_small_tiles", tiles)
+    try:
+        test_forward_soft_against_the_oracle(case)
+        assert tiles != 2 or "soft_small_out_kernel" in F.fff_last_launch(), F.fff_last_launch()
+    finally:
+        F.fff_debug_option("soft_small_tiles", 0)
