@@ -229,9 +229,9 @@ int fff_forward_soft(const void* x, const void* node_w, const void* node_b,
  *   out [T, O]; may be x itself (same pointer, O == D), any other overlap is
  *   FFF_ERR_ALIAS; leaf_idx [T] int32 may be NULL
  *   Rows that are 16-byte aligned with D and O multiples of 8 (bf16) or 4 (fp32)
- *   and at most 4096 (bf16) or 2048 (fp32) features take the vector kernels;
- *   any other shape an element-wise kernel (correct, slow; option
- *   "last_block_kernel" reads 1 or 2 after a call).  Needs no workspace.  Other arguments, ownership, asynchrony and errors as
+ *   and at most 4096 (bf16) or 2048 (fp32) features are what option
+ *   "last_block_kernel" reports as 1 after a call, any other shape as 2 (some of
+ *   those take an element-wise kernel: correct, slow).  Needs no workspace.  Other arguments, ownership, asynchrony and errors as
  *   for fff_forward_hard.
  */
 int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
@@ -299,7 +299,7 @@ int fff_release_workspace(void);
  * Read-only, describing the last call: "last_path" (1..5 as above), "last_leaf_path"
  * (1 = gather kernel, 2 = the two tile kernels, 3 = both, each on its share of the tiles),
  * "last_walk_top" (tree levels the descent or fused launch kept in LDS),
- * "last_block_kernel" (fff_forward_block: 1 = a vector kernel, 2 = the element-wise one),
+ * "last_block_kernel" (fff_forward_block: 1 = rows of whole aligned 16-byte pieces, 2 = any other rows),
  * "last_block_top" (node levels fff_forward_block kept in LDS).
  * Unknown names or negative values return FFF_ERR_UNSUPPORTED.
  */

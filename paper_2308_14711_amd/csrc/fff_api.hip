@@ -275,7 +275,7 @@ int choose_path(const Problem& p) {
     if (g_opt.path == kPathAuto && token_ok &&
         p.T <= (fused_ok ? g_opt.token_max_T : 6 * g_opt.token_max_T))
         return kPathToken;
-    if (!fused_ok && !staged_ok) return token_ok ? kPathToken : kPathGeneric;
+    if (!fused_ok && !staged_ok) return token_ok && p.T <= 6 * g_opt.token_max_T ? kPathToken : kPathGeneric;
     // The fused launch gathers, per token, the leaf's output-weight and bias rows from a table of
     // 2^depth (leaf_width + 1) rows.  Once that table outgrows the L2 of an XCD most of those rows
     // come back from memory; the launch cut in two (walk and hidden neurons per token, then the
@@ -723,6 +723,21 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
                              vec_ok(leaf_b2, O, p.bf16);
     begin_device_call();
     g_opt.last_block_kernel = vector_rows ? 1 : 2;
+    if (T <= g_opt.token_max_T * 2 && token_wide_ok(p, node_size)) {
+        WideNodes wide;
+        wide.gamma = ln_gamma;
+        wide.beta = ln_beta;
+        wide.w1 = node_w1;
+        wide.b1 = node_b1;
+        wide.w2 = node_w2;
+        wide.b2 = node_b2;
+        wide.n = node_size;
+        wide.residual = residual != 0;
+        wide.eps = ln_eps;
+        g_block_tuning.last_top = 0;
+        hipError_t e = launch_token_block(p, leaf_idx, (hipStream_t)stream, nullptr, nullptr, &wide);
+        return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
+    }
     hipError_t e = launch_forward_block(p, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2,
                                         node_size, residual != 0, leaf_idx, (hipStream_t)stream, vector_rows);
     return e == hipSuccess ? FFF_OK : set_device_error(e, "block kernel launch");

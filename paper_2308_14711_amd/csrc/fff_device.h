@@ -75,8 +75,11 @@ template <int LANES> __device__ __forceinline__ float group_sum(float v) {
     v += row_rotate<2>(v);
     v += row_rotate<1>(v);
     if (LANES == 64) {
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
+        // rows of 16 lanes, then halves of the wave, exchanged in the vector unit (a shuffle goes through LDS)
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
     }
     return v;
 }
@@ -113,6 +116,43 @@ __device__ __forceinline__ uint4 load_stream(const uint4* p) {
 __device__ __forceinline__ void store_stream(uint4* p, const uint4& v) {
     const u32x4_t u = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(u, (u32x4_t*)p);
+}
+
+// ---- rows of any length, 16 bytes at a time ---------------------------------------------------------------
+//
+// A row of n elements is taken in ceil(n / VE) pieces of VE elements (VE = 8 bf16 or 4 fp32 = 16 bytes); the last
+// one is the window [n - VE, n), so that every access lies inside the row (n >= VE).  Rows then start at any
+// element: the 16-byte accesses are declared with the alignment of an element, which costs the compiler nothing
+// (gfx950 takes global dwordx4 accesses at any address) and the memory system one more line per 1 KB.  A window
+// repeats elements of the piece before it: a token row drops them (drop_first), so that whatever the
+// weight rows hold there does not count; an output row writes them twice, with the same value.
+typedef u32x4_t u32x4_any_t __attribute__((aligned(2)));
+__device__ __forceinline__ uint4 load_any(const void* p) {
+    const u32x4_t v = *(const u32x4_any_t*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 load_any_stream(const void* p) {
+    const u32x4_t v = __builtin_nontemporal_load((const u32x4_any_t*)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store_any(void* p, const uint4& v) {
+    *(u32x4_any_t*)p = u32x4_t{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ void store_any_stream(void* p, const uint4& v) {
+    __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, (u32x4_any_t*)p);
+}
+// byte offset of piece c in a row of row_bytes (pieces past the row's end: its last window)
+__device__ __forceinline__ int piece_offset(int c, int row_bytes) {
+    return 16 * c < row_bytes - 16 ? 16 * c : row_bytes - 16;
+}
+// The piece as loaded at piece_offset(c), without the elements that piece c - 1 already holds (all of them for c past the row).
+template <bool BF16> __device__ __forceinline__ uint4 drop_first(const uint4& v, int c, int row_bytes) {
+    const int bytes = 16 * c - piece_offset(c, row_bytes);    // 0 (almost always) .. 16 and more
+    const auto part = [&](uint32_t w, int at) {
+        if (!BF16) return bytes > at ? 0u : w;
+        return bytes >= at + 4 ? 0u : bytes == at + 2 ? w & 0xffff0000u : w;
+    };
+    return make_uint4(part(v.x, 0), part(v.y, 4), part(v.z, 8), part(v.w, 12));
 }
 
 // v or zeros, component by component (a conditional on the 16-byte struct itself is lowered

@@ -158,15 +158,28 @@ hipError_t launch_leaf_tiles(const Problem& p, const int32_t* slot_leaf, const i
 
 // Whole forward pass in one launch, one block per token: the small-batch path, built for the
 // latency of the dependent loads rather than for throughput; needs token_shape_ok(p).
-constexpr size_t kTokenMaxLds = 144 * 1024;
-constexpr int64_t kTokenMaxBlocks = 8192;
 // given_leaf (optional): the leaf of every token, or gate: the candidates to pick it from (the pick goes to
 // leaf_idx); then only the leaf networks run (the node weights are not read, token_shape_ok's
 // condition on them does not apply).
 struct GateCandidates;
+// wide (optional): nodes of `n` hidden neurons on the layer-normalised token (gamma null: no normalisation), plus the
+// token itself when `residual`: fff_forward_block's small batches; needs token_wide_ok(p, n).
+struct WideNodes {
+    const void* gamma = nullptr;
+    const void* beta = nullptr;
+    const void* w1 = nullptr;   // [nodes, n, D]
+    const void* b1 = nullptr;   // [nodes, n]
+    const void* w2 = nullptr;   // [nodes, n]
+    const void* b2 = nullptr;   // [nodes]
+    int n = 1;
+    bool residual = false;
+    float eps = 0;
+};
 bool token_shape_ok(const Problem& p);
+bool token_wide_ok(const Problem& p, int node_size);
 hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s,
-                              const int32_t* given_leaf = nullptr, const GateCandidates* gate = nullptr);
+                              const int32_t* given_leaf = nullptr, const GateCandidates* gate = nullptr,
+                              const WideNodes* wide = nullptr);
 
 // Gating of a mixture of experts with one engaged expert (fff_moe_gate.hip).  launch_moe_gate leaves, per
 // token, the best (logit, expert) of every block of experts in `cand` (moe_gate_words(T, n_experts)

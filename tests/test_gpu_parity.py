@@ -604,3 +604,27 @@ def test_loading_the_library_before_torch_in_a_fresh_process():
     print("\n[case] fresh process: library first, torch second", flush=True)
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+
+
+TOKEN_ROWS = [
+    # D, O on both sides of the piece and wave boundaries of the one-block-per-token kernel, rows that start anywhere
+    # D,   O,    depth, L,  dtype
+    (8,    8,    1,     1,  W.DTYPE_BF16), (9,    17,   7,     3,  W.DTYPE_BF16), (77,   9,    6,     4,  W.DTYPE_BF16),
+    (511,  513,  5,     8,  W.DTYPE_BF16), (513,  511,  6,     33, W.DTYPE_BF16), (1023, 5,    3,     65, W.DTYPE_BF16),
+    (1025, 4097, 4,     2,  W.DTYPE_BF16), (2049, 30,   9,     7,  W.DTYPE_BF16), (4097, 64,   3,     9,  W.DTYPE_BF16),
+    (8191, 10,   2,     2,  W.DTYPE_BF16), (4,    4,    2,     1,  W.DTYPE_F32),  (5,    3,    10,    2,  W.DTYPE_F32),
+    (255,  257,  5,     5,  W.DTYPE_F32),  (671,  671,  7,     32, W.DTYPE_F32),  (2051, 2049, 3,     3,  W.DTYPE_F32),
+    (4095, 6,    2,     4,  W.DTYPE_F32),
+]
+
+
+@pytest.mark.parametrize("case", TOKEN_ROWS, ids=["D%d_O%d_d%d_L%d_%s" % (c[0], c[1], c[2], c[3], "bf16" if c[4] else "f32")
+                                                  for c in TOKEN_ROWS])
+def test_token_block_rows_of_any_length(case):
+    import paper_2308_14711_amd as F
+    D, O, depth, L, dtype = case
+    print("\n[case] token rows T=37 D=%d O=%d depth=%d L=%d dtype=%d seed 19" % case, flush=True)
+    w = W.make_layer("rows", 37, D, O, depth, L, W.ACT_GELU, dtype, seed=19)
+    out, idx = run_forward(w)
+    assert F.fff_get_option("last_path") == 4 and "token_block_kernel" in F.fff_last_launch(), F.fff_last_launch()
+    _log("rows D=%d O=%d" % (D, O), check_against_oracle(w, out, idx))
