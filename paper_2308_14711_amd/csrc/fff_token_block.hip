@@ -372,6 +372,15 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
                 }
             }
         }
+        // In place (out = x) a row's last window, which may overlap the piece before, is read before anything is stored.
+        // Rows longer than the block have their second pieces still to read: at most one a thread, as rows of x end at 1024 pieces.
+        uint4 res_far;
+        const bool far = BLOCK && a.wide.residual && a.opieces > kTokenBlock;
+        if (far) {
+            const int cf = threadIdx.x + kTokenBlock;
+            res_far = load_any(a.x + t * a.xbytes + piece_offset(cf < a.opieces ? cf : a.opieces - 1, a.obytes));
+            __syncthreads();
+        }
         if (grp == 0 && c < a.opieces) {
             add(b2, 1.0f);
             if (BLOCK && a.wide.residual) add(res, 1.0f);
@@ -384,7 +393,7 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
             for (int e = 0; e < E; ++e) y[e] = 0.0f;
             for (int r = 0; r < a.L; ++r) add(load_any(w2 + (int64_t)r * a.obytes + at), hidden_of(r));
             add(load_any(a.b2 + (int64_t)n * a.obytes + at), 1.0f);
-            if (BLOCK && a.wide.residual) add(load_any(a.x + t * a.xbytes + at), 1.0f);
+            if (far) add(res_far, 1.0f);
             store_any(a.out + t * a.obytes + at, narrow<BF16>(y));
         }
     } else {        // rows shorter than a piece

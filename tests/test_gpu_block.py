@@ -138,6 +138,9 @@ def test_block_in_place_and_without_an_index_buffer():
     print("\n[case] block in place (out = x), then without leaf_idx", flush=True)
     _check(("in_place", 900, 768, 768, 6, 3, 4, W.ACT_GELU, BF16, True, True), in_place=True)
     _check(("in_place_f32", 300, 128, 128, 4, 2, 2, W.ACT_RELU, F32, True, True), in_place=True)
+    # rows of one piece more than a small batch's block has threads: their last window overlaps the piece before
+    _check(("in_place_odd", 65, 2050, 2050, 3, 2, 2, W.ACT_RELU, F32, True, True), in_place=True)
+    _check(("in_place_odd_bf16", 65, 4101, 4101, 3, 2, 2, W.ACT_GELU, BF16, True, True), in_place=True)
     _check(("no_idx", 900, 768, 768, 6, 3, 4, W.ACT_GELU, BF16, True, True), want_idx=False)
 
 
