@@ -27,7 +27,7 @@ thread_local std::string g_last_error;
 constexpr int kMaxNotes = 8;
 LaunchNote g_notes[kMaxNotes];
 int g_n_notes = 0;
-std::string g_last_launch;
+std::mutex g_notes_mu;   // forward calls of several threads note their kernels in one list
 
 // One workspace per device: the library's own block (grown on demand), or the caller's
 // (fff_set_workspace), which takes precedence while it is set.
@@ -118,7 +118,10 @@ Layout layout_for(int64_t T, int depth, int64_t extra_words = 0) {
 // launch checks below report this call's errors only.
 void begin_device_call() {
     g_last_error.clear();
-    g_n_notes = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_notes_mu);
+        g_n_notes = 0;
+    }
     (void)hipGetLastError();
 }
 
@@ -535,9 +538,10 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
 
 }  // namespace
 
-LaunchNote& next_launch_note() {
-    const int i = g_n_notes < kMaxNotes ? g_n_notes++ : kMaxNotes - 1;
-    return g_notes[i];
+void add_launch_note(const LaunchNote& note) {
+    std::lock_guard<std::mutex> lock(g_notes_mu);
+    if (g_n_notes == kMaxNotes) --g_n_notes;
+    g_notes[g_n_notes++] = note;
 }
 
 }  // namespace fff
@@ -938,7 +942,9 @@ const char* fff_status_string(int status) {
 const char* fff_last_device_error(void) { return g_last_error.c_str(); }
 
 const char* fff_last_launch(void) {
-    std::string text;
+    static thread_local std::string text;   // each caller its own: the pointer stays good while others ask
+    text.clear();
+    std::lock_guard<std::mutex> lock(g_notes_mu);
     for (int i = 0; i < g_n_notes; ++i) {
         if (i) text += " + ";
         int arg = 0;
@@ -952,8 +958,7 @@ const char* fff_last_launch(void) {
             }
         }
     }
-    g_last_launch.swap(text);
-    return g_last_launch.c_str();
+    return text.c_str();
 }
 
 int fff_version(void) { return 300; }

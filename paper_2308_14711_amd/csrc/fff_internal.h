@@ -55,10 +55,10 @@ struct LaunchNote {
     const char* fmt;
     intptr_t args[kMaxArgs];
 };
-LaunchNote& next_launch_note();
+void add_launch_note(const LaunchNote& note);
 template <class... A> inline void note_launch(const char* fmt, A... args) {
     static_assert(sizeof...(A) <= LaunchNote::kMaxArgs, "");
-    next_launch_note() = LaunchNote{fmt, {(intptr_t)args...}};
+    add_launch_note(LaunchNote{fmt, {(intptr_t)args...}});
 }
 
 // Per-block leaf counts, the hand-over from the descent to the bucketing stage: block b of the
