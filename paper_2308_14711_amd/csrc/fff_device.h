@@ -75,13 +75,21 @@ template <int LANES> __device__ __forceinline__ float group_sum(float v) {
     v += row_rotate<2>(v);
     v += row_rotate<1>(v);
     if (LANES == 64) {
-        // rows of 16 lanes, then halves of the wave, exchanged in the vector unit (a shuffle goes through LDS)
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
     }
     return v;
+}
+
+// group_sum<64> for a kernel whose time is its chain of instructions: rows of 16 lanes, then halves of the wave, are exchanged
+// in the vector unit, where a shuffle is a round trip through LDS.  The streaming kernels keep the shuffles, whose
+// wait other waves cover (16384 tokens of 4096 features, depth 15, fused walk: 239 us with shuffles, 243 with exchanges).
+__device__ __forceinline__ float wave_sum(float v) {
+    v = group_sum<16>(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
 __device__ __forceinline__ float activate(float v, int act) {

@@ -698,7 +698,7 @@ __global__ __launch_bounds__(512) void soft_small_out_kernel(const SoftArgs a, i
         if (n >= a.NN) return;
         float s = 0.0f;
         for (int64_t b = lane; b < n_parts; b += kWave) s += ent_part[b * a.NN + n];
-        s = group_sum<64>(s);
+        s = wave_sum(s);
         if (lane == 0) entropy[n] = s / (float)a.T;
         return;
     }

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
             // mean, then the mean of squared deviations (divisor D), over the waves of the slot
             float* partial = lds_all;
             const auto slot_sum = [&](float v) {
-                v = group_sum<kWave>(v);
+                v = wave_sum(v);
                 if (H == 1) return v;
                 if (lane == 0) partial[wv] = v;
                 __syncthreads();
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
             if constexpr (BLOCK) {
                 const float v = lane < rows ? raw_value<BF16>(scale) * activate(logit, a.act) : 0.0f;    // one hidden neuron a lane
                 if (s == 1) {
-                    logit = group_sum<kWave>(v) + raw_value<BF16>(out_bias);
+                    logit = wave_sum(v) + raw_value<BF16>(out_bias);
                 } else {
                     const int my = lane < nodes ? lane : nodes - 1;
                     logit = raw_value<BF16>(out_bias);
