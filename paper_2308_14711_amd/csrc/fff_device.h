@@ -139,15 +139,8 @@ __device__ __forceinline__ uint4 load_any(const void* p) {
     const u32x4_t v = *(const u32x4_any_t*)p;
     return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ uint4 load_any_stream(const void* p) {
-    const u32x4_t v = __builtin_nontemporal_load((const u32x4_any_t*)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 __device__ __forceinline__ void store_any(void* p, const uint4& v) {
     *(u32x4_any_t*)p = u32x4_t{v.x, v.y, v.z, v.w};
-}
-__device__ __forceinline__ void store_any_stream(void* p, const uint4& v) {
-    __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, (u32x4_any_t*)p);
 }
 // byte offset of piece c in a row of row_bytes (pieces past the row's end: its last window)
 __device__ __forceinline__ int piece_offset(int c, int row_bytes) {
@@ -161,6 +154,32 @@ template <bool BF16> __device__ __forceinline__ uint4 drop_first(const uint4& v,
         return bytes >= at + 4 ? 0u : bytes == at + 2 ? w & 0xffff0000u : w;
     };
     return make_uint4(part(v.x, 0), part(v.y, 4), part(v.z, 8), part(v.w, 12));
+}
+
+// a piece in fp32, and back
+template <bool BF16> __device__ __forceinline__ void widen(const uint4& v, float* f);
+template <> __device__ __forceinline__ void widen<false>(const uint4& v, float* f) {
+    f[0] = __uint_as_float(v.x);
+    f[1] = __uint_as_float(v.y);
+    f[2] = __uint_as_float(v.z);
+    f[3] = __uint_as_float(v.w);
+}
+template <> __device__ __forceinline__ void widen<true>(const uint4& v, float* f) {
+    f[0] = bf16_lo(v.x);
+    f[1] = bf16_hi(v.x);
+    f[2] = bf16_lo(v.y);
+    f[3] = bf16_hi(v.y);
+    f[4] = bf16_lo(v.z);
+    f[5] = bf16_hi(v.z);
+    f[6] = bf16_lo(v.w);
+    f[7] = bf16_hi(v.w);
+}
+template <bool BF16> __device__ __forceinline__ uint4 narrow(const float* f);
+template <> __device__ __forceinline__ uint4 narrow<false>(const float* f) {
+    return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
+}
+template <> __device__ __forceinline__ uint4 narrow<true>(const float* f) {
+    return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
 }
 
 // v or zeros, component by component (a conditional on the 16-byte struct itself is lowered

@@ -220,7 +220,10 @@ hipError_t launch_forward_block(const Problem& p, const void* gamma, const void*
                                 const void* node_b2, int node_size, bool residual, int32_t* leaf_idx,
                                 hipStream_t s, bool vector_rows = true);
 
-// Whole forward pass in one launch, one token per lane group (any shape).
+// Whole forward pass in one launch for rows at any element, 16-byte pieces; needs rows_shape_ok(p).
+bool rows_shape_ok(const Problem& p);
+hipError_t launch_fused_rows(const Problem& p, int32_t* leaf_idx, hipStream_t s);
+// Whole forward pass in one launch, a wave a token, element-wise (any shape).
 hipError_t launch_fused_generic(const Problem& p, int32_t* leaf_idx, hipStream_t s);
 
 // Contractions [T, K] x [K, N]: blocks of 16 mt x 16 nt results, and estimates of the time in us with a

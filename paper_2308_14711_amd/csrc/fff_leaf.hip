@@ -122,6 +122,123 @@ __global__ __launch_bounds__(256) void leaf_gather_kernel(
     }
 }
 
+// Whole forward pass for rows that are not whole 16-byte pieces or not aligned to them: a token owns LPT lanes (16 up to
+// 64 pieces, a wave beyond), which hold its row as pieces at any element (load_any), and goes from the root
+// to its output row in one launch.
+//
+// Bound by the chain of trips to the caches, one a level and two in the leaf, and by how many tokens walk at once: with 16 lanes a
+// token four of them share a wave, so that 20000 tokens are resident together, where a wave per token with element-wise loads
+// (fused_generic_kernel) took two and a half rounds of longer trips (20011 tokens of 77 bf16 features, depth 6, 4 neurons, 9 outputs:
+// 19.8 -> 7.5 us a call).  The elements a last window repeats, and whole
+// pieces past the row, are zeros on both sides of a product: an infinite weight or feature counts once.
+template <bool BF16, int LPT, int NV>
+__global__ __launch_bounds__(256) void fused_rows_kernel(const Problem p, int32_t* __restrict__ leaf_out, int out_pieces) {
+    constexpr int VE = Elem<BF16>::kPerVec;
+    constexpr int kRows = NV == 1 ? 4 : 2;       // neurons requested together
+    extern __shared__ float hbuf[];     // [256 / LPT][L]
+    const int sub = threadIdx.x % LPT, g = threadIdx.x / LPT;
+    const int64_t slot = (int64_t)blockIdx.x * (256 / LPT) + g;
+    const int64_t t = slot < p.T ? slot : p.T - 1;      // groups past the end repeat the last token and store nothing
+    const int xbytes = (int)p.D * (16 / VE);
+    const char* const xrow = (const char*)p.x + t * xbytes;
+    const auto node_row = [&](int64_t i) { return (const char*)p.node_w + i * xbytes; };
+    int off[NV];
+    uint4 xv[NV], mask[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int c = sub + v * LPT;
+        off[v] = piece_offset(c, xbytes);
+        mask[v] = drop_first<BF16>(make_uint4(~0u, ~0u, ~0u, ~0u), c, xbytes);
+        xv[v] = load_any(xrow + off[v]);
+    }
+    const auto masked = [&](const uint4& w, int v) {
+        return make_uint4(w.x & mask[v].x, w.y & mask[v].y, w.z & mask[v].z, w.w & mask[v].w);
+    };
+#pragma unroll
+    for (int v = 0; v < NV; ++v) xv[v] = masked(xv[v], v);
+    const auto dot = [&](const uint4 (&w)[NV]) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc = Elem<BF16>::dot(xv[v], masked(w[v], v), acc);
+        return group_sum<LPT>(acc);
+    };
+    int node = 0;
+    for (int m = 0; m < p.depth; ++m) {
+        uint4 w[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) w[v] = load_any(node_row(node) + off[v]);
+        const float bias = Elem<BF16>::load(p.node_b, node);
+        node = 2 * node + 1 + (dot(w) + bias >= 0.0f ? 1 : 0);
+    }
+    const int64_t leaf = node - ((1 << p.depth) - 1);
+    if (leaf_out && sub == 0 && slot < p.T) leaf_out[t] = (int32_t)leaf;
+
+    float* const h = hbuf + g * p.L;
+    const char* const w1 = (const char*)p.leaf_w1 + leaf * p.L * xbytes;
+    for (int r0 = 0; r0 < p.L; r0 += kRows) {
+        uint4 w[kRows][NV];
+        float b[kRows];
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {       // past the last neuron the last one again, not stored
+            const int r = r0 + j < p.L ? r0 + j : p.L - 1;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) w[j][v] = load_any(w1 + (int64_t)r * xbytes + off[v]);
+            b[j] = Elem<BF16>::load(p.leaf_b1, leaf * p.L + r);
+        }
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+            const float v = activate(dot(w[j]) + b[j], p.act);
+            if (sub == 0 && r0 + j < p.L) h[r0 + j] = v;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // a group is within a wave
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (slot >= p.T) return;
+    if (out_pieces) {
+        const int obytes = (int)p.O * (16 / VE);
+        const char* const w2 = (const char*)p.leaf_w2 + leaf * p.L * obytes;
+        for (int c = sub; c < out_pieces; c += LPT) {
+            const int at = piece_offset(c, obytes);
+            float y[VE], f[VE];
+            widen<BF16>(load_any((const char*)p.leaf_b2 + leaf * obytes + at), y);
+            for (int r = 0; r < p.L; ++r) {
+                widen<BF16>(load_any(w2 + (int64_t)r * obytes + at), f);
+                const float hr = h[r];
+#pragma unroll
+                for (int e = 0; e < VE; ++e) y[e] = fmaf(hr, f[e], y[e]);
+            }
+            store_any((char*)p.out + t * obytes + at, narrow<BF16>(y));
+        }
+    } else {
+        for (int64_t o = sub; o < p.O; o += LPT) {
+            float y = Elem<BF16>::load(p.leaf_b2, leaf * p.O + o);
+            for (int r = 0; r < p.L; ++r) y = fmaf(h[r], Elem<BF16>::load(p.leaf_w2, (leaf * p.L + r) * p.O + o), y);
+            Elem<BF16>::store(p.out, t * p.O + o, y);
+        }
+    }
+}
+
+template <bool BF16, int LPT, int NV>
+static hipError_t run_rows(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
+    constexpr int VE = Elem<BF16>::kPerVec, kGroups = 256 / LPT;
+    note_launch("fused_rows_kernel<%s,%d,%d>", BF16 ? "bf16" : "f32", LPT, NV);
+    // output rows of up to 16 elements: one trip with an element a lane
+    const int out_pieces = p.O > 16 ? (int)((p.O + VE - 1) / VE) : 0;
+    fused_rows_kernel<BF16, LPT, NV><<<dim3((unsigned)((p.T + kGroups - 1) / kGroups)), dim3(256),
+                                       sizeof(float) * kGroups * p.L, s>>>(p, leaf_idx, out_pieces);
+    return hipGetLastError();
+}
+
+template <bool BF16> static hipError_t dispatch_rows(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
+    const int64_t pieces = (p.D + Elem<BF16>::kPerVec - 1) / Elem<BF16>::kPerVec;
+    if (pieces <= 16) return run_rows<BF16, 16, 1>(p, leaf_idx, s);
+    if (pieces <= 32) return run_rows<BF16, 16, 2>(p, leaf_idx, s);
+    if (pieces <= 64) return run_rows<BF16, 16, 4>(p, leaf_idx, s);
+    if (pieces <= 128) return run_rows<BF16, 64, 2>(p, leaf_idx, s);
+    return run_rows<BF16, 64, 4>(p, leaf_idx, s);
+}
+
 // Whole forward pass, any shape, any alignment: one wave per token, element
 // loads.  The fallback for shapes the vector kernels do not take, and the
 // single launch used for small batches.
@@ -228,6 +345,17 @@ hipError_t launch_leaf_gather(const Problem& p, const int32_t* leaf_idx, const i
     if (split > 0 && (!order || !slot_leaf)) return hipErrorInvalidValue;
     return p.bf16 ? dispatch_gather<true>(p, leaf_idx, order, s, slot_leaf, split)
                   : dispatch_gather<false>(p, leaf_idx, order, s, slot_leaf, split);
+}
+
+// Rows of one to 256 pieces, leaves of up to 64 neurons, output rows whose byte offsets fit 32 bits
+bool rows_shape_ok(const Problem& p) {
+    const int64_t per = p.bf16 ? 8 : 4;
+    return p.D >= per && (p.D + per - 1) / per <= 256 && p.L <= 64 && p.O <= (1 << 24) && p.depth < 31;
+}
+
+hipError_t launch_fused_rows(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
+    if (p.T == 0) return hipSuccess;
+    return p.bf16 ? dispatch_rows<true>(p, leaf_idx, s) : dispatch_rows<false>(p, leaf_idx, s);
 }
 
 hipError_t launch_fused_generic(const Problem& p, int32_t* leaf_idx, hipStream_t s) {

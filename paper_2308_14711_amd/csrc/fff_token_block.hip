@@ -55,31 +55,6 @@ struct TokenArgs {
 // where the leaf comes from: the tree, the gating candidates of a mixture of experts, or a list
 enum { kFromTree = 0, kFromGate = 1, kFromList = 2 };
 
-template <bool BF16> __device__ __forceinline__ void widen(const uint4& v, float* f);
-template <> __device__ __forceinline__ void widen<false>(const uint4& v, float* f) {
-    f[0] = __uint_as_float(v.x);
-    f[1] = __uint_as_float(v.y);
-    f[2] = __uint_as_float(v.z);
-    f[3] = __uint_as_float(v.w);
-}
-template <> __device__ __forceinline__ void widen<true>(const uint4& v, float* f) {
-    f[0] = bf16_lo(v.x);
-    f[1] = bf16_hi(v.x);
-    f[2] = bf16_lo(v.y);
-    f[3] = bf16_hi(v.y);
-    f[4] = bf16_lo(v.z);
-    f[5] = bf16_hi(v.z);
-    f[6] = bf16_lo(v.w);
-    f[7] = bf16_hi(v.w);
-}
-template <bool BF16> __device__ __forceinline__ uint4 narrow(const float* f);
-template <> __device__ __forceinline__ uint4 narrow<false>(const float* f) {
-    return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
-}
-template <> __device__ __forceinline__ uint4 narrow<true>(const float* f) {
-    return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
-}
-
 // One element, widened only where it is used: the conversion would wait for the load, and with it for all loads before it.
 template <bool BF16> __device__ __forceinline__ uint32_t load_raw(const void* p, int64_t i) {
     return BF16 ? ((const uint16_t*)p)[i] : ((const uint32_t*)p)[i];

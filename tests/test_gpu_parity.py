@@ -628,3 +628,45 @@ def test_token_block_rows_of_any_length(case):
     out, idx = run_forward(w)
     assert F.fff_get_option("last_path") == 4 and "token_block_kernel" in F.fff_last_launch(), F.fff_last_launch()
     _log("rows D=%d O=%d" % (D, O), check_against_oracle(w, out, idx))
+
+
+ROWS = [
+    # rows that are not whole 16-byte pieces, on batches past the one-block-per-token launch: T, D, O, depth, L, act, dtype
+    # (16 lanes a token up to 64 pieces, a wave up to 256; output rows of up to 16 elements go element by element)
+    (3073, 9, 9, 3, 1, W.ACT_RELU, W.DTYPE_BF16),
+    (3080, 121, 16, 6, 4, W.ACT_GELU, W.DTYPE_BF16),
+    (4001, 129, 17, 5, 5, W.ACT_RELU, W.DTYPE_BF16),
+    (3075, 255, 25, 0, 33, W.ACT_GELU, W.DTYPE_BF16),
+    (3073, 511, 203, 4, 3, W.ACT_GELU, W.DTYPE_BF16),
+    (3074, 513, 1, 7, 64, W.ACT_RELU, W.DTYPE_BF16),
+    (3079, 1025, 40, 2, 2, W.ACT_GELU, W.DTYPE_BF16),
+    (3073, 2047, 300, 3, 7, W.ACT_GELU, W.DTYPE_BF16),
+    (3100, 5, 3, 2, 2, W.ACT_GELU, W.DTYPE_F32),
+    (3085, 255, 18, 6, 9, W.ACT_RELU, W.DTYPE_F32),
+    (3073, 257, 33, 4, 1, W.ACT_GELU, W.DTYPE_F32),
+    (3077, 1023, 65, 3, 6, W.ACT_GELU, W.DTYPE_F32),
+]
+
+
+@pytest.mark.parametrize("case", ROWS, ids=["%dx%d_to_%d_d%d_L%d_%s" % (c[:5] + (("f32", "bf16")[c[6] == W.DTYPE_BF16],)) for c in ROWS])
+def test_rows_at_any_element(case):
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L, act, dtype = case
+    print("\n[case] rows at any element T=%d D=%d O=%d depth=%d L=%d dtype=%d seed 6" % (T, D, O, depth, L, dtype), flush=True)
+    w = W.make_layer("rows", T, D, O, depth, L, act, dtype, seed=6)
+    dev = to_device(w)
+    out, idx = run_forward(w, dev)
+    assert "fused_rows_kernel" in F.fff_last_launch()
+    check_against_oracle(w, out, idx)
+    if depth:
+        # an infinite last weight of the root (in a window that repeats elements) decides as it does element by element
+        dev["node_w"][0, -1] = float("inf")
+        _, idx = run_forward(w, dev)
+        F.fff_set_option("path", 3)
+        try:
+            _, want = run_forward(w, dev)
+        finally:
+            F.fff_set_option("path", 0)
+        top = depth - 1
+        assert torch.equal(idx >> top, want >> top)
