@@ -275,10 +275,16 @@ int choose_path(const Problem& p) {
     // (measured crossovers on 768-wide rows: the fused launch, with its smallest tiles, takes 9-12 us
     // from 256 to 2048 tokens, this one 9 us up to 512 tokens and 13-16 at 1024; leaves too wide for
     // the fused launch leave only the staged path, which overtakes between 2048 and 4096 tokens)
-    if (g_opt.path == kPathAuto && token_ok &&
-        p.T <= (fused_ok ? g_opt.token_max_T : 6 * g_opt.token_max_T))
-        return kPathToken;
-    if (!fused_ok && !staged_ok) return token_ok && p.T <= 6 * g_opt.token_max_T ? kPathToken : kPathGeneric;
+    // Rows that are not whole pieces leave fused_rows_kernel, whose time hardly grows with the batch but with every neuron
+    // (token block / rows, us a launch: 301 bf16 features, 8 neurons, 512 tokens 7.6/10.4, 768 10.7/10.4; 999, 32 neurons, 1024
+    // 23.4/29.1, 1536 33.6/30.2; 599 fp32, 2 neurons, 256 6.1/6.4, 512 8.0/6.6; 77, 4 neurons, 512 6.6/4.2).
+    int64_t token_limit = fused_ok ? g_opt.token_max_T : 6 * g_opt.token_max_T;
+    if (!fused_ok && !staged_ok && rows_shape_ok(p)) {
+        const int64_t limit = g_opt.token_max_T / 2 + 36 * (int64_t)p.L;
+        if (limit < token_limit) token_limit = limit;
+    }
+    if (g_opt.path == kPathAuto && token_ok && p.T <= token_limit) return kPathToken;
+    if (!fused_ok && !staged_ok) return token_ok && p.T <= token_limit ? kPathToken : kPathGeneric;
     // The fused launch gathers, per token, the leaf's output-weight and bias rows from a table of
     // 2^depth (leaf_width + 1) rows.  Once that table outgrows the L2 of an XCD most of those rows
     // come back from memory; the launch cut in two (walk and hidden neurons per token, then the
@@ -487,7 +493,7 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
     if (path == kPathGeneric) {
         // rows of at least one piece by 16-byte pieces at any element (20011 tokens of 77 features: 7.5 us against 19.8 element by
         // element); option path = 3 asks for the element-wise kernel
-        hipError_t e = g_opt.path == kPathAuto && rows_shape_ok(p) ? launch_fused_rows(p, leaf_idx, s)
+        hipError_t e = g_opt.path != kPathGeneric && rows_shape_ok(p) ? launch_fused_rows(p, leaf_idx, s)
                                                                    : launch_fused_generic(p, leaf_idx, s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "generic kernel launch");
     }
@@ -838,7 +844,8 @@ static int64_t* option_slot(const char* name) {
 
 // Experiment switches (fff_debug_option); 0 = the built-in choice everywhere.
 //   "token_max_T"    batches of up to this many tokens take the one-block-per-token launch (6 times
-//                    that where leaf_width > 8 rules out the fused launch); default 512
+//                    that where leaf_width > 8 rules out the fused launch, half of it and 36 a
+//                    neuron for rows that are not whole pieces); default 512
 //   "walk_tpg", "walk_block", "walk_top", "walk_bpc", "walk_prefetch"
 //                    descent / fused kernel: tokens per lane group, threads per block, k + 1 = at most
 //                    k LDS-staged levels, persistent blocks per compute unit, next-tile prefetch;

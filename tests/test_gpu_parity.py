@@ -642,6 +642,8 @@ ROWS = [
     (3079, 1025, 40, 2, 2, W.ACT_GELU, W.DTYPE_BF16),
     (3073, 2047, 300, 3, 7, W.ACT_GELU, W.DTYPE_BF16),
     (3100, 5, 3, 2, 2, W.ACT_GELU, W.DTYPE_F32),
+    (545, 301, 301, 8, 8, W.ACT_GELU, W.DTYPE_BF16),        # the first batch past the one-block-per-token launch
+    (1409, 99, 99, 3, 32, W.ACT_RELU, W.DTYPE_BF16),
     (3085, 255, 18, 6, 9, W.ACT_RELU, W.DTYPE_F32),
     (3073, 257, 33, 4, 1, W.ACT_GELU, W.DTYPE_F32),
     (3077, 1023, 65, 3, 6, W.ACT_GELU, W.DTYPE_F32),
