@@ -322,7 +322,9 @@ def test_block_random_shapes(case):
     # one block per token: rows that start anywhere, wide and narrow nodes, several waves a row, short and long outputs
     ("token_77", 50, 77, 77, 5, 4, 3, W.ACT_GELU, BF16, True, True), ("token_1x", 33, 520, 9, 7, 1, 17, W.ACT_RELU, BF16, True, False),
     ("token_64n", 20, 1030, 1030, 3, 64, 2, W.ACT_GELU, BF16, True, True), ("token_f32", 41, 2050, 5, 4, 3, 66, W.ACT_GELU, F32, True, False),
-    ("token_plain", 29, 4090, 4090, 3, 9, 1, W.ACT_RELU, F32, False, True)], ids=lambda c: c[0])
+    ("token_plain", 29, 4090, 4090, 3, 9, 1, W.ACT_RELU, F32, False, True),
+    # larger batches of rows that are not whole pieces, whose tokens meet at least 80 chunks of 64 elements (80, 115)
+    ("token_far", 1025, 257, 33, 4, 3, 4, W.ACT_GELU, F32, True, False), ("token_far_bf16", 1100, 301, 301, 5, 4, 3, W.ACT_RELU, BF16, True, True)], ids=lambda c: c[0])
 def test_block_one_block_per_token(case):
     import paper_2308_14711_amd as F
     print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5" % case, flush=True)
