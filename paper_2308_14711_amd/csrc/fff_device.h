@@ -132,8 +132,8 @@ __device__ __forceinline__ void store_stream(uint4* p, const uint4& v) {
 // one is the window [n - VE, n), so that every access lies inside the row (n >= VE).  Rows then start at any
 // element: the 16-byte accesses are declared with the alignment of an element, which costs the compiler nothing
 // (gfx950 takes global dwordx4 accesses at any address) and the memory system one more line per 1 KB.  A window
-// repeats elements of the piece before it: a token row drops them (drop_first), so that whatever the
-// weight rows hold there does not count; an output row writes them twice, with the same value.
+// repeats elements of the piece before it: a product drops them on both sides (drop_first on the token and as a mask on the
+// weights: zeros of the token alone would make NaN of an infinite weight); an output row writes them twice, with the same value.
 typedef u32x4_t u32x4_any_t __attribute__((aligned(2)));
 __device__ __forceinline__ uint4 load_any(const void* p) {
     const u32x4_t v = *(const u32x4_any_t*)p;

@@ -80,7 +80,8 @@ __device__ __forceinline__ void wave_sums_of_8(const float (&v)[8], float (&out)
 // SPLIT: log2 H; NV: pieces of a row per lane; BLOCK: wide nodes on the normalised token, which is kept in fp32.
 //
 // No load is predicated by lane (that compiles to guarded loads and a wait each): lanes past the end of a row read
-// its last window against zeros of the token row; whole waves skip the rows that are not there.
+// its last window and drop the result, and elements that a last window repeats are cleared on both sides of the
+// product (0 * inf is NaN); whole waves skip the rows that are not there.
 // With two waves a SIMD every instruction of a wave costs 4 to 8 cycles, as much in all as the memory round trips: row addresses are made
 // by the lanes at once (lane q: row q), sums reduced eight at a time, the cases told apart by templates.
 template <bool BF16, int SPLIT, int NV, int SRC, bool BLOCK>
@@ -101,8 +102,14 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
     const int c0 = part * (NV * kWave) + lane;      // this lane's first piece of an input row
     const int64_t t = blockIdx.x;
     int off[NV];
+    bool past[NV];      // the piece lies past the row's end
 #pragma unroll
-    for (int v = 0; v < NV; ++v) off[v] = piece_offset(c0 + v * kWave, a.xbytes);
+    for (int v = 0; v < NV; ++v) {
+        off[v] = piece_offset(c0 + v * kWave, a.xbytes);
+        past[v] = 16 * (c0 + v * kWave) >= a.xbytes;
+    }
+    // does this wave hold a window that repeats elements of the piece before it?
+    const bool repeats = (a.xbytes & 15) != 0 && a.xbytes / 16 / (NV * kWave) == part;
 
     // the token row as loaded, and in fp32 where it is normalised
     uint4 xv[NV], w[kRows][NV];
@@ -127,25 +134,36 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
         float p[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) p[i] = 0.0f;
+        if (repeats) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const uint4 held = drop_first<BF16>(make_uint4(~0u, ~0u, ~0u, ~0u), c0 + v * kWave, a.xbytes);
+#pragma unroll
+                for (int i = 0; i < kRows; ++i)
+                    if (q0 + i * kSlots < rows)
+                        w[i][v] = make_uint4(w[i][v].x & held.x, w[i][v].y & held.y, w[i][v].z & held.z, w[i][v].w & held.w);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < kRows; ++i) {
             if (q0 + i * kSlots >= rows) continue;
-            float d = 0.0f;
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
+                float d = 0.0f;
                 if constexpr (BLOCK) {
-                    float f[E];
+                    float f[E], d1 = 0.0f;
                     widen<BF16>(w[i][v], f);
 #pragma unroll
                     for (int e = 0; e < E; e += 2) {
-                        p[i] = fmaf(f[e], z[v][e], p[i]);
-                        d = fmaf(f[e + 1], z[v][e + 1], d);
+                        d = fmaf(f[e], z[v][e], d);
+                        d1 = fmaf(f[e + 1], z[v][e + 1], d1);
                     }
+                    d += d1;
                 } else {
-                    p[i] = Elem<BF16>::dot(xv[v], w[i][v], p[i]);
+                    d = Elem<BF16>::dot(xv[v], w[i][v], d);
                 }
+                p[i] += past[v] ? 0.0f : d;
             }
-            if (BLOCK) p[i] += d;
         }
         float sum[2];
         wave_sums_of_8(p, sum);

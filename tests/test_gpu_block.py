@@ -330,3 +330,46 @@ def test_block_one_block_per_token(case):
     print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5" % case, flush=True)
     _check(case)
     assert "token_block_kernel" in F.fff_last_launch(), F.fff_last_launch()
+
+
+INFINITE = [
+    # rows that leave lanes idle, end in a window that repeats elements, or both
+    # name,       T,  D,    O,   depth, n, L, act,        dtype, norm,  residual
+    ("f32_64",    50, 64,   24,  3, 2, 3, W.ACT_RELU, F32,  True,  False), ("bf16_77",   50, 77,   77, 3, 4, 3, W.ACT_RELU, BF16, True,  True),
+    ("bf16_200",  50, 200,  40,  3, 1, 5, W.ACT_RELU, BF16, False, False), ("bf16_768",  50, 768,  768, 3, 3, 2, W.ACT_RELU, BF16, True, True),
+    ("f32_2052",  40, 2052, 16,  2, 2, 3, W.ACT_RELU, F32,  True,  False), ("bf16_4099", 40, 4099, 32, 2, 2, 2, W.ACT_RELU, BF16, True, False),
+]
+
+
+def _check_infinite(case, launched):
+    """An infinite last weight of the root's first hidden neuron and of every leaf's second neuron: routing and
+    infinities as the oracle has them, which multiplies every element once."""
+    import torch
+    import paper_2308_14711_amd as F
+    name, T, D, O, depth, n, L, act, dtype, norm, residual = case
+    print("\n[case] block, infinite weights, %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 31" % case, flush=True)
+    x, ln, nodes, leaves = _inputs(name, T, D, O, depth, n, L, act, dtype, norm, 31)
+    inf = np.uint16(0x7F80) if dtype == BF16 else np.float32(np.inf)
+    nodes, leaves = [a.copy() for a in nodes], [a.copy() for a in leaves]
+    nodes[0][0, 0, -1] = inf
+    leaves[0][:, 1, -1] = inf
+    out = torch.full((T, O), 7.0, dtype=torch.bfloat16 if dtype == BF16 else torch.float32, device="cuda")
+    idx = torch.full((T,), -9, dtype=torch.int32, device="cuda")
+    F.fff_forward_block(_upload(x), *[None if a is None else _upload(a) for a in ln], 1e-5, *[_upload(a) for a in nodes],
+                        *[_upload(a) for a in leaves], depth, n, L, act, residual, out, idx)
+    torch.cuda.synchronize()
+    assert launched in F.fff_last_launch(), F.fff_last_launch()
+    ref_out, ref_idx, margin = oracle.forward_block(x, ln[0], ln[1], 1e-5, *nodes, *leaves, depth, n, L, act, residual)
+    same = idx.cpu().numpy() == ref_idx
+    assert (margin[~same] < ROUTING_MARGIN).all() and same.sum() > T // 2, "routing differs from the oracle"
+    got, want = out_to_f64(out)[same], ref_out[same]
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
+    assert np.array_equal(np.isinf(got), np.isinf(want))
+    fin = np.isfinite(want)
+    scale = np.abs(np.where(fin, want, 0)).max(axis=1, keepdims=True) + 1e-30
+    assert (np.abs(np.where(fin, got, 0) - np.where(fin, want, 0)) <= TOL[dtype] * scale).all()
+
+
+@pytest.mark.parametrize("case", INFINITE, ids=[c[0] for c in INFINITE])
+def test_block_infinite_weights_one_block_per_token(case):
+    _check_infinite(case, "token_block_kernel")

@@ -672,3 +672,54 @@ def test_rows_at_any_element(case):
             F.fff_set_option("path", 0)
         top = depth - 1
         assert torch.equal(idx >> top, want >> top)
+
+
+def _same_values(got, want, tol):
+    """Equal infinities and NaNs, and finite values within tol of the row's largest finite one."""
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    assert np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
+    fin = np.where(np.isfinite(want), want, 0.0)
+    err = np.abs(np.where(np.isfinite(got), got, 0.0) - fin).max(axis=1) / np.maximum(np.abs(fin).max(axis=1), 1e-30)
+    assert err.max() <= tol
+
+
+# rows that leave lanes of the one-block-per-token kernel idle, end in a window that repeats elements, or both
+INFINITE = [(64, 24, W.DTYPE_F32), (77, 9, W.DTYPE_BF16), (301, 301, W.DTYPE_BF16), (768, 768, W.DTYPE_BF16), (784, 10, W.DTYPE_F32),
+            (1030, 33, W.DTYPE_BF16), (2052, 16, W.DTYPE_F32), (4099, 40, W.DTYPE_BF16), (4104, 8, W.DTYPE_BF16), (8184, 8, W.DTYPE_BF16)]
+
+
+@pytest.mark.parametrize("where", ["node", "leaf", "given"])
+@pytest.mark.parametrize("case", INFINITE, ids=["D%d_O%d_%s" % (c[0], c[1], ("f32", "bf16")[c[2] == W.DTYPE_BF16]) for c in INFINITE])
+def test_infinite_weights_on_small_batches(case, where):
+    """0 * inf is NaN: an infinite last weight of a row must not meet the zeros that stand for what the row does not
+    hold.  Against the oracle, which multiplies every element once."""
+    import torch
+    import paper_2308_14711_amd as F
+    D, O, dtype = case
+    T, depth, L = 61, 3, 5
+    print("\n[case] infinite weights (%s) T=%d D=%d O=%d dtype=%d seed 23" % (where, T, D, O, dtype), flush=True)
+    w = W.make_layer("inf", T, D, O, depth, L, W.ACT_RELU, dtype, seed=23)
+    ins = [a.copy() for a in oracle_inputs(w)]
+    inf = np.uint16(0x7F80) if dtype == W.DTYPE_BF16 else np.float32(np.inf)
+    if where == "node":
+        ins[1][0, -1] = inf                   # the root's last weight
+    else:
+        ins[3][:, 1, -1] = inf                # the last input weight of every leaf's second neuron
+    dev = {}
+    for k, a in zip(W.TENSORS, ins):
+        t = torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).cuda()
+        dev[k] = t.view(torch.bfloat16) if a.dtype == np.uint16 else t
+    ref_out, ref_idx, margin = oracle.forward_hard(*ins, depth, L, W.ACT_RELU)
+    if where == "given":
+        keep = np.ones(T, bool)
+        idx = torch.from_numpy(ref_idx.astype(np.int32)).cuda()
+        out = torch.full((T, O), 7.0, dtype=dev["x"].dtype, device="cuda")
+        F.fff_leaf_forward(dev["x"], dev["leaf_w1"], dev["leaf_b1"], dev["leaf_w2"], dev["leaf_b2"], idx, depth, L, W.ACT_RELU, out)
+        torch.cuda.synchronize()
+    else:
+        out, idx = run_forward(w, dev)
+        keep = idx.cpu().numpy() == ref_idx
+        assert (margin[~keep] < ROUTING_MARGIN).all(), "routing differs from the oracle"
+        assert keep.sum() > T // 2
+    assert "token_block_kernel" in F.fff_last_launch(), F.fff_last_launch()
+    _same_values(out_to_f64(out)[keep], ref_out[keep], TOL[dtype])
