@@ -77,14 +77,16 @@ __device__ __forceinline__ void wave_sums_of_8(const float (&v)[8], float (&out)
     }
 }
 
-// SPLIT: log2 H; NV: pieces of a row per lane; BLOCK: wide nodes on the normalised token, which is kept in fp32.
+// SPLIT: log2 H; NV: pieces of a row per lane; BLOCK: wide nodes on the normalised token, which is kept in fp32;
+// ODD: rows that are not whole pieces.
 //
 // No load is predicated by lane (that compiles to guarded loads and a wait each): lanes past the end of a row read
-// its last window and drop the result, and elements that a last window repeats are cleared on both sides of the
-// product (0 * inf is NaN); whole waves skip the rows that are not there.
+// its last window; whole waves skip the rows that are not there.  What such lanes and windows repeat must not count even where it
+// is infinite (0 * inf is NaN): of whole pieces a lane past the row drops its sum, of odd rows the weights are cleared like the
+// token.  (The clearing behind a branch cost every launch a wait: 64 tokens of 768 features, depth 11 5.7 -> 6.3 us.)
 // With two waves a SIMD every instruction of a wave costs 4 to 8 cycles, as much in all as the memory round trips: row addresses are made
 // by the lanes at once (lane q: row q), sums reduced eight at a time, the cases told apart by templates.
-template <bool BF16, int SPLIT, int NV, int SRC, bool BLOCK>
+template <bool BF16, int SPLIT, int NV, int SRC, bool BLOCK, bool ODD>
 __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const TokenArgs a) {
     constexpr int E = Elem<BF16>::kPerVec;
     constexpr int H = 1 << SPLIT, kSlots = kTokenWaves >> SPLIT;
@@ -108,8 +110,12 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
         off[v] = piece_offset(c0 + v * kWave, a.xbytes);
         past[v] = 16 * (c0 + v * kWave) >= a.xbytes;
     }
-    // does this wave hold a window that repeats elements of the piece before it?
-    const bool repeats = (a.xbytes & 15) != 0 && a.xbytes / 16 / (NV * kWave) == part;
+    // what a piece of a row holds that the pieces before it do not
+    uint4 held[ODD ? NV : 1];
+    if constexpr (ODD) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) held[v] = drop_first<BF16>(make_uint4(~0u, ~0u, ~0u, ~0u), c0 + v * kWave, a.xbytes);
+    }
 
     // the token row as loaded, and in fp32 where it is normalised
     uint4 xv[NV], w[kRows][NV];
@@ -134,22 +140,14 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
         float p[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) p[i] = 0.0f;
-        if (repeats) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const uint4 held = drop_first<BF16>(make_uint4(~0u, ~0u, ~0u, ~0u), c0 + v * kWave, a.xbytes);
-#pragma unroll
-                for (int i = 0; i < kRows; ++i)
-                    if (q0 + i * kSlots < rows)
-                        w[i][v] = make_uint4(w[i][v].x & held.x, w[i][v].y & held.y, w[i][v].z & held.z, w[i][v].w & held.w);
-            }
-        }
 #pragma unroll
         for (int i = 0; i < kRows; ++i) {
             if (q0 + i * kSlots >= rows) continue;
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 float d = 0.0f;
+                if constexpr (ODD)
+                    w[i][v] = make_uint4(w[i][v].x & held[v].x, w[i][v].y & held[v].y, w[i][v].z & held[v].z, w[i][v].w & held[v].w);
                 if constexpr (BLOCK) {
                     float f[E], d1 = 0.0f;
                     widen<BF16>(w[i][v], f);
@@ -162,7 +160,8 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
                 } else {
                     d = Elem<BF16>::dot(xv[v], w[i][v], d);
                 }
-                p[i] += past[v] ? 0.0f : d;
+                d = !ODD && past[v] ? 0.0f : d;
+                p[i] = v > 0 ? p[i] + d : d;
             }
         }
         float sum[2];
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(kTokenBlock, 4) void token_block_kernel(const Token
     }
 }
 
-template <bool BF16, int SPLIT, int NV, int SRC, bool BLOCK>
+template <bool BF16, int SPLIT, int NV, int SRC, bool BLOCK, bool ODD>
 hipError_t run_token(TokenArgs a, hipStream_t s) {
     constexpr int E = Elem<BF16>::kPerVec;
     constexpr int H = 1 << SPLIT;
@@ -428,17 +427,22 @@ hipError_t run_token(TokenArgs a, hipStream_t s) {
                                               (a.out_vec && a.groups > 1 ? (size_t)a.groups * a.opieces * E : 0));
     note_launch("token_block_kernel<%s,%d,%d,%s> levels=%d %s", BF16 ? "bf16" : "f32", H, NV,
                 BLOCK ? "block" : SRC == kFromTree ? "hard" : SRC == kFromGate ? "gate" : "list", a.levels, a.out_vec ? "vec" : "elem");
-    token_block_kernel<BF16, SPLIT, NV, SRC, BLOCK><<<dim3((unsigned)a.T), dim3(kTokenBlock), lds_bytes, s>>>(a);
+    token_block_kernel<BF16, SPLIT, NV, SRC, BLOCK, ODD><<<dim3((unsigned)a.T), dim3(kTokenBlock), lds_bytes, s>>>(a);
     return hipGetLastError();
 }
 
+template <bool BF16, int SRC, bool BLOCK, bool ODD>
+hipError_t pick_rows(const TokenArgs& a, int pieces, hipStream_t s) {
+    if (pieces <= 64) return run_token<BF16, 0, 1, SRC, BLOCK, ODD>(a, s);
+    if (pieces <= 128) return run_token<BF16, 1, 1, SRC, BLOCK, ODD>(a, s);
+    if (pieces <= 256) return run_token<BF16, 2, 1, SRC, BLOCK, ODD>(a, s);
+    if (pieces <= 512) return run_token<BF16, 3, 1, SRC, BLOCK, ODD>(a, s);
+    return run_token<BF16, 3, 2, SRC, BLOCK, ODD>(a, s);
+}
 template <bool BF16, int SRC, bool BLOCK>
 hipError_t dispatch_token(const TokenArgs& a, int pieces, hipStream_t s) {
-    if (pieces <= 64) return run_token<BF16, 0, 1, SRC, BLOCK>(a, s);
-    if (pieces <= 128) return run_token<BF16, 1, 1, SRC, BLOCK>(a, s);
-    if (pieces <= 256) return run_token<BF16, 2, 1, SRC, BLOCK>(a, s);
-    if (pieces <= 512) return run_token<BF16, 3, 1, SRC, BLOCK>(a, s);
-    return run_token<BF16, 3, 2, SRC, BLOCK>(a, s);
+    if (SRC != kFromGate && (a.xbytes & 15)) return pick_rows<BF16, SRC, BLOCK, SRC != kFromGate>(a, pieces, s);   // (the gating takes whole pieces)
+    return pick_rows<BF16, SRC, BLOCK, false>(a, pieces, s);
 }
 
 template <bool BF16> hipError_t pick_token(const TokenArgs& a, int pieces, bool wide, hipStream_t s) {
