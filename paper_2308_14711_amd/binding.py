@@ -46,7 +46,9 @@ def lib() -> ctypes.CDLL:
     """The loaded C-ABI library.  Built first if no library is there at all."""
     global _lib
     if _lib is None:
-        if not os.path.exists(_build.LIB):
+        # both libraries or neither: a rebuild after this one is loaded would put a second copy of it, with
+        # options and workspaces of its own, behind the native module
+        if _build.missing():
             _build.build_library(force=True)
         # PyTorch ships a HIP runtime of its own; the tensors and streams handed to this library
         # live in that one.  Loading torch first makes the library bind to the same runtime instance
@@ -99,7 +101,8 @@ def _native():
     if _native_module is None:
         lib()
         if not os.path.exists(_build.TORCH_LIB):
-            _build.build_library(force=True)
+            raise RuntimeError("%s is gone since %s was loaded: build again and start anew"
+                               % (os.path.basename(_build.TORCH_LIB), os.path.basename(_build.LIB)))
         from . import _fff_torch
         _native_module = _fff_torch
     return _native_module

@@ -118,6 +118,11 @@ def _compile(src: str) -> str:
     return obj
 
 
+def missing() -> bool:
+    """Whether one of the libraries that binding.py loads has yet to be built."""
+    return not (os.path.exists(LIB) and os.path.exists(TORCH_LIB))
+
+
 def stale() -> bool:
     libs = (LIB, PROBE_LIB, TORCH_LIB)
     if not all(os.path.exists(f) for f in libs):

@@ -319,3 +319,19 @@ def test_header_is_plain_c99_and_links_from_c(tmp_path):
                            str(src), "-o", str(exe), "-L", libdir, "-lfff_hip", "-Wl,-rpath," + libdir])
     out = subprocess.check_output([str(exe)], text=True).strip().split("|")
     assert int(out[0]) == F.fff_version() and out[1] == "out overlaps x" and out[2] == "1" and out[3] == "1"
+
+
+def test_nothing_is_rebuilt_behind_a_loaded_library(L, monkeypatch, tmp_path):
+    """A second copy of the library, with options and workspaces of its own, would take the forward calls."""
+    from paper_2308_14711_amd import binding
+    from paper_2308_14711_amd import build as b
+    built = []
+    monkeypatch.setattr(b, "build_library", lambda *a, **k: built.append(1))
+    monkeypatch.setattr(b, "TORCH_LIB", str(tmp_path / "not_there.so"))
+    monkeypatch.setattr(binding, "_native_module", None)
+    with pytest.raises(RuntimeError, match="not_there.so"):
+        binding._native()
+    assert not built
+    # nothing loaded yet: the missing half is built before the first library is
+    monkeypatch.setattr(binding, "_lib", None)
+    assert binding.lib() is not None and built == [1]
