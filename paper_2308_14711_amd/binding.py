@@ -95,12 +95,20 @@ def lib() -> ctypes.CDLL:
 _native_module = None
 
 
+class _NotBuilt:
+    """In the place of the native module where torch came without its headers: no call is ordinary."""
+    forward_hard = moe_top1_forward = forward_soft = forward_block = staticmethod(lambda *args: -1)
+
+
 def _native():
     """The native half of the binding (built with the library, loaded after it)."""
     global _native_module
     if _native_module is None:
         lib()
         if not os.path.exists(_build.TORCH_LIB):
+            if not _build.torch_headers():
+                _native_module = _NotBuilt
+                return _native_module
             raise RuntimeError("%s is gone since %s was loaded: build again and start anew"
                                % (os.path.basename(_build.TORCH_LIB), os.path.basename(_build.LIB)))
         from . import _fff_torch

@@ -3,6 +3,7 @@ library for gfx950 with hipcc, in-tree."""
 from __future__ import annotations
 
 import concurrent.futures
+import importlib.util
 import os
 import re
 import subprocess
@@ -92,12 +93,16 @@ def _object(src: str) -> str:
     return os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
 
 
-def _torch_dirs() -> tuple:
-    """(include directories, library directory) of the installed torch."""
-    import torch
-    root = os.path.dirname(torch.__file__)
-    inc = os.path.join(root, "include")
-    return [inc, os.path.join(inc, "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]], os.path.join(root, "lib")
+def torch_headers() -> list:
+    """Include directories of the native half of the binding; empty where torch, its C++ headers or Python's are not installed."""
+    spec = importlib.util.find_spec("torch")
+    if spec is None:
+        return []
+    inc = os.path.join(os.path.dirname(spec.origin), "include")
+    python = sysconfig.get_paths()["include"]
+    there = os.path.exists(os.path.join(inc, "torch", "csrc", "autograd", "python_variable.h")) and \
+        os.path.exists(os.path.join(python, "Python.h"))
+    return [inc, os.path.join(inc, "torch", "csrc", "api", "include"), python] if there else []
 
 
 def _compile(src: str) -> str:
@@ -106,7 +111,7 @@ def _compile(src: str) -> str:
         import torch
         cmd = [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
                "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I/opt/rocm/include"] + \
-              [f for d in _torch_dirs()[0] for f in ("-isystem", d)] + ["-c", os.path.join(CSRC, src), "-o", obj]
+              [f for d in torch_headers() for f in ("-isystem", d)] + ["-c", os.path.join(CSRC, src), "-o", obj]
     else:
         cmd = [_hipcc()] + HIPCC_FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -120,11 +125,11 @@ def _compile(src: str) -> str:
 
 def missing() -> bool:
     """Whether one of the libraries that binding.py loads has yet to be built."""
-    return not (os.path.exists(LIB) and os.path.exists(TORCH_LIB))
+    return not os.path.exists(LIB) or not os.path.exists(TORCH_LIB) and bool(torch_headers())
 
 
 def stale() -> bool:
-    libs = (LIB, PROBE_LIB, TORCH_LIB)
+    libs = (LIB, PROBE_LIB) + ((TORCH_LIB,) if torch_headers() else ())
     if not all(os.path.exists(f) for f in libs):
         return True
     t = min(os.path.getmtime(f) for f in libs)
@@ -154,21 +159,26 @@ def _object_is_current(src: str) -> bool:
 def build_library(force: bool = True, jobs: int = 8) -> str:
     """Compile every kernel source for gfx950 and link the shared libraries.  force=False compiles
     only the sources that changed since their object file was made (or nothing, if the libraries
-    are newer than every source)."""
+    are newer than every source).  The C-ABI library needs no torch: without torch's headers the native half of
+    the binding is left out (binding.py then makes every call through ctypes)."""
     if not force and not stale():
         return LIB
     packed_fp32_is_off()
     os.makedirs(OBJ_DIR, exist_ok=True)
-    todo = [s for s in [TORCH_SOURCE] + SOURCES + PROBE_SOURCES if force or not _object_is_current(s)]
+    torch_sources = [TORCH_SOURCE] if torch_headers() else []
+    todo = [s for s in torch_sources + SOURCES + PROBE_SOURCES if force or not _object_is_current(s)]
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
         list(ex.map(_compile, todo))
     _link([_object(s) for s in SOURCES], LIB)
     _link([_object(s) for s in PROBE_SOURCES], PROBE_LIB)
-    # the torch libraries are found in the process (binding.py imports torch first), libfff_hip.so next to it
-    torch_lib = _torch_dirs()[1]
-    _link([_object(TORCH_SOURCE)], TORCH_LIB,
-          ["-L" + HERE, "-lfff_hip", "-L" + torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
-           "-Wl,-rpath,$ORIGIN"])
+    if torch_sources:
+        # the torch libraries are found in the process (binding.py imports torch first), libfff_hip.so next to it
+        torch_lib = os.path.join(os.path.dirname(torch_headers()[0]), "lib")
+        _link([_object(TORCH_SOURCE)], TORCH_LIB,
+              ["-L" + HERE, "-lfff_hip", "-L" + torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+               "-Wl,-rpath,$ORIGIN"])
+    elif os.path.exists(TORCH_LIB):
+        os.remove(TORCH_LIB)        # (of another torch: it would be loaded beside the new library)
     return LIB
 
 

@@ -335,3 +335,25 @@ def test_nothing_is_rebuilt_behind_a_loaded_library(L, monkeypatch, tmp_path):
     # nothing loaded yet: the missing half is built before the first library is
     monkeypatch.setattr(binding, "_lib", None)
     assert binding.lib() is not None and built == [1]
+
+
+def test_library_is_built_without_torch_headers(L, monkeypatch, tmp_path):
+    """The C ABI needs no torch: without its headers the native half of the binding is left out, and calls go through ctypes."""
+    from paper_2308_14711_amd import binding
+    from paper_2308_14711_amd import build as b
+    compiled, linked = [], []
+    monkeypatch.setattr(b, "packed_fp32_is_off", lambda: None)
+    monkeypatch.setattr(b, "_compile", compiled.append)
+    monkeypatch.setattr(b, "_link", lambda objs, lib, flags=(): linked.append(lib))
+    monkeypatch.setattr(b, "TORCH_LIB", str(tmp_path / "_fff_torch.so"))
+    monkeypatch.setattr(b, "OBJ_DIR", str(tmp_path))
+    assert b.torch_headers()
+    b.build_library()
+    assert b.TORCH_SOURCE in compiled and linked == [b.LIB, b.PROBE_LIB, b.TORCH_LIB]
+    compiled.clear(), linked.clear()
+    find = b.importlib.util.find_spec
+    monkeypatch.setattr(b.importlib.util, "find_spec", lambda name, *a: None if name == "torch" else find(name, *a))
+    b.build_library()
+    assert sorted(compiled) == sorted(b.SOURCES + b.PROBE_SOURCES) and linked == [b.LIB, b.PROBE_LIB]
+    monkeypatch.setattr(binding, "_native_module", None)
+    assert binding._native().forward_hard(*range(14)) == -1
