@@ -135,7 +135,12 @@ PyObject* forward_hard(PyObject*, PyObject* const* args, Py_ssize_t n) {
     a.node_b = c.need(2, {((int64_t)1 << a.depth) - 1});
     int32_t* idx = (int32_t*)c.dense(11, at::ScalarType::Int, {a.T});
     void* s = c.stream(12);
-    auto entry = PyObject_IsTrue(args[13]) == 1 ? fff_forward_hard_static : fff_forward_hard;
+    const int truth = PyObject_IsTrue(args[13]);
+    if (truth < 0) {        // a value without one: the caller's own test of it says why
+        PyErr_Clear();
+        c.ok = false;
+    }
+    auto entry = truth == 1 ? fff_forward_hard_static : fff_forward_hard;
     return answer(c, [&] {
         return entry(a.x, a.node_w, a.node_b, a.w1, a.b1, a.w2, a.b2, a.depth, a.width, a.act, a.out, idx, s, a.T, a.D,
                      a.O, c.code());

@@ -357,3 +357,11 @@ def test_library_is_built_without_torch_headers(L, monkeypatch, tmp_path):
     assert sorted(compiled) == sorted(b.SOURCES + b.PROBE_SOURCES) and linked == [b.LIB, b.PROBE_LIB]
     monkeypatch.setattr(binding, "_native_module", None)
     assert binding._native().forward_hard(*range(14)) == -1
+
+
+def test_a_flag_without_a_truth_value_is_refused_with_its_own_error(L):
+    import torch
+    import paper_2308_14711_amd as F
+    x = torch.zeros(2, 8)
+    with pytest.raises(RuntimeError, match="ambiguous"):
+        F.fff_forward_hard(x, x, x, x, x, x, x, 1, 1, 0, x, static_scratch=torch.zeros(2))
