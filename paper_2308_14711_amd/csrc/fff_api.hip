@@ -738,9 +738,9 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
     g_opt.last_block_kernel = vector_rows ? 1 : 2;
     // Small batches, and any batch whose rows are not whole pieces when its tokens meet much: the element-wise kernel's time goes with
     // the rows a token meets times their chunks of 64 elements (generic / token block, us, 24000 tokens: 20 chunks 126/256,
-    // 56 265/270, 200 955/423, 640 3940/538).  (A launch ends at 2^32 threads, 512 a token.)
+    // 56 265/270, 200 955/423, 640 3940/538).
     const int64_t chunks = ((int64_t)depth * node_size + leaf_width) * ((D + 63) / 64);
-    const bool far_rows = !vector_rows && chunks >= 80 && T <= ((int64_t)1 << 22);
+    const bool far_rows = !vector_rows && chunks >= 80;
     if ((T <= g_opt.token_max_T * 2 || far_rows) && token_wide_ok(p, node_size)) {
         WideNodes wide;
         wide.gamma = ln_gamma;

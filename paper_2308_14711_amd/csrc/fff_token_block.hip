@@ -28,6 +28,7 @@ constexpr int kTokenPieces = 8;         // 16-byte pieces of weight rows a lane 
 constexpr int kMaxLevels = 6;           // of a round trip: its decisions come out of one ballot
 constexpr int kOutGroups = 4;           // partial output rows that meet in LDS, at most
 constexpr int kTokenMaxPieces = 1024;
+constexpr int64_t kTokenMaxBlocks = 1 << 22;    // of a launch, which ends at 2^32 threads
 
 struct TokenArgs {
     const char* x;
@@ -473,19 +474,13 @@ hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s
                               const GateCandidates* gate, const WideNodes* wide) {
     const int per = p.bf16 ? 8 : 4, es = p.bf16 ? 2 : 4;
     TokenArgs a;
-    a.x = (const char*)p.x;
     a.node_w = (const char*)(wide ? wide->w1 : p.node_w);
     a.node_b = wide ? wide->b1 : p.node_b;
     a.w1 = (const char*)p.leaf_w1;
     a.b1 = p.leaf_b1;
     a.w2 = (const char*)p.leaf_w2;
     a.b2 = (const char*)p.leaf_b2;
-    a.out = (char*)p.out;
-    a.leaf_idx = leaf_idx;
-    a.given_leaf = given_leaf;
-    a.gate = gate ? *gate : GateCandidates{};
     a.wide = wide ? *wide : WideNodes{};
-    a.T = p.T;
     a.D = (int)p.D;
     a.O = (int)p.O;
     a.depth = p.depth;
@@ -496,7 +491,17 @@ hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s
     a.act = p.act;
     a.out_vec = p.O >= per;
     const int pieces = (int)((p.D + per - 1) / per);
-    return p.bf16 ? pick_token<true>(a, pieces, wide != nullptr, s) : pick_token<false>(a, pieces, wide != nullptr, s);
+    hipError_t e = hipSuccess;
+    for (int64_t t = 0; t < p.T && e == hipSuccess; t += kTokenMaxBlocks) {
+        a.x = (const char*)p.x + t * a.xbytes;
+        a.out = (char*)p.out + t * a.obytes;
+        a.leaf_idx = leaf_idx ? leaf_idx + t : nullptr;
+        a.given_leaf = given_leaf ? given_leaf + t : nullptr;
+        a.gate = gate ? GateCandidates{gate->val + t * gate->n, gate->idx + t * gate->n, gate->n} : GateCandidates{};
+        a.T = p.T - t < kTokenMaxBlocks ? p.T - t : kTokenMaxBlocks;
+        e = p.bf16 ? pick_token<true>(a, pieces, wide != nullptr, s) : pick_token<false>(a, pieces, wide != nullptr, s);
+    }
+    return e;
 }
 
 }  // namespace fff

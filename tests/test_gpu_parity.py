@@ -723,3 +723,38 @@ def test_infinite_weights_on_small_batches(case, where):
         assert keep.sum() > T // 2
     assert "token_block_kernel" in F.fff_last_launch(), F.fff_last_launch()
     _same_values(out_to_f64(out)[keep], ref_out[keep], TOL[dtype])
+
+
+def _same_bits_alone(run, T, parts):
+    """A launch over T tokens against the same tokens in calls of their own (a block computes its token alone): the same bits."""
+    import torch
+    out, idx = run(slice(0, T))
+    for part in parts:
+        o, i = run(part)
+        assert torch.equal(out[part].view(torch.int16), o.view(torch.int16)) and torch.equal(idx[part], i), part
+
+
+def test_one_block_per_token_beyond_one_launch():
+    """A launch ends at 2^32 threads, 2^23 blocks of this kernel; larger batches take several."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L = (1 << 23) + 5, 8, 8, 2, 1
+    print("\n[case] one block per token T=%d D=%d O=%d depth=%d L=%d seed 41" % (T, D, O, depth, L), flush=True)
+    dev = to_device(W.make_layer("slices", 8, D, O, depth, L, W.ACT_RELU, W.DTYPE_BF16, seed=41))
+    x = torch.randn((T, D), generator=torch.Generator(device="cuda").manual_seed(41), device="cuda").bfloat16()
+
+    def run(part):
+        n = len(range(*part.indices(T)))
+        out = torch.full((n, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+        idx = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        F.fff_forward_hard(x[part], dev["node_w"], dev["node_b"], dev["leaf_w1"], dev["leaf_b1"], dev["leaf_w2"], dev["leaf_b2"],
+                           depth, L, W.ACT_RELU, out, idx)
+        torch.cuda.synchronize()
+        assert "token_block_kernel" in F.fff_last_launch()
+        return out, idx
+
+    F.fff_set_option("path", 4)
+    try:
+        _same_bits_alone(run, T, [slice(0, 300), slice((1 << 22) - 150, (1 << 22) + 150), slice((1 << 23) - 150, T)])
+    finally:
+        F.fff_set_option("path", 0)
