@@ -284,7 +284,11 @@ int choose_path(const Problem& p) {
         if (limit < token_limit) token_limit = limit;
     }
     if (g_opt.path == kPathAuto && token_ok && p.T <= token_limit) return kPathToken;
-    if (!fused_ok && !staged_ok) return token_ok && p.T <= token_limit ? kPathToken : kPathGeneric;
+    // Whole rows of leaves wider than the staged path takes go one block a token at any batch size: their alternative is the
+    // element-wise kernel (4312 tokens of 464 bf16 features, 240 neurons: 391 us against 168).  Not so rows of other
+    // lengths (30616 tokens of 9 features, 385 neurons: 706 against 2571).
+    if (!fused_ok && !staged_ok)
+        return token_ok && (p.T <= token_limit || (p.L > 64 && token_rows_ok(p))) ? kPathToken : kPathGeneric;
     // The fused launch gathers, per token, the leaf's output-weight and bias rows from a table of
     // 2^depth (leaf_width + 1) rows.  Once that table outgrows the L2 of an XCD most of those rows
     // come back from memory; the launch cut in two (walk and hidden neurons per token, then the
@@ -434,7 +438,7 @@ int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& w
 // The leaf networks at given leaves: small batches go one block per token, larger ones are bucketed.
 int run_leaf_any(const Problem& p, const int32_t* leaf_idx, hipStream_t s) {
     if (g_opt.path != kPathStaged && token_shape_ok(p) && p.T <= 6 * g_opt.token_max_T) {
-        hipError_t e = launch_token_block(p, nullptr, s, leaf_idx);
+        hipError_t e = token_rows_better(p) ? launch_token_rows(p, nullptr, s, leaf_idx) : launch_token_block(p, nullptr, s, leaf_idx);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
     Workspace ws;
@@ -499,7 +503,7 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
     }
     if (path == kPathToken) {
         if (marks) stage_mark(s);
-        hipError_t e = launch_token_block(p, leaf_idx, s);
+        hipError_t e = token_rows_better(p) ? launch_token_rows(p, leaf_idx, s) : launch_token_block(p, leaf_idx, s);
         for (int k = 0; marks && k < 4; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
@@ -666,17 +670,18 @@ int fff_moe_top1_forward(const void* x, const void* gate_w, const void* gate_b, 
     GateCandidates gate;
     hipError_t e = launch_moe_gate(x, gate_w, gate_b, T, D, G, ws.extra, &gate, s);
     if (e != hipSuccess) return set_device_error(e, "gating kernel launch");
-    // the experts are leaves: small batches one block per token, larger ones bucketed
-    if (g_opt.path != kPathStaged && token_shape_ok(p) && T <= 6 * g_opt.token_max_T) {
+    // the experts are leaves: small batches one block per token (token_block_kernel picks the expert by itself), larger ones bucketed
+    const bool small = g_opt.path != kPathStaged && token_shape_ok(p) && T <= 6 * g_opt.token_max_T;
+    const bool picks = small && !token_rows_better(p, true);
+    if (!picks && (e = launch_moe_pick(gate, T, ei, s)) != hipSuccess) return set_device_error(e, "gating kernel launch");
+    stage_mark(s);
+    if (small) {
         g_opt.last_path = kPathToken;
-        stage_mark(s);
-        e = launch_token_block(p, expert_idx, s, nullptr, &gate);
+        e = picks ? launch_token_block(p, expert_idx, s, nullptr, &gate) : launch_token_rows(p, nullptr, s, ei);
         for (int k = 0; k < 3; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
     g_opt.last_path = kPathStaged;
-    if ((e = launch_moe_pick(gate, T, ei, s)) != hipSuccess) return set_device_error(e, "gating kernel launch");
-    stage_mark(s);
     return run_leaf_stage(p, ei, ws, s, true);
 }
 
@@ -871,11 +876,13 @@ static int64_t* option_slot(const char* name) {
 //                    were out of memory (FFF_ERR_WORKSPACE; the call after them allocates again)
 //   "soft_small_tiles" fff_forward_soft: 1 = the 64 x 128 MFMA tile for every contraction, 2 = the
 //                    small-batch kernels (slices of K) wherever they fit, 0 = by estimated time
+//   "token_kernel"   one block per token: 1 = token_block_kernel, 2 = token_rows_kernel (for the rows it takes)
 //   "walk_plain_x"   the descent reads token rows 1 = without the streaming hint, 2 = with it,
 //                    0 = without it while the batch fits half the last-level cache
 static int64_t* debug_slot(const char* name) {
     if (!name) return nullptr;
     if (!std::strcmp(name, "token_max_T")) return &g_opt.token_max_T;
+    if (!std::strcmp(name, "token_kernel")) return &g_token_kernel;
     if (!std::strcmp(name, "walk_tpg")) return &g_walk_tuning.tpg;
     if (!std::strcmp(name, "walk_block")) return &g_walk_tuning.block;
     if (!std::strcmp(name, "walk_top")) return &g_walk_tuning.top;

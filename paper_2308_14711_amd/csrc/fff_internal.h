@@ -181,6 +181,13 @@ hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s
                               const int32_t* given_leaf = nullptr, const GateCandidates* gate = nullptr,
                               const WideNodes* wide = nullptr);
 
+// The same for whole aligned rows of up to 512 pieces, a wave holding whole rows; blocks stride over the batch.
+// token_rows_better: whether it takes the call and is the faster one (picks: of a mixture, whose pick the other launch saves).
+extern int64_t g_token_kernel;      // experiment switch "token_kernel"
+bool token_rows_ok(const Problem& p);
+bool token_rows_better(const Problem& p, bool picks = false);
+hipError_t launch_token_rows(const Problem& p, int32_t* leaf_idx, hipStream_t s, const int32_t* given_leaf = nullptr);
+
 // Gating of a mixture of experts with one engaged expert (fff_moe_gate.hip).  launch_moe_gate leaves, per
 // token, the best (logit, expert) of every block of experts in `cand` (moe_gate_words(T, n_experts)
 // words); the token-block launch picks among them itself, launch_moe_pick writes expert_idx[t] =

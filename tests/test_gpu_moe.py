@@ -25,6 +25,10 @@ CASES = [
     ("small_16",       17,   72,  24,  5,  3,  True),
     ("small_32",       200,  264, 64,  9,  2,  False),
     ("small_64",       255,  520, 64,  11, 1,  True),
+    # the pick as a launch of its own before the experts run one block a token: wide experts, larger batches of short rows
+    ("wide_experts",   90,   264, 72,  3,  70, True),
+    ("wide_uneven",    300,  520, 2048, 2, 66, False),
+    ("short_rows",     1025, 64,  48,  6,  5,  True),
     ("one_token_moe",  1,    8,   8,   3,  1,  False),
     # the end point of the paper's sweep (section "Inference speed comparison": 768-wide, experts of 32
     # neurons, batch 256, up to 2^15 experts), at full size

@@ -693,6 +693,10 @@ INFINITE = [(64, 24, W.DTYPE_F32), (77, 9, W.DTYPE_BF16), (301, 301, W.DTYPE_BF1
 def test_infinite_weights_on_small_batches(case, where):
     """0 * inf is NaN: an infinite last weight of a row must not meet the zeros that stand for what the row does not
     hold.  Against the oracle, which multiplies every element once."""
+    _infinite_weights(case, where, "token_block_kernel")
+
+
+def _infinite_weights(case, where, kernel):
     import torch
     import paper_2308_14711_amd as F
     D, O, dtype = case
@@ -703,6 +707,9 @@ def test_infinite_weights_on_small_batches(case, where):
     inf = np.uint16(0x7F80) if dtype == W.DTYPE_BF16 else np.float32(np.inf)
     if where == "node":
         ins[1][0, -1] = inf                   # the root's last weight
+    elif where == "last_output":
+        ins[5][:, -1, 0] = inf                # the first output weight of every leaf's last neuron
+        ins[4][:, -1] = np.uint16(0x40A0) if dtype == W.DTYPE_BF16 else 5.0     # (which is active)
     else:
         ins[3][:, 1, -1] = inf                # the last input weight of every leaf's second neuron
     dev = {}
@@ -721,7 +728,7 @@ def test_infinite_weights_on_small_batches(case, where):
         keep = idx.cpu().numpy() == ref_idx
         assert (margin[~keep] < ROUTING_MARGIN).all(), "routing differs from the oracle"
         assert keep.sum() > T // 2
-    assert "token_block_kernel" in F.fff_last_launch(), F.fff_last_launch()
+    assert kernel in F.fff_last_launch(), F.fff_last_launch()
     _same_values(out_to_f64(out)[keep], ref_out[keep], TOL[dtype])
 
 
@@ -754,7 +761,58 @@ def test_one_block_per_token_beyond_one_launch():
         return out, idx
 
     F.fff_set_option("path", 4)
+    F.fff_debug_option("token_kernel", 1)
     try:
         _same_bits_alone(run, T, [slice(0, 300), slice((1 << 22) - 150, (1 << 22) + 150), slice((1 << 23) - 150, T)])
     finally:
         F.fff_set_option("path", 0)
+        F.fff_debug_option("token_kernel", 0)
+
+
+TOKEN_KERNELS = [
+    # which of the two one-block-per-token kernels a call takes, on both sides of the lines between them
+    # T,   D,    O,    depth, L,   dtype,        kernel
+    (3500, 64,   32,   3,     65,  W.DTYPE_BF16, "token_rows_kernel<bf16,1,3,vec>"),     # past the batch where narrower leaves leave this path
+    (3300, 72,   3,    2,     66,  W.DTYPE_F32,  "token_rows_kernel<f32,1,3,elem>"),     # output rows shorter than a piece
+    (3200, 520,  45,   4,     70,  W.DTYPE_BF16, "token_block_kernel<bf16,2,1,hard>"),   # output rows that are not whole pieces
+    (300,  1024, 1024, 3,     70,  W.DTYPE_F32,  "token_rows_kernel<f32,4,3,vec>"),
+    (41,   4096, 4096, 2,     65,  W.DTYPE_BF16, "token_rows_kernel<bf16,8,2,vec>"),
+    (300,  4096, 64,   2,     66,  W.DTYPE_BF16, "token_block_kernel<bf16,8,1,hard>"),   # long rows next to short ones
+    (257,  4096, 64,   1,     193, W.DTYPE_BF16, "token_rows_kernel<bf16,8,2,vec>"),
+    (500,  64,   64,   0,     97,  W.DTYPE_BF16, "token_rows_kernel<bf16,1,3,vec>"),
+    (256,  512,  512,  5,     12,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),   # a token a compute unit and one more
+    (257,  512,  512,  5,     12,  W.DTYPE_BF16, "token_rows_kernel<bf16,1,3,vec>"),
+    (257,  520,  512,  5,     12,  W.DTYPE_BF16, "token_block_kernel<bf16,2,1,hard>"),
+    (100,  520,  512,  5,     41,  W.DTYPE_BF16, "token_rows_kernel<bf16,2,3,vec>"),
+    (700,  256,  30,   7,     32,  W.DTYPE_BF16, "token_rows_kernel<bf16,1,3,elem>"),
+    (700,  256,  30,   7,     33,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),
+    (270,  512,  21,   4,     16,  W.DTYPE_F32,  "token_rows_kernel<f32,2,3,elem>"),
+    (3100, 301,  24,   3,     65,  W.DTYPE_BF16, "fused_generic_kernel"),                # rows of other lengths
+]
+
+
+@pytest.mark.parametrize("case", TOKEN_KERNELS, ids=["T%d_D%d_O%d_d%d_L%d_%s" % (c[:5] + (c[6].split("<")[0],)) for c in TOKEN_KERNELS])
+def test_which_kernel_takes_a_block_per_token(case):
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L, dtype, kernel = case
+    print("\n[case] token kernels T=%d D=%d O=%d depth=%d L=%d dtype=%d seed 43, %s" % case, flush=True)
+    w = W.make_layer("token_kernels", T, D, O, depth, L, W.ACT_GELU, dtype, seed=43)
+    out, idx = run_forward(w)
+    assert F.fff_last_launch().startswith(kernel), F.fff_last_launch()
+    check_against_oracle(w, out, idx)
+
+
+@pytest.mark.parametrize("case", [(64, 24, W.DTYPE_F32), (768, 768, W.DTYPE_BF16), (784, 10, W.DTYPE_F32), (2040, 8, W.DTYPE_BF16),
+                                  (3000, 30, W.DTYPE_BF16)], ids=lambda c: "D%d_O%d" % c[:2])
+@pytest.mark.parametrize("where", ["node", "leaf", "given", "last_output"])
+def test_infinite_weights_in_whole_rows(case, where):
+    """As above for the kernel whose waves hold whole rows; with five neurons three of its waves have none, and repeat the last
+    one's output weights."""
+    import paper_2308_14711_amd as F
+    F.fff_debug_option("token_kernel", 2)
+    F.fff_set_option("path", 4)
+    try:
+        _infinite_weights(case, where, "token_rows_kernel")
+    finally:
+        F.fff_set_option("path", 0)
+        F.fff_debug_option("token_kernel", 0)
