@@ -741,12 +741,20 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
                              vec_ok(leaf_b2, O, p.bf16);
     begin_device_call();
     g_opt.last_block_kernel = vector_rows ? 1 : 2;
-    // Small batches, and any batch whose rows are not whole pieces when its tokens meet much: the element-wise kernel's time goes with
-    // the rows a token meets times their chunks of 64 elements (generic / token block, us, 24000 tokens: 20 chunks 126/256,
+    // Any batch whose rows are not whole pieces when its tokens meet much: the element-wise kernel's time goes with the rows a
+    // token meets times their chunks of 64 elements (generic / token block, us, 24000 tokens: 20 chunks 126/256,
     // 56 265/270, 200 955/423, 640 3940/538).
     const int64_t chunks = ((int64_t)depth * node_size + leaf_width) * ((D + 63) / 64);
     const bool far_rows = !vector_rows && chunks >= 80;
-    if ((T <= g_opt.token_max_T * 2 || far_rows) && token_wide_ok(p, node_size)) {
+    // Small batches, from 480 calls of both sides: up to 256 tokens always (a token a compute unit), up to 512 unless the rows are
+    // short and few (313 tokens of 112 fp32 features, 7 rows met: 5.6 / 4.5 us of the kernels below), up to 1024 where a
+    // token meets enough of them: 50 short ones (932 tokens of 96, 7 rows 9.0 / 4.1; 1019 of 48 bf16, 16 rows 11.3 / 6.6),
+    // 12 long ones or ones that are not whole pieces (998 of 23, 8 rows 11.4 / 7.7).
+    const int64_t met = (int64_t)depth * node_size + leaf_width, small = g_opt.token_max_T;
+    const bool short_rows = (D > O ? D : O) * es <= 64 * 16;
+    const int64_t enough = T <= small / 2 ? 0 : T <= small ? (vector_rows && short_rows ? 12 : 0)
+                           : vector_rows ? (short_rows ? 50 : 12) : short_rows ? 12 : 0;
+    if (((T <= 2 * small && met > enough) || far_rows) && token_wide_ok(p, node_size)) {
         WideNodes wide;
         wide.gamma = ln_gamma;
         wide.beta = ln_beta;

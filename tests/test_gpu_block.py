@@ -373,3 +373,29 @@ def _check_infinite(case, launched):
 @pytest.mark.parametrize("case", INFINITE, ids=[c[0] for c in INFINITE])
 def test_block_infinite_weights_one_block_per_token(case):
     _check_infinite(case, "token_block_kernel")
+
+
+SMALL_RULE = [
+    # which side takes a small batch: the rows a token meets (depth * n + L) decide from 257 tokens on
+    ("short_few_256",   256,  112,  112,  1, 3, 4,  W.ACT_GELU, F32,  True,  True,  "token_block_kernel"),
+    ("short_few_257",   257,  112,  112,  1, 3, 4,  W.ACT_GELU, F32,  True,  True,  "block_group_kernel"),
+    ("short_13_512",    512,  112,  112,  3, 3, 4,  W.ACT_GELU, F32,  True,  True,  "token_block_kernel"),
+    ("short_13_513",    513,  112,  112,  3, 3, 4,  W.ACT_GELU, F32,  True,  True,  "block_group_kernel"),
+    ("short_51_513",    513,  512,  512,  5, 8, 11, W.ACT_RELU, BF16, True,  True,  "token_block_kernel"),
+    ("short_51_1025",   1025, 512,  512,  5, 8, 11, W.ACT_RELU, BF16, True,  True,  "block_group_kernel"),
+    ("long_few_400",    400,  1040, 1040, 1, 2, 1,  W.ACT_GELU, BF16, True,  True,  "token_block_kernel"),
+    ("long_few_600",    600,  1040, 1040, 3, 2, 6,  W.ACT_GELU, BF16, True,  True,  "block_kernel"),
+    ("long_13_600",     600,  1040, 1040, 4, 2, 5,  W.ACT_GELU, BF16, True,  True,  "token_block_kernel"),
+    ("odd_few_512",     512,  23,   23,   2, 2, 4,  W.ACT_RELU, BF16, True,  True,  "token_block_kernel"),
+    ("odd_few_513",     513,  23,   23,   2, 2, 4,  W.ACT_RELU, BF16, True,  True,  "block_generic_kernel"),
+    ("odd_13_513",      513,  23,   23,   4, 2, 5,  W.ACT_RELU, BF16, True,  False, "token_block_kernel"),
+    ("odd_long_600",    600,  601,  40,   2, 1, 1,  W.ACT_GELU, BF16, False, False, "token_block_kernel"),
+]
+
+
+@pytest.mark.parametrize("case", SMALL_RULE, ids=[c[0] for c in SMALL_RULE])
+def test_block_which_kernel_takes_a_small_batch(case):
+    import paper_2308_14711_amd as F
+    print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5, %s" % case, flush=True)
+    _check(case[:-1])
+    assert F.fff_last_launch().startswith(case[-1]), F.fff_last_launch()
