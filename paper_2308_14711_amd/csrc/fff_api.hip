@@ -882,8 +882,9 @@ static int64_t* option_slot(const char* name) {
 //                    the fold kernel whenever the descent has left counts
 //   "fail_workspace_growth" n = the next n growths of the library's own workspace fail as if the device
 //                    were out of memory (FFF_ERR_WORKSPACE; the call after them allocates again)
-//   "soft_small_tiles" fff_forward_soft: 1 = the 64 x 128 MFMA tile for every contraction, 2 = the
-//                    small-batch kernels (slices of K) wherever they fit, 0 = by estimated time
+//   "soft_small_tiles" fff_forward_soft: 1 = the 64 x 128 MFMA tile for every contraction (from 2048 tokens on, up to
+//                    255 nodes, the 128-row nodes + mixture launch), 2 = the small-batch kernels (slices of K) wherever
+//                    they fit, 0 = by estimated time
 //   "token_kernel"   one block per token: 1 = token_block_kernel, 2 = token_rows_kernel (for the rows it takes)
 //   "walk_plain_x"   the descent reads token rows 1 = without the streaming hint, 2 = with it,
 //                    0 = without it while the batch fits half the last-level cache

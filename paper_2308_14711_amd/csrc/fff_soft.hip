@@ -18,7 +18,7 @@
 #include "fff_mfma_tile.h"
 
 namespace fff {
-int64_t g_soft_small_tiles = 0;     // experiment switch: 1 = the 64 x 128 tile for every contraction, 2 = the small-batch kernels
+int64_t g_soft_small_tiles = 0;     // experiment switch: 1 = the 64 x 128 tile for every contraction (the 128-row nodes + mixture launch from 2048 rows on), 2 = the small-batch kernels
 namespace {
 
 struct SoftArgs {
@@ -890,7 +890,7 @@ hipError_t launch_forward_soft(const Problem& p, int32_t* scratch, float* mix_ou
     const bool own_weights = own_ok && hidden == kSmall;
     const int groups = small_node_groups(a.NN);
     const double fused16_cost = (double)((p.T + 4095) / 4096) * (7 + 0.0019 * a.D + (groups - 1) * (2 + 0.0025 * a.D));
-    const bool rows16 = fused_nodes && (g_soft_small_tiles == 2 || fused16_cost < 8 + big_cost(p.T, 1, a.D));
+    const bool rows16 = fused_nodes && g_soft_small_tiles != 1 && (g_soft_small_tiles == 2 || fused16_cost < 8 + big_cost(p.T, 1, a.D));
 
     // ---- nodes, mixture weights, entropy sums
     int64_t ent_parts = 0;                   // rows of partial sums somebody has left in ent_part

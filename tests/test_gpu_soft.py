@@ -219,3 +219,57 @@ def test_forward_soft_small_batch_kernels(case, tiles):
         assert tiles != 2 or "soft_small_out_kernel" in F.fff_last_launch(), F.fff_last_launch()
     finally:
         F.fff_debug_option("soft_small_tiles", 0)
+
+
+LARGE_NODES = [
+    # the 128-row nodes + mixture launch: every depth it takes (one leaf a lane up to 64 leaves, two at 128, four at 256), ragged and whole
+    # last tiles, K2 with and without zeros behind the leaves
+    # name,         T,    D,   O,  depth, L, act
+    ("nodes_d1",    2049, 64,  24, 1, 2,  W.ACT_GELU),
+    ("nodes_d2",    2176, 72,  16, 2, 1,  W.ACT_RELU),
+    ("nodes_d3",    2111, 40,  8,  3, 5,  W.ACT_GELU),
+    ("nodes_d4",    2050, 136, 40, 4, 3,  W.ACT_RELU),
+    ("nodes_d5",    2303, 96,  48, 5, 2,  W.ACT_GELU),
+    ("nodes_d6",    2200, 64,  32, 6, 1,  W.ACT_RELU),
+    ("nodes_d7",    2177, 200, 72, 7, 3,  W.ACT_GELU),
+    ("nodes_d8",    2063, 264, 64, 8, 2,  W.ACT_RELU),
+    ("nodes_d8_L3", 2304, 64,  24, 8, 3,  W.ACT_GELU),
+]
+
+
+@pytest.mark.parametrize("case", LARGE_NODES, ids=[c[0] for c in LARGE_NODES])
+def test_forward_soft_large_nodes_launch(case):
+    import paper_2308_14711_amd as F
+    F.fff_debug_option("soft_small_tiles", 1)
+    try:
+        test_forward_soft_against_the_oracle(case)
+        assert "soft_nodes_mix_kernel<128>" in F.fff_last_launch(), F.fff_last_launch()
+    finally:
+        F.fff_debug_option("soft_small_tiles", 0)
+
+
+@pytest.mark.parametrize("depth", [7, 8])
+def test_large_nodes_launch_into_a_buffer_that_is_only_4_byte_aligned(depth):
+    """As above for the 128-row launch, whose lanes store four weights as one piece at depth 8, and for a ragged last tile."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, L = 2101, 64, 32, 1
+    w = W.make_layer("mix_align", T, D, O, depth, L, W.ACT_RELU, W.DTYPE_BF16, seed=5)
+    dev = to_device(w)
+    NL = 1 << depth
+    out = torch.empty((T, O), dtype=torch.bfloat16, device="cuda")
+    aligned = torch.full((T, NL), float("nan"), dtype=torch.float32, device="cuda")
+    backing = torch.full((T * NL + 4,), float("nan"), dtype=torch.float32, device="cuda")
+    shifted = backing[1:1 + T * NL].view(T, NL)
+    assert shifted.data_ptr() % 16 == 4
+    F.fff_debug_option("soft_small_tiles", 1)
+    try:
+        for mix in (aligned, shifted):
+            F.fff_forward_soft(dev["x"], dev["node_w"], dev["node_b"], dev["leaf_w1"], dev["leaf_b1"], dev["leaf_w2"],
+                               dev["leaf_b2"], depth, L, w.act, out, mix, None)
+            assert "soft_nodes_mix_kernel<128>" in F.fff_last_launch()
+        torch.cuda.synchronize()
+    finally:
+        F.fff_debug_option("soft_small_tiles", 0)
+    assert bool(torch.isfinite(shifted).all()) and torch.equal(aligned, shifted)
+    assert bool(torch.isnan(backing[0])) and bool(torch.isnan(backing[1 + T * NL:]).all())
