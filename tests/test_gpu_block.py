@@ -399,3 +399,59 @@ def test_block_which_kernel_takes_a_small_batch(case):
     print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5, %s" % case, flush=True)
     _check(case[:-1])
     assert F.fff_last_launch().startswith(case[-1]), F.fff_last_launch()
+
+
+@pytest.fixture
+def without_small_batches():
+    """Every batch takes the kernels of large ones (but for odd rows whose tokens meet 80 chunks of 64 elements and more)."""
+    import paper_2308_14711_amd as F
+    old = F.fff_debug_option("token_max_T")
+    F.fff_debug_option("token_max_T", 0)
+    yield
+    F.fff_debug_option("token_max_T", old)
+
+
+def _large_batch_kernel(case):
+    _, T, D, O, depth, n, L, act, dtype, norm, residual = case
+    per = 8 if dtype == BF16 else 4
+    pieces = max(D, O) // per
+    if D % per or O % per or pieces > 512:
+        return "token_block_kernel" if (depth * n + L) * ((D + 63) // 64) >= 80 else "block_generic_kernel"
+    return "block_group_kernel" if pieces <= 128 else "block_kernel"
+
+
+LARGE_KERNELS = [c for c in CASES if c[1] <= 1024] + GENERIC + _random_block_cases(24, 2024) + [
+    # one-wave kernel: rows of one to eight pieces a lane
+    ("wave_f32_3",  90,  600,  600,  3, 2, 3, W.ACT_GELU, F32,  True,  True), ("wave_bf16_3", 77, 1400, 64, 4, 3, 2, W.ACT_RELU, BF16, True, False),
+    ("wave_f32_6",  50,  1400, 1400, 2, 1, 5, W.ACT_RELU, F32,  False, True), ("wave_bf16_8", 65, 4000, 4000, 2, 4, 1, W.ACT_GELU, BF16, True, True),
+    # element-wise kernel: its grid strides beyond 8192 tokens
+    ("odd_many",    8200, 21,  21,   2, 2, 3, W.ACT_GELU, F32,  True,  True), ("odd_1100",   1100, 77, 30, 3, 3, 4, W.ACT_RELU, BF16, True, False)]
+
+
+@pytest.mark.parametrize("case", LARGE_KERNELS, ids=lambda c: c[0])
+def test_block_kernels_of_large_batches_on_small_shapes(case, without_small_batches):
+    import paper_2308_14711_amd as F
+    print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5, large-batch kernels" % case, flush=True)
+    _check(case)
+    assert F.fff_last_launch().startswith(_large_batch_kernel(case)), F.fff_last_launch()
+
+
+@pytest.mark.parametrize("case", [
+    ("group_bf16", 900, 768, 768, 6, 3, 4, W.ACT_GELU, BF16, True, True), ("group_f32", 300, 128, 128, 4, 2, 2, W.ACT_RELU, F32, True, True),
+    ("wave_bf16", 130, 2048, 2048, 3, 2, 2, W.ACT_GELU, BF16, True, True), ("wave_f32", 70, 1028, 1028, 3, 2, 2, W.ACT_RELU, F32, True, True),
+    ("generic_bf16", 200, 77, 77, 4, 2, 3, W.ACT_GELU, BF16, True, True), ("generic_f32", 150, 50, 50, 3, 3, 2, W.ACT_RELU, F32, True, True)], ids=lambda c: c[0])
+def test_block_kernels_of_large_batches_in_place(case, without_small_batches):
+    import paper_2308_14711_amd as F
+    print("\n[case] block in place %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5" % case, flush=True)
+    _check(case, in_place=True)
+    assert F.fff_last_launch().startswith(_large_batch_kernel(case)), F.fff_last_launch()
+
+
+@pytest.mark.parametrize("case", GENERIC[:2] + GENERIC[4:5], ids=[c[0] for c in GENERIC[:2] + GENERIC[4:5]])
+def test_block_rows_that_are_not_whole_pieces_on_larger_batches(case):
+    """Below 80 chunks of 64 elements a token the element-wise kernel keeps every batch of more than 1024 tokens."""
+    import paper_2308_14711_amd as F
+    case = (case[0], 1025) + case[2:]
+    print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5" % case, flush=True)
+    _check(case)
+    assert F.fff_last_launch().startswith("block_generic_kernel"), F.fff_last_launch()
