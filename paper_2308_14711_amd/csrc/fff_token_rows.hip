@@ -276,17 +276,21 @@ bool token_rows_ok(const Problem& p) {
            p.D / (p.bf16 ? 8 : 4) <= 8 * kWave;
 }
 
-// The line between the two kernels, from 2200 calls of both (us, token_block / this one).
+// The line between the two kernels, from 3100 calls of both (us, token_block / this one).
 // Leaves of more than 64 neurons are this one's: token_block_kernel takes 64 at a time with a barrier and a trip each, and its
 // threads read their output pieces one after the other (107 tokens of 168 bf16 features, 160 neurons 12.8 / 9.4; 40 of 1040, 417
 // neurons 98.9 / 36.2).  But batches that fill the chip with long rows next to short ones stay there while the leaf is no wider than
 // 192, as this kernel holds both in registers of the longer one's length (2440 tokens of 376 bf16 features and 3328 outputs,
 // 85 neurons 94 / 174), and so do output rows that are not whole pieces, which it writes element by element (366 tokens of
 // 152 features and 113 outputs, 436 neurons 50 / 138), except those shorter than a piece, element-wise on both sides.
-// Below 65 neurons this one has more blocks on a compute unit and is the faster one for short rows beyond a token a compute unit
-// (529 tokens of 144 fp32 features, depth 6, 38 neurons 10.2 / 7.2), and from 40 neurons on (150 of 1312 bf16, 57
-// neurons 18.3 / 13.5).  A mixture's pick is a launch of its own with this kernel: short rows from 1024 tokens on (2825 tokens
-// of 72 features, 18 neurons 29.8 / 23.5).
+// Below 65 neurons token_block_kernel's trees are the faster ones, this kernel's leaves: up to 256 tokens the line is at 32 neurons
+// (256 of 768 bf16 features, depth 9, 32 neurons 7.8 / 7.1, 16 neurons 6.5 / 6.7).  Beyond a token a compute unit this one has
+// more blocks on it, while a row is 64 pieces (529 tokens of 144 fp32 features, depth 6, 38 neurons 10.2 / 7.2) and up to 128 for such
+// leaves, or trees of more than eight levels while there are two tokens a unit (400 of 768 bf16, depth 9, 4 neurons 7.7 / 6.8, depth
+// 4 5.6 / 6.1); longer rows take its registers (two thirds the speed at 256 pieces).  With output rows that are not whole pieces
+// only narrow leaves (1502 of 288 bf16 features, 23 outputs, 16 neurons 17.1 / 11.2; 290 of 152 fp32, 55 outputs, 32 neurons
+// 5.8 / 7.5).  A mixture's pick is a launch of its own with this kernel: short rows from 1024 tokens on (2825 tokens of 72
+// features, 18 neurons 29.8 / 23.5).
 bool token_rows_better(const Problem& p, bool picks) {
     if (g_token_kernel == 1 || !token_rows_ok(p)) return false;
     if (g_token_kernel == 2) return true;
@@ -296,8 +300,9 @@ bool token_rows_better(const Problem& p, bool picks) {
     if (p.O < per && (p.L > 64 || (full && !picks && longer <= 128))) return true;
     if (p.L > 64) return whole && (!full || longer <= 128 || 2 * shorter > longer || p.L > 192);
     if (picks) return whole && p.T > 1024 && longer <= 64;
-    if (!full) return whole && p.L > 40;
-    return whole ? longer <= 64 : (p.L <= 32 && longer <= 64) || (p.L <= 16 && longer <= 128);
+    if (!full) return whole && p.L >= 32;
+    if (!whole) return (p.L <= 32 && p.T > 512 && longer <= 64) || (p.L <= 16 && longer <= 128);
+    return longer <= 64 || (longer <= 128 && (p.L >= 32 || (p.depth > 8 && p.T <= 512)));
 }
 
 hipError_t launch_token_rows(const Problem& p, int32_t* leaf_idx, hipStream_t s, const int32_t* given_leaf) {

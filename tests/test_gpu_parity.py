@@ -783,7 +783,12 @@ TOKEN_KERNELS = [
     (256,  512,  512,  5,     12,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),   # a token a compute unit and one more
     (257,  512,  512,  5,     12,  W.DTYPE_BF16, "token_rows_kernel<bf16,1,3,vec>"),
     (257,  520,  512,  5,     12,  W.DTYPE_BF16, "token_block_kernel<bf16,2,1,hard>"),
-    (100,  520,  512,  5,     41,  W.DTYPE_BF16, "token_rows_kernel<bf16,2,3,vec>"),
+    (257,  520,  512,  9,     12,  W.DTYPE_BF16, "token_rows_kernel<bf16,2,3,vec>"),
+    (513,  520,  512,  9,     12,  W.DTYPE_BF16, "token_block_kernel<bf16,2,1,hard>"),
+    (513,  1024, 512,  5,     32,  W.DTYPE_BF16, "token_rows_kernel<bf16,2,3,vec>"),
+    (513,  1032, 512,  5,     32,  W.DTYPE_BF16, "token_block_kernel<bf16,4,1,hard>"),
+    (100,  520,  512,  5,     31,  W.DTYPE_BF16, "token_block_kernel<bf16,2,1,hard>"),
+    (100,  520,  512,  5,     32,  W.DTYPE_BF16, "token_rows_kernel<bf16,2,3,vec>"),
     (700,  256,  30,   7,     32,  W.DTYPE_BF16, "token_rows_kernel<bf16,1,3,elem>"),
     (700,  256,  30,   7,     33,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),
     (270,  512,  21,   4,     16,  W.DTYPE_F32,  "token_rows_kernel<f32,2,3,elem>"),
