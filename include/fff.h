@@ -283,7 +283,8 @@ int fff_release_workspace(void);
  *   "path"           0 = choose by shape and batch size (default), 1 = one fused launch
  *                    (walk, leaf network and output row per token; leaf_width <= 8),
  *                    2 = staged (descent, bucketing, leaf kernels), 3 = the element-wise
- *                    fallback kernel, 4 = one block per token (small batches), 5 = the fused
+ *                    kernel (as "last_path", also the automatic choice's kernel for rows that are not
+ *                    whole 16-byte pieces), 4 = one block per token (small batches), 5 = the fused
  *                    launch cut in two (walk and hidden neurons per token, then the output
  *                    rows by column slices, one slice of all rows per XCD; leaf_width <= 8,
  *                    16-byte aligned output rows); a path the shape does not allow falls back

@@ -468,8 +468,8 @@ bool token_wide_ok(const Problem& p, int node_size) { return token_shape_ok(p) &
 // 9 tokens of 2256 fp32 features, depth 14 23.3 -> 11.4 us (no kernel of this kind took the row), 174 of 2768 79 -> 14; 1003 of 1416 bf16 features,
 // 16 neurons 40.5 -> 26.7; 2 of 64, depth 11 7.0 -> 4.7; 196 of 664, depth 12 8.0 -> 7.7; odd rows, which the element-wise kernels took:
 // 3 of 671 fp32 features, 32 neurons 64 -> 7.6, 1361 of 974 74 -> 25; wide nodes: 113 tokens of 712, four neurons a node 22 -> 8.
-// What bounds it: the round trips (1800 cycles each) while the batch is small; 256 tokens of 768, 32 neurons a leaf: 25 MB of leaf
-// weights from beyond the L2s, 4.1 us of the call's 10.
+// What bounds it: the round trips (1800 cycles each).  Where the leaf outweighs the tree, or the batch wants more than two blocks a
+// compute unit, token_rows_kernel is ahead (token_rows_better).
 hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s, const int32_t* given_leaf,
                               const GateCandidates* gate, const WideNodes* wide) {
     const int per = p.bf16 ? 8 : 4, es = p.bf16 ? 2 : 4;
