@@ -48,12 +48,13 @@ __device__ __forceinline__ void mfma_tile_64x128(const uint16_t* __restrict__ A,
     const int pc = tid & 7;                      // this thread's piece of every row it loads
     const int64_t ta0 = m0 + (tid >> 3), ta1 = ta0 + 32;
     const int64_t eb0 = n0 + (tid >> 3), eb1 = eb0 + 32, eb2 = eb0 + 64, eb3 = eb0 + 96;
-    const uint16_t* const pa0 = A + (ta0 < M ? ta0 : M - 1) * lda + 8 * pc;
-    const uint16_t* const pa1 = A + (ta1 < M ? ta1 : M - 1) * lda + 8 * pc;
-    const uint16_t* const pb0 = B + (eb0 < N ? eb0 : N - 1) * ldb + 8 * pc;
-    const uint16_t* const pb1 = B + (eb1 < N ? eb1 : N - 1) * ldb + 8 * pc;
-    const uint16_t* const pb2 = B + (eb2 < N ? eb2 : N - 1) * ldb + 8 * pc;
-    const uint16_t* const pb3 = B + (eb3 < N ? eb3 : N - 1) * ldb + 8 * pc;
+    const int in = 8 * pc < D ? 8 * pc : 0;      // (rows shorter than a chunk: their first piece again, not what lies behind the row)
+    const uint16_t* const pa0 = A + (ta0 < M ? ta0 : M - 1) * lda + in;
+    const uint16_t* const pa1 = A + (ta1 < M ? ta1 : M - 1) * lda + in;
+    const uint16_t* const pb0 = B + (eb0 < N ? eb0 : N - 1) * ldb + in;
+    const uint16_t* const pb1 = B + (eb1 < N ? eb1 : N - 1) * ldb + in;
+    const uint16_t* const pb2 = B + (eb2 < N ? eb2 : N - 1) * ldb + in;
+    const uint16_t* const pb3 = B + (eb3 < N ? eb3 : N - 1) * ldb + in;
     const bool va0 = ta0 < M, va1 = ta1 < M;
     const bool vb0 = eb0 < N, vb1 = eb1 < N, vb2 = eb2 < N, vb3 = eb3 < N;
     const int sa0 = tile_swz(tid >> 3, pc), sa1 = tile_swz((tid >> 3) + 32, pc);
@@ -211,19 +212,20 @@ __device__ __forceinline__ void mfma_tile_128x256_body(const uint16_t* __restric
     // registers of twelve 64-bit pointers (a tile spans at most 256 rows, far below 4 GB)
     const char* const a_base = (const char*)(A + m0 * lda);
     const char* const b_base = (const char*)(B + n0 * ldb);
+    const int in = kInterior || 8 * pc < K ? 16 * pc : 0;    // (rows shorter than a chunk: their first piece again, nothing behind the row)
     uint32_t oa[4], ob[8];
     bool va[4], vb[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int64_t r = r0 + 32 * i;
         va[i] = m0 + r < M;
-        oa[i] = (uint32_t)((va[i] ? r : M - 1 - m0) * lda * 2 + 16 * pc);
+        oa[i] = (uint32_t)((va[i] ? r : M - 1 - m0) * lda * 2 + in);
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int64_t r = r0 + 32 * i;
         vb[i] = n0 + r < N;
-        ob[i] = (uint32_t)((vb[i] ? r : N - 1 - n0) * ldb * 2 + 16 * pc);
+        ob[i] = (uint32_t)((vb[i] ? r : N - 1 - n0) * ldb * 2 + in);
     }
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)

@@ -273,3 +273,43 @@ def test_large_nodes_launch_into_a_buffer_that_is_only_4_byte_aligned(depth):
         F.fff_debug_option("soft_small_tiles", 0)
     assert bool(torch.isfinite(shifted).all()) and torch.equal(aligned, shifted)
     assert bool(torch.isnan(backing[0])) and bool(torch.isnan(backing[1 + T * NL:]).all())
+
+
+@pytest.mark.parametrize("D", [8, 32])
+def test_rows_shorter_than_a_chunk_end_with_their_allocation(D):
+    """The contraction tiles load 64 elements of K at a time; rows of fewer repeat their first piece.  Here the last row of the tokens
+    is the last thing of an allocation (16 MiB, a segment of its own in torch's allocator)."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, O, depth, L = (16 << 20) // (2 * D), 8, 2, 1
+    print("\n[case] soft and gating, rows at the end of an allocation, T=%d D=%d seed 51" % (T, D), flush=True)
+    n = 300
+    w = W.make_layer("ends", n, D, O, depth, L, W.ACT_RELU, W.DTYPE_BF16, seed=51)
+    dev = to_device(w)
+    torch.cuda.empty_cache()
+    x = torch.zeros((T, D), dtype=torch.bfloat16, device="cuda")
+    x[-n:] = dev["x"]
+    out = torch.full((T, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ref_out, _ = oracle.forward_soft(*oracle_inputs(w), depth, L, W.ACT_RELU)
+    leaves = [dev[k] for k in ("leaf_w1", "leaf_b1", "leaf_w2", "leaf_b2")]
+    try:
+        for tiles in (0, 1):
+            F.fff_debug_option("soft_small_tiles", tiles)
+            out.fill_(float("nan"))
+            F.fff_forward_soft(x, dev["node_w"], dev["node_b"], *leaves, depth, L, W.ACT_RELU, out)
+            torch.cuda.synchronize()
+            got = out_to_f64(out[-n:])
+            err = np.abs(got - ref_out).max(axis=1) / np.maximum(np.abs(ref_out).max(axis=1), 1e-30)
+            assert np.isfinite(got).all() and err.max() <= TOL[W.DTYPE_BF16]
+    finally:
+        F.fff_debug_option("soft_small_tiles", 0)
+    gw, gb = W.moe_gate(1 << depth, D, W.DTYPE_BF16, seed=51)
+    up = lambda a: torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
+    idx = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+    F.fff_moe_top1_forward(x, up(gw), up(gb), *leaves, depth, L, W.ACT_RELU, out, idx)
+    torch.cuda.synchronize()
+    assert "moe_gate_kernel" in F.fff_last_launch(), F.fff_last_launch()
+    ins = [w.bits[k] for k in ("leaf_w1", "leaf_b1", "leaf_w2", "leaf_b2")]
+    _, ref_idx, margin = oracle.moe_top1(w.bits["x"], gw, gb, *ins, L, W.ACT_RELU)
+    same = idx[-n:].cpu().numpy() == ref_idx
+    assert (margin[~same] < 1e-4).all()
