@@ -871,10 +871,12 @@ hipError_t launch_forward_soft(const Problem& p, int32_t* scratch, float* mix_ou
     // ---- which kernel makes each contraction.  The 128 x 256 tile where batch and width fill it, the
     // 64 x 128 tile in between, slices of K over a block's waves where tiles leave the chip idle.
     enum Kind { kSmall, kTile, kBig };
+    // (a small block is 512 threads on 32 rows, and a launch ends at 2^32 threads: narrow contractions would ask for more)
+    const bool small_ok = p.T < ((int64_t)1 << 27);
     const auto pick = [&](double small, double tile, double big, bool big_ok) {
         if (g_soft_small_tiles == 1) return kTile;
-        if (g_soft_small_tiles == 2) return kSmall;
-        if (small <= tile && (small <= big || !big_ok)) return kSmall;
+        if (g_soft_small_tiles == 2 && small_ok) return kSmall;
+        if (small_ok && small <= tile && (small <= big || !big_ok)) return kSmall;
         return big_ok && big < tile ? kBig : kTile;
     };
     const bool big_rows = p.T >= 16 * kBigM;

@@ -313,3 +313,33 @@ def test_rows_shorter_than_a_chunk_end_with_their_allocation(D):
     _, ref_idx, margin = oracle.moe_top1(w.bits["x"], gw, gb, *ins, L, W.ACT_RELU)
     same = idx[-n:].cpu().numpy() == ref_idx
     assert (margin[~same] < 1e-4).all()
+
+
+def test_forward_soft_on_more_tokens_than_one_launch_of_small_blocks_holds():
+    """2^28 rows of eight features against two leaves: a narrow hidden contraction, whose small blocks would need 2^32 threads."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L = (1 << 28) + 37, 8, 8, 1, 1
+    print("\n[case] soft T=%d D=%d O=%d depth=%d L=%d seed 52" % (T, D, O, depth, L), flush=True)
+    n = 200
+    w = W.make_layer("many", n, D, O, depth, L, W.ACT_RELU, W.DTYPE_BF16, seed=52)
+    dev = to_device(w)
+    x = torch.zeros((T, D), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty((T, O), dtype=torch.bfloat16, device="cuda")
+    places = [slice(0, n), slice((1 << 27) - 100, (1 << 27) + 100), slice(T - n, T)]
+    for at in places:
+        x[at] = dev["x"]
+        out[at] = float("nan")
+    try:
+        F.fff_forward_soft(x, dev["node_w"], dev["node_b"], dev["leaf_w1"], dev["leaf_b1"], dev["leaf_w2"], dev["leaf_b2"],
+                           depth, L, W.ACT_RELU, out)
+        torch.cuda.synchronize()
+        ref_out, _ = oracle.forward_soft(*oracle_inputs(w), depth, L, W.ACT_RELU)
+        for at in places:
+            got = out_to_f64(out[at])
+            err = np.abs(got - ref_out).max(axis=1) / np.maximum(np.abs(ref_out).max(axis=1), 1e-30)
+            assert np.isfinite(got).all() and err.max() <= TOL[W.DTYPE_BF16]
+    finally:
+        del x, out
+        torch.cuda.empty_cache()
+        F.fff_release_workspace()
