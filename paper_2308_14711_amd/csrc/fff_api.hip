@@ -282,6 +282,10 @@ int choose_path(const Problem& p) {
     if (!fused_ok && !staged_ok && rows_shape_ok(p)) {
         const int64_t limit = g_opt.token_max_T / 2 + 36 * (int64_t)p.L;
         if (limit < token_limit) token_limit = limit;
+    } else if (!fused_ok && !staged_ok && p.D <= 64 && !token_rows_ok(p)) {
+        // such rows with wider leaves leave the element-wise kernel, a wave a token, which takes a row of up to 64 features at a time
+        // (token block / element-wise: 2181 tokens of 9 bf16 features, 168 neurons 94 / 62; 1161 of 11, 116 neurons 39 / 43)
+        token_limit = 3 * g_opt.token_max_T;
     }
     if (g_opt.path == kPathAuto && token_ok && p.T <= token_limit) return kPathToken;
     // Whole rows of leaves wider than the staged path takes go one block a token at any batch size: their alternative is the

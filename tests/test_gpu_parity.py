@@ -793,6 +793,9 @@ TOKEN_KERNELS = [
     (700,  256,  30,   7,     33,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),
     (270,  512,  21,   4,     16,  W.DTYPE_F32,  "token_rows_kernel<f32,2,3,elem>"),
     (3100, 301,  24,   3,     65,  W.DTYPE_BF16, "fused_generic_kernel"),                # rows of other lengths
+    (1536, 15,   15,   3,     88,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),
+    (1537, 15,   15,   3,     88,  W.DTYPE_BF16, "fused_generic_kernel"),
+    (1537, 65,   15,   3,     88,  W.DTYPE_BF16, "token_block_kernel<bf16,1,1,hard>"),
 ]
 
 
