@@ -298,7 +298,8 @@ int fff_release_workspace(void);
  *   "stage_timing"   1 = fff_forward_hard records hipEvents around its stages
  *                    (read them with fff_stage_times); 0 (default) = off
  * Read-only, describing the last call: "last_path" (1..5 as above), "last_leaf_path"
- * (1 = gather kernel, 2 = the two tile kernels, 3 = both, each on its share of the tiles),
+ * (1 = gather kernel, 2 = the two tile kernels, 3 = both, each on its share of the tiles, 4 = the launch that
+ * takes the last levels of the walk with the leaf: "leaf_path" 0 only),
  * "last_walk_top" (tree levels the descent or fused launch kept in LDS),
  * "last_block_kernel" (fff_forward_block: 1 = rows of whole aligned 16-byte pieces, 2 = any other rows),
  * "last_block_top" (node levels fff_forward_block kept in LDS).

@@ -396,9 +396,53 @@ int run_bucket(const int32_t* leaf_idx, int64_t T, int depth, const Workspace& w
     return FFF_OK;
 }
 
+int64_t g_subtree = 0;   // debug option "subtree"
+
+// How many of the last levels the subtree launch takes; -1: whole descent and leaf kernels.
+//
+// Wherever tokens are grouped the subtree launch is ahead of the leaf kernels, by 1.22 (bf16) and 1.28 (fp32) on average over 975 random
+// calls of both (25216 tokens, 768-wide, depth 8, 8 neurons, fp32 103 -> 77 us; 50432 bf16 71 -> 68, 12000 1024-wide, 16 neurons
+// 41 -> 31), except where
+//   - there are fewer tiles of 64 tokens than compute units and rows of more than 4 KB, whose pieces a tile walks in turn (14315 tokens,
+//     3168-wide, 93 / 99), fp32 on half as many (3521 tokens of 856, 12 neurons 38 / 48), or bf16 leaves of up to 8 neurons, where little is
+//     to be had (16384 tokens of 768, depth 8 34 / 30 us),
+//   - output rows are many times the input rows (34782 tokens, 88 to 584 features, 16 neurons 37 / 45),
+//   - leaves see few tokens (19686 of fp32, depth 11 41 / 44; 5679 of bf16, depth 11, 16 neurons 19 / 29).
+// A tile wants whole groups: k grows until a group has 128 tokens on average, while the columns computed for all of a group stay few (48;
+// one block of 16 for fp32, whose matrix instructions run at a sixteenth of the rate): 50432 tokens, 8 neurons, depth 10, k = 0, 1, 2: 93, 91,
+// 83 us; fp32, 12000 tokens, depth 8, 4 neurons 53, 47, 50.
+int subtree_levels(const Problem& p, bool leaves_given) {
+    if (g_subtree == 1 || g_opt.leaf_path != 0 || g_opt.leaf_split != 0 || !g_opt.bucketing) return -1;
+    if (g_subtree >= 2) {
+        const int k = leaves_given ? 0 : (int)g_subtree - 2;
+        return subtree_shape_ok(p, k) ? k : -1;
+    }
+    const int64_t row_bytes = p.D * (p.bf16 ? 2 : 4);
+    const int64_t cus = device_info().cus;
+    const bool filled = p.T >= 64 * cus || (row_bytes <= 4096 && (p.bf16 ? p.L > 8 : p.T > 32 * cus));
+    if (!filled || p.T >> p.depth < (p.bf16 ? 8 : 16) || (p.bf16 && p.O > 4 * p.D)) return -1;
+    int pick = -1;
+    for (int k = 0; k <= (leaves_given ? 0 : 3); ++k) {
+        if (!subtree_shape_ok(p, k)) continue;
+        if (pick >= 0 && subtree_columns(k, 1, p.L) > (p.bf16 ? 48 : 16)) break;
+        pick = k;
+        if (p.T >> (p.depth - k) >= 128) break;
+    }
+    return pick;
+}
+
 int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& ws, hipStream_t s,
                    bool timed = false, const DescentCounts* dc = nullptr) {
     hipError_t e;
+    if (subtree_levels(p, true) == 0) {
+        const int rc = run_bucket(leaf_idx, p.T, p.depth, ws, nullptr, ws.offset, ws.perm, ws.slot_leaf, s, dc);
+        if (rc != FFF_OK) return rc;
+        if (timed) stage_mark(s);
+        g_opt.last_leaf_path = 4;
+        e = launch_subtree(p, 0, ws.perm, ws.offset, nullptr, s);
+        for (int i = 0; timed && i < 2; ++i) stage_mark(s);
+        return e == hipSuccess ? FFF_OK : set_device_error(e, "subtree kernel launch");
+    }
     if (!g_opt.bucketing) {
         if (timed) stage_mark(s);
         g_opt.last_leaf_path = 1;
@@ -547,6 +591,20 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
     dc.M = fold ? ws.fold : nullptr;
     dc.capacity = kFoldWords;
     if (marks) stage_mark(s);
+    const int k = subtree_levels(p, false);
+    if (k > 0) {
+        Problem top = p;
+        top.depth = p.depth - k;
+        if ((e = launch_descend(top, ws.leaf_idx, s, &dc)) != hipSuccess) return set_device_error(e, "descent kernel launch");
+        if (marks) stage_mark(s);
+        const int rc = run_bucket(ws.leaf_idx, p.T, top.depth, ws, nullptr, ws.offset, ws.perm, ws.slot_leaf, s, &dc);
+        if (rc != FFF_OK) return rc;
+        if (marks) stage_mark(s);
+        g_opt.last_leaf_path = 4;
+        e = launch_subtree(p, k, ws.perm, ws.offset, leaf_idx, s);
+        for (int i = 0; marks && i < 2; ++i) stage_mark(s);
+        return e == hipSuccess ? FFF_OK : set_device_error(e, "subtree kernel launch");
+    }
     e = launch_descend(p, li, s, &dc);
     if (e != hipSuccess) return set_device_error(e, "descent kernel launch");
     if (marks) stage_mark(s);
@@ -876,6 +934,8 @@ static int64_t* option_slot(const char* name) {
 //   "leaf_split"     staged leaf stage on the tile kernels: 1..16 = a tile (16 consecutive slots of the
 //                    bucketed order) with at least this many runs of equal leaf goes to the gather
 //                    kernel instead; 0 or above 16 = no split
+//   "subtree"        the launch that takes the last levels, the leaf and the output rows of grouped tokens (the staged
+//                    path): 0 = by size, 1 = never, k + 2 = with k of the last levels wherever the shape allows it
 //   "bucket_kernel"  0 = choose by size (the token-chunk kernel up to 131072 tokens and 4096 leaves;
 //                    beyond that the segment kernels for up to 4096 leaves, else the leaf-range kernel
 //                    up to 2^21 tokens and 2^19 leaves, else the chunk-matrix kernels), 1 = the
@@ -904,6 +964,7 @@ static int64_t* debug_slot(const char* name) {
     if (!std::strcmp(name, "walk_plain_x")) return &g_walk_tuning.plain_x;
     if (!std::strcmp(name, "block_top")) return &g_block_tuning.top;
     if (!std::strcmp(name, "leaf_split")) return &g_opt.leaf_split;
+    if (!std::strcmp(name, "subtree")) return &g_subtree;
     if (!std::strcmp(name, "bucket_kernel")) return &g_opt.bucket_kernel;
     if (!std::strcmp(name, "soft_small_tiles")) return &g_soft_small_tiles;
     if (!std::strcmp(name, "fail_workspace_growth")) return &g_fail_growths;

@@ -551,7 +551,7 @@ __global__ __launch_bounds__(1024) void chunk_counts_kernel(const int32_t* __res
 }
 
 __global__ __launch_bounds__(1024) void bucket_fold_kernel(const int32_t* __restrict__ leaf_idx, int64_t T,
-                                                           int n_leaves, int64_t share, int n_blocks,
+                                                           int n_leaves, int64_t share, int n_rows, int own_rows,
                                                            const int32_t* __restrict__ M,
                                                            int32_t* __restrict__ count, int32_t* __restrict__ offset,
                                                            int32_t* __restrict__ perm, int32_t* __restrict__ slot_leaf) {
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(1024) void bucket_fold_kernel(const int32_t* __rest
     __shared__ int32_t s_leaf[kFoldMaxShare];
     __shared__ int32_t s_wsum[16];
     const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, first_row = b * own_rows;     // (the rows of M before the block's own)
     const int64_t lo = (int64_t)b * share;
     const int64_t hi = lo + share < T ? lo + share : T;
     const int n_own = hi > lo ? (int)(hi - lo) : 0;
@@ -575,8 +575,8 @@ __global__ __launch_bounds__(1024) void bucket_fold_kernel(const int32_t* __rest
         const int groups = n_leaves / 4;
         ranges = 1024 / groups < 16 ? 1024 / groups : 16;
         const int g = tid % groups, r = tid / groups;
-        const int per = (n_blocks + ranges - 1) / ranges;
-        const int b0 = r * per, b1 = b0 + per < n_blocks ? b0 + per : n_blocks;
+        const int per = (n_rows + ranges - 1) / ranges;
+        const int b0 = r * per, b1 = b0 + per < n_rows ? b0 + per : n_rows;
         int4 tot = make_int4(0, 0, 0, 0), bef = make_int4(0, 0, 0, 0);
         constexpr int kBatch = 8;
         if (r < ranges) {
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(1024) void bucket_fold_kernel(const int32_t* __rest
                 }
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
-                    const int in = bb + u < b1, early = bb + u < b;
+                    const int in = bb + u < b1, early = bb + u < first_row;
                     tot.x += in ? v[u].x : 0; tot.y += in ? v[u].y : 0; tot.z += in ? v[u].z : 0; tot.w += in ? v[u].w : 0;
                     bef.x += early && in ? v[u].x : 0; bef.y += early && in ? v[u].y : 0;
                     bef.z += early && in ? v[u].z : 0; bef.w += early && in ? v[u].w : 0;
@@ -602,14 +602,14 @@ __global__ __launch_bounds__(1024) void bucket_fold_kernel(const int32_t* __rest
     } else {                                          // one or two leaves: a row is shorter than a vector
         ranges = 16;
         const int l = tid % n_leaves, r = tid / n_leaves;
-        const int per = (n_blocks + ranges - 1) / ranges;
-        const int b0 = r * per, b1 = b0 + per < n_blocks ? b0 + per : n_blocks;
+        const int per = (n_rows + ranges - 1) / ranges;
+        const int b0 = r * per, b1 = b0 + per < n_rows ? b0 + per : n_rows;
         if (r < ranges) {
             int32_t tot = 0, bef = 0;
             for (int bb = b0; bb < b1; ++bb) {
                 const int32_t c = M[(int64_t)bb * n_leaves + l];
                 tot += c;
-                bef += bb < b ? c : 0;
+                bef += bb < first_row ? c : 0;
             }
             s_tot[r * n_leaves + l] = tot;
             s_bef[r * n_leaves + l] = bef;
@@ -677,8 +677,8 @@ hipError_t launch_bucket_fold(const int32_t* leaf_idx, int64_t T, int depth, con
                               int32_t* count, int32_t* offset, int32_t* perm, int32_t* slot_leaf, hipStream_t s) {
     if (dc.blocks <= 0 || !bucket_fold_ok(depth, dc.blocks, dc.share)) return hipErrorInvalidValue;
     note_launch("bucket_fold_kernel");
-    bucket_fold_kernel<<<dim3((unsigned)dc.blocks), dim3(1024), 0, s>>>(leaf_idx, T, 1 << depth, dc.share, dc.blocks,
-                                                                       dc.M, count, offset, perm, slot_leaf);
+    bucket_fold_kernel<<<dim3((unsigned)dc.blocks), dim3(1024), 0, s>>>(leaf_idx, T, 1 << depth, dc.share, dc.n_rows > 0 ? dc.n_rows : dc.blocks,
+                                                                       dc.rows, dc.M, count, offset, perm, slot_leaf);
     return hipGetLastError();
 }
 

@@ -69,6 +69,7 @@ struct DescentCounts {
     int64_t capacity = 0;
     int blocks = 0;          // out: blocks that wrote a row of M; 0 = the launch left no counts
     int64_t share = 0;       // out: tokens per block
+    int rows = 1, n_rows = 0; // out: rows of M a block's tokens are counted in (0 rows in all: one a block)
 };
 constexpr int kFoldMaxLeaves = 1024;
 constexpr int kFoldMaxShare = 1024;
@@ -175,6 +176,20 @@ struct WideNodes {
     bool residual = false;
     float eps = 0;
 };
+// The last k levels of the walk, the leaf network and the output row of tokens grouped by the node of
+// level depth - k they have reached (perm, and offset [2^(depth - k) + 1]); needs subtree_shape_ok(p, k).
+// leaf_idx (optional): the leaf reached.  k = 0: the leaf networks alone.
+// wide (optional): fff_forward_block's nodes, norm and residual; stats [2 T]: what launch_subtree_levels from the root left.
+constexpr int kSubtreeMaxColumns = 128;
+int64_t subtree_columns(int k, int node_size, int L);
+bool subtree_shape_ok(const Problem& p, int k, const WideNodes* wide = nullptr);
+hipError_t launch_subtree(const Problem& p, int k, const int32_t* perm, const int32_t* offset, int32_t* leaf_idx, hipStream_t s,
+                          const WideNodes* wide = nullptr, float* stats = nullptr);
+// Levels base_level .. base_level + k - 1 of wide nodes: node_idx[t] = position of the node reached in its level.  perm and offset as above
+// for base_level > 0, null for the root (dc, optional: per-tile counts for launch_bucket_fold).
+hipError_t launch_subtree_levels(const Problem& p, int base_level, int k, const int32_t* perm, const int32_t* offset, int32_t* node_idx,
+                                 hipStream_t s, const WideNodes& wide, float* stats, DescentCounts* dc);
+
 bool token_shape_ok(const Problem& p);
 bool token_wide_ok(const Problem& p, int node_size);
 hipError_t launch_token_block(const Problem& p, int32_t* leaf_idx, hipStream_t s,
