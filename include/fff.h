@@ -231,7 +231,11 @@ int fff_forward_soft(const void* x, const void* node_w, const void* node_b,
  *   Rows that are 16-byte aligned with D and O multiples of 8 (bf16) or 4 (fp32)
  *   and at most 4096 (bf16) or 2048 (fp32) features are what option
  *   "last_block_kernel" reports as 1 after a call, any other shape as 2 (some of
- *   those take an element-wise kernel: correct, slow).  Needs no workspace.  Other arguments, ownership, asynchrony and errors as
+ *   those take an element-wise kernel: correct, slow).  Needs no workspace: large batches work in scratch
+ *   of this entry point's own (at most four blocks of up to 64 MB a device, allocated on first use, handed from call to call by
+ *   events, so that calls may overlap on any streams; fff_release_workspace frees them), and without it -- during stream capture, while a
+ *   caller's workspace is set, or where it cannot be had -- take a launch that needs none, whose results agree within rounding.
+ *   Other arguments, ownership, asynchrony and errors as
  *   for fff_forward_hard.
  */
 int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
@@ -248,7 +252,7 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
  *   fff_workspace_bytes       fff_forward_hard, fff_descend, fff_bucket, fff_leaf_forward
  *   fff_workspace_bytes_moe   fff_moe_top1_forward (the above plus the gating candidates)
  *   fff_workspace_bytes_soft  fff_forward_soft (the dense intermediates)
- * fff_forward_block uses none.
+ * fff_forward_block uses none of it.
  */
 size_t fff_workspace_bytes(int64_t T, int depth);
 size_t fff_workspace_bytes_moe(int64_t T, int log2_experts);
@@ -275,7 +279,7 @@ int fff_set_workspace(void* dev_ptr, size_t bytes, void* stream);
 int fff_reserve_workspace(int64_t T, int depth);
 int fff_reserve_workspace_bytes(size_t bytes);
 
-/* Free the library-owned workspaces of all devices (call with no work in flight). */
+/* Free the library-owned workspaces, and fff_forward_block's scratch, of all devices (call with no work in flight). */
 int fff_release_workspace(void);
 
 /*

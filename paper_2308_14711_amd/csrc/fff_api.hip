@@ -225,6 +225,79 @@ int get_workspace(int64_t T, int depth, Workspace* ws, Layout* lay, hipStream_t 
     return FFF_OK;
 }
 
+// ---- scratch of fff_forward_block's grouped launches.  That entry point needs no workspace: calls of it overlap freely, on any streams,
+// with each other and with calls that work in the device's workspace.  Its scratch is therefore its own, a few blocks a
+// device, each handed from call to call by an event: a call takes the block its stream used last, else one whose work is done, else
+// allocates one; with none left, during capture, or where the caller has forbidden allocations by setting a workspace, it
+// takes the launch that needs none.  fff_release_workspace gives the blocks back.
+struct BlockScratch {
+    void* base = nullptr;
+    size_t bytes = 0;
+    hipEvent_t done = nullptr;
+    hipStream_t last = nullptr;      // compared only
+};
+constexpr int kBlockScratches = 4;
+constexpr size_t kMaxBlockScratch = (size_t)64 << 20;
+BlockScratch g_block_scratch[kMaxDevices][kBlockScratches];
+std::mutex g_block_mu;               // held from the choice of a block to the record of its event
+
+// allowed while another thread of the program captures (this call itself is not captured)
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// g_block_mu held.  Null: none to be had.
+BlockScratch* take_block_scratch(size_t need, hipStream_t s) {
+    int dev = 0;
+    if (need > kMaxBlockScratch || current_device(&dev) != FFF_OK) return nullptr;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    {
+        std::lock_guard<std::mutex> lock(g_mu);
+        if (g_ws[dev].user_base) return nullptr;
+    }
+    RelaxedCapture relaxed;
+    BlockScratch *found = nullptr, *empty = nullptr;
+    for (BlockScratch& b : g_block_scratch[dev])
+        if (b.base && b.last == s) found = &b;
+    for (BlockScratch& b : g_block_scratch[dev]) {
+        if (found) break;
+        if (!b.base) {
+            if (!empty) empty = &b;
+        } else if (hipEventQuery(b.done) == hipSuccess) {
+            found = &b;
+        }
+    }
+    (void)hipGetLastError();            // (hipErrorNotReady is no error)
+    if (found && found->bytes < need) {
+        if (hipFree(found->base) != hipSuccess) (void)hipGetLastError();      // (waits for its work)
+        found->base = nullptr;
+        found->bytes = 0;
+        empty = found;
+        found = nullptr;
+    }
+    if (found) {
+        // work of another stream that had this handle before may still be under way; of this one's own it is no wait
+        if (hipStreamWaitEvent(s, found->done, 0) == hipSuccess) return found;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (!empty) return nullptr;
+    void* p = nullptr;
+    if ((!empty->done && hipEventCreateWithFlags(&empty->done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) || hipMalloc(&p, need) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    empty->base = p;
+    empty->bytes = need;
+    return empty;
+}
+
 constexpr int64_t kMaxElems = (int64_t)1 << 40;
 constexpr int64_t kMaxTokens = ((int64_t)1 << 31) - 1024;
 constexpr int kMaxLeafWidth = 4096;
@@ -494,6 +567,111 @@ int run_leaf_any(const Problem& p, const int32_t* leaf_idx, hipStream_t s) {
     const int rc = get_workspace(p.T, p.depth, &ws, &lay, s);
     if (rc != FFF_OK) return rc;
     return run_leaf_stage(p, leaf_idx, ws, s);   // falls back per shape inside
+}
+
+// How fff_forward_block's tree is cut for the grouped launches: levels from the root in one or two launches, `leaf` levels with the leaves.
+struct BlockCut {
+    int first = 0, second = 0, leaf = 0;
+};
+bool cut_at(const Problem& p, const WideNodes& wide, int leaf, BlockCut* cut) {
+    const auto fits = [&](int k) { return subtree_columns(k, wide.n, 0) <= kSubtreeMaxColumns; };
+    if (leaf >= p.depth || !subtree_shape_ok(p, leaf, &wide)) return false;
+    const int above = p.depth - leaf;
+    cut->leaf = leaf;
+    cut->second = fits(above) ? 0 : above / 2;
+    cut->first = above - cut->second;
+    return fits(cut->first);
+}
+
+// Estimates of both sides' time in us, fitted to 2125 random calls (half of them within 9 and 17 %): the grouped launches' goes with
+// the rows' bytes (and the columns computed for them, in blocks of 16), one launch a token's with the bytes of the weight rows that a
+// token meets.  The grouped launches are taken where they are estimated a fifth faster (fp32, whose sums have been made more exact since the
+// fit, a third): 388 further calls that so change their route, 1.79 (bf16) and 2.15 (fp32) on average (50432 tokens, 768-wide, depth 8, 4
+// neurons a node, 8 a leaf 219 -> 141 us; 20000 of 512 to 1600 features 209 -> 72), one in twenty-five more than 5 % slower.
+double grouped_estimate(const Problem& p, const WideNodes& wide, const BlockCut& c) {
+    const auto blocks = [](int64_t cols) {
+        const int64_t b = (cols + 15) / 16;
+        return (double)(b <= 2 ? b : b <= 4 ? 4 : b <= 6 ? 6 : 8);
+    };
+    const double es = p.bf16 ? 2e-6 : 4e-6, in = es * (double)(p.T * p.D), out = es * (double)(p.T * p.O);
+    const double first = blocks(subtree_columns(c.first, wide.n, 0)), second = c.second ? blocks(subtree_columns(c.second, wide.n, 0)) : 0;
+    const double last = blocks(subtree_columns(c.leaf, wide.n, p.L)), steps = (double)(((p.L + 1) * (1 << c.leaf) + 15) / 16);
+    const double groups = (double)((int64_t)1 << (p.depth - c.leaf));
+    if (p.bf16)
+        return 30 + (c.second ? 12 + 0.49 * in : 0) + in * (0.56 + 0.05 * first + 0.067 * second + 0.063 * last) + out * (0.35 + 0.04 * steps) +
+               0.0067 * groups;
+    return 32 + (c.second ? 12 + 0.28 * in : 0) + in * (0.24 + 0.116 * first + 0.158 * second + 0.14 * last) + out * (0.18 + 0.032 * steps) +
+           0.0079 * groups;
+}
+double ungrouped_estimate(const Problem& p, const WideNodes& wide) {
+    const double es = p.bf16 ? 2e-6 : 4e-6, T = (double)p.T, out = es * (double)(p.T * p.O), levels = 1e-3 * T * p.depth, neurons = 1e-3 * T * p.L;
+    const double node_rows = es * T * p.depth * wide.n * (double)p.D, leaf_rows = es * T * p.L * (double)(p.D + p.O);
+    const bool lane_groups = (p.D > p.O ? p.D : p.O) * (p.bf16 ? 2 : 4) <= 2048;
+    if (p.bf16)
+        return lane_groups ? 7.5 + 0.38 * out + 0.068 * node_rows + 0.045 * leaf_rows + 0.048 * levels + 0.018 * neurons
+                           : 8 + 0.123 * node_rows + 0.61 * levels + 0.42 * neurons;
+    return lane_groups ? 6.8 + 0.18 * out + 0.052 * node_rows + 0.046 * leaf_rows + 0.047 * levels
+                       : 6.3 + 0.55 * out + 0.105 * node_rows + 0.1 * leaf_rows + 0.2 * levels;
+}
+
+bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
+    if (g_subtree == 1 || p.T > 131072) return false;       // (the bucketing launch's limit)
+    if (g_subtree >= 2) return cut_at(p, wide, (int)g_subtree - 2, cut);
+    // Rows that 16 lanes hold stay in their one launch up to 160 tokens a compute unit: it needs no scratch and gives the same bits eager and
+    // captured, which callers of such batches have (40000 tokens, 768-wide, depth 8: 177 us there, 122 grouped).
+    if ((p.D > p.O ? p.D : p.O) * (p.bf16 ? 2 : 4) <= 2048 && p.T <= 160 * (int64_t)device_info().cus) return false;
+    double best = ungrouped_estimate(p, wide) / (p.bf16 ? 1.2 : 1.35);
+    bool found = false;
+    for (int leaf = 0; leaf <= 4; ++leaf) {
+        BlockCut c;
+        if (!cut_at(p, wide, leaf, &c)) continue;
+        const double t = grouped_estimate(p, wide, c);
+        if (t < best) best = t, *cut = c, found = true;
+    }
+    return found;
+}
+
+int run_block_grouped(const Problem& p, const WideNodes& wide, int32_t* leaf_idx, hipStream_t s, bool* done) {
+    BlockCut cut;
+    if (!block_cut(p, wide, &cut)) return FFF_OK;
+    const int above = cut.first + cut.second;
+    if (!bucket_hist_ok(p.T, above)) return FFF_OK;
+    const int64_t row = round_up(p.T, kAlignWords), groups = round_up(((int64_t)1 << above) + 1, kAlignWords);
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    BlockScratch* const b = take_block_scratch(sizeof(int32_t) * (5 * row + groups + kFoldWords), s);
+    if (!b) return FFF_OK;
+    *done = true;
+    Workspace ws = {};
+    int32_t* const idx = (int32_t*)b->base;
+    int32_t* const node = idx + row;                  // (of the second launch from the root)
+    ws.perm = node + row;
+    float* const stats = (float*)(ws.perm + row);     // [T] mean and deviation
+    ws.offset = (int32_t*)stats + 2 * row;
+    DescentCounts dc;
+    dc.M = ws.offset + groups;
+    dc.capacity = kFoldWords;
+    const auto bucket = [&](const int32_t* at, int depth, const DescentCounts* counts) -> hipError_t {
+        return counts && counts->blocks > 0 ? launch_bucket_fold(at, p.T, depth, *counts, nullptr, ws.offset, ws.perm, nullptr, s)
+                                            : launch_bucket_hist(at, p.T, depth, nullptr, ws.offset, ws.perm, nullptr, s);
+    };
+    hipError_t e = launch_subtree_levels(p, 0, cut.first, nullptr, nullptr, idx, s, wide, stats, &dc);
+    if (e == hipSuccess) e = bucket(idx, cut.first, &dc);
+    if (e == hipSuccess && cut.second) {
+        e = launch_subtree_levels(p, cut.first, cut.second, ws.perm, ws.offset, node, s, wide, stats, nullptr);
+        if (e == hipSuccess) e = bucket(node, above, nullptr);
+    }
+    if (e == hipSuccess) e = launch_subtree(p, cut.leaf, ws.perm, ws.offset, leaf_idx, s, &wide, stats);
+    b->last = s;
+    const hipError_t recorded = hipEventRecord(b->done, s);
+    if (recorded != hipSuccess) {
+        // nobody could wait for this call's work: wait here, and forget the block
+        (void)hipStreamSynchronize(s);
+        (void)hipFree(b->base);
+        b->base = nullptr;
+        b->bytes = 0;
+    }
+    if (e == hipSuccess) e = recorded;
+    return e == hipSuccess ? FFF_OK : set_device_error(e, "block kernel launch");
 }
 
 // Host-side argument checks of fff_forward_hard (no HIP call).  FFF_OK with *empty set: nothing to do.
@@ -831,6 +1009,21 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
         hipError_t e = launch_token_block(p, leaf_idx, (hipStream_t)stream, nullptr, nullptr, &wide);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
+    if (vector_rows) {
+        WideNodes wide;
+        wide.gamma = ln_gamma;
+        wide.beta = ln_beta;
+        wide.w1 = node_w1;
+        wide.b1 = node_b1;
+        wide.w2 = node_w2;
+        wide.b2 = node_b2;
+        wide.n = node_size;
+        wide.residual = residual != 0;
+        wide.eps = ln_eps;
+        bool done = false;
+        rc = run_block_grouped(p, wide, leaf_idx, (hipStream_t)stream, &done);
+        if (rc != FFF_OK || done) return rc;
+    }
     hipError_t e = launch_forward_block(p, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2,
                                         node_size, residual != 0, leaf_idx, (hipStream_t)stream, vector_rows);
     return e == hipSuccess ? FFF_OK : set_device_error(e, "block kernel launch");
@@ -894,6 +1087,7 @@ int fff_reserve_workspace(int64_t T, int depth) {
 }
 
 int fff_release_workspace(void) {
+    std::lock_guard<std::mutex> block_lock(g_block_mu);
     std::lock_guard<std::mutex> lock(g_mu);
     int cur = 0;
     if (hipGetDevice(&cur) != hipSuccess) return FFF_ERR_DEVICE;
@@ -903,6 +1097,13 @@ int fff_release_workspace(void) {
         if (hipSetDevice(d) != hipSuccess || hipFree(g_ws[d].base) != hipSuccess) rc = FFF_ERR_DEVICE;
         g_ws[d].base = nullptr;
         g_ws[d].bytes = 0;
+    }
+    for (int d = 0; d < kMaxDevices; ++d) {
+        for (BlockScratch& b : g_block_scratch[d]) {
+            if (b.base && (hipSetDevice(d) != hipSuccess || hipFree(b.base) != hipSuccess)) rc = FFF_ERR_DEVICE;
+            if (b.done) (void)hipEventDestroy(b.done);
+            b = BlockScratch();
+        }
     }
     (void)hipSetDevice(cur);
     return rc;
@@ -934,8 +1135,8 @@ static int64_t* option_slot(const char* name) {
 //   "leaf_split"     staged leaf stage on the tile kernels: 1..16 = a tile (16 consecutive slots of the
 //                    bucketed order) with at least this many runs of equal leaf goes to the gather
 //                    kernel instead; 0 or above 16 = no split
-//   "subtree"        the launch that takes the last levels, the leaf and the output rows of grouped tokens (the staged
-//                    path): 0 = by size, 1 = never, k + 2 = with k of the last levels wherever the shape allows it
+//   "subtree"        the launch that takes the last levels, the leaf and the output rows of grouped tokens (fff_forward_hard's
+//                    staged path, fff_forward_block): 0 = by size, 1 = never, k + 2 = with k of the last levels wherever the shape allows it
 //   "bucket_kernel"  0 = choose by size (the token-chunk kernel up to 131072 tokens and 4096 leaves;
 //                    beyond that the segment kernels for up to 4096 leaves, else the leaf-range kernel
 //                    up to 2^21 tokens and 2^19 leaves, else the chunk-matrix kernels), 1 = the
