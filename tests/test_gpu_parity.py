@@ -256,6 +256,34 @@ def test_bucket_stage_is_bit_exact(depth, T, kind, kernel):
         F.fff_debug_option("bucket_kernel", 0)
 
 
+@pytest.mark.parametrize("share", [256, 257, 511, 512, 513])
+@pytest.mark.parametrize("kind", ["u", "one"])
+def test_bucket_fold_at_the_edges_of_its_threads_per_token(share, kind):
+    """256 blocks of `share` tokens: up to 256 a token's rank is counted by four threads, up to 512 by
+    two, beyond that by one; the last block is a few tokens short."""
+    import torch
+    import paper_2308_14711_amd as F
+    depth, T = 8, 256 * share - 3
+    print("\n[case] bucket fold share=%d T=%d %s" % (share, T, kind), flush=True)
+    rng = np.random.default_rng(share)
+    li = rng.integers(0, 1 << depth, T).astype(np.int32) if kind == "u" else np.full(T, 5, np.int32)
+    count, offset, perm = oracle.bucket(li, depth)
+    d_li = torch.from_numpy(li).cuda()
+    d_count = torch.full((1 << depth,), -1, dtype=torch.int32, device="cuda")
+    d_offset = torch.full(((1 << depth) + 1,), -1, dtype=torch.int32, device="cuda")
+    d_perm = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+    F.fff_debug_option("bucket_kernel", 5)
+    try:
+        F.fff_bucket(d_li, depth, d_count, d_offset, d_perm)
+        torch.cuda.synchronize()
+        assert "bucket_fold_kernel" in F.fff_last_launch(), F.fff_last_launch()
+    finally:
+        F.fff_debug_option("bucket_kernel", 0)
+    assert np.array_equal(d_count.cpu().numpy(), count)
+    assert np.array_equal(d_offset.cpu().numpy(), offset)
+    assert np.array_equal(d_perm.cpu().numpy(), perm)
+
+
 def test_split_launch_equals_the_fused_one_bit_for_bit():
     """The fused launch cut in two (walk + hidden neurons, then output rows by column slices) does the
     same additions in the same order as the single launch: same bits, on rows of 12 lines (4 slices),
