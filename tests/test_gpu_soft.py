@@ -343,3 +343,31 @@ def test_forward_soft_on_more_tokens_than_one_launch_of_small_blocks_holds():
         del x, out
         torch.cuda.empty_cache()
         F.fff_release_workspace()
+
+
+@pytest.mark.parametrize("depth,L,act", [(7, 4, W.ACT_GELU), (2, 124, W.ACT_RELU), (8, 2, W.ACT_GELU)])
+def test_hidden_contraction_with_aligned_and_unaligned_biases(depth, L, act):
+    """Leaf widths that are multiples of 4 with biases at 8 bytes take a lane's mixture weights together, all
+    others look them up neuron by neuron: the same bits from both, and the oracle's rows (512
+    neurons: whole column tiles, 496: a ragged one; 16300 tokens: a ragged row tile)."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O = 16300, 512, 24
+    print("\n[case] soft hidden T=%d D=%d O=%d depth=%d L=%d act=%d seed 23" % (T, D, O, depth, L, act), flush=True)
+    w = W.make_layer("hidden_bias", T, D, O, depth, L, act, W.DTYPE_BF16, seed=23)
+    dev = to_device(w)
+    b1 = dev["leaf_b1"]
+    moved = torch.zeros(b1.numel() + 1, dtype=b1.dtype, device="cuda")
+    moved[1:] = b1.flatten()
+    outs = []
+    for bias in (b1, moved[1:].view(b1.shape)):
+        out = torch.full((T, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+        F.fff_forward_soft(dev["x"], dev["node_w"], dev["node_b"], dev["leaf_w1"], bias, dev["leaf_w2"], dev["leaf_b2"],
+                           depth, L, act, out, None, None)
+        torch.cuda.synchronize()
+        assert "soft_hidden_big_kernel" in F.fff_last_launch(), F.fff_last_launch()
+        outs.append(out)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    ref = oracle.forward_soft(*oracle_inputs(w), depth, L, act)[0]
+    err = np.abs(out_to_f64(outs[0]) - ref).max(axis=1) / np.maximum(np.abs(ref).max(axis=1), 1e-30)
+    assert err.max() <= TOL[W.DTYPE_BF16], "row error %.3e" % err.max()
