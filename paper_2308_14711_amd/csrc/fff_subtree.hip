@@ -356,8 +356,14 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
     float* const S = (float*)ring;                          // [kTok][kPitch]
     float* const hid = S + kTok * kPitch;                   // the hidden activations
     if (!BF16) {
+        // (a sum that met or reached an infinity is that sum alone: what its additions lost is inf - inf then)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] += lost[BF16 ? 0 : b];
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float l = lost[BF16 ? 0 : b][q];
+                acc[b][q] += fabsf(l) < __builtin_inff() ? l : 0.0f;
+            }
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) *(f32x4_t*)(S + tok * kPitch + 16 * b + 4 * kg) = acc[b];

@@ -123,3 +123,100 @@ def test_which_batches_take_it(T, D, O, depth, L, dtype, expect):
     torch.cuda.synchronize()
     assert expect in F.fff_last_launch(), F.fff_last_launch()
     assert not out.any()
+
+
+def _both_launches(call, shape):
+    """(rows, leaves, launch) of a call through the subtree launch and through the launches it stands for."""
+    import torch
+    import paper_2308_14711_amd as F
+    res = []
+    for option in (None, 1):
+        old = F.fff_debug_option("subtree")
+        if option:
+            F.fff_debug_option("subtree", option)
+        out = torch.full(shape, 7.0, dtype=torch.float32, device="cuda")
+        idx = torch.full(shape[:1], -9, dtype=torch.int32, device="cuda")
+        call(out, idx)
+        torch.cuda.synchronize()
+        F.fff_debug_option("subtree", old)
+        res.append((out_to_f64(out), idx.cpu().numpy(), F.fff_last_launch()))
+    assert "subtree_kernel" in res[0][2] and "subtree_kernel" not in res[1][2], (res[0][2], res[1][2])
+    return res
+
+
+def _same_infinities(a, b):
+    (got, gi, _), (ref, ri, _) = a, b
+    assert np.array_equal(gi, ri), "leaves differ at %s" % np.nonzero(gi != ri)[0][:5]
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert np.array_equal(got[np.isinf(got)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    scale = np.where(fin, np.abs(ref), 0).max(axis=1, keepdims=True)
+    assert (np.abs(np.where(fin, got, 0) - np.where(fin, ref, 0)) <= 1e-5 * scale).all()
+
+
+def _plant(what, x, nodes, w1):
+    """Infinities of both signs in tokens, node weights ([NN, D]) or leaf weights, or finite values whose sums overflow."""
+    if what == "tokens":
+        x[3, 5], x[40, 0], x[77, -1], x[100, 17] = np.inf, -np.inf, np.inf, -np.inf
+    elif what == "nodes":
+        nodes[0, -1] = nodes[2:7:2, 7] = np.inf
+        nodes[1:7:2, 2] = -np.inf
+    elif what == "leaves":
+        w1[::2, 0, -1], w1[1::2, 1, 0], w1[1::4, 2, 30] = np.inf, -np.inf, np.inf
+    else:                                                  # the first two products are finite, their sum is not
+        x[:400, 0] = x[:400, 33] = 1.5
+        x[400:, 33] = 0
+        for a in (nodes[0], w1[::2, 1]):
+            a[..., 0] = a[..., 33] = 2e38
+        for a in (nodes[1], nodes[2], w1[1::2, 2]):
+            a[..., 0] = a[..., 33] = -2e38
+
+
+@pytest.mark.parametrize("what", ["tokens", "nodes", "leaves", "overflow"])
+@pytest.mark.parametrize("act", [RELU, GELU], ids=["relu", "gelu"])
+@pytest.mark.parametrize("k", [0, 2])
+def test_infinite_pre_activations_in_fp32(what, act, k, forced):
+    """fp32 pre-activations that are infinite, or overflow, stay infinities: routing, infinities and NaN as in the launches before."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L = 1500, 132, 68, 4, 6
+    print("\n[case] subtree fp32 infinities in %s act=%d k=%d seed 15" % (what, act, k), flush=True)
+    w = W.make_layer("subtree_pre_inf", T, D, O, depth, L, act, F32, seed=15)
+    host = [np.array(w.device_array(t)) for t in W.TENSORS]
+    _plant(what, host[0], host[1], host[3])
+    dev = [torch.from_numpy(a).cuda() for a in host]
+    forced(k)
+    call = lambda out, idx: F.fff_forward_hard(*dev, depth, L, act, out, idx)
+    new, old = _both_launches(call, (T, O))
+    assert what == "nodes" or not np.isfinite(old[0]).all()
+    _same_infinities(new, old)
+    if k == 0:
+        given = torch.from_numpy(old[1]).cuda()
+        leaf = lambda out, idx: F.fff_leaf_forward(dev[0], *dev[3:], given, depth, L, act, out)
+        _same_infinities(*_both_launches(leaf, (T, O)))
+
+
+@pytest.mark.parametrize("what", ["tokens", "nodes", "leaves", "overflow"])
+@pytest.mark.parametrize("act", [RELU, GELU], ids=["relu", "gelu"])
+def test_infinite_pre_activations_in_the_grouped_block(what, act, forced):
+    """The same for fff_forward_block without a norm: levels from the root, last levels and leaves.  (Rows of 128 features: whole
+    pieces for every lane of the launch before, whose idle lanes would multiply an infinite weight by zero.)"""
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, n, L = 1500, 128, 68, 5, 3, 4
+    print("\n[case] grouped block fp32 infinities in %s act=%d seed 16" % (what, act), flush=True)
+    w = W.make_layer("block_pre_inf", T, D, O, depth, L, act, F32, seed=16)
+    nodes = [np.array(a) for a in W.wide_nodes(depth, n, D, F32, seed=16)]
+    host = [np.array(w.device_array(t)) for t in ("x", "leaf_w1", "leaf_b1", "leaf_w2", "leaf_b2")]
+    _plant(what, host[0], nodes[0][:, 0], host[1])
+    x, *leaves = [torch.from_numpy(a).cuda() for a in host]
+    d_nodes = [torch.from_numpy(a).cuda() for a in nodes]
+    forced(2)
+    old_T = F.fff_debug_option("token_max_T")
+    F.fff_debug_option("token_max_T", 0)
+    try:
+        call = lambda out, idx: F.fff_forward_block(x, None, None, 0.0, *d_nodes, *leaves, depth, n, L, act, False, out, idx)
+        new, old = _both_launches(call, (T, O))
+    finally:
+        F.fff_debug_option("token_max_T", old_T)
+    _same_infinities(new, old)
