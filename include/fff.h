@@ -231,11 +231,8 @@ int fff_forward_soft(const void* x, const void* node_w, const void* node_b,
  *   Rows that are 16-byte aligned with D and O multiples of 8 (bf16) or 4 (fp32)
  *   and at most 4096 (bf16) or 2048 (fp32) features are what option
  *   "last_block_kernel" reports as 1 after a call, any other shape as 2 (some of
- *   those take an element-wise kernel: correct, slow).  Needs no workspace: large batches work in scratch
- *   of this entry point's own (at most four blocks of up to 64 MB a device, allocated on first use, handed from call to call by
- *   events, so that calls may overlap on any streams; fff_release_workspace frees them), and without it -- during stream capture, while a
- *   caller's workspace is set, or where it cannot be had -- take a launch that needs none, whose results agree within rounding.
- *   Other arguments, ownership, asynchrony and errors as
+ *   those take an element-wise kernel: correct, slow).  Needs no workspace and allocates nothing, so calls may
+ *   overlap in time on any streams.  Other arguments, ownership, asynchrony and errors as
  *   for fff_forward_hard.
  */
 int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
@@ -246,13 +243,35 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
                       void* stream, int64_t T, int64_t D, int64_t O, int dtype);
 
 /*
+ * fff_forward_block_scratch: the same with scratch of the caller's, in which large batches run grouped by the subtree
+ * they reach, on the matrix cores (several launches; logits are summed in another order, so a token
+ * within rounding of a threshold may reach another leaf than through fff_forward_block).
+ * Which launches run depends on the sizes, dtype and alignment alone.
+ *   scratch        device memory, 256-byte aligned, of one call from its launches until they have run (calls on one
+ *                  stream may share it); needs no initial value; NULL: as fff_forward_block
+ *   scratch_bytes  at least fff_block_scratch_bytes of the same sizes (norm: ln_gamma given; 0: these
+ *                  sizes never use scratch, or are out of range)
+ * Errors: as for fff_forward_block; FFF_ERR_WORKSPACE (scratch misaligned, or too short for a call that uses it),
+ * FFF_ERR_ALIAS (scratch overlaps x, out or leaf_idx).
+ */
+int fff_forward_block_scratch(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
+                              const void* node_w1, const void* node_b1, const void* node_w2,
+                              const void* node_b2, const void* leaf_w1, const void* leaf_b1,
+                              const void* leaf_w2, const void* leaf_b2, int depth, int node_size,
+                              int leaf_width, int act, int residual, void* out, int32_t* leaf_idx,
+                              void* stream, int64_t T, int64_t D, int64_t O, int dtype,
+                              void* scratch, size_t scratch_bytes);
+size_t fff_block_scratch_bytes(int64_t T, int64_t D, int64_t O, int depth, int node_size, int leaf_width, int norm,
+                               int dtype);
+
+/*
  * Workspace sizes, in bytes (0 for arguments out of range).  Sizes follow from
  * the Definition's counts alone: T tokens, 2^depth leaves (experts), leaves of
  * leaf_width neurons, O outputs.
  *   fff_workspace_bytes       fff_forward_hard, fff_descend, fff_bucket, fff_leaf_forward
  *   fff_workspace_bytes_moe   fff_moe_top1_forward (the above plus the gating candidates)
  *   fff_workspace_bytes_soft  fff_forward_soft (the dense intermediates)
- * fff_forward_block uses none of it.
+ * fff_forward_block uses none.
  */
 size_t fff_workspace_bytes(int64_t T, int depth);
 size_t fff_workspace_bytes_moe(int64_t T, int log2_experts);
@@ -279,7 +298,7 @@ int fff_set_workspace(void* dev_ptr, size_t bytes, void* stream);
 int fff_reserve_workspace(int64_t T, int depth);
 int fff_reserve_workspace_bytes(size_t bytes);
 
-/* Free the library-owned workspaces, and fff_forward_block's scratch, of all devices (call with no work in flight). */
+/* Free the library-owned workspaces of all devices (call with no work in flight). */
 int fff_release_workspace(void);
 
 /*

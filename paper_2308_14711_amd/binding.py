@@ -67,6 +67,9 @@ def lib() -> ctypes.CDLL:
         L.fff_forward_soft.argtypes = [vp] * 7 + [i32, i32, i32, vp, vp, vp, vp, i64, i64, i64, i32]
         L.fff_forward_block.argtypes = ([vp] * 3 + [ctypes.c_float] + [vp] * 8 + [i32] * 5 + [vp, vp, vp] +
                                         [i64, i64, i64, i32])
+        L.fff_forward_block_scratch.argtypes = L.fff_forward_block.argtypes + [vp, ctypes.c_size_t]
+        L.fff_block_scratch_bytes.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32]
+        L.fff_block_scratch_bytes.restype = ctypes.c_size_t
         L.fff_workspace_bytes.argtypes = [i64, i32]
         L.fff_workspace_bytes.restype = ctypes.c_size_t
         L.fff_workspace_bytes_moe.argtypes = [i64, i32]
@@ -319,12 +322,37 @@ def fff_forward_soft(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, dept
            where)
 
 
+def _torch_scratch(nbytes: int, stream):
+    """Memory of torch's allocator for one call on `stream`, which may be freed once the call has enqueued its work.  None where
+    there is none to be had: out of memory, or a stream that is captured by other means than torch's
+    graphs, whose replays would work in what the allocator has given to another owner since."""
+    import torch
+    if stream is None:
+        stream = torch.cuda.current_stream()
+    elif not isinstance(stream, torch.cuda.Stream):
+        handle = _stream_handle(stream)
+        stream = torch.cuda.ExternalStream(handle) if handle else torch.cuda.default_stream()
+    with torch.cuda.stream(stream):
+        try:
+            buf = torch.empty((nbytes,), dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            return None
+        if torch.cuda.is_current_stream_capturing():
+            at = buf.data_ptr()
+            for segment in torch.cuda.memory_snapshot():
+                if segment["address"] <= at < segment["address"] + segment["total_size"]:
+                    return buf if tuple(segment["segment_pool_id"]) != (0, 0) else None
+            return None
+    return buf
+
+
 def fff_forward_block(x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2, leaf_w1, leaf_b1,
                       leaf_w2, leaf_b2, depth, node_size, leaf_width, act, residual, out, leaf_idx=None,
                       stream=None) -> None:
     """Forward_I with nodes of `node_size` hidden neurons as a pre-norm residual layer:
     out = FFF(LayerNorm(x)) (+ x when `residual`); ln_gamma = ln_beta = None skips the
-    normalisation.  out may be x itself."""
+    normalisation.  out may be x itself.  Large batches work in scratch of torch's allocator
+    (fff_forward_block_scratch), captured by torch.cuda.graph or not."""
     rc = (_native_module or _native()).forward_block(x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2,
                                                      leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, node_size, leaf_width,
                                                      act, residual, out, leaf_idx, stream)
@@ -347,12 +375,21 @@ def fff_forward_block(x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, n
         _check_leaves(where, x, T, D, O, depth, leaf_width, leaf_w1, leaf_b1, leaf_w2, leaf_b2, out, leaf_idx, "leaf_idx")
     _check_dense(x, ln_gamma, ln_beta, node_w1, node_b1, node_w2, node_b2, leaf_w1, leaf_b1, leaf_w2, leaf_b2,
                  out, leaf_idx)
-    _check(lib().fff_forward_block(_ptr(x), _ptr(ln_gamma), _ptr(ln_beta), float(ln_eps), _ptr(node_w1),
-                                   _ptr(node_b1), _ptr(node_w2), _ptr(node_b2), _ptr(leaf_w1), _ptr(leaf_b1),
-                                   _ptr(leaf_w2), _ptr(leaf_b2), depth, node_size, leaf_width, act,
-                                   int(bool(residual)), _ptr(out), _ptr(leaf_idx), _stream_handle(stream),
-                                   T, D, O, _dtype_code(x)),
+    need, scratch = 0, None
+    if _in_range(depth, leaf_width, node_size):
+        need = fff_block_scratch_bytes(T, D, O, depth, node_size, leaf_width, ln_gamma is not None, _dtype_code(x))
+        scratch = _torch_scratch(need, stream) if need else None
+    _check(lib().fff_forward_block_scratch(_ptr(x), _ptr(ln_gamma), _ptr(ln_beta), float(ln_eps), _ptr(node_w1),
+                                           _ptr(node_b1), _ptr(node_w2), _ptr(node_b2), _ptr(leaf_w1), _ptr(leaf_b1),
+                                           _ptr(leaf_w2), _ptr(leaf_b2), depth, node_size, leaf_width, act,
+                                           int(bool(residual)), _ptr(out), _ptr(leaf_idx), _stream_handle(stream),
+                                           T, D, O, _dtype_code(x), _ptr(scratch), need),
            where)
+
+
+def fff_block_scratch_bytes(T: int, D: int, O: int, depth: int, node_size: int, leaf_width: int, norm: bool,
+                            dtype: int) -> int:
+    return int(lib().fff_block_scratch_bytes(T, D, O, depth, node_size, leaf_width, int(bool(norm)), dtype))
 
 
 def fff_workspace_bytes(T: int, depth: int) -> int:

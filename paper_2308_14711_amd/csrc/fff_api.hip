@@ -225,79 +225,6 @@ int get_workspace(int64_t T, int depth, Workspace* ws, Layout* lay, hipStream_t 
     return FFF_OK;
 }
 
-// ---- scratch of fff_forward_block's grouped launches.  That entry point needs no workspace: calls of it overlap freely, on any streams,
-// with each other and with calls that work in the device's workspace.  Its scratch is therefore its own, a few blocks a
-// device, each handed from call to call by an event: a call takes the block its stream used last, else one whose work is done, else
-// allocates one; with none left, during capture, or where the caller has forbidden allocations by setting a workspace, it
-// takes the launch that needs none.  fff_release_workspace gives the blocks back.
-struct BlockScratch {
-    void* base = nullptr;
-    size_t bytes = 0;
-    hipEvent_t done = nullptr;
-    hipStream_t last = nullptr;      // compared only
-};
-constexpr int kBlockScratches = 4;
-constexpr size_t kMaxBlockScratch = (size_t)64 << 20;
-BlockScratch g_block_scratch[kMaxDevices][kBlockScratches];
-std::mutex g_block_mu;               // held from the choice of a block to the record of its event
-
-// allowed while another thread of the program captures (this call itself is not captured)
-struct RelaxedCapture {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-};
-
-// g_block_mu held.  Null: none to be had.
-BlockScratch* take_block_scratch(size_t need, hipStream_t s) {
-    int dev = 0;
-    if (need > kMaxBlockScratch || current_device(&dev) != FFF_OK) return nullptr;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    {
-        std::lock_guard<std::mutex> lock(g_mu);
-        if (g_ws[dev].user_base) return nullptr;
-    }
-    RelaxedCapture relaxed;
-    BlockScratch *found = nullptr, *empty = nullptr;
-    for (BlockScratch& b : g_block_scratch[dev])
-        if (b.base && b.last == s) found = &b;
-    for (BlockScratch& b : g_block_scratch[dev]) {
-        if (found) break;
-        if (!b.base) {
-            if (!empty) empty = &b;
-        } else if (hipEventQuery(b.done) == hipSuccess) {
-            found = &b;
-        }
-    }
-    (void)hipGetLastError();            // (hipErrorNotReady is no error)
-    if (found && found->bytes < need) {
-        if (hipFree(found->base) != hipSuccess) (void)hipGetLastError();      // (waits for its work)
-        found->base = nullptr;
-        found->bytes = 0;
-        empty = found;
-        found = nullptr;
-    }
-    if (found) {
-        // work of another stream that had this handle before may still be under way; of this one's own it is no wait
-        if (hipStreamWaitEvent(s, found->done, 0) == hipSuccess) return found;
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (!empty) return nullptr;
-    void* p = nullptr;
-    if ((!empty->done && hipEventCreateWithFlags(&empty->done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) || hipMalloc(&p, need) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    empty->base = p;
-    empty->bytes = need;
-    return empty;
-}
-
 constexpr int64_t kMaxElems = (int64_t)1 << 40;
 constexpr int64_t kMaxTokens = ((int64_t)1 << 31) - 1024;
 constexpr int kMaxLeafWidth = 4096;
@@ -580,7 +507,7 @@ bool cut_at(const Problem& p, const WideNodes& wide, int leaf, BlockCut* cut) {
     cut->leaf = leaf;
     cut->second = fits(above) ? 0 : above / 2;
     cut->first = above - cut->second;
-    return fits(cut->first);
+    return fits(cut->first) && bucket_hist_ok(p.T, above);
 }
 
 // Estimates of both sides' time in us, fitted to 2125 random calls (half of them within 9 and 17 %): the grouped launches' goes with
@@ -615,7 +542,7 @@ double ungrouped_estimate(const Problem& p, const WideNodes& wide) {
 }
 
 bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
-    if (g_subtree == 1 || p.T > 131072) return false;       // (the bucketing launch's limit)
+    if (g_subtree == 1) return false;
     if (g_subtree >= 2) return cut_at(p, wide, (int)g_subtree - 2, cut);
     // Rows that 16 lanes hold stay in their one launch up to 160 tokens a compute unit: it needs no scratch and gives the same bits eager and
     // captured, which callers of such batches have (40000 tokens, 768-wide, depth 8: 177 us there, 122 grouped).
@@ -631,24 +558,29 @@ bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
     return found;
 }
 
-int run_block_grouped(const Problem& p, const WideNodes& wide, int32_t* leaf_idx, hipStream_t s, bool* done) {
-    BlockCut cut;
-    if (!block_cut(p, wide, &cut)) return FFF_OK;
+// Scratch of the grouped launches, in words: node reached (twice), grouped order, mean and deviation of T tokens, group offsets, counts.
+struct BlockScratch {
+    int64_t row, groups, total;
+};
+BlockScratch block_scratch(int64_t T, const BlockCut& cut) {
+    BlockScratch b;
+    b.row = round_up(T, kAlignWords);
+    b.groups = round_up(((int64_t)1 << (cut.first + cut.second)) + 1, kAlignWords);
+    b.total = 5 * b.row + b.groups + kFoldWords;
+    return b;
+}
+
+int run_block_grouped(const Problem& p, const WideNodes& wide, const BlockCut& cut, void* scratch, int32_t* leaf_idx, hipStream_t s) {
     const int above = cut.first + cut.second;
-    if (!bucket_hist_ok(p.T, above)) return FFF_OK;
-    const int64_t row = round_up(p.T, kAlignWords), groups = round_up(((int64_t)1 << above) + 1, kAlignWords);
-    std::lock_guard<std::mutex> lock(g_block_mu);
-    BlockScratch* const b = take_block_scratch(sizeof(int32_t) * (5 * row + groups + kFoldWords), s);
-    if (!b) return FFF_OK;
-    *done = true;
+    const BlockScratch b = block_scratch(p.T, cut);
     Workspace ws = {};
-    int32_t* const idx = (int32_t*)b->base;
-    int32_t* const node = idx + row;                  // (of the second launch from the root)
-    ws.perm = node + row;
-    float* const stats = (float*)(ws.perm + row);     // [T] mean and deviation
-    ws.offset = (int32_t*)stats + 2 * row;
+    int32_t* const idx = (int32_t*)scratch;
+    int32_t* const node = idx + b.row;                // (of the second launch from the root)
+    ws.perm = node + b.row;
+    float* const stats = (float*)(ws.perm + b.row);   // [T] mean and deviation
+    ws.offset = (int32_t*)stats + 2 * b.row;
     DescentCounts dc;
-    dc.M = ws.offset + groups;
+    dc.M = ws.offset + b.groups;
     dc.capacity = kFoldWords;
     const auto bucket = [&](const int32_t* at, int depth, const DescentCounts* counts) -> hipError_t {
         return counts && counts->blocks > 0 ? launch_bucket_fold(at, p.T, depth, *counts, nullptr, ws.offset, ws.perm, nullptr, s)
@@ -661,17 +593,25 @@ int run_block_grouped(const Problem& p, const WideNodes& wide, int32_t* leaf_idx
         if (e == hipSuccess) e = bucket(node, above, nullptr);
     }
     if (e == hipSuccess) e = launch_subtree(p, cut.leaf, ws.perm, ws.offset, leaf_idx, s, &wide, stats);
-    b->last = s;
-    const hipError_t recorded = hipEventRecord(b->done, s);
-    if (recorded != hipSuccess) {
-        // nobody could wait for this call's work: wait here, and forget the block
-        (void)hipStreamSynchronize(s);
-        (void)hipFree(b->base);
-        b->base = nullptr;
-        b->bytes = 0;
-    }
-    if (e == hipSuccess) e = recorded;
     return e == hipSuccess ? FFF_OK : set_device_error(e, "block kernel launch");
+}
+
+// Whether one block a token takes a call of fff_forward_block: by estimate of what its tokens meet.
+bool block_by_token(const Problem& p, int node_size, bool vector_rows) {
+    // Any batch whose rows are not whole pieces when its tokens meet much: the element-wise kernel's time goes with the rows a
+    // token meets times their chunks of 64 elements (generic / token block, us, 24000 tokens: 20 chunks 126/256,
+    // 56 265/270, 200 955/423, 640 3940/538).
+    const int64_t chunks = ((int64_t)p.depth * node_size + p.L) * ((p.D + 63) / 64);
+    const bool far_rows = !vector_rows && chunks >= 80;
+    // Small batches, from 480 calls of both sides: up to 256 tokens always (a token a compute unit), up to 512 unless the rows are
+    // short and few (313 tokens of 112 fp32 features, 7 rows met: 5.6 / 4.5 us of the kernels below), up to 1024 where a
+    // token meets enough of them: 50 short ones (932 tokens of 96, 7 rows 9.0 / 4.1; 1019 of 48 bf16, 16 rows 11.3 / 6.6),
+    // 12 long ones or ones that are not whole pieces (998 of 23, 8 rows 11.4 / 7.7).
+    const int64_t met = (int64_t)p.depth * node_size + p.L, small = g_opt.token_max_T;
+    const bool short_rows = (p.D > p.O ? p.D : p.O) * (p.bf16 ? 2 : 4) <= 64 * 16;
+    const int64_t enough = p.T <= small / 2 ? 0 : p.T <= small ? (vector_rows && short_rows ? 12 : 0)
+                           : vector_rows ? (short_rows ? 50 : 12) : short_rows ? 12 : 0;
+    return ((p.T <= 2 * small && met > enough) || far_rows) && token_wide_ok(p, node_size);
 }
 
 // Host-side argument checks of fff_forward_hard (no HIP call).  FFF_OK with *empty set: nothing to do.
@@ -951,11 +891,12 @@ int fff_forward_soft(const void* x, const void* node_w, const void* node_b, cons
     return e == hipSuccess ? FFF_OK : set_device_error(e, "soft forward kernel launch");
 }
 
-int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
-                      const void* node_w1, const void* node_b1, const void* node_w2, const void* node_b2,
-                      const void* leaf_w1, const void* leaf_b1, const void* leaf_w2, const void* leaf_b2,
-                      int depth, int node_size, int leaf_width, int act, int residual, void* out,
-                      int32_t* leaf_idx, void* stream, int64_t T, int64_t D, int64_t O, int dtype) {
+int fff_forward_block_scratch(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
+                              const void* node_w1, const void* node_b1, const void* node_w2, const void* node_b2,
+                              const void* leaf_w1, const void* leaf_b1, const void* leaf_w2, const void* leaf_b2,
+                              int depth, int node_size, int leaf_width, int act, int residual, void* out,
+                              int32_t* leaf_idx, void* stream, int64_t T, int64_t D, int64_t O, int dtype,
+                              void* scratch, size_t scratch_bytes) {
     int rc = check_common(depth, T, D, dtype);
     if (rc == FFF_OK) rc = check_leaf(depth, leaf_width, act, T, D, O);
     if (rc != FFF_OK) return rc;
@@ -971,62 +912,74 @@ int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, 
     // in place (out == x with rows of one width) is fine: a wave reads its token before it writes it
     if (!(out == x && O == D) && overlaps(x, T * D * es, out, T * O * es)) return FFF_ERR_ALIAS;
     if (leaf_idx && overlaps(leaf_idx, T * 4, out, T * O * es)) return FFF_ERR_ALIAS;
+    if (scratch) {
+        if ((reinterpret_cast<uintptr_t>(scratch) & 255u) != 0) return FFF_ERR_WORKSPACE;
+        if (overlaps(scratch, (int64_t)scratch_bytes, x, T * D * es) || overlaps(scratch, (int64_t)scratch_bytes, out, T * O * es) ||
+            (leaf_idx && overlaps(scratch, (int64_t)scratch_bytes, leaf_idx, T * 4)))
+            return FFF_ERR_ALIAS;
+    }
     Problem p{x, nullptr, nullptr, leaf_w1, leaf_b1, leaf_w2, leaf_b2, out, leaf_idx,
               T, D, O, depth, leaf_width, act, dtype == FFF_BF16};
+    WideNodes wide;
+    wide.gamma = ln_gamma;
+    wide.beta = ln_beta;
+    wide.w1 = node_w1;
+    wide.b1 = node_b1;
+    wide.w2 = node_w2;
+    wide.b2 = node_b2;
+    wide.n = node_size;
+    wide.residual = residual != 0;
+    wide.eps = ln_eps;
     // rows of whole 16-byte pieces, short enough for a lane group or a wave to hold, take the vector
     // kernels; everything else the element-wise one
     const bool vector_rows = block_shape_ok(x, out, leaf_w1, leaf_w2, D, O, p.bf16) &&
                              (depth == 0 || vec_ok(node_w1, D, p.bf16)) &&
                              (!ln_gamma || (vec_ok(ln_gamma, D, p.bf16) && vec_ok(ln_beta, D, p.bf16))) &&
                              vec_ok(leaf_b2, O, p.bf16);
+    const bool by_token = block_by_token(p, node_size, vector_rows);
+    BlockCut cut;
+    const bool grouped = scratch && vector_rows && !by_token && block_cut(p, wide, &cut);
+    if (grouped && scratch_bytes < (size_t)block_scratch(T, cut).total * sizeof(int32_t)) {
+        g_last_error = "the scratch holds " + std::to_string(scratch_bytes) + " bytes, this call needs " +
+                       std::to_string((size_t)block_scratch(T, cut).total * sizeof(int32_t));
+        return FFF_ERR_WORKSPACE;
+    }
     begin_device_call();
     g_opt.last_block_kernel = vector_rows ? 1 : 2;
-    // Any batch whose rows are not whole pieces when its tokens meet much: the element-wise kernel's time goes with the rows a
-    // token meets times their chunks of 64 elements (generic / token block, us, 24000 tokens: 20 chunks 126/256,
-    // 56 265/270, 200 955/423, 640 3940/538).
-    const int64_t chunks = ((int64_t)depth * node_size + leaf_width) * ((D + 63) / 64);
-    const bool far_rows = !vector_rows && chunks >= 80;
-    // Small batches, from 480 calls of both sides: up to 256 tokens always (a token a compute unit), up to 512 unless the rows are
-    // short and few (313 tokens of 112 fp32 features, 7 rows met: 5.6 / 4.5 us of the kernels below), up to 1024 where a
-    // token meets enough of them: 50 short ones (932 tokens of 96, 7 rows 9.0 / 4.1; 1019 of 48 bf16, 16 rows 11.3 / 6.6),
-    // 12 long ones or ones that are not whole pieces (998 of 23, 8 rows 11.4 / 7.7).
-    const int64_t met = (int64_t)depth * node_size + leaf_width, small = g_opt.token_max_T;
-    const bool short_rows = (D > O ? D : O) * es <= 64 * 16;
-    const int64_t enough = T <= small / 2 ? 0 : T <= small ? (vector_rows && short_rows ? 12 : 0)
-                           : vector_rows ? (short_rows ? 50 : 12) : short_rows ? 12 : 0;
-    if (((T <= 2 * small && met > enough) || far_rows) && token_wide_ok(p, node_size)) {
-        WideNodes wide;
-        wide.gamma = ln_gamma;
-        wide.beta = ln_beta;
-        wide.w1 = node_w1;
-        wide.b1 = node_b1;
-        wide.w2 = node_w2;
-        wide.b2 = node_b2;
-        wide.n = node_size;
-        wide.residual = residual != 0;
-        wide.eps = ln_eps;
+    if (by_token) {
         g_block_tuning.last_top = 0;
         hipError_t e = launch_token_block(p, leaf_idx, (hipStream_t)stream, nullptr, nullptr, &wide);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
-    if (vector_rows) {
-        WideNodes wide;
-        wide.gamma = ln_gamma;
-        wide.beta = ln_beta;
-        wide.w1 = node_w1;
-        wide.b1 = node_b1;
-        wide.w2 = node_w2;
-        wide.b2 = node_b2;
-        wide.n = node_size;
-        wide.residual = residual != 0;
-        wide.eps = ln_eps;
-        bool done = false;
-        rc = run_block_grouped(p, wide, leaf_idx, (hipStream_t)stream, &done);
-        if (rc != FFF_OK || done) return rc;
-    }
+    if (grouped) return run_block_grouped(p, wide, cut, scratch, leaf_idx, (hipStream_t)stream);
     hipError_t e = launch_forward_block(p, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2,
                                         node_size, residual != 0, leaf_idx, (hipStream_t)stream, vector_rows);
     return e == hipSuccess ? FFF_OK : set_device_error(e, "block kernel launch");
+}
+
+int fff_forward_block(const void* x, const void* ln_gamma, const void* ln_beta, float ln_eps,
+                      const void* node_w1, const void* node_b1, const void* node_w2, const void* node_b2,
+                      const void* leaf_w1, const void* leaf_b1, const void* leaf_w2, const void* leaf_b2,
+                      int depth, int node_size, int leaf_width, int act, int residual, void* out,
+                      int32_t* leaf_idx, void* stream, int64_t T, int64_t D, int64_t O, int dtype) {
+    return fff_forward_block_scratch(x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2, leaf_w1, leaf_b1, leaf_w2, leaf_b2,
+                                     depth, node_size, leaf_width, act, residual, out, leaf_idx, stream, T, D, O, dtype, nullptr, 0);
+}
+
+size_t fff_block_scratch_bytes(int64_t T, int64_t D, int64_t O, int depth, int node_size, int leaf_width, int norm, int dtype) {
+    if (check_common(depth, T, D, dtype) != FFF_OK || check_leaf(depth, leaf_width, 0, T, D, O) != FFF_OK || T == 0 || depth == 0 ||
+        node_size < 1 || node_size > kMaxLeafWidth)
+        return 0;
+    Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+              T, D, O, depth, leaf_width, 0, dtype == FFF_BF16};
+    alignas(16) static const char some[16] = {};       // (asked for alignment only)
+    WideNodes wide;
+    wide.gamma = wide.beta = norm ? some : nullptr;
+    wide.n = node_size;
+    BlockCut cut;
+    if (!block_shape_ok(nullptr, nullptr, nullptr, nullptr, D, O, p.bf16) || block_by_token(p, node_size, true) || !block_cut(p, wide, &cut))
+        return 0;
+    return (size_t)block_scratch(T, cut).total * sizeof(int32_t);
 }
 
 size_t fff_workspace_bytes(int64_t T, int depth) {
@@ -1087,7 +1040,6 @@ int fff_reserve_workspace(int64_t T, int depth) {
 }
 
 int fff_release_workspace(void) {
-    std::lock_guard<std::mutex> block_lock(g_block_mu);
     std::lock_guard<std::mutex> lock(g_mu);
     int cur = 0;
     if (hipGetDevice(&cur) != hipSuccess) return FFF_ERR_DEVICE;
@@ -1097,13 +1049,6 @@ int fff_release_workspace(void) {
         if (hipSetDevice(d) != hipSuccess || hipFree(g_ws[d].base) != hipSuccess) rc = FFF_ERR_DEVICE;
         g_ws[d].base = nullptr;
         g_ws[d].bytes = 0;
-    }
-    for (int d = 0; d < kMaxDevices; ++d) {
-        for (BlockScratch& b : g_block_scratch[d]) {
-            if (b.base && (hipSetDevice(d) != hipSuccess || hipFree(b.base) != hipSuccess)) rc = FFF_ERR_DEVICE;
-            if (b.done) (void)hipEventDestroy(b.done);
-            b = BlockScratch();
-        }
     }
     (void)hipSetDevice(cur);
     return rc;

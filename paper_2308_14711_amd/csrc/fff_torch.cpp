@@ -11,6 +11,7 @@
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 
 #include "../../include/fff.h"
@@ -183,6 +184,22 @@ PyObject* forward_soft(PyObject*, PyObject* const* args, Py_ssize_t n) {
     });
 }
 
+// Scratch of one call from torch's allocator, in the order of the call's stream: handed back once the call has enqueued its work.
+// Null where there is none to be had (nothing may throw past the released interpreter lock).
+struct Scratch {
+    void* p = nullptr;
+    Scratch(size_t bytes, hipStream_t s) {
+        try {
+            p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, s);
+        } catch (const std::exception&) {
+        }
+    }
+    ~Scratch() {
+        if (p) c10::hip::HIPCachingAllocator::raw_delete(p);
+    }
+    Scratch(const Scratch&) = delete;
+};
+
 // x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2, leaf_w1, leaf_b1, leaf_w2, leaf_b2,
 // depth, node_size, leaf_width, act, residual, out, leaf_idx, stream
 PyObject* forward_block(PyObject*, PyObject* const* args, Py_ssize_t n) {
@@ -202,8 +219,20 @@ PyObject* forward_block(PyObject*, PyObject* const* args, Py_ssize_t n) {
     int32_t* idx = (int32_t*)c.dense(18, at::ScalarType::Int, {a.T});
     void* s = c.stream(19);
     return answer(c, [&] {
-        return fff_forward_block(a.x, gamma, beta, (float)eps, w1, b1, w2, b2, a.w1, a.b1, a.w2, a.b2, a.depth, (int)size,
-                                 a.width, a.act, residual, a.out, idx, s, a.T, a.D, a.O, c.code());
+        const auto call = [&](void* scratch, size_t bytes) {
+            return fff_forward_block_scratch(a.x, gamma, beta, (float)eps, w1, b1, w2, b2, a.w1, a.b1, a.w2, a.b2, a.depth, (int)size, a.width,
+                                             a.act, residual, a.out, idx, s, a.T, a.D, a.O, c.code(), scratch, bytes);
+        };
+        const size_t bytes = fff_block_scratch_bytes(a.T, a.D, a.O, a.depth, (int)size, a.width, gamma != nullptr, c.code());
+        if (bytes == 0) return call(nullptr, 0);
+        // (a captured call is left to binding.py, which finds out who captures)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing((hipStream_t)s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return -1;
+        }
+        const Scratch scratch(bytes, (hipStream_t)s);
+        return call(scratch.p, bytes);
     });
 }
 

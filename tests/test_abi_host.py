@@ -140,6 +140,24 @@ def test_forward_block_rejects_bad_arguments_on_the_host(L):
     assert blk(out=ctypes.c_void_p((1 << 20) + 32)) == ALIAS
 
 
+def test_block_scratch_is_checked_on_the_host(L):
+    import paper_2308_14711_amd as F
+    OK, NULL, WORKSPACE, ALIAS = 0, 1, 6, 8
+    size = lambda T=50000, D=768, O=768, depth=8, n=4, width=8, norm=True, dtype=1: F.fff_block_scratch_bytes(T, D, O, depth, n, width, norm, dtype)
+    assert 20 * 50000 < size() < 24 * 50000 + (1 << 20) and 0 < size(norm=False)
+    assert size(T=128) == 0 and size(T=1 << 20) == 0 and size(D=77, O=77) == 0 and size(width=17) == 0    # never grouped
+    for bad in (dict(T=-1), dict(T=0), dict(depth=0), dict(depth=25), dict(n=0), dict(width=0), dict(D=0), dict(O=0), dict(dtype=2)):
+        assert size(**bad) == 0, bad
+    p = lambda mb, off=0: ctypes.c_void_p((mb << 20) + off)
+    call = lambda scratch, nbytes, T=50000, x=p(1024): L.fff_forward_block_scratch(
+        x, p(2), p(3), 1e-5, p(4), p(5), p(6), p(7), p(8), p(9), p(10), p(11), 8, 4, 8, 0, 1, p(2048), None, None, T, 768, 768, 1,
+        scratch, nbytes)
+    assert call(p(4096), size(), T=0) == OK and call(p(4096), size(), x=None) == NULL
+    assert call(p(4096, 128), size()) == WORKSPACE and call(p(4096), size() - 1) == WORKSPACE
+    assert str(size()) in L.fff_last_device_error().decode()
+    assert call(p(2048), size()) == ALIAS and call(p(1030), size()) == ALIAS
+
+
 def test_bench_probe_library_is_separate_and_checks_its_arguments():
     """The microbenchmarks of bench.py live in a library of their own: the product ABI exports none
     of them, and the probe library rejects bad arguments on the host."""

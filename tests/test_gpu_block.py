@@ -265,7 +265,7 @@ def test_block_nan_token_is_routed_like_the_oracle_and_spoils_only_its_own_row()
 
 
 def test_block_captured_in_a_hip_graph_and_replayed():
-    """The call enqueues one kernel and allocates nothing: it can be captured, and every replay, with
+    """A batch of this size enqueues one kernel and allocates nothing: it can be captured, and every replay, with
     eager work and synchronisations in between, must reproduce the eager result bit for bit."""
     import torch
     import paper_2308_14711_amd as F

@@ -1,5 +1,7 @@
 """fff_forward_block's grouped launches (levels from the root on the matrix cores, bucketing, subtree launch) against the oracle, on several
-streams, and where they must not run: during capture and with a caller's workspace."""
+streams, captured, and where there is no scratch for them."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -65,73 +67,139 @@ def _state(case, seed):
 STREAMS = ("streams", 6000, 256, 256, 7, 4, 6, GELU, BF16, True, True)
 
 
+def _rows(F, d, case=STREAMS):
+    import torch
+    out = torch.empty((case[1], case[3]), dtype=torch.bfloat16, device="cuda")
+    _call(F, d, case, out)
+    torch.cuda.synchronize()
+    return out
+
+
+def _grouped_and_not(F, d):
+    """The call's rows through the grouped launches and through the one launch that needs no scratch."""
+    grouped = _rows(F, d)
+    assert "subtree_kernel" in F.fff_last_launch()
+    F.fff_debug_option("subtree", 1)
+    plain = _rows(F, d)
+    assert "subtree_kernel" not in F.fff_last_launch()
+    F.fff_debug_option("subtree", 5)
+    return grouped, plain
+
+
 def test_calls_overlap_on_several_streams(forced):
-    """More streams than scratch blocks, calls of different inputs in flight together, twice: every result is that of the call alone (the
-    calls that find no block take the launch without scratch, within its rounding)."""
+    """Calls of different inputs in flight together on six streams (and on one given by its handle), three times: every result is that of
+    the call alone, bit for bit."""
     import torch
     import paper_2308_14711_amd as F
     print("\n[case] grouped block on six streams T=6000 D=256 depth=7 n=4 L=6", flush=True)
     forced(3)
     states = [_state(STREAMS, 20 + i) for i in range(6)]
-    alone, ungrouped = [], []
-    for grouped, results in ((True, alone), (False, ungrouped)):
-        F.fff_debug_option("subtree", 5 if grouped else 1)
-        for d in states:
-            results.append(torch.empty((6000, 256), dtype=torch.bfloat16, device="cuda"))
-            _call(F, d, STREAMS, results[-1])
-            torch.cuda.synchronize()
-    F.fff_debug_option("subtree", 5)
+    alone = [_rows(F, d) for d in states]
     streams = [torch.cuda.Stream() for _ in states]
     outs = [[torch.empty_like(alone[0]) for _ in range(3)] for _ in states]
     torch.cuda.synchronize()
     for rep in range(3):
         for s, d, o in zip(streams, states, outs):
-            with torch.cuda.stream(s):
-                _call(F, d, STREAMS, o[rep])
+            if s is streams[0]:
+                F.fff_forward_block(d[0], d[1], d[2], 1e-5, *d[3:], 7, 4, 6, GELU, True, o[rep], None, s.cuda_stream)
+            else:
+                with torch.cuda.stream(s):
+                    _call(F, d, STREAMS, o[rep])
+            assert "subtree_kernel" in F.fff_last_launch()
     torch.cuda.synchronize()
-    for i, o in enumerate(outs):
-        for got in o:
-            assert torch.equal(got, alone[i]) or torch.equal(got, ungrouped[i])
+    for want, o in zip(alone, outs):
+        assert all(torch.equal(got, want) for got in o)
 
 
-def test_no_scratch_during_capture_or_with_a_callers_workspace(forced):
+def test_same_bits_eager_captured_and_beside_a_callers_workspace(forced):
     import torch
     import paper_2308_14711_amd as F
-    print("\n[case] grouped block captured, with a caller's workspace, after a release; T=6000 D=256 depth=7 n=4 L=6", flush=True)
-    d = _state(STREAMS, 31)
+    print("\n[case] grouped block captured, and with a caller's workspace; T=6000 D=256 depth=7 n=4 L=6", flush=True)
+    d, other = _state(STREAMS, 31), _state(STREAMS, 32)
     forced(3)
-    out = torch.empty((6000, 256), dtype=torch.bfloat16, device="cuda")
-    _call(F, d, STREAMS, out)
-    torch.cuda.synchronize()
-    assert "subtree_kernel" in F.fff_last_launch()
-    grouped = out.clone()
-    F.fff_debug_option("subtree", 1)
-    _call(F, d, STREAMS, out)
-    torch.cuda.synchronize()
-    plain = out.clone()
-    F.fff_debug_option("subtree", 5)
+    grouped, _ = _grouped_and_not(F, d)
+    want_other = _rows(F, other)
+    out, out2 = torch.empty_like(grouped), torch.empty_like(grouped)
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         _call(F, d, STREAMS, out)
-    assert "subtree_kernel" not in F.fff_last_launch()
+        assert "subtree_kernel" in F.fff_last_launch()
+        _call(F, other, STREAMS, out2)
     for _ in range(3):
         out.fill_(float("nan"))
-        _call(F, d, STREAMS, torch.empty_like(out))         # eager work between the replays
+        out2.fill_(float("nan"))
+        scribble = [torch.full((1 << 20,), 255, dtype=torch.uint8, device="cuda") for _ in range(8)]     # eager work between the replays
+        assert torch.equal(_rows(F, other), want_other)
         g.replay()
         torch.cuda.synchronize()
-        assert torch.equal(out, plain)
-    buf = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+        assert torch.equal(out, grouped) and torch.equal(out2, want_other)
+        del scribble
+    buf = torch.full((1 << 20,), 77, dtype=torch.uint8, device="cuda")
     F.fff_set_workspace(buf)
     try:
-        _call(F, d, STREAMS, out)
-        torch.cuda.synchronize()
-        assert "subtree_kernel" not in F.fff_last_launch() and torch.equal(out, plain)
+        assert torch.equal(_rows(F, d), grouped) and "subtree_kernel" in F.fff_last_launch()
+        assert (buf[256:] == 77).all()
     finally:
         F.fff_set_workspace(None)
-    F.fff_release_workspace()
-    _call(F, d, STREAMS, out)
+
+
+def test_without_scratch_the_one_launch_runs(forced):
+    """A stream captured by other means than torch's graphs, no memory left, and the entry point of the C ABI that takes no scratch."""
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] grouped block without scratch: captured outside torch, out of memory, C ABI; T=6000 D=256 depth=7 n=4 L=6", flush=True)
+    d = _state(STREAMS, 33)
+    forced(3)
+    grouped, plain = _grouped_and_not(F, d)
+    out = torch.full_like(plain, float("nan"))
+    hip = ctypes.CDLL("libamdhip64.so")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    s, graph, execution = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
     torch.cuda.synchronize()
-    assert "subtree_kernel" in F.fff_last_launch() and torch.equal(out, grouped)
+    assert hip.hipStreamBeginCapture(s, 1) == 0                  # thread-local
+    try:
+        F.fff_forward_block(d[0], d[1], d[2], 1e-5, *d[3:], 7, 4, 6, GELU, True, out, None, side)
+    finally:
+        ended = hip.hipStreamEndCapture(s, ctypes.byref(graph))
+    assert ended == 0 and "subtree_kernel" not in F.fff_last_launch()
+    assert hip.hipGraphInstantiate(ctypes.byref(execution), graph, None, None, ctypes.c_size_t(0)) == 0
+    for _ in range(3):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(execution, s) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out, plain)
+    assert hip.hipGraphExecDestroy(execution) == 0 and hip.hipGraphDestroy(graph) == 0
+    out.fill_(float("nan"))
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    try:
+        keep = []
+        try:                                                     # what the allocator still holds free
+            while True:
+                keep.append(torch.empty(1 << 19, dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            pass
+        _call(F, d, STREAMS, out)
+        assert "subtree_kernel" not in F.fff_last_launch()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(out, plain)
+    L, p = F.lib(), lambda t: ctypes.c_void_p(t.data_ptr())
+    args = lambda o: [p(t) for t in d[:3]] + [1e-5] + [p(t) for t in d[3:]] + [7, 4, 6, GELU, 1, p(o), None, None, 6000, 256, 256, 1]
+    need = F.fff_block_scratch_bytes(6000, 256, 256, 7, 4, 6, True, BF16)
+    scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
+    for entry, more, want in ((L.fff_forward_block, [], plain), (L.fff_forward_block_scratch, [None, 0], plain),
+                              (L.fff_forward_block_scratch, [p(scratch), need], grouped)):
+        out.fill_(float("nan"))
+        assert entry(*args(out), *more) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    assert L.fff_forward_block_scratch(*args(out), p(scratch), need - 1) == 6
+    assert L.fff_forward_block_scratch(*args(out), ctypes.c_void_p(scratch.data_ptr() + 16), need) == 6
+    assert L.fff_forward_block_scratch(*args(out), p(out), need) == 8
 
 
 @pytest.mark.parametrize("T,D,O,depth,n,L,dtype,expect", [
