@@ -946,8 +946,8 @@ int fff_forward_block_scratch(const void* x, const void* ln_gamma, const void* l
     }
     begin_device_call();
     g_opt.last_block_kernel = vector_rows ? 1 : 2;
+    g_block_tuning.last_top = 0;        // (of this call; the lane groups say what they keep)
     if (by_token) {
-        g_block_tuning.last_top = 0;
         hipError_t e = launch_token_block(p, leaf_idx, (hipStream_t)stream, nullptr, nullptr, &wide);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }

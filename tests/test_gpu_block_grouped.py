@@ -86,6 +86,18 @@ def _grouped_and_not(F, d):
     return grouped, plain
 
 
+def test_last_block_top_is_of_the_last_call(forced):
+    import paper_2308_14711_amd as F
+    case = ("top", 32768) + STREAMS[2:]
+    print("\n[case] grouped block, last_block_top after a call with levels in LDS T=32768 D=256 depth=7 n=4 L=6", flush=True)
+    d = _state(case, 40)
+    forced(3)
+    for option, staged in ((1, True), (5, False)):
+        F.fff_debug_option("subtree", option)
+        _rows(F, d, case)
+        assert ("subtree_kernel" not in F.fff_last_launch()) == staged and (F.fff_get_option("last_block_top") > 0) == staged
+
+
 def test_calls_overlap_on_several_streams(forced):
     """Calls of different inputs in flight together on six streams (and on one given by its handle), three times: every result is that of
     the call alone, bit for bit."""
