@@ -297,10 +297,13 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
 
     // fp32 products are added up 16 at a time, from zero, and these sums with what their additions lose kept beside them (mostly in the
     // shadow of the matrix instructions; 78 -> 80 us): one chain over the whole row would round as often as the row is long (25216
-    // tokens of 768, 8 neurons: results off by 4.1e-7 in one chain, 0.93e-7 so, 0.99e-7 in the gather kernel, which adds over lanes)
-    f32x4_t acc[NB], lost[BF16 ? 1 : NB];
+    // tokens of 768, 8 neurons: results off by 4.1e-7 in one chain, 0.93e-7 so, 0.99e-7 in the gather kernel, which adds over lanes).
+    // The second bf16 row of a normalised token has sums of its own as well.  Either remainder counts only where it is finite: an infinite
+    // product or sum makes inf - inf of it, and the sum beside it is the right result alone.
+    constexpr bool REST = !BF16 || LN;
+    f32x4_t acc[NB], rest[REST ? NB : 1];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = lost[BF16 ? 0 : b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < NB; ++b) acc[b] = rest[REST ? b : 0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const auto multiply = [&](int kc, auto tail) {
         const uint4* xs = ring + (kc % kStages) * kStagePieces;
         const uint4* ws = xs + kTok * 8;
@@ -326,13 +329,13 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
                     acc[b] = mfma_piece<BF16>(wr[b], hi, acc[b]);
                 } else {
                     const f32x4_t t = mfma_piece<BF16>(wr[b], hi, f32x4_t{0.f, 0.f, 0.f, 0.f}), sum = acc[b] + t, part = sum - acc[b];
-                    lost[BF16 ? 0 : b] += (acc[b] - (sum - part)) + (t - part);
+                    rest[REST ? b : 0] += (acc[b] - (sum - part)) + (t - part);
                     acc[b] = sum;
                 }
             }
             if (LN && BF16) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) acc[b] = mfma_piece<BF16>(wr[b], lo, acc[b]);
+                for (int b = 0; b < NB; ++b) rest[REST ? b : 0] = mfma_piece<BF16>(wr[b], lo, rest[REST ? b : 0]);
             }
         }
     };
@@ -355,14 +358,13 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
     // ---- the walk: a token's four lanes (j, 0..3) go together
     float* const S = (float*)ring;                          // [kTok][kPitch]
     float* const hid = S + kTok * kPitch;                   // the hidden activations
-    if (!BF16) {
-        // (a sum that met or reached an infinity is that sum alone: what its additions lost is inf - inf then)
+    if (REST) {
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float l = lost[BF16 ? 0 : b][q];
-                acc[b][q] += fabsf(l) < __builtin_inff() ? l : 0.0f;
+                const float r = rest[REST ? b : 0][q];
+                acc[b][q] += fabsf(r) < __builtin_inff() ? r : 0.0f;
             }
     }
 #pragma unroll

@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 
 import fff_workloads as W
+import oracle
+from fff_testlib import ROUTING_MARGIN, TOL, out_to_f64
 from test_gpu_block import _check, _inputs, _upload
 
 pytestmark = pytest.mark.gpu
@@ -231,3 +233,41 @@ def test_which_batches_take_them(T, D, O, depth, n, L, dtype, expect):
     torch.cuda.synchronize()
     assert ("subtree_kernel" in F.fff_last_launch()) == expect, F.fff_last_launch()
     assert not out.any()
+
+
+@pytest.mark.parametrize("what", ["gamma", "nodes", "leaves"])
+def test_infinite_gammas_and_weights_on_normalised_bf16_rows(what, forced):
+    """An infinite scale of one feature, or infinite weights: routing, infinities and NaN as the oracle has them (both bf16 rows of a
+    token meet an infinite weight, the second with any sign or zero).  The same for calls of rows of up to 1024 features with longer output
+    rows, whose launch without scratch has the token in fp32."""
+    import torch
+    import paper_2308_14711_amd as F
+    case = ("inf", 700, 512, 1040, 5, 3, 4, RELU, BF16, True, False)
+    name, T, D, O, depth, n, L, act, dtype, norm, residual = case
+    print("\n[case] grouped block bf16 infinities in %s T=%d D=%d O=%d depth=%d n=%d L=%d seed 41" % ((what,) + case[1:7]), flush=True)
+    forced(2)
+    x, ln, nodes, leaves = _inputs(*case[:-1], 41)
+    ln, nodes, leaves = [a.copy() for a in ln], [a.copy() for a in nodes], [a.copy() for a in leaves]
+    inf, minus_inf = np.uint16(0x7F80), np.uint16(0xFF80)
+    if what == "gamma":
+        ln[0][17] = inf
+    elif what == "nodes":
+        nodes[0][0, 0, -1], nodes[0][1:3, 1, 30] = inf, minus_inf
+    else:
+        leaves[0][::2, 1, -1], leaves[0][1::2, 2, 100] = inf, minus_inf
+    d = [_upload(x)] + [_upload(a) for a in ln] + [_upload(a) for a in nodes] + [_upload(a) for a in leaves]
+    out = torch.full((T, O), 7.0, dtype=torch.bfloat16, device="cuda")
+    idx = torch.full((T,), -9, dtype=torch.int32, device="cuda")
+    _call(F, d, case, out, idx)
+    torch.cuda.synchronize()
+    assert "subtree_kernel" in F.fff_last_launch()
+    ref, ref_idx, margin = oracle.forward_block(x, *ln, 1e-5, *nodes, *leaves, depth, n, L, act, residual)
+    same = idx.cpu().numpy() == ref_idx
+    assert (margin[~same] < ROUTING_MARGIN).all() and same.sum() > T // 2, "routing differs from the oracle"
+    got, want = out_to_f64(out)[same], ref[same]
+    assert not np.isfinite(want).all() or what == "nodes"
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    assert np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
+    fin = np.isfinite(want)
+    scale = np.where(fin, np.abs(want), 0).max(axis=1, keepdims=True) + 1e-30
+    assert (np.abs(np.where(fin, got, 0) - np.where(fin, want, 0)) <= TOL[dtype] * scale).all()
