@@ -431,6 +431,21 @@ int subtree_levels(const Problem& p, bool leaves_given) {
     return pick;
 }
 
+// Which of the two leaf stages is ahead: the MFMA tile path (hidden activations rounded to bf16), or the gather kernel (fp32
+// ones, which the subtree launch in its place keeps).
+//
+// The tile path pays once a leaf has a few neurons (for 1-2 the VALU gather kernel is leaner)
+// and a tile of 16 slots holds few different leaves: from 8 tokens a leaf on average (measured
+// on 768-wide rows, 50432 tokens, 8 neurons: 12 tokens a leaf 118 us tiles against 128 gather,
+// 6 tokens a leaf 168 against 151; leaves of more than 8 neurons always, the gather kernel
+// needs twice the time there); up to 8192 tokens only from 32 tokens a leaf (4096 tokens, 8
+// neurons, 8 tokens a leaf: 40 us against 32)
+bool leaf_tiles_pay(const Problem& p) {
+    const int64_t per_leaf = p.depth < 40 ? p.T >> p.depth : 0;
+    const bool filled = (p.T > 32 * (int64_t)device_info().cus && (p.L > 8 || per_leaf >= 8)) || per_leaf >= 32;
+    return tiles_shape_ok(p) && p.L >= 3 && filled;
+}
+
 int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& ws, hipStream_t s,
                    bool timed = false, const DescentCounts* dc = nullptr) {
     hipError_t e;
@@ -439,7 +454,7 @@ int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& w
         if (rc != FFF_OK) return rc;
         if (timed) stage_mark(s);
         g_opt.last_leaf_path = 4;
-        e = launch_subtree(p, 0, ws.perm, ws.offset, nullptr, s);
+        e = launch_subtree(p, 0, ws.perm, ws.offset, nullptr, s, !leaf_tiles_pay(p));
         for (int i = 0; timed && i < 2; ++i) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "subtree kernel launch");
     }
@@ -454,16 +469,7 @@ int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& w
     const int rc = run_bucket(leaf_idx, p.T, p.depth, ws, nullptr, nullptr, ws.perm, ws.slot_leaf, s, dc);
     if (rc != FFF_OK) return rc;
     if (timed) stage_mark(s);
-    // the MFMA tile path pays once a leaf has a few neurons (for 1-2 the VALU gather kernel is leaner)
-    // and a tile of 16 slots holds few different leaves: from 8 tokens a leaf on average (measured
-    // on 768-wide rows, 50432 tokens, 8 neurons: 12 tokens a leaf 118 us tiles against 128 gather,
-    // 6 tokens a leaf 168 against 151; leaves of more than 8 neurons always, the gather kernel
-    // needs twice the time there); up to 8192 tokens only from 32 tokens a leaf (4096 tokens, 8
-    // neurons, 8 tokens a leaf: 40 us against 32)
-    const int64_t per_leaf = p.depth < 40 ? p.T >> p.depth : 0;
-    const bool filled = (p.T > 32 * (int64_t)device_info().cus && (p.L > 8 || per_leaf >= 8)) || per_leaf >= 32;
-    const bool tiles = g_opt.leaf_path != 1 && tiles_shape_ok(p) &&
-                       (g_opt.leaf_path == 2 || (p.L >= 3 && filled));
+    const bool tiles = g_opt.leaf_path != 1 && tiles_shape_ok(p) && (g_opt.leaf_path == 2 || leaf_tiles_pay(p));
     // On request ("leaf_split"), tiles whose 16 slots hold that many different leaves or more are
     // left to the gather kernel, one lane group per token, and the tile kernels keep the tiles of
     // well-filled buckets.  Not the default: on every shape measured one of the two kernels alone
@@ -592,7 +598,7 @@ int run_block_grouped(const Problem& p, const WideNodes& wide, const BlockCut& c
         e = launch_subtree_levels(p, cut.first, cut.second, ws.perm, ws.offset, node, s, wide, stats, nullptr);
         if (e == hipSuccess) e = bucket(node, above, nullptr);
     }
-    if (e == hipSuccess) e = launch_subtree(p, cut.leaf, ws.perm, ws.offset, leaf_idx, s, &wide, stats);
+    if (e == hipSuccess) e = launch_subtree(p, cut.leaf, ws.perm, ws.offset, leaf_idx, s, true, &wide, stats);
     return e == hipSuccess ? FFF_OK : set_device_error(e, "block kernel launch");
 }
 
@@ -719,7 +725,7 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
         if (rc != FFF_OK) return rc;
         if (marks) stage_mark(s);
         g_opt.last_leaf_path = 4;
-        e = launch_subtree(p, k, ws.perm, ws.offset, leaf_idx, s);
+        e = launch_subtree(p, k, ws.perm, ws.offset, leaf_idx, s, !leaf_tiles_pay(p));
         for (int i = 0; marks && i < 2; ++i) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "subtree kernel launch");
     }

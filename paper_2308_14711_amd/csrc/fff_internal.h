@@ -179,12 +179,13 @@ struct WideNodes {
 // The last k levels of the walk, the leaf network and the output row of tokens grouped by the node of
 // level depth - k they have reached (perm, and offset [2^(depth - k) + 1]); needs subtree_shape_ok(p, k).
 // leaf_idx (optional): the leaf reached.  k = 0: the leaf networks alone.
-// wide (optional): fff_forward_block's nodes, norm and residual; stats [2 T]: what launch_subtree_levels from the root left.
+// fp32_hidden (bf16 calls): hidden activations in all bits of fp32, not in the 16 of two bf16 values.
+// wide (optional): fff_forward_block's nodes, norm and residual (hidden activations in all bits of fp32); stats [2 T]: what launch_subtree_levels from the root left.
 constexpr int kSubtreeMaxColumns = 128;
 int64_t subtree_columns(int k, int node_size, int L);
 bool subtree_shape_ok(const Problem& p, int k, const WideNodes* wide = nullptr);
 hipError_t launch_subtree(const Problem& p, int k, const int32_t* perm, const int32_t* offset, int32_t* leaf_idx, hipStream_t s,
-                          const WideNodes* wide = nullptr, float* stats = nullptr);
+                          bool fp32_hidden, const WideNodes* wide = nullptr, float* stats = nullptr);
 // Levels base_level .. base_level + k - 1 of wide nodes: node_idx[t] = position of the node reached in its level.  perm and offset as above
 // for base_level > 0, null for the root (dc, optional: per-tile counts for launch_bucket_fold).
 hipError_t launch_subtree_levels(const Problem& p, int base_level, int k, const int32_t* perm, const int32_t* offset, int32_t* node_idx,

@@ -52,6 +52,8 @@ struct SubtreeArgs {
     const int32_t* offset;   // [groups + 1]; null: one group of all tokens in their order
     int64_t T;
     int groups, row_bytes, pieces, O, L, act, k, n, base_level, cols, node_cols, residual;
+    int row_parts;           // bf16 rows that make a normalised token: 2, or 3 (all of fp32)
+    int hidden_parts;        // bf16 values that make a hidden activation: 2, or 3
     float eps;
 };
 
@@ -143,9 +145,11 @@ constexpr int hidden_pitch(int steps) { return 4 * steps + 1; }
 enum { kLinear, kWide, kNorm };     // nodes: one neuron, n hidden neurons, n hidden neurons on the normalised token
 
 // A piece of a token's row as the matrix instruction takes it.  A normalised bf16 row is the sum of two bf16
-// rows, hi = bf16(z) and lo = bf16(z - hi): a relative 2^-17 of each element, below the accumulation noise.
+// rows, hi = bf16(z) and lo = bf16(z - hi): a relative 2^-17 of each element, as block_group_kernel keeps it; or of three,
+// lo2 = z - hi - lo, which is all of the fp32 row, as block_kernel keeps it.
 template <bool BF16, bool LN>
-__device__ __forceinline__ void token_piece(const uint4& x, const uint4& g, const uint4& b, float mean, float rstd, uint4* hi, uint4* lo) {
+__device__ __forceinline__ void token_piece(const uint4& x, const uint4& g, const uint4& b, float mean, float rstd, bool three, uint4* hi,
+                                            uint4* lo, uint4* lo2) {
     if (!LN) {
         *hi = x;
         return;
@@ -163,6 +167,12 @@ __device__ __forceinline__ void token_piece(const uint4& x, const uint4& g, cons
 #pragma unroll
         for (int e = 0; e < E; ++e) f[e] -= gf[e];
         *lo = narrow<BF16>(f);
+        if (three) {
+            widen<BF16>(*lo, gf);
+#pragma unroll
+            for (int e = 0; e < E; ++e) f[e] -= gf[e];
+            *lo2 = narrow<BF16>(f);
+        }
     }
 }
 
@@ -170,8 +180,8 @@ template <int LB>
 __device__ __forceinline__ void write_rows_f32(const SubtreeArgs& a, const float* hid, const int32_t* s_tok, const int32_t* s_sub, int n,
                                                int64_t first_leaf);
 template <bool RESIDUAL>
-__device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint4* hid, const int32_t* s_tok, const int32_t* s_sub, int n,
-                                                int64_t first_leaf, int steps);
+__device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint4* hid, const uint2* third, int third_pitch, const int32_t* s_tok,
+                                                const int32_t* s_sub, int n, int64_t first_leaf, int steps);
 
 // LEAF: the last k levels, the leaf and the output row; else k levels, the node reached, and (from the root) the tile's counts.
 template <bool BF16, int NODES, bool LEAF, int NB>
@@ -304,6 +314,7 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
     f32x4_t acc[NB], rest[REST ? NB : 1];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = rest[REST ? b : 0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const bool three = LN && BF16 && a.row_parts == 3;
     const auto multiply = [&](int kc, auto tail) {
         const uint4* xs = ring + (kc % kStages) * kStagePieces;
         const uint4* ws = xs + kTok * 8;
@@ -312,8 +323,8 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
             const int piece = 8 * kc + 2 * kg + u;
             const bool in = !decltype(tail)::value || piece < a.pieces;
             const int gp = LN ? (in ? piece : 0) : 0;
-            uint4 hi, lo;
-            token_piece<BF16, LN>(xs[tile_swz(tok, 2 * kg + u)], s_gamma[gp], s_beta[gp], mean, rstd, &hi, &lo);
+            uint4 hi, lo, lo2;
+            token_piece<BF16, LN>(xs[tile_swz(tok, 2 * kg + u)], s_gamma[gp], s_beta[gp], mean, rstd, three, &hi, &lo, &lo2);
             if (decltype(tail)::value) hi = keep_if(in, hi);
             if (decltype(tail)::value && LN && BF16) lo = keep_if(in, lo);
             uint4 wr[NB];
@@ -336,6 +347,11 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
             if (LN && BF16) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) rest[REST ? b : 0] = mfma_piece<BF16>(wr[b], lo, rest[REST ? b : 0]);
+                if (three) {
+                    if (decltype(tail)::value) lo2 = keep_if(in, lo2);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) rest[REST ? b : 0] = mfma_piece<BF16>(wr[b], lo2, rest[REST ? b : 0]);
+                }
             }
         }
     };
@@ -416,14 +432,29 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
         const int pairs = a.L << a.k, steps = (pairs + (1 << a.k) + 15) / 16, pitch = hidden_pitch(steps);
         uint4* const hrow = (uint4*)hid + tok * pitch;
         for (int i = kg; i < 4 * steps; i += 4) hrow[i] = make_uint4(0, 0, 0, 0);
+        // (the third values go where the token's row of S was, whose readers are this token's lanes, done with it)
+        constexpr int kThirdPitch = kPitch / 2;
+        static_assert(4 * (NB + 1) + 1 <= kThirdPitch, "the third values of a token fit its row of S");
+        uint2* const third = (uint2*)S;
+        uint2* const trow = third + tok * kThirdPitch;
+        const bool exact = a.hidden_parts == 3;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (exact)
+            for (int i = kg; i < 4 * steps; i += 4) trow[i] = make_uint2(0, 0);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const auto put = [&](int p, float v) {
             uint16_t* const at = (uint16_t*)(hrow + p / 4) + p % 4;
             const uint16_t hi = f32_to_bf16(v);
+            const bool whole = (hi & 0x7f80) == 0x7f80;                // (an infinite value is its hi alone)
+            const float left = whole ? 0.0f : v - bf16_to_f32(hi);
+            const uint16_t lo = f32_to_bf16(left);
             at[0] = hi;
-            at[4] = (hi & 0x7f80) == 0x7f80 ? 0 : f32_to_bf16(v - bf16_to_f32(hi));      // (an infinite value is its hi alone)
+            at[4] = lo;
+            if (exact) ((uint16_t*)(trow + p / 4))[p % 4] = f32_to_bf16(left - bf16_to_f32(lo));
         };
 #pragma unroll
         for (int i = 0; i < kMaxL / 4; ++i)
@@ -434,7 +465,7 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
             s_sub[tok] = sub;
         }
         __syncthreads();
-        write_rows_mfma<WIDE>(a, (const uint4*)hid, s_tok, s_sub, at.n, first_leaf, steps);
+        write_rows_mfma<WIDE>(a, (const uint4*)hid, exact ? third : nullptr, kThirdPitch, s_tok, s_sub, at.n, first_leaf, steps);
         return;
     }
     if (kg == 0) s_sub[tok] = live ? sub : 1 << a.k;        // tokens past the tile's end sort last
@@ -514,7 +545,9 @@ __device__ __forceinline__ void write_rows_f32(const SubtreeArgs& a, const float
 
 // The same for bf16 on the matrix cores, for the whole tile at once: out[token][o] over (leaf, neuron) pairs and, for the
 // biases, one pair a leaf whose activation is 1.  A token's activations are zero outside its own leaf; they are the sum of two
-// bf16 values, so that 16 pairs fill the 32 K slots of an instruction against the same weights.  Each wave takes 64
+// bf16 values, so that 16 pairs fill the 32 K slots of an instruction against the same weights, or (third) of three, which is
+// all of the fp32 value: 16 more slots (fff_forward_block, 50432 tokens of 768, 4 neurons a node, 8 a leaf: 138 -> 145 us; two steps'
+// third values in one instruction of 32 slots spill: 150).  Each wave takes 64
 // columns of all 64 tokens at a time, so that a weight is loaded, and turned around, once a tile: weights are
 // contiguous along o while the instruction wants K contiguous, so a lane loads 4 consecutive o of its 4 rows, and
 // column j of the c-th instruction stands for o = 64 R + 4 j + c.
@@ -524,8 +557,8 @@ __device__ __forceinline__ uint32_t pair_of(uint32_t a, uint32_t b, int hi) {
 
 // Columns 64 r .. 64 r + 63 of the tile's output rows, a token after the other from its own leaf's weights: for weights that
 // are not finite, which against the zeros of another leaf's token, or the lower half of an activation, would make NaN.
-__device__ __forceinline__ void write_rows_apart(const SubtreeArgs& a, const uint4* hid, int pitch, const int32_t* s_tok, const int32_t* s_sub, int n,
-                                              int64_t first_leaf, int r) {
+__device__ __forceinline__ void write_rows_apart(const SubtreeArgs& a, const uint4* hid, int pitch, const uint2* third, int third_pitch,
+                                              const int32_t* s_tok, const int32_t* s_sub, int n, int64_t first_leaf, int r) {
     const int lane = threadIdx.x & 63, O = a.O, o = 64 * r + lane;
     if (o >= O) return;
     for (int i = 0; i < n; ++i) {
@@ -534,7 +567,9 @@ __device__ __forceinline__ void write_rows_apart(const SubtreeArgs& a, const uin
         float y = Elem<true>::load(a.b2, leaf * O + o);
         for (int k = 0; k < a.L; ++k) {
             const int p = s_sub[i] * a.L + k;
-            const float v = bf16_to_f32(h[8 * (p / 4) + p % 4]) + bf16_to_f32(h[8 * (p / 4) + 4 + p % 4]);
+            float v = bf16_to_f32(h[8 * (p / 4) + 4 + p % 4]);
+            if (third) v += bf16_to_f32(((const uint16_t*)(third + i * third_pitch))[p]);
+            v += bf16_to_f32(h[8 * (p / 4) + p % 4]);
             y = fmaf(v, Elem<true>::load(a.w2, (leaf * a.L + k) * O + o), y);
         }
         if (a.residual) y += Elem<true>::load(a.x, t * O + o);
@@ -543,8 +578,8 @@ __device__ __forceinline__ void write_rows_apart(const SubtreeArgs& a, const uin
 }
 
 template <bool RESIDUAL>
-__device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint4* hid, const int32_t* s_tok, const int32_t* s_sub, int n,
-                                                int64_t first_leaf, int steps) {
+__device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint4* hid, const uint2* third, int third_pitch, const int32_t* s_tok,
+                                                const int32_t* s_sub, int n, int64_t first_leaf, int steps) {
     constexpr int kAhead = 5;                                // steps requested together
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, j = lane & 15, kg = lane >> 4;
     const int O = a.O, ranges = (O + 63) / 64, pairs = a.L << a.k, rows = pairs + (1 << a.k), pitch = hidden_pitch(steps);
@@ -613,12 +648,23 @@ __device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint
 #pragma unroll
                     for (int c = 0; c < 4; ++c) acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[c], acc[g][c], 0, 0, 0);
                 }
+                if (third) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const s16x4_t fa = __builtin_bit_cast(s16x4_t, third[(16 * g + j) * third_pitch + 4 * (s0 + s) + kg]);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const uint4 w4 = __builtin_bit_cast(uint4, fb[c]);
+                            acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa, __builtin_bit_cast(s16x4_t, make_uint2(w4.x, w4.y)), acc[g][c], 0, 0, 0);
+                        }
+                    }
+                }
             }
         }
         // the next range's weights before this one's rows leave: a wait for a load is a wait for everything before it
         if (r + 4 < ranges) request_weights(r + 4, 0);
         if (__ballot(most.x >= 0x7f80 || most.y >= 0x7f80)) {
-            write_rows_apart(a, hid, pitch, s_tok, s_sub, n, first_leaf, r);
+            write_rows_apart(a, hid, pitch, third, third_pitch, s_tok, s_sub, n, first_leaf, r);
             continue;
         }
         const bool whole = 64 * r + 64 <= O;
@@ -664,7 +710,7 @@ template <int NODES, bool LEAF> hipError_t dispatch(const SubtreeArgs& a, bool b
     return bf16 ? dispatch_cols<true, NODES, LEAF>(a, tiles, s) : dispatch_cols<false, NODES, LEAF>(a, tiles, s);
 }
 
-SubtreeArgs make_args(const Problem& p, int base_level, int k, const WideNodes* wide, float* stats) {
+SubtreeArgs make_args(const Problem& p, int base_level, int k, const WideNodes* wide, float* stats, bool fp32_hidden) {
     SubtreeArgs a = {};
     a.x = (const char*)p.x;
     a.node_w = (const char*)(wide ? wide->w1 : p.node_w);
@@ -694,6 +740,10 @@ SubtreeArgs make_args(const Problem& p, int base_level, int k, const WideNodes* 
     a.k = k;
     a.base_level = base_level;
     a.node_cols = ((1 << k) - 1) * (wide ? wide->n : 1);
+    // as precise as the launch that a call takes otherwise: fff_forward_block's kernels have activations in fp32, and rows
+    // beyond those of 16 lanes too
+    a.row_parts = wide && p.O * 2 > kMaxNormPieces * 16 ? 3 : 2;
+    a.hidden_parts = wide || fp32_hidden ? 3 : 2;
     return a;
 }
 
@@ -713,9 +763,9 @@ bool subtree_shape_ok(const Problem& p, int k, const WideNodes* wide) {
 }
 
 hipError_t launch_subtree(const Problem& p, int k, const int32_t* perm, const int32_t* offset, int32_t* leaf_idx, hipStream_t s,
-                          const WideNodes* wide, float* stats) {
+                          bool fp32_hidden, const WideNodes* wide, float* stats) {
     if (p.T == 0) return hipSuccess;
-    SubtreeArgs a = make_args(p, p.depth - k, k, wide, stats);
+    SubtreeArgs a = make_args(p, p.depth - k, k, wide, stats, fp32_hidden);
     a.leaf_idx = leaf_idx;
     a.perm = perm;
     a.offset = offset;
@@ -728,7 +778,7 @@ hipError_t launch_subtree(const Problem& p, int k, const int32_t* perm, const in
 hipError_t launch_subtree_levels(const Problem& p, int base_level, int k, const int32_t* perm, const int32_t* offset, int32_t* node_idx,
                                  hipStream_t s, const WideNodes& wide, float* stats, DescentCounts* dc) {
     if (p.T == 0) return hipSuccess;
-    SubtreeArgs a = make_args(p, base_level, k, &wide, stats);
+    SubtreeArgs a = make_args(p, base_level, k, &wide, stats, false);
     a.leaf_idx = node_idx;
     a.perm = perm;
     a.offset = offset;

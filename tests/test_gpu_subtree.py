@@ -220,3 +220,146 @@ def test_infinite_pre_activations_in_the_grouped_block(what, act, forced):
     finally:
         F.fff_debug_option("token_max_T", old_T)
     _same_infinities(new, old)
+
+
+def _whole_numbers(T, D, O, depth, L, shape_of_nodes):
+    """Tokens, nodes and leaves of small whole numbers whose sums are exact in fp32.  A leaf's first two neurons have up to 22 bits and
+    differ in the lowest 13; their output weights are 1 and -1, so an output is that difference."""
+    import torch
+    g = torch.Generator().manual_seed(17)
+    r = lambda shape, low, high: torch.randint(low, high + 1, shape, generator=g).to(torch.bfloat16)
+    nodes, leaves, half = (1 << depth) - 1, 1 << depth, D // 2
+    x = r((T, D), -2, 2)
+    x[:, :half] = x[:, :half].abs()
+    w1 = torch.zeros((leaves, L, D), dtype=torch.bfloat16)
+    w1[:, 0, :half] = r((leaves, half), 1, 63) * 1024
+    w1[:, 1, :half] = w1[:, 0, :half]
+    w1[:, :2, half:] = r((leaves, 2, D - half), -63, 63)
+    w2 = torch.zeros((leaves, L, O), dtype=torch.bfloat16)
+    w2[:, 0], w2[:, 1] = 1, -1
+    node_w = r((nodes,) + shape_of_nodes + (D,), -3, 3)
+    return x, node_w, w1, torch.zeros((leaves, L), dtype=torch.bfloat16), w2, torch.zeros((leaves, O), dtype=torch.bfloat16)
+
+
+def _bits(t):
+    import torch
+    return np.ascontiguousarray(t.contiguous().view(torch.int16).numpy().view(np.uint16))
+
+
+@pytest.mark.parametrize("T,depth,L,k", [(1000, 6, 9, 0), (1000, 6, 16, 1), (1500, 7, 12, 2), (700, 5, 2, 0), (700, 5, 2, 3)])
+def test_hidden_activations_keep_all_bits_where_the_gather_kernel_does(T, depth, L, k, forced):
+    """The batches of 8 to 31 tokens a leaf (and leaves of two neurons) that go to the gather kernel otherwise, in fp32: exact."""
+    import oracle
+    import torch
+    import paper_2308_14711_amd as F
+    D, O = 64, 72
+    print("\n[case] subtree whole numbers T=%d depth=%d L=%d k=%d seed 17" % (T, depth, L, k), flush=True)
+    x, node_w, w1, b1, w2, b2 = _whole_numbers(T, D, O, depth, L, ())
+    node_b = torch.zeros(len(node_w), dtype=torch.bfloat16)
+    forced(k)
+    out = torch.full((T, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+    F.fff_forward_hard(*[t.cuda() for t in (x, node_w, node_b, w1, b1, w2, b2)], depth, L, RELU, out)
+    torch.cuda.synchronize()
+    assert "subtree_kernel" in F.fff_last_launch()
+    ref, _, _ = oracle.forward_hard(*[_bits(t) for t in (x, node_w, node_b, w1, b1, w2, b2)], depth, L, RELU)
+    want = torch.from_numpy(ref).to(torch.bfloat16)
+    assert (want != 0).float().mean() > 0.9 and torch.equal(out.cpu(), want)
+
+
+def test_hidden_activations_keep_all_bits_in_the_grouped_block(forced):
+    import oracle
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, n, L = 1000, 64, 72, 6, 2, 5
+    print("\n[case] grouped block whole numbers T=%d depth=%d n=%d L=%d k=2 seed 17" % (T, depth, n, L), flush=True)
+    x, node_w, w1, b1, w2, b2 = _whole_numbers(T, D, O, depth, L, (n,))
+    nodes = [node_w, torch.zeros(node_w.shape[:2], dtype=torch.bfloat16), torch.ones(node_w.shape[:2], dtype=torch.bfloat16),
+             torch.full(node_w.shape[:1], -20, dtype=torch.bfloat16)]
+    forced(2)
+    old_T = F.fff_debug_option("token_max_T")
+    F.fff_debug_option("token_max_T", 0)
+    out = torch.full((T, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+    F.fff_forward_block(x.cuda(), None, None, 0.0, *[t.cuda() for t in nodes + [w1, b1, w2, b2]], depth, n, L, RELU, False, out)
+    torch.cuda.synchronize()
+    F.fff_debug_option("token_max_T", old_T)
+    assert "subtree_kernel" in F.fff_last_launch()
+    ref, idx, _ = oracle.forward_block(_bits(x), None, None, 0.0, *[_bits(t) for t in nodes + [w1, b1, w2, b2]], depth, n, L, RELU, False)
+    want = torch.from_numpy(ref).to(torch.bfloat16)
+    assert len(set(idx.tolist())) > 8 and (want != 0).float().mean() > 0.9 and torch.equal(out.cpu(), want)
+
+
+@pytest.mark.parametrize("D", [512, 1024, 136])
+def test_normalised_rows_keep_all_bits_where_output_rows_are_longer(D, forced):
+    """Output rows of more than 1024 features, whose launch without scratch has the normalised token in fp32.  A leaf neuron of
+    ones sums a token's normalised elements, which is zero but for rounding: about sqrt(D) 2^-25 from fp32 elements (measured here: the
+    launch without scratch), sqrt(D) 2^-18 from pairs of bf16 ones, a hundred times that.  Twice the former is allowed."""
+    import torch
+    import paper_2308_14711_amd as F
+    T, O, depth, n, L = 600, 1032, 2, 1, 2
+    print("\n[case] grouped block sums of normalised rows T=%d D=%d O=%d k=1 seed 18" % (T, D, O), flush=True)
+    g = torch.Generator().manual_seed(18)
+    bf = lambda t: t.to(torch.bfloat16).cuda()
+    ones, zeros = (lambda *s: bf(torch.ones(s))), (lambda *s: bf(torch.zeros(s)))
+    x, node_w = bf(torch.randn(T, D, generator=g)), bf(torch.randn(3, n, D, generator=g))
+    w1 = ones(4, L, D)
+    w1[:, 1] = -1
+    w2 = ones(4, L, O)
+    forced(1)
+    old_T = F.fff_debug_option("token_max_T")
+    F.fff_debug_option("token_max_T", 0)
+    rms = []
+    for option in (3, 1):
+        F.fff_debug_option("subtree", option)
+        out = torch.full((T, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+        F.fff_forward_block(x, ones(D), zeros(D), 1e-5, node_w, zeros(3, n), ones(3, n), zeros(3), w1, zeros(4, L), w2, zeros(4, O), depth, n, L,
+                            RELU, False, out)
+        torch.cuda.synchronize()
+        assert ("subtree_kernel" in F.fff_last_launch()) == (option == 3), F.fff_last_launch()
+        rms.append(out.double().pow(2).mean().sqrt().item())
+    F.fff_debug_option("token_max_T", old_T)
+    print("   rms %.3e, launch without scratch %.3e" % tuple(rms), flush=True)
+    assert 0 < rms[0] <= 2 * rms[1]
+
+
+@pytest.mark.parametrize("T,D,O,depth,n,L,act,dtype,k", [
+    (6000, 768, 768, 4, 0, 8, GELU, BF16, 0), (3000, 392, 392, 7, 0, 12, GELU, BF16, 1),          # in the place of the tile kernels, the gather kernel
+    (4000, 768, 768, 5, 0, 8, GELU, F32, 0), (4000, 256, 392, 6, 0, 4, RELU, F32, 1),
+    (3000, 768, 768, 6, 4, 8, GELU, BF16, 2), (3000, 272, 1536, 4, 4, 16, RELU, BF16, 1), (3000, 512, 512, 6, 4, 8, GELU, F32, 1)], ids=str)
+def test_error_against_64_bits_is_no_larger_than_without_it(T, D, O, depth, n, L, act, dtype, k, forced):
+    """2-norm of the difference from the oracle (64 bits) through the subtree launch, and through the launches it stands for.  A bf16 call's
+    error is its last rounding's: results that differ by less than that round alike but for ties (1e-4 allowed); sums in fp32 differ by
+    their order (5 % allowed)."""
+    import oracle
+    import torch
+    import paper_2308_14711_amd as F
+    from fff_testlib import oracle_inputs
+    print("\n[case] subtree error T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d k=%d seed 19" % (T, D, O, depth, n, L, act, dtype, k), flush=True)
+    w = W.make_layer("subtree_error", T, D, O, depth, L, act, dtype, seed=19)
+    dev, ins = to_device(w), oracle_inputs(w)
+    up = lambda a: torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16) if dtype == BF16 else torch.from_numpy(a).cuda()
+    forced(k)
+    old_T = F.fff_debug_option("token_max_T")
+    F.fff_debug_option("token_max_T", 0)
+    errors = []
+    if n:
+        nodes, ln = W.wide_nodes(depth, n, D, dtype, seed=19), W.layer_norm_params(D, dtype, seed=19)
+        ref, ref_idx, _ = oracle.forward_block(ins[0], *ln, 1e-5, *nodes, *ins[3:], depth, n, L, act, False)
+        args = [up(np.ascontiguousarray(a)) for a in list(ln) + list(nodes)]
+    else:
+        ref, ref_idx, _ = oracle.forward_hard(*ins, depth, L, act)
+    for option in (k + 2, 1):
+        F.fff_debug_option("subtree", option)
+        out = torch.empty((T, O), dtype=dev["x"].dtype, device="cuda")
+        idx = torch.empty((T,), dtype=torch.int32, device="cuda")
+        if n:
+            F.fff_forward_block(dev["x"], *args[:2], 1e-5, *args[2:], *[dev[t] for t in W.TENSORS[3:]], depth, n, L, act, False, out, idx)
+        else:
+            F.fff_forward_hard(*[dev[t] for t in W.TENSORS], depth, L, act, out, idx)
+        torch.cuda.synchronize()
+        assert ("subtree_kernel" in F.fff_last_launch()) == (option > 1), F.fff_last_launch()
+        same = idx.cpu().numpy() == ref_idx
+        assert same.mean() > 0.99
+        errors.append(np.linalg.norm(out_to_f64(out)[same] - ref[same]) / np.linalg.norm(ref[same]))
+    F.fff_debug_option("token_max_T", old_T)
+    print("   %.5e, without it %.5e" % tuple(errors), flush=True)
+    assert errors[0] <= errors[1] * (1.0001 if dtype == BF16 else 1.05)
