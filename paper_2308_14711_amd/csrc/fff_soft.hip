@@ -401,6 +401,7 @@ __global__ __launch_bounds__(256, 2) void soft_hidden_big_kernel(const SoftArgs 
         big_tile_flush(tile, a.hid, a.K2, a.T, NH, t0, n0);
         return;
     }
+    const bool four_of_a_leaf = a.L % 4 == 0;            // (biases at any address)
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
         const uint32_t n = (uint32_t)(n0 + 128 * wn + 16 * nt + 4 * kg);   // this lane's neurons n .. n + 3
@@ -428,8 +429,9 @@ __global__ __launch_bounds__(256, 2) void soft_hidden_big_kernel(const SoftArgs 
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
             float m[4];
+            m[0] = mrow[mt][leaf[0]];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) m[q] = mrow[mt][leaf[q]];
+            for (int q = 1; q < 4; ++q) m[q] = four_of_a_leaf ? m[0] : mrow[mt][leaf[q]];
             f32x4_t v;
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = activate_bulk(acc[mt][nt][q] + bias[q], GELU ? 1 : 0) * m[q];
