@@ -400,14 +400,18 @@ int64_t g_subtree = 0;   // debug option "subtree"
 
 // How many of the last levels the subtree launch takes; -1: whole descent and leaf kernels.
 //
-// Wherever tokens are grouped the subtree launch is ahead of the leaf kernels, by 1.22 (bf16) and 1.28 (fp32) on average over 975 random
-// calls of both (25216 tokens, 768-wide, depth 8, 8 neurons, fp32 103 -> 77 us; 50432 bf16 71 -> 68, 12000 1024-wide, 16 neurons
-// 41 -> 31), except where
+// Where tokens are grouped the subtree launch is mostly ahead of the leaf kernels (25216 tokens, 768-wide, depth 8, 8 neurons, fp32: leaf
+// kernels 103 us, subtree launch 80; 50432 bf16 71 / 66; 12000 1024-wide, 16 neurons 41 / 31).  Not so, in the same order, where
 //   - there are fewer tiles of 64 tokens than compute units and rows of more than 4 KB, whose pieces a tile walks in turn (14315 tokens,
-//     3168-wide, 93 / 99), fp32 on half as many (3521 tokens of 856, 12 neurons 38 / 48), or bf16 leaves of up to 8 neurons, where little is
+//     3168-wide 93 / 99), fp32 on half as many (3521 tokens of 856, 12 neurons 38 / 48), or bf16 leaves of up to 8 neurons, where little is
 //     to be had (16384 tokens of 768, depth 8 34 / 30 us),
-//   - output rows are many times the input rows (34782 tokens, 88 to 584 features, 16 neurons 37 / 45),
-//   - leaves see few tokens (19686 of fp32, depth 11 41 / 44; 5679 of bf16, depth 11, 16 neurons 19 / 29).
+//   - output rows are three times as long as input rows and more (34782 tokens, 88 to 584 features, 16 neurons 37 / 45),
+//   - leaves see few tokens (19686 of fp32, depth 11 41 / 44; 5679 of bf16, depth 11, 16 neurons 19 / 29),
+//   - leaves are small, while the launch computes 16 columns of whatever a tile holds: fewer than 3 neurons, in fp32 4 (26448 bf16 tokens
+//     of 128, depth 8, one neuron 15 / 21; 12168 fp32 ones of 656 to 912, depth 9, one neuron 22 / 38), or fp32 and less than 8 KB of rows for a token (30567 of 136, depth 10, 9 neurons 28 / 40),
+//   - the leaves are given, so that small groups cannot be merged: fewer than 64 tokens a leaf (fp32: and fewer tiles than compute units), or
+//     1024 leaves of less than 8 KB of rows for a token (bf16, 42600 tokens of 112, 8 neurons 24 / 32; fp32 16386 of 176, 6 neurons 18 / 35).
+// Of 6000 random calls in whose place these lines put 3000 here, 1.27 times as fast on average, 39 are more than 5 % slower for it.
 // A tile wants whole groups: k grows until a group has 128 tokens on average, while the columns computed for all of a group stay few (48;
 // one block of 16 for fp32, whose matrix instructions run at a sixteenth of the rate): 50432 tokens, 8 neurons, depth 10, k = 0, 1, 2: 93, 91,
 // 83 us; fp32, 12000 tokens, depth 8, 4 neurons 53, 47, 50.
@@ -417,10 +421,11 @@ int subtree_levels(const Problem& p, bool leaves_given) {
         const int k = leaves_given ? 0 : (int)g_subtree - 2;
         return subtree_shape_ok(p, k) ? k : -1;
     }
-    const int64_t row_bytes = p.D * (p.bf16 ? 2 : 4);
+    const int64_t es = p.bf16 ? 2 : 4, row_bytes = p.D * es, leaf_bytes = p.L * (p.D + p.O) * es;
     const int64_t cus = device_info().cus;
-    const bool filled = p.T >= 64 * cus || (row_bytes <= 4096 && (p.bf16 ? p.L > 8 : p.T > 32 * cus));
-    if (!filled || p.T >> p.depth < (p.bf16 ? 8 : 16) || (p.bf16 && p.O > 4 * p.D)) return -1;
+    const bool filled = p.T >= 64 * cus || (row_bytes <= 4096 && (p.bf16 ? p.L > 8 : !leaves_given && p.T > 32 * cus));
+    if (!filled || p.O > 3 * p.D || p.T >> p.depth < (leaves_given ? 64 : p.bf16 ? 8 : 16)) return -1;
+    if (p.L < (p.bf16 ? 3 : 4) || (!p.bf16 && leaf_bytes < 8192) || (leaves_given && p.depth >= 10 && leaf_bytes < 8192)) return -1;
     int pick = -1;
     for (int k = 0; k <= (leaves_given ? 0 : 3); ++k) {
         if (!subtree_shape_ok(p, k)) continue;
@@ -428,7 +433,7 @@ int subtree_levels(const Problem& p, bool leaves_given) {
         pick = k;
         if (p.T >> (p.depth - k) >= 128) break;
     }
-    return pick;
+    return pick >= 0 && !p.bf16 && p.T >> (p.depth - pick) < 32 ? -1 : pick;
 }
 
 // Which of the two leaf stages is ahead: the MFMA tile path (hidden activations rounded to bf16), or the gather kernel (fp32
@@ -446,10 +451,11 @@ bool leaf_tiles_pay(const Problem& p) {
     return tiles_shape_ok(p) && p.L >= 3 && filled;
 }
 
-int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& ws, hipStream_t s,
+// subtree: whether the subtree launch takes the leaves
+int run_leaf_stage(const Problem& p, const int32_t* leaf_idx, const Workspace& ws, hipStream_t s, bool subtree,
                    bool timed = false, const DescentCounts* dc = nullptr) {
     hipError_t e;
-    if (subtree_levels(p, true) == 0) {
+    if (subtree) {
         const int rc = run_bucket(leaf_idx, p.T, p.depth, ws, nullptr, ws.offset, ws.perm, ws.slot_leaf, s, dc);
         if (rc != FFF_OK) return rc;
         if (timed) stage_mark(s);
@@ -499,7 +505,7 @@ int run_leaf_any(const Problem& p, const int32_t* leaf_idx, hipStream_t s) {
     Layout lay;
     const int rc = get_workspace(p.T, p.depth, &ws, &lay, s);
     if (rc != FFF_OK) return rc;
-    return run_leaf_stage(p, leaf_idx, ws, s);   // falls back per shape inside
+    return run_leaf_stage(p, leaf_idx, ws, s, subtree_levels(p, true) == 0);   // falls back per shape inside
 }
 
 // How fff_forward_block's tree is cut for the grouped launches: levels from the root in one or two launches, `leaf` levels with the leaves.
@@ -732,7 +738,7 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
     e = launch_descend(p, li, s, &dc);
     if (e != hipSuccess) return set_device_error(e, "descent kernel launch");
     if (marks) stage_mark(s);
-    return run_leaf_stage(p, li, ws, s, marks, &dc);
+    return run_leaf_stage(p, li, ws, s, k == 0, marks, &dc);
 }
 
 }  // namespace
@@ -868,7 +874,7 @@ int fff_moe_top1_forward(const void* x, const void* gate_w, const void* gate_b, 
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
     g_opt.last_path = kPathStaged;
-    return run_leaf_stage(p, ei, ws, s, true);
+    return run_leaf_stage(p, ei, ws, s, subtree_levels(p, true) == 0, true);
 }
 
 int fff_forward_soft(const void* x, const void* node_w, const void* node_b, const void* leaf_w1,

@@ -109,6 +109,10 @@ def test_leaf_stage_alone(forced):
     (16384, 768, 768, 8, 8, BF16, "k=1"), (16383, 768, 768, 8, 8, BF16, "leaf_hidden_kernel"),         # a tile a compute unit
     (8193, 512, 512, 5, 12, BF16, "k=0"), (8193, 2304, 256, 5, 12, BF16, "leaf_hidden_kernel"),        # wider leaves: rows of up to 4 KB
     (16384, 128, 520, 6, 16, BF16, "leaf_hidden_kernel"),                                                # output rows four times the input rows
+    (16384, 128, 392, 6, 16, BF16, "leaf_hidden_kernel"), (16384, 128, 384, 6, 16, BF16, "k=0"),        # and three times
+    (8193, 768, 768, 6, 4, F32, "k=0"), (8193, 1024, 1024, 6, 3, F32, "leaf_gather_kernel"),            # fp32: four neurons
+    (9000, 128, 128, 6, 8, F32, "k=0"), (9000, 124, 124, 6, 8, F32, "leaf_gather_kernel"),              # fp32: 8 KB of leaf rows
+    (20000, 192, 192, 10, 9, F32, "leaf_gather_kernel"),                                                 # fp32: 32 tokens a group
     (8193, 512, 512, 6, 8, F32, "k=0"), (8192, 512, 512, 9, 8, F32, "fused"), (20000, 512, 512, 11, 8, F32, "leaf_gather_kernel"),
 ], ids=str)
 def test_which_batches_take_it(T, D, O, depth, L, dtype, expect):
@@ -119,9 +123,33 @@ def test_which_batches_take_it(T, D, O, depth, L, dtype, expect):
     z = lambda *s: torch.zeros(s, dtype=dt, device="cuda")
     n = 1 << depth
     out = torch.empty((T, O), dtype=dt, device="cuda")
-    F.fff_forward_hard(z(T, D), z(n - 1, D), z(n - 1), z(n, L, D), z(n, L), z(n, L, O), z(n, O), depth, L, RELU, out)
+    staged = D * L < 2000                               # (would go to the fused launch)
+    F.fff_set_option("path", 2 if staged else 0)
+    try:
+        F.fff_forward_hard(z(T, D), z(n - 1, D), z(n - 1), z(n, L, D), z(n, L), z(n, L, O), z(n, O), depth, L, RELU, out)
+    finally:
+        F.fff_set_option("path", 0)
     torch.cuda.synchronize()
     assert expect in F.fff_last_launch(), F.fff_last_launch()
+    assert not out.any()
+
+
+@pytest.mark.parametrize("T,D,O,depth,L,dtype,expect", [
+    (16384, 512, 512, 8, 8, BF16, True), (16383, 512, 512, 8, 8, BF16, False), (16384, 512, 512, 9, 8, BF16, False),      # 64 tokens a leaf
+    (65536, 256, 256, 10, 8, BF16, True), (65536, 248, 248, 10, 8, BF16, False),                                           # 1024 leaves: 8 KB
+    (16384, 512, 512, 7, 8, F32, True), (16383, 512, 512, 7, 8, F32, False), (30000, 900, 900, 5, 2, F32, False),
+    (30000, 904, 904, 5, 2, BF16, False), (30000, 904, 904, 5, 3, BF16, True),
+], ids=str)
+def test_which_batches_of_given_leaves_take_it(T, D, O, depth, L, dtype, expect):
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] subtree rule, leaves given T=%d D=%d O=%d depth=%d L=%d dtype=%d" % (T, D, O, depth, L, dtype), flush=True)
+    z = lambda *s: torch.zeros(s, dtype=torch.bfloat16 if dtype == BF16 else torch.float32, device="cuda")
+    n = 1 << depth
+    out = z(T, O).fill_(float("nan"))
+    F.fff_leaf_forward(z(T, D), z(n, L, D), z(n, L), z(n, L, O), z(n, O), torch.arange(T, dtype=torch.int32, device="cuda") % n, depth, L, RELU, out)
+    torch.cuda.synchronize()
+    assert ("subtree_kernel" in F.fff_last_launch()) == expect, F.fff_last_launch()
     assert not out.any()
 
 
