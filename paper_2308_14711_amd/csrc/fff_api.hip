@@ -3,6 +3,7 @@
 // (Algorithm 1): descent -> bucketing -> leaf networks with fused output rows.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -522,44 +523,75 @@ bool cut_at(const Problem& p, const WideNodes& wide, int leaf, BlockCut* cut) {
     return fits(cut->first) && bucket_hist_ok(p.T, above);
 }
 
-// Estimates of both sides' time in us, fitted to 2125 random calls (half of them within 9 and 17 %): the grouped launches' goes with
-// the rows' bytes (and the columns computed for them, in blocks of 16), one launch a token's with the bytes of the weight rows that a
-// token meets.  The grouped launches are taken where they are estimated a fifth faster (fp32, whose sums have been made more exact since the
-// fit, a third): 388 further calls that so change their route, 1.79 (bf16) and 2.15 (fp32) on average (50432 tokens, 768-wide, depth 8, 4
-// neurons a node, 8 a leaf 219 -> 141 us; 20000 of 512 to 1600 features 209 -> 72), one in twenty-five more than 5 % slower.
+// Estimates of both sides' time in us: sums of terms, their weights fitted to random calls of 600 to 131072 tokens that take more than 25 us
+// (profiles/grouped_block_estimates.csv: 1200 calls, all cuts).  Half of the estimates are within 5 % (grouped) and 7 % (one launch).
+template <int N> double weighted(const double (&weight)[N], const double (&term)[N]) {
+    double t = 0;
+    for (int i = 0; i < N; ++i) t += weight[i] * term[i];
+    return t;
+}
+
+// The grouped launches' time goes with the tiles of each launch (a partly filled one ends every group; 512 run at a time), times the
+// row's pieces of 128 bytes (more where rows do not start on lines), and the columns computed for them in blocks of 16, and the output
+// row's ranges of 64 columns and their steps.
 double grouped_estimate(const Problem& p, const WideNodes& wide, const BlockCut& c) {
     const auto blocks = [](int64_t cols) {
         const int64_t b = (cols + 15) / 16;
         return (double)(b <= 2 ? b : b <= 4 ? 4 : b <= 6 ? 6 : 8);
     };
-    const double es = p.bf16 ? 2e-6 : 4e-6, in = es * (double)(p.T * p.D), out = es * (double)(p.T * p.O);
-    const double first = blocks(subtree_columns(c.first, wide.n, 0)), second = c.second ? blocks(subtree_columns(c.second, wide.n, 0)) : 0;
-    const double last = blocks(subtree_columns(c.leaf, wide.n, p.L)), steps = (double)(((p.L + 1) * (1 << c.leaf) + 15) / 16);
-    const double groups = (double)((int64_t)1 << (p.depth - c.leaf));
-    if (p.bf16)
-        return 30 + (c.second ? 12 + 0.49 * in : 0) + in * (0.56 + 0.05 * first + 0.067 * second + 0.063 * last) + out * (0.35 + 0.04 * steps) +
-               0.0067 * groups;
-    return 32 + (c.second ? 12 + 0.28 * in : 0) + in * (0.24 + 0.116 * first + 0.158 * second + 0.14 * last) + out * (0.18 + 0.032 * steps) +
-           0.0079 * groups;
-}
-double ungrouped_estimate(const Problem& p, const WideNodes& wide) {
-    const double es = p.bf16 ? 2e-6 : 4e-6, T = (double)p.T, out = es * (double)(p.T * p.O), levels = 1e-3 * T * p.depth, neurons = 1e-3 * T * p.L;
-    const double node_rows = es * T * p.depth * wide.n * (double)p.D, leaf_rows = es * T * p.L * (double)(p.D + p.O);
-    const bool lane_groups = (p.D > p.O ? p.D : p.O) * (p.bf16 ? 2 : 4) <= 2048;
-    if (p.bf16)
-        return lane_groups ? 7.5 + 0.38 * out + 0.068 * node_rows + 0.045 * leaf_rows + 0.048 * levels + 0.018 * neurons
-                           : 8 + 0.123 * node_rows + 0.61 * levels + 0.42 * neurons;
-    return lane_groups ? 6.8 + 0.18 * out + 0.052 * node_rows + 0.046 * leaf_rows + 0.047 * levels
-                       : 6.3 + 0.55 * out + 0.105 * node_rows + 0.1 * leaf_rows + 0.2 * levels;
+    const double T = (double)p.T;
+    const auto tiles = [&](int level) {         // in thousands
+        const double groups = (double)((int64_t)1 << level), a_group = T / groups;
+        const double t = level == 0 ? T / 64 : T / 64 + groups * (a_group < 0.5 ? a_group : 0.5);
+        return 1e-3 * (t < 256 ? 256 : 0.7 * t + 0.3 * 512 * ceil(t / 512));
+    };
+    const double second = c.second ? 1 : 0, norm = wide.gamma ? 1 : 0, residual = p.D == p.O ? 1 : 0;   // (if it can have one)
+    const double pieces = (double)((p.D * (p.bf16 ? 2 : 4) + 127) / 128), ranges = (double)((p.O + 63) / 64);
+    const double parts = !wide.gamma || !p.bf16 ? 1 : subtree_row_parts(p);
+    const double steps = (double)(((p.L + 1) * (1 << c.leaf) + 15) / 16);
+    const double first_cols = blocks(subtree_columns(c.first, wide.n, 0)), second_cols = blocks(subtree_columns(c.second, wide.n, 0));
+    const double leaf_cols = blocks(subtree_columns(c.leaf, wide.n, p.L));
+    const double t1 = tiles(0), t2 = second * tiles(c.first), t3 = tiles(c.first + c.second);
+    const double off_lines = p.D * (p.bf16 ? 2 : 4) % 128 ? 1 : 0, out_off_lines = p.O * (p.bf16 ? 2 : 4) % 128 ? 1 : 0;
+    const double term[15] = {1, second, t1 * pieces, t1 * pieces * norm, t1 * pieces * first_cols * parts, t2 * pieces, t2 * pieces * norm,
+                             t2 * pieces * second_cols * parts, t3 * pieces * leaf_cols * parts, t3 * ranges, t3 * ranges * steps,
+                             t3 * ranges * residual, t1 + t2 + t3, (t1 + t2 + t3) * pieces * off_lines, t3 * ranges * out_off_lines};
+    constexpr double bf16[15] = {16, 10.2, 1.32, 3.65, 0.156, 0.487, 1.84, 0.151, 0.162, 0.572, 0.488, 0.571, 8.83, 0.037, 0.491};
+    constexpr double f32[15] = {19, 8.68, 0, 1.93, 1.01, 0.429, 1.09, 1.04, 1.08, 2.13, 0.324, 1.64, 7.95, 0.208, 0};
+    return weighted(p.bf16 ? bf16 : f32, term);
 }
 
+// One launch a token's time goes with the pieces a lane holds of each weight row that a token meets (rows in flight together: batches), and
+// with these rows' bytes, the more where all rows together outgrow an L2.  Lanes with eight pieces are the slowest.
+double ungrouped_estimate(const Problem& p, const WideNodes& wide) {
+    const int64_t longest = ((p.D > p.O ? p.D : p.O) * (p.bf16 ? 2 : 4) + 15) / 16;
+    const bool lane_groups = longest <= 128;
+    const int64_t held = (longest + (lane_groups ? 15 : 63)) / (lane_groups ? 16 : 64);
+    const int64_t nv = held <= 2 ? (lane_groups ? 2 : held) : held <= 4 ? 4 : held <= 6 && lane_groups ? 6 : 8;
+    const int64_t together = lane_groups ? (nv >= 6 ? 2 : 4) : nv >= 8 ? 1 : nv >= 4 ? 2 : 4;
+    const bool narrow = wide.n == 1 && lane_groups;
+    const int64_t node_batches = narrow ? 1 : (wide.n + together - 1) / together, node_rows = narrow ? 1 : node_batches * together;
+    const int64_t leaf_rows = (p.L + together - 1) / together * together;
+    const double es = p.bf16 ? 2e-6 : 4e-6, T = 1e-3 * (double)p.T, D = (double)p.D, O = (double)p.O, v = T * (double)nv, eight = nv == 8 ? 1 : 0;
+    const double nodes = (double)(p.depth * node_rows), leaf = (double)leaf_rows;
+    const double table = es * (wide.n * D + p.L * (D + O)) * (double)((int64_t)1 << p.depth) / 4;
+    const double met = 1e3 * es * T * (p.depth * wide.n * D + p.L * (D + O));
+    const double term[12] = {1, 1e3 * es * T * O, v * nodes, T * (double)(p.depth * node_batches), v * leaf, met,
+                             met * (table < 4 ? table : 4), v, v * eight, v * nodes * eight, v * leaf * eight, wide.gamma ? v : 0};
+    constexpr double bf16_lanes[12] = {12, 0.0931, 0.00724, 0.0115, 0.013, 0.00333, 0.0064, 0, 0.0335, 0.00328, 0.00967, 0.0703};
+    constexpr double bf16_waves[12] = {12.2, 0.143, 0.0471, 0, 0.0542, 0.00712, 0.00665, 0.00999, 0.162, 0.0228, 0.0545, 0.103};
+    constexpr double f32_lanes[12] = {14.5, 0.0699, 0.00321, 0.0235, 0.00777, 0.00797, 0.00538, 0, 0.0159, 0.00105, 0.00151, 0.0277};
+    constexpr double f32_waves[12] = {12.4, 0.0827, 0.0362, 0, 0.0482, 0.00321, 0.00653, 0, 0.143, 0.0104, 0.0172, 0.0802};
+    return p.bf16 ? weighted(lane_groups ? bf16_lanes : bf16_waves, term) : weighted(lane_groups ? f32_lanes : f32_waves, term);
+}
+
+// The grouped launches are taken where they are estimated to be 1.15 times as fast: 1199 of 6360 further random calls, 1.86 times as fast on
+// average, 7 of them more than 5 % slower (50432 tokens, 768-wide, depth 8, 4 neurons a node, 8 a leaf: 219 us in one launch, 145 grouped;
+// 20000 of 512 to 1600 features 209 and 72).  The cut that is estimated fastest takes 0.7 % longer than the fastest on average.
 bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
     if (g_subtree == 1) return false;
     if (g_subtree >= 2) return cut_at(p, wide, (int)g_subtree - 2, cut);
-    // Rows that 16 lanes hold stay in their one launch up to 160 tokens a compute unit: it needs no scratch and gives the same bits eager and
-    // captured, which callers of such batches have (40000 tokens, 768-wide, depth 8: 177 us there, 122 grouped).
-    if ((p.D > p.O ? p.D : p.O) * (p.bf16 ? 2 : 4) <= 2048 && p.T <= 160 * (int64_t)device_info().cus) return false;
-    double best = ungrouped_estimate(p, wide) / (p.bf16 ? 1.2 : 1.35);
+    double best = ungrouped_estimate(p, wide) / 1.15;
     bool found = false;
     for (int leaf = 0; leaf <= 4; ++leaf) {
         BlockCut c;

@@ -183,6 +183,7 @@ struct WideNodes {
 // wide (optional): fff_forward_block's nodes, norm and residual (hidden activations in all bits of fp32); stats [2 T]: what launch_subtree_levels from the root left.
 constexpr int kSubtreeMaxColumns = 128;
 int64_t subtree_columns(int k, int node_size, int L);
+int subtree_row_parts(const Problem& p);
 bool subtree_shape_ok(const Problem& p, int k, const WideNodes* wide = nullptr);
 hipError_t launch_subtree(const Problem& p, int k, const int32_t* perm, const int32_t* offset, int32_t* leaf_idx, hipStream_t s,
                           bool fp32_hidden, const WideNodes* wide = nullptr, float* stats = nullptr);

@@ -740,14 +740,17 @@ SubtreeArgs make_args(const Problem& p, int base_level, int k, const WideNodes* 
     a.k = k;
     a.base_level = base_level;
     a.node_cols = ((1 << k) - 1) * (wide ? wide->n : 1);
-    // as precise as the launch that a call takes otherwise: fff_forward_block's kernels have activations in fp32, and rows
-    // beyond those of 16 lanes too
-    a.row_parts = wide && p.O * 2 > kMaxNormPieces * 16 ? 3 : 2;
+    a.row_parts = subtree_row_parts(p);
+    // as precise as the launch that a call takes otherwise: fff_forward_block's kernels have activations in fp32
     a.hidden_parts = wide || fp32_hidden ? 3 : 2;
     return a;
 }
 
 }  // namespace
+
+// Normalised bf16 rows: as precise as the launch that a call takes otherwise, which has pairs where 16 lanes hold the longest
+// row of a call, and fp32 beyond.
+int subtree_row_parts(const Problem& p) { return p.O * 2 > kMaxNormPieces * 16 ? 3 : 2; }
 
 int64_t subtree_columns(int k, int node_size, int L) { return (((int64_t)1 << k) - 1) * node_size + ((int64_t)L << k); }
 

@@ -156,8 +156,17 @@ STAGED = [
 ]
 
 
+@pytest.fixture
+def without_grouped_launches():
+    """Large batches keep the launch that needs no scratch."""
+    import paper_2308_14711_amd as F
+    F.fff_debug_option("subtree", 1)
+    yield
+    F.fff_debug_option("subtree", 0)
+
+
 @pytest.mark.parametrize("case", STAGED, ids=[c[0] for c in STAGED])
-def test_block_with_top_levels_in_lds(case):
+def test_block_with_top_levels_in_lds(case, without_grouped_launches):
     import torch
     import paper_2308_14711_amd as F
     print("\n[case] block %s T=%d D=%d O=%d depth=%d n=%d L=%d act=%d dtype=%d norm=%s residual=%s seed 5, %d levels in LDS" % case, flush=True)

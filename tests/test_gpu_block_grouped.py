@@ -217,9 +217,10 @@ def test_without_scratch_the_one_launch_runs(forced):
 
 
 @pytest.mark.parametrize("T,D,O,depth,n,L,dtype,expect", [
-    (40961, 768, 768, 8, 4, 8, BF16, True), (40960, 768, 768, 8, 4, 8, BF16, False),      # rows that 16 lanes hold: 160 tokens a compute unit
-    (20000, 512, 1600, 7, 4, 8, BF16, True), (2000, 512, 1600, 7, 4, 8, BF16, False),      # longer rows: by estimate
+    (50432, 768, 768, 8, 4, 8, BF16, True), (30000, 768, 768, 8, 4, 8, BF16, True), (16384, 768, 768, 8, 4, 8, BF16, False),      # by estimate
+    (20000, 512, 1600, 7, 4, 8, BF16, True), (2000, 512, 1600, 7, 4, 8, BF16, False),
     (45000, 64, 64, 3, 1, 2, BF16, False), (20000, 1032, 1032, 7, 4, 8, BF16, False),      # few rows met; a normalised row of more than 1024
+    (50000, 768, 768, 8, 4, 17, BF16, False),                                               # leaves of more than 16 neurons
 ], ids=str)
 def test_which_batches_take_them(T, D, O, depth, n, L, dtype, expect):
     import torch
