@@ -448,8 +448,9 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const auto put = [&](int p, float v) {
             uint16_t* const at = (uint16_t*)(hrow + p / 4) + p % 4;
-            const uint16_t hi = f32_to_bf16(v);
-            const bool whole = (hi & 0x7f80) == 0x7f80;                // (an infinite value is its hi alone)
+            const uint16_t near = f32_to_bf16(v);
+            const bool whole = !(fabsf(v) < __builtin_inff());                                   // (an infinite value is its hi alone)
+            const uint16_t hi = !whole && (near & 0x7fff) == 0x7f80 ? near - 1 : near;           // (a finite one does not round to infinity)
             const float left = whole ? 0.0f : v - bf16_to_f32(hi);
             const uint16_t lo = f32_to_bf16(left);
             at[0] = hi;

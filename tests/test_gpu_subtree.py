@@ -316,6 +316,31 @@ def test_hidden_activations_keep_all_bits_in_the_grouped_block(forced):
     assert len(set(idx.tolist())) > 8 and (want != 0).float().mean() > 0.9 and torch.equal(out.cpu(), want)
 
 
+def test_a_finite_activation_beyond_the_largest_bf16_value_stays_finite(forced):
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L = 300, 64, 72, 4, 9
+    print("\n[case] subtree activations between the largest bf16 and fp32 values T=%d depth=%d L=%d k=1" % (T, depth, L), flush=True)
+    z = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")
+    most = torch.finfo(torch.bfloat16).max
+    x, node_w, w1, b1, w2 = z(T, D) + 1, z(15, D), z(16, L, D), z(16, L), z(16, L, O)
+    node_w[0::2, 3], node_w[1::2, 3] = 1, -1
+    w1[:, 2, 5], b1[:, 2], w2[:, 2] = most, 1e36, 2.0 ** -20
+    outs = []
+    forced(1)
+    for option in (3, 1):
+        F.fff_debug_option("subtree", option)
+        out = z(T, O).fill_(float("nan"))
+        if option == 1:
+            F.fff_set_option("leaf_path", 1)                     # the gather kernel
+        F.fff_forward_hard(x, node_w, z(15), w1, b1, w2, z(16, O), depth, L, RELU, out)
+        F.fff_set_option("leaf_path", 0)
+        torch.cuda.synchronize()
+        assert ("subtree_kernel" if option == 3 else "leaf_gather_kernel") in F.fff_last_launch(), F.fff_last_launch()
+        outs.append(out)
+    assert torch.isfinite(outs[1]).all() and (outs[1] > 3e32).all() and torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("D", [512, 1024, 136])
 def test_normalised_rows_keep_all_bits_where_output_rows_are_longer(D, forced):
     """Output rows of more than 1024 features, whose launch without scratch has the normalised token in fp32.  A leaf neuron of
