@@ -586,7 +586,7 @@ double ungrouped_estimate(const Problem& p, const WideNodes& wide) {
 }
 
 // The grouped launches are taken where they are estimated to be 1.15 times as fast: 1199 of 6360 further random calls, 1.86 times as fast on
-// average, 7 of them more than 5 % slower (50432 tokens, 768-wide, depth 8, 4 neurons a node, 8 a leaf: 219 us in one launch, 145 grouped;
+// average, 7 of them more than 5 % slower (50432 tokens, 768-wide, depth 8, 4 neurons a node, 8 a leaf: 219 us in one launch, 141 grouped;
 // 20000 of 512 to 1600 features 209 and 72).  The cut that is estimated fastest takes 0.7 % longer than the fastest on average.
 bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
     if (g_subtree == 1) return false;

@@ -52,7 +52,6 @@ struct SubtreeArgs {
     const int32_t* offset;   // [groups + 1]; null: one group of all tokens in their order
     int64_t T;
     int groups, row_bytes, pieces, O, L, act, k, n, base_level, cols, node_cols, residual;
-    int row_parts;           // bf16 rows that make a normalised token: 2, or 3 (all of fp32)
     int hidden_parts;        // bf16 values that make a hidden activation: 2, or 3
     float eps;
 };
@@ -142,14 +141,15 @@ constexpr int ring_bytes(int nb) { return ring_stages(nb) * stage_rows(nb) * 128
 // elements e and 4 + e of piece i; rows an odd number of pieces apart.
 constexpr int hidden_pitch(int steps) { return 4 * steps + 1; }
 
-enum { kLinear, kWide, kNorm };     // nodes: one neuron, n hidden neurons, n hidden neurons on the normalised token
+// nodes: one neuron, n hidden neurons, n hidden neurons on the normalised token (bf16: in two parts, or in three)
+enum { kLinear, kWide, kNorm, kNormWhole };
 
 // A piece of a token's row as the matrix instruction takes it.  A normalised bf16 row is the sum of two bf16
 // rows, hi = bf16(z) and lo = bf16(z - hi): a relative 2^-17 of each element, as block_group_kernel keeps it; or of three,
 // lo2 = z - hi - lo, which is all of the fp32 row, as block_kernel keeps it.
-template <bool BF16, bool LN>
-__device__ __forceinline__ void token_piece(const uint4& x, const uint4& g, const uint4& b, float mean, float rstd, bool three, uint4* hi,
-                                            uint4* lo, uint4* lo2) {
+template <bool BF16, bool LN, bool THREE>
+__device__ __forceinline__ void token_piece(const uint4& x, const uint4& g, const uint4& b, float mean, float rstd, uint4* hi, uint4* lo,
+                                            uint4* lo2) {
     if (!LN) {
         *hi = x;
         return;
@@ -167,7 +167,7 @@ __device__ __forceinline__ void token_piece(const uint4& x, const uint4& g, cons
 #pragma unroll
         for (int e = 0; e < E; ++e) f[e] -= gf[e];
         *lo = narrow<BF16>(f);
-        if (three) {
+        if (THREE) {
             widen<BF16>(*lo, gf);
 #pragma unroll
             for (int e = 0; e < E; ++e) f[e] -= gf[e];
@@ -186,7 +186,7 @@ __device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint
 // LEAF: the last k levels, the leaf and the output row; else k levels, the node reached, and (from the root) the tile's counts.
 template <bool BF16, int NODES, bool LEAF, int NB>
 __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
-    constexpr bool LN = NODES == kNorm, WIDE = NODES != kLinear;
+    constexpr bool LN = NODES >= kNorm, WIDE = NODES != kLinear, THREE = BF16 && NODES == kNormWhole;
     constexpr int kStages = ring_stages(NB), kRowsW = stage_rows(NB) - kTok;
     constexpr int kLoads = 2 + kRowsW / 32;                 // of a wave, a stage
     constexpr int kStagePieces = stage_rows(NB) * 8;
@@ -308,13 +308,13 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
     // fp32 products are added up 16 at a time, from zero, and these sums with what their additions lose kept beside them (mostly in the
     // shadow of the matrix instructions; 78 -> 80 us): one chain over the whole row would round as often as the row is long (25216
     // tokens of 768, 8 neurons: results off by 4.1e-7 in one chain, 0.93e-7 so, 0.99e-7 in the gather kernel, which adds over lanes).
-    // The second bf16 row of a normalised token has sums of its own as well.  Either remainder counts only where it is finite: an infinite
-    // product or sum makes inf - inf of it, and the sum beside it is the right result alone.
-    constexpr bool REST = !BF16 || LN;
+    // The second and third bf16 rows of a normalised token in three parts have sums of their own as well.  Either remainder counts only where
+    // it is finite: an infinite product or sum makes inf - inf of it, and the sum beside it is the right result alone.  (Two parts go into
+    // one sum, as in block_group_kernel, whose weights have to be finite too.)
+    constexpr bool REST = !BF16 || THREE;
     f32x4_t acc[NB], rest[REST ? NB : 1];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = rest[REST ? b : 0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const bool three = LN && BF16 && a.row_parts == 3;
     const auto multiply = [&](int kc, auto tail) {
         const uint4* xs = ring + (kc % kStages) * kStagePieces;
         const uint4* ws = xs + kTok * 8;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
             const bool in = !decltype(tail)::value || piece < a.pieces;
             const int gp = LN ? (in ? piece : 0) : 0;
             uint4 hi, lo, lo2;
-            token_piece<BF16, LN>(xs[tile_swz(tok, 2 * kg + u)], s_gamma[gp], s_beta[gp], mean, rstd, three, &hi, &lo, &lo2);
+            token_piece<BF16, LN, THREE>(xs[tile_swz(tok, 2 * kg + u)], s_gamma[gp], s_beta[gp], mean, rstd, &hi, &lo, &lo2);
             if (decltype(tail)::value) hi = keep_if(in, hi);
             if (decltype(tail)::value && LN && BF16) lo = keep_if(in, lo);
             uint4 wr[NB];
@@ -344,14 +344,16 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
                     acc[b] = sum;
                 }
             }
-            if (LN && BF16) {
+            if (LN && BF16 && !THREE) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] = mfma_piece<BF16>(wr[b], lo, acc[b]);
+            }
+            if (THREE) {
+                if (decltype(tail)::value) lo2 = keep_if(in, lo2);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) rest[REST ? b : 0] = mfma_piece<BF16>(wr[b], lo, rest[REST ? b : 0]);
-                if (three) {
-                    if (decltype(tail)::value) lo2 = keep_if(in, lo2);
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) rest[REST ? b : 0] = mfma_piece<BF16>(wr[b], lo2, rest[REST ? b : 0]);
-                }
+                for (int b = 0; b < NB; ++b) rest[REST ? b : 0] = mfma_piece<BF16>(wr[b], lo2, rest[REST ? b : 0]);
             }
         }
     };
@@ -547,8 +549,8 @@ __device__ __forceinline__ void write_rows_f32(const SubtreeArgs& a, const float
 // The same for bf16 on the matrix cores, for the whole tile at once: out[token][o] over (leaf, neuron) pairs and, for the
 // biases, one pair a leaf whose activation is 1.  A token's activations are zero outside its own leaf; they are the sum of two
 // bf16 values, so that 16 pairs fill the 32 K slots of an instruction against the same weights, or (third) of three, which is
-// all of the fp32 value: 16 more slots (fff_forward_block, 50432 tokens of 768, 4 neurons a node, 8 a leaf: 138 -> 145 us; two steps'
-// third values in one instruction of 32 slots spill: 150).  Each wave takes 64
+// all of the fp32 value: 16 more slots (fff_forward_block, 50432 tokens of 768, 4 neurons a node, 8 a leaf: 139.7 -> 141.1 us; two
+// steps' third values in one instruction of 32 slots spill: 150).  Each wave takes 64
 // columns of all 64 tokens at a time, so that a weight is loaded, and turned around, once a tile: weights are
 // contiguous along o while the instruction wants K contiguous, so a lane loads 4 consecutive o of its 4 rows, and
 // column j of the c-th instruction stands for o = 64 R + 4 j + c.
@@ -694,7 +696,7 @@ __device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint
 }
 
 template <bool BF16, int NODES, bool LEAF, int NB> hipError_t run(const SubtreeArgs& a, int64_t tiles, hipStream_t s) {
-    note_launch("subtree_kernel<%s,%s%s,%d> k=%d", BF16 ? "bf16" : "f32", NODES == kNorm ? "norm," : NODES == kWide ? "wide," : "", LEAF ? "leaf" : "levels", NB, a.k);
+    note_launch("subtree_kernel<%s,%s%s,%d> k=%d", BF16 ? "bf16" : "f32", NODES == kNorm ? "norm," : NODES == kNormWhole ? "norm3," : NODES == kWide ? "wide," : "", LEAF ? "leaf" : "levels", NB, a.k);
     subtree_kernel<BF16, NODES, LEAF, NB><<<dim3((unsigned)((tiles + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, s>>>(a);
     return hipGetLastError();
 }
@@ -709,6 +711,10 @@ template <bool BF16, int NODES, bool LEAF> hipError_t dispatch_cols(const Subtre
 }
 template <int NODES, bool LEAF> hipError_t dispatch(const SubtreeArgs& a, bool bf16, int64_t tiles, hipStream_t s) {
     return bf16 ? dispatch_cols<true, NODES, LEAF>(a, tiles, s) : dispatch_cols<false, NODES, LEAF>(a, tiles, s);
+}
+template <bool LEAF> hipError_t dispatch_wide(const Problem& p, const SubtreeArgs& a, int64_t tiles, hipStream_t s) {
+    if (!a.gamma) return dispatch<kWide, LEAF>(a, p.bf16, tiles, s);
+    return p.bf16 && subtree_row_parts(p) == 3 ? dispatch_cols<true, kNormWhole, LEAF>(a, tiles, s) : dispatch<kNorm, LEAF>(a, p.bf16, tiles, s);
 }
 
 SubtreeArgs make_args(const Problem& p, int base_level, int k, const WideNodes* wide, float* stats, bool fp32_hidden) {
@@ -741,7 +747,6 @@ SubtreeArgs make_args(const Problem& p, int base_level, int k, const WideNodes* 
     a.k = k;
     a.base_level = base_level;
     a.node_cols = ((1 << k) - 1) * (wide ? wide->n : 1);
-    a.row_parts = subtree_row_parts(p);
     // as precise as the launch that a call takes otherwise: fff_forward_block's kernels have activations in fp32
     a.hidden_parts = wide || fp32_hidden ? 3 : 2;
     return a;
@@ -775,8 +780,7 @@ hipError_t launch_subtree(const Problem& p, int k, const int32_t* perm, const in
     a.offset = offset;
     a.cols = a.node_cols + (p.L << k);
     const int64_t tiles = p.T / kTok + a.groups;             // at most: every group ends in a partly filled tile
-    if (!wide) return dispatch<kLinear, true>(a, p.bf16, tiles, s);
-    return wide->gamma ? dispatch<kNorm, true>(a, p.bf16, tiles, s) : dispatch<kWide, true>(a, p.bf16, tiles, s);
+    return wide ? dispatch_wide<true>(p, a, tiles, s) : dispatch<kLinear, true>(a, p.bf16, tiles, s);
 }
 
 hipError_t launch_subtree_levels(const Problem& p, int base_level, int k, const int32_t* perm, const int32_t* offset, int32_t* node_idx,
@@ -798,7 +802,7 @@ hipError_t launch_subtree_levels(const Problem& p, int base_level, int k, const 
             dc->n_rows = (int)tiles;
         }
     }
-    return wide.gamma ? dispatch<kNorm, false>(a, p.bf16, tiles, s) : dispatch<kWide, false>(a, p.bf16, tiles, s);
+    return dispatch_wide<false>(p, a, tiles, s);
 }
 
 }  // namespace fff
