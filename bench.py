@@ -415,7 +415,7 @@ def soft_bench(args, np, torch, W, F):
 
 def block_bench(args, np, torch, W, F):
     """Forward_I with nodes of --node-size hidden neurons as a pre-norm residual layer, on the shapes of
-    the chosen workload (bf16 ones with O = D).  One step = one call of fff_forward_block = one kernel;
+    the chosen workload (bf16 ones with O = D).  One step = one call of fff_forward_block;
     its duration comes from events on the stream of the calls.  Roofline: HBM, every tensor once."""
     import oracle
     w = W.config(args.config, keep_f32=False, T=args.tokens or None)
@@ -455,8 +455,7 @@ def block_bench(args, np, torch, W, F):
     kernel_ms = e0.elapsed_time(e1) / args.steps
     launch = F.fff_last_launch()
     es = 2 if w.dtype == W.DTYPE_BF16 else 4
-    # rows of up to 128 16-byte pieces take the 16-lanes-per-token kernel, longer ones a wave per token
-    kernel = "block_group_kernel" if max(w.D, w.O) * es <= 128 * 16 else "block_kernel"
+    kernel = launch.split("<")[0]                     # (the first of the grouped launches, or the one launch)
     # rows a token meets on its way: what the kernel asks of the caches per token
     row_bytes = es * (w.depth * n * w.D + w.leaf_width * (w.D + w.O))
     # the oracle on a prefix of the batch: parity of those rows, and its rate
