@@ -17,7 +17,7 @@
 //
 // What bounds it: a tile reads its token rows, then writes its output rows, and the tiles of a compute unit do so nearly in step.
 // 50432 tokens of 768 bf16 features, 256 leaves of 8 neurons, k = 0: 34 us (77 MB in at 4.5, 77 MB out at 5 TB/s, 3 us until the first
-// row arrives) where the two leaf kernels take 18 + 19; fp32, 25216 tokens: 38 us, the gather kernel 65.  Measured and not kept: token
+// row arrives) where the two leaf kernels take 18 + 19; fp32, 25216 tokens: 42 us, the gather kernel 65.  Measured and not kept: token
 // rows straight to registers in the instruction's layout (64 bytes of 16 rows a load: 47 us), 96 to 128 tokens a block, output rows 16
 // tokens at a time (more waves, but a chain of loads each: 36 -> 43 us), a deeper ring (no change).
 #include "fff_device.h"
