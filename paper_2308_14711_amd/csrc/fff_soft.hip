@@ -349,11 +349,12 @@ template <> __global__ __launch_bounds__(256, 2) void soft_nodes_mix_kernel<kBig
     if (ent_part != nullptr && tid < NN) ent_part[(t0 / kBigM) * a.NN + tid] = ent;
 }
 
+typedef uint32_t u32x2_any_t __attribute__((ext_vector_type(2), aligned(2)));       // (the memory system takes it at any address)
 // GELU, ONE_LEAF: template parameters -- chosen per element at run time either puts a branch around
 // every one of a lane's 128 evaluations, which then run one after the other, each behind its own trip for a
-// mixture weight.  ONE_LEAF (leaf widths that are multiples of 4, biases at 8 bytes): a lane's four consecutive
+// mixture weight.  ONE_LEAF (leaf widths that are multiples of 4; biases at any element): a lane's four consecutive
 // neurons belong to one leaf, and all 32 weights and 8 bias pieces of its tile are requested together (50432 tokens
-// of 768, 256 leaves of 8, GELU: the call 485 -> 469 us, the same bits).
+// of 768, 256 leaves of 8, GELU: the call 485 -> 469 us, the same bits; biases at an odd element 462 -> 443).
 template <bool GELU, bool ONE_LEAF>
 __global__ __launch_bounds__(256, 2) void soft_hidden_big_kernel(const SoftArgs a) {
     __shared__ BigTileLds tile;
@@ -382,7 +383,8 @@ __global__ __launch_bounds__(256, 2) void soft_hidden_big_kernel(const SoftArgs 
         for (int nt = 0; nt < 8; ++nt) {
             const uint32_t n = (uint32_t)(n0 + 128 * wn + 16 * nt + 4 * kg), nc = n < last ? n : last - 3;     // (a multiple of 4)
             const uint32_t leaf = nc / L32;
-            b[nt] = *(const uint2*)(a.b1 + nc);
+            const u32x2_any_t bias = *(const u32x2_any_t*)(a.b1 + nc);
+            b[nt] = make_uint2(bias.x, bias.y);
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) m[nt][mt] = mrow[mt][leaf];
         }
@@ -401,7 +403,6 @@ __global__ __launch_bounds__(256, 2) void soft_hidden_big_kernel(const SoftArgs 
         big_tile_flush(tile, a.hid, a.K2, a.T, NH, t0, n0);
         return;
     }
-    const bool four_of_a_leaf = a.L % 4 == 0;            // (biases at any address)
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
         const uint32_t n = (uint32_t)(n0 + 128 * wn + 16 * nt + 4 * kg);   // this lane's neurons n .. n + 3
@@ -429,9 +430,8 @@ __global__ __launch_bounds__(256, 2) void soft_hidden_big_kernel(const SoftArgs 
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
             float m[4];
-            m[0] = mrow[mt][leaf[0]];
 #pragma unroll
-            for (int q = 1; q < 4; ++q) m[q] = four_of_a_leaf ? m[0] : mrow[mt][leaf[q]];
+            for (int q = 0; q < 4; ++q) m[q] = mrow[mt][leaf[q]];
             f32x4_t v;
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = activate_bulk(acc[mt][nt][q] + bias[q], GELU ? 1 : 0) * m[q];
@@ -988,7 +988,7 @@ hipError_t launch_forward_soft(const Problem& p, int32_t* scratch, float* mix_ou
     if (hidden == kBig) {
         note_launch("soft_hidden_big_kernel");
         const dim3 g(big_grid(p.T, (NH + kBigN - 1) / kBigN));
-        const bool one_leaf = a.L % 4 == 0 && (reinterpret_cast<uintptr_t>(a.b1) & 7u) == 0;
+        const bool one_leaf = a.L % 4 == 0;
         const auto launch = [&](auto kern) { kern<<<g, dim3(256), 0, s>>>(a); };
         if (a.act != 0) one_leaf ? launch(soft_hidden_big_kernel<true, true>) : launch(soft_hidden_big_kernel<true, false>);
         else one_leaf ? launch(soft_hidden_big_kernel<false, true>) : launch(soft_hidden_big_kernel<false, false>);

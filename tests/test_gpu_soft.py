@@ -347,8 +347,8 @@ def test_forward_soft_on_more_tokens_than_one_launch_of_small_blocks_holds():
 
 @pytest.mark.parametrize("depth,L,act", [(7, 4, W.ACT_GELU), (2, 124, W.ACT_RELU), (8, 2, W.ACT_GELU)])
 def test_hidden_contraction_with_aligned_and_unaligned_biases(depth, L, act):
-    """Leaf widths that are multiples of 4 with biases at 8 bytes take a lane's mixture weights together, all
-    others look them up neuron by neuron: the same bits from both, and the oracle's rows (512
+    """Leaf widths that are multiples of 4 take a lane's mixture weights together and 8 bytes of biases at any element, all
+    others look them up neuron by neuron: the same bits from aligned and unaligned biases, and the oracle's rows (512
     neurons: whole column tiles, 496: a ragged one; 16300 tokens: a ragged row tile)."""
     import torch
     import paper_2308_14711_amd as F
