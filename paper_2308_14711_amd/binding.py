@@ -406,7 +406,8 @@ def fff_workspace_bytes_soft(T: int, O: int, depth: int, leaf_width: int) -> int
 
 def fff_set_workspace(buf, stream=None) -> None:
     """Every later call on the current device works in `buf` (a dense device tensor the caller keeps
-    alive), or in the library's own workspace again for buf = None."""
+    alive), or in the library's own workspace again for buf = None.  (fff_forward_block needs no workspace: its scratch is
+    torch's either way.)"""
     if buf is None:
         _check(lib().fff_set_workspace(None, 0, _stream_handle(stream)), "fff_set_workspace")
         return

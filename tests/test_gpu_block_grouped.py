@@ -36,6 +36,9 @@ CASES = [
     ("seven",      1500, 1024, 264,  9,     1, 5,  GELU, BF16,  True,  False, 2),        # seven levels from the root; the longest row
     ("two_steps",  2000, 136,  136,  8,     8, 4,  RELU, BF16,  True,  True,  2),        # 8 neurons a node: levels in two launches
     ("wide16",     1000, 200,  200,  4,     16, 16, GELU, BF16, True,  True,  1),        # 48 columns with the leaves
+    ("whole",      1500, 1024, 1040, 9,     1, 5,  GELU, BF16,  True,  False, 2),        # output rows of more than 1024: rows in three parts
+    ("whole_two",  1300, 136,  1032, 8,     8, 4,  RELU, BF16,  True,  False, 2),        # the same, levels in two launches, an odd stage
+    ("whole_one",  65,   8,    1032, 2,     1, 1,  GELU, BF16,  True,  False, 1),
     ("plain",      1100, 2056, 40,   5,     3, 6,  RELU, BF16,  False, False, 2),        # no normalisation: rows of any length
     ("f32",        1300, 512,  512,  6,     4, 8,  GELU, F32,   True,  True,  1),
     ("f32_two",    1200, 100,  68,   9,     2, 3,  RELU, F32,   True,  False, 2),        # 100 features: three pieces and a quarter of a stage
