@@ -189,10 +189,14 @@ PyObject* forward_soft(PyObject*, PyObject* const* args, Py_ssize_t n) {
 struct Scratch {
     void* p = nullptr;
     Scratch(size_t bytes, hipStream_t s) {
+        // an allocator with nothing left asks the device, which must not spoil what another thread captures just now
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
         try {
             p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, s);
         } catch (const std::exception&) {
         }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     ~Scratch() {
         if (p) c10::hip::HIPCachingAllocator::raw_delete(p);

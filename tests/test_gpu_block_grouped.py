@@ -160,6 +160,39 @@ def test_same_bits_eager_captured_and_beside_a_callers_workspace(forced):
         F.fff_set_workspace(None)
 
 
+def test_a_call_beside_another_threads_capture(forced):
+    """An eager call for whose scratch the allocator has to ask the device, while another thread captures: both are what they are alone."""
+    import threading
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] grouped block beside another thread's capture T=6000 D=256 depth=7 n=4 L=6", flush=True)
+    d, other = _state(STREAMS, 35), _state(STREAMS, 36)
+    forced(3)
+    want, want_other = _rows(F, d), _rows(F, other)
+    out, out_other = torch.full_like(want, float("nan")), torch.full_like(want, float("nan"))
+    side, failed = torch.cuda.Stream(), []
+
+    def eager():
+        try:
+            F.fff_forward_block(other[0], other[1], other[2], 1e-5, *other[3:], 7, 4, 6, GELU, True, out_other, None, side)
+        except Exception as e:
+            failed.append(e)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        t = threading.Thread(target=eager)
+        t.start()
+        t.join()
+        _call(F, d, STREAMS, out)
+    assert not failed, failed
+    torch.cuda.synchronize()
+    assert torch.equal(out_other, want_other)
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+
+
 def test_without_scratch_the_one_launch_runs(forced):
     """A stream captured by other means than torch's graphs, no memory left, and the entry point of the C ABI that takes no scratch."""
     import torch
