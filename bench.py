@@ -733,7 +733,7 @@ def hard_bench(name, args, np, torch, W, F, headline=True):
                     "std_ms": round(float(np.std(batch_ms)), 5), "median_ms": round(float(np.median(batch_ms)), 5)}
 
     alg = algorithmic_bytes(w, ref_idx)
-    path_names = {1: "fused", 2: "staged", 3: "generic", 4: "token_block", 5: "split"}
+    path_names = {1: "fused", 2: "staged", 3: "generic", 4: "token_block", 5: "split", 6: "grouped"}
 
     # per-stage durations: HIP events recorded by the library on the call's stream
     stages = {}
@@ -744,9 +744,12 @@ def hard_bench(name, args, np, torch, W, F, headline=True):
         torch.cuda.synchronize()
         d_ms, b_ms, l_ms, l2_ms, calls = F.fff_stage_times()
         F.fff_set_option("stage_timing", 0)
-        single = F.fff_get_option("last_path") not in (2, 5)
+        single = F.fff_get_option("last_path") not in (2, 5, 6)
         if F.fff_get_option("last_path") == 5:      # walk + hidden neurons per token, then output rows by column slices
             names = (("walk_hidden", d_ms), ("leaf_slices", l_ms))
+        elif F.fff_get_option("last_path") == 6:    # top levels, grouping, the rest in that order (the bytes of node rows are left to the rest)
+            alg = dict(alg, descent=w.T * w.D * (2 if w.dtype == 1 else 4) + 4 * w.T, walk_grouped=alg["path"])
+            names = (("descent", d_ms), ("bucketing", b_ms), ("walk_grouped", l_ms))
         elif single:     # one launch did the whole path: it carries the whole path's bytes
             alg = dict(alg, walk_fused=alg["path"], token_block=alg["path"])
             names = ((("token_block" if F.fff_get_option("last_path") == 4 else "walk_fused"), d_ms),)
@@ -766,7 +769,7 @@ def hard_bench(name, args, np, torch, W, F, headline=True):
         names_in_order = [k.strip() for k in kernels.split(" + ")]
         dom_kernel = kernels if len(stages) == 1 else None
         if dom_kernel is None:
-            pos = {"descent": 0, "leaf_output": -1, "leaf_hidden": -2, "leaf": -1, "walk_hidden": 0, "leaf_slices": -1}.get(dom)
+            pos = {"descent": 0, "leaf_output": -1, "leaf_hidden": -2, "leaf": -1, "walk_hidden": 0, "leaf_slices": -1, "walk_grouped": -1}.get(dom)
             dom_kernel = names_in_order[pos] if pos is not None and names_in_order else dom
         measured = None if args.tokens else measured_traffic(w.name, dom_kernel)
         ceiling = copy_ceiling_once(torch)

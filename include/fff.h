@@ -310,7 +310,10 @@ int fff_release_workspace(void);
  *                    whole 16-byte pieces), 4 = one block per token (small batches), 5 = the fused
  *                    launch cut in two (walk and hidden neurons per token, then the output
  *                    rows by column slices, one slice of all rows per XCD; leaf_width <= 8,
- *                    16-byte aligned output rows); a path the shape does not allow falls back
+ *                    16-byte aligned output rows), 6 = the fused launch with the tokens grouped by the
+ *                    node they reach after the top levels (2 <= depth, up to 131072 tokens, leaf_width
+ *                    <= 8, 16-byte aligned output rows; the same bits as 1; uses the workspace, and is
+ *                    path 1 where there is none to be had); a path the shape does not allow falls back
  *                    to one it does
  *   "leaf_path"      staged path only: 0 = choose by shape and bucket size (default),
  *                    1 = always the gather kernel, 2 = the MFMA tile kernels whenever the
@@ -320,7 +323,7 @@ int fff_release_workspace(void);
  *                    0 = in token order (no bucketing stage)
  *   "stage_timing"   1 = fff_forward_hard records hipEvents around its stages
  *                    (read them with fff_stage_times); 0 (default) = off
- * Read-only, describing the last call: "last_path" (1..5 as above), "last_leaf_path"
+ * Read-only, describing the last call: "last_path" (1..6 as above), "last_leaf_path"
  * (1 = gather kernel, 2 = the two tile kernels, 3 = both, each on its share of the tiles, 4 = the launch that
  * takes the last levels of the walk with the leaf: "leaf_path" 0 only),
  * "last_walk_top" (tree levels the descent or fused launch kept in LDS),

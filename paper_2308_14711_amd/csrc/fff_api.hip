@@ -43,7 +43,7 @@ DeviceWs g_ws[kMaxDevices];
 std::mutex g_mu;
 
 struct Options {
-    int64_t path = 0;            // 0 auto, 1 fused walk, 2 staged, 3 generic one-wave-per-token
+    int64_t path = 0;            // 0 auto, 1 fused walk, 2 staged, 3 generic one-wave-per-token, ..., 6 grouped walk
     int64_t leaf_path = 0;       // 0 auto, 1 gather kernel only, 2 MFMA tiles whenever the shape allows
     int64_t bucketing = 1;       // 0: leaf kernel visits tokens in token order
     int64_t stage_timing = 0;    // 1: bracket the stages of fff_forward_hard with events
@@ -258,7 +258,7 @@ bool staged_shape_ok(const Problem& p) {
     return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.L <= 64;
 }
 
-enum { kPathAuto = 0, kPathFused = 1, kPathStaged = 2, kPathGeneric = 3, kPathToken = 4, kPathSplit = 5 };
+enum { kPathAuto = 0, kPathFused = 1, kPathStaged = 2, kPathGeneric = 3, kPathToken = 4, kPathSplit = 5, kPathGrouped = 6 };
 
 // One launch that keeps the token row in registers from the root to the output
 // row wins while a leaf is narrow (its weights are a few rows per token, like a
@@ -602,6 +602,60 @@ bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
     return found;
 }
 
+// How many levels the grouped walk goes through before it groups (of 5 .. 9 the best on average for every row length, +- 1 %).
+constexpr int kGroupLevel = 6;
+
+bool grouped_shape_ok(const Problem& p) {
+    return fused_shape_ok(p) && p.depth >= 2 && p.T >= 1 && p.T <= 131072 && vec_ok(p.out, p.O, p.bf16) && vec_ok(p.leaf_w2, p.O, p.bf16) &&
+           vec_ok(p.leaf_b2, p.O, p.bf16);
+}
+
+// Whether a call that `path` would take goes to the grouped walk instead.
+//
+// Below the top levels every token of the fused launch wants rows of its own, and once the tables outgrow an L2 most of them come from
+// memory (16384 tokens, 4096-wide, depth 15, 4 neurons, skewed: 1636 MB moved, 236 us).  Tokens of one subtree that run on one XCD at
+// the same time find them in its L2, and a row that both tokens of a wave want is fetched once (850 MB, 217 us); the price is a second
+// read of the token rows and two launches more.  In the place of the split launch (65536 tokens, 768-wide, one neuron, depth 13) 101
+// -> 86 us; of the staged path with more leaves than its fast bucketing takes (58703 fp32 tokens, 360-wide, depth 13, 4 neurons,
+// skewed) 213 -> 100.  Not so while the tables are small against the rows (the split launch at depth 11: 69 and 71).
+// By estimates in us of the grouped walk and of what the call would take, terms and weights below, fitted to 4300 random calls with
+// uniform and with skewed leaves (8200 to 131072 tokens, rows of 512 bytes to 16 KB, depth 8 to 16; half of the estimates are within
+// 9 % for the grouped walk and 13 % for the others): of the 1591 calls that the line at 1.05 takes 1.16 times as fast on average, 90
+// more than 5 % slower.  Where the subtree launch has the lower end of the tree it stays ahead.
+bool walk_grouped(const Problem& p, int path) {
+    if (g_opt.path == kPathGrouped) return grouped_shape_ok(p);
+    if (g_opt.path != kPathAuto || g_opt.leaf_path != 0 || g_opt.leaf_split != 0 || !g_opt.bucketing || g_subtree != 0) return false;
+    if (path != kPathFused && path != kPathSplit && path != kPathStaged) return false;
+    const int64_t es = p.bf16 ? 2 : 4;
+    if (p.T <= 32 * (int64_t)device_info().cus || p.D * es < 512 || p.O > 2 * p.D || 4 * p.O < p.D || p.depth < 8 || p.depth > 16 ||
+        !grouped_shape_ok(p) || (path == kPathStaged && subtree_levels(p, false) >= 0))
+        return false;
+    const double T = (double)p.T, node = 1e-6 * (double)(p.D * es), leaf = 1e-6 * (double)((p.L * (p.D + p.O) + p.O) * es);    // MB
+    const double leaves = (double)((int64_t)1 << p.depth);
+    // rows that some token meets, if all leaves are as likely
+    double met = leaf * leaves * (1 - exp(-T / leaves));
+    for (int m = 0; m < p.depth; ++m) met += node * (double)(1 << m) * (1 - exp(-T / (double)(1 << m)));
+    const double x = T * node, out = T * 1e-6 * (double)(p.O * es), leaf_rows = T * leaf;
+    const bool wide = p.D * es > 2048;
+    const double grouped_term[5] = {1, x, out, x * (p.depth - 6) + leaf_rows, met};
+    constexpr double grouped_short[5] = {17.1, 0.348, 0.0207, 0.0493, 0.0599}, grouped_wide[5] = {19.9, 0.414, 0.0257, 0.0402, 0.0864};
+    const double grouped = weighted(wide ? grouped_wide : grouped_short, grouped_term);
+    double now;
+    if (path == kPathStaged) {
+        const double term[6] = {1, x, out, x * (p.depth - 5), leaf_rows, met};
+        constexpr double gather_short[6] = {16.4, 0, 0.0349, 0.143, 0.0257, 0.187}, gather_wide[6] = {14.1, 0.457, 0.0178, 0.0634, 0.0324, 0.163};
+        constexpr double tiles_short[6] = {25, 0.146, 0, 0.0608, 0, 1.04}, tiles_wide[6] = {29.8, 0.671, 0.184, 0, 0.0018, 0.599};
+        now = leaf_tiles_pay(p) ? weighted(wide ? tiles_wide : tiles_short, term) : weighted(wide ? gather_wide : gather_short, term);
+    } else {
+        const double rows = x * (p.depth - 5) + leaf_rows, beyond = log2(met / 4);
+        const double term[6] = {1, x, out, rows, rows * (beyond < 0 ? 0 : beyond > 4 ? 4 : beyond), met};
+        constexpr double fused_short[6] = {7.56, 0.176, 0, 0.0615, 0.0037, 0.0551}, fused_wide[6] = {9.35, 0.148, 0.0916, 0.0699, 0.0023, 0.0606};
+        constexpr double split_short[6] = {9.06, 0.159, 0.0822, 0.0589, 0.0029, 0.0503}, split_wide[6] = {14.8, 0.153, 0.0887, 0.0527, 0.0036, 0.0723};
+        now = path == kPathFused ? weighted(wide ? fused_wide : fused_short, term) : weighted(wide ? split_wide : split_short, term);
+    }
+    return now > 1.05 * grouped;
+}
+
 // Scratch of the grouped launches, in words: node reached (twice), grouped order, mean and deviation of T tokens, group offsets, counts.
 struct BlockScratch {
     int64_t row, groups, total;
@@ -696,6 +750,40 @@ int scratch_on_device(void** ptr) {
     return FFF_OK;
 }
 
+// The first kGroupLevel levels for every token, the tokens grouped by the node they reach, then the rest of the fused launch in that
+// order: the same bits as the fused launch.  *done stays false, and nothing is enqueued, where there is no workspace to be had (the fused
+// launch needs none).
+int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch, bool* done) {
+    const int level = p.depth <= kGroupLevel ? p.depth - 1 : kGroupLevel;
+    const bool marks = fixed_scratch == nullptr;
+    Workspace ws;
+    Layout lay;
+    if (fixed_scratch) {
+        lay = layout_for(p.T, p.depth);
+        carve(fixed_scratch, lay, &ws);
+    } else if (get_workspace(p.T, p.depth, &ws, &lay, s) != FFF_OK) {
+        g_last_error.clear();
+        return FFF_OK;
+    }
+    *done = true;
+    g_opt.last_path = kPathGrouped;
+    Problem top = p;
+    top.depth = level;
+    DescentCounts dc;
+    dc.M = ws.hidden;
+    dc.capacity = kTilesMaxLeafWidth / 2 * p.T < kFoldWords ? kTilesMaxLeafWidth / 2 * p.T : kFoldWords;
+    if (marks) stage_mark(s);
+    hipError_t e = launch_descend(top, ws.leaf_idx, s, &dc);
+    if (e != hipSuccess) return set_device_error(e, "descent kernel launch");
+    if (marks) stage_mark(s);
+    const int rc = run_bucket(ws.leaf_idx, p.T, level, ws, nullptr, nullptr, ws.perm, nullptr, s, &dc);
+    if (rc != FFF_OK) return rc;
+    if (marks) stage_mark(s);
+    e = launch_walk_grouped(p, level, ws.perm, ws.leaf_idx, leaf_idx, s);
+    for (int i = 0; marks && i < 2; ++i) stage_mark(s);
+    return e == hipSuccess ? FFF_OK : set_device_error(e, "grouped walk kernel launch");
+}
+
 // The launches of Forward_I.  fixed_scratch == nullptr: the staged path works in the device's
 // workspace and the stages are bracketed by events when "stage_timing" is on.  Otherwise that block
 // of device memory (large enough for layout_for(T, depth): the caller has checked) is carved
@@ -716,6 +804,11 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
         hipError_t e = token_rows_better(p) ? launch_token_rows(p, leaf_idx, s) : launch_token_block(p, leaf_idx, s);
         for (int k = 0; marks && k < 4; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
+    }
+    if (walk_grouped(p, path)) {
+        bool done = false;
+        const int rc = run_walk_grouped(p, leaf_idx, s, fixed_scratch, &done);
+        if (done) return rc;
     }
     if (path == kPathFused) {
         if (marks) stage_mark(s);

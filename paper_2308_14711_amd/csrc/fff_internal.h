@@ -81,6 +81,9 @@ bool bucket_fold_ok(int depth, int64_t blocks, int64_t share);
 hipError_t launch_descend(const Problem& p, int32_t* leaf_idx, hipStream_t s, DescentCounts* dc = nullptr);
 // Descent + leaf network + output row in one launch; needs fused_shape_ok(p).
 hipError_t launch_walk_fused(const Problem& p, int32_t* leaf_idx, hipStream_t s);
+// The fused launch's lower part for tokens grouped (perm) by the node of level base_level they have reached (start [T]); needs
+// fused_shape_ok(p).
+hipError_t launch_walk_grouped(const Problem& p, int base_level, const int32_t* perm, const int32_t* start, int32_t* leaf_idx, hipStream_t s);
 // The fused launch cut in two for leaf tables that outgrow an L2: walk + hidden neurons per token
 // (launch_walk_hidden: leaf_idx [T] and hidden [T, L] fp32 out), then the output rows by column
 // slices (launch_leaf_slices): every XCD writes one slice of all rows, so that its L2 only ever

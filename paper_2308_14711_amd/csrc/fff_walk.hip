@@ -44,6 +44,29 @@ __device__ __forceinline__ float row_dot(const uint4 (&xv)[NV], int sub, int nve
     return acc0 + acc1;
 }
 
+// The same for the TPG tokens of a lane group, row k at row_of(k).  SHARE: a row that all of the wave's tokens want (their nodes are
+// equal) is fetched once.
+template <bool BF16, int LPT, int NV, int TPG, bool TIGHT, bool SHARE, typename RowOf>
+__device__ __forceinline__ void row_dots(const uint4 (&xv)[TPG][NV], int sub, int nvec, const int (&node)[TPG], RowOf row_of, float (&s)[TPG]) {
+    if (SHARE && LPT == kWave && TPG == 2 && node[0] == node[TPG - 1]) {
+        const uint4* row = row_of(0);
+        uint4 wv[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int v = sub + i * LPT;
+            wv[i] = (TIGHT || v < nvec) ? row[v] : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < TPG; ++k) s[k] = row_dot<BF16, LPT, NV, TIGHT>(xv[k], sub, nvec, [&](int v) { return wv[(v - sub) / LPT]; });
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < TPG; ++k) {
+        const uint4* row = row_of(k);
+        s[k] = row_dot<BF16, LPT, NV, TIGHT>(xv[k], sub, nvec, [&](int v) { return row[v]; });
+    }
+}
+
 template <bool BF16> __device__ __forceinline__ void unpack_vec(const uint4& v, float* f);
 template <> __device__ __forceinline__ void unpack_vec<false>(const uint4& v, float* f) {
     f[0] = __uint_as_float(v.x); f[1] = __uint_as_float(v.y);
@@ -79,15 +102,20 @@ struct WalkArgs {
     float* hidden_out;       // fused only, may be null: [T, L] hidden activations (fp32) instead of the output rows
     int32_t* block_counts;   // descent only, may be null: [blocks, 2^depth] tokens of every leaf in each block's share
     int plain_x;             // descent only: read the token rows without the streaming hint
+    const int32_t* perm;     // grouped only: token ids in the order of the nodes they have reached
+    const int32_t* start;    // grouped only: [T] the node of level base_level that a token has reached
+    int base_level;
 };
 
 // MODE: kWalkDescend writes leaf_idx only; kWalkFused also the leaf network (L <= 8) and the output
-// row; kWalkHidden the leaf's hidden neurons, stored fp32 for a launch that writes the rows.
+// row; kWalkHidden the leaf's hidden neurons, stored fp32 for a launch that writes the rows;
+// kWalkGrouped is kWalkFused for tokens grouped by the node of level base_level they have reached.
 // TIGHT: D (and, when fused with vector output, O) is exactly LPT * NV vectors.
-constexpr int kWalkDescend = 0, kWalkFused = 1, kWalkHidden = 2;
+constexpr int kWalkDescend = 0, kWalkFused = 1, kWalkHidden = 2, kWalkGrouped = 3;
 template <bool BF16, int LPT, int NV, int TPG, int kWalkBlock, int MODE, bool TIGHT, bool PREFETCH>
 __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
     constexpr bool HIDDEN = MODE == kWalkHidden, DESCEND = MODE == kWalkDescend;   // else the fused launch
+    constexpr bool GROUPED = MODE == kWalkGrouped;
     extern __shared__ uint4 lds[];                 // [(2^top - 1) * nvec] rows, then (2^top - 1) biases, then the leaf counts
     constexpr int VE = Elem<BF16>::kPerVec;
     const int nvec = a.nvec;
@@ -110,13 +138,14 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
 
     // this block's tokens, taken a.chunk at a time: slot g TPG + k of a round holds token
     // base + g TPG + k while that is inside the round and the share (else the last token, unused)
-    const int64_t lo = (int64_t)blockIdx.x * a.share;
+    const int64_t lo = (GROUPED ? xcd_contiguous_block() : (int64_t)blockIdx.x) * a.share;
     const int64_t hi = lo + a.share < a.T ? lo + a.share : a.T;
     auto fetch_rows = [&](int64_t base, uint4 (&xr)[TPG][NV]) {
 #pragma unroll
         for (int k = 0; k < TPG; ++k) {
             const int64_t tt = base + (int64_t)g * TPG + k;
-            const uint4* xrow = a.x + ((g * TPG + k < a.chunk && tt < hi) ? tt : a.T - 1) * nvec;
+            const int64_t slot = (g * TPG + k < a.chunk && tt < hi) ? tt : a.T - 1;
+            const uint4* xrow = a.x + (GROUPED ? (int64_t)a.perm[slot] : slot) * nvec;
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 const int v = sub + i * LPT;
@@ -137,6 +166,7 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
             const int64_t tt = base + (int64_t)g * TPG + k;
             live[k] = g * TPG + k < a.chunk && tt < hi;
             t[k] = live[k] ? tt : a.T - 1;
+            if (GROUPED) t[k] = a.perm[t[k]];
         }
         // PREFETCH: the rows of this tile were requested one iteration ago; request the next
         // tile's now, so that they travel while this tile walks the tree
@@ -148,10 +178,13 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
         }
         int node[TPG];
 #pragma unroll
-        for (int k = 0; k < TPG; ++k) node[k] = 0;
+        for (int k = 0; k < TPG; ++k) {
+            node[k] = GROUPED ? (1 << a.base_level) - 1 + a.start[t[k]] : 0;
+            if (GROUPED && LPT == kWave) node[k] = __builtin_amdgcn_readfirstlane(node[k]);
+        }
 
         // levels whose rows sit in LDS
-        for (int m = 0; m < a.top; ++m) {
+        for (int m = 0; !GROUPED && m < a.top; ++m) {
             float s[TPG];
 #pragma unroll
             for (int k = 0; k < TPG; ++k) {
@@ -165,18 +198,16 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
             }
         }
         // deeper levels: one row fetch per token per level, TPG of them in flight
-        for (int m = a.top; m < a.depth; ++m) {
+        for (int m = GROUPED ? a.base_level : a.top; m < a.depth; ++m) {
             float s[TPG], bias[TPG];
 #pragma unroll
-            for (int k = 0; k < TPG; ++k) {
-                const uint4* row = a.node_w + (int64_t)node[k] * nvec;
-                bias[k] = Elem<BF16>::load(a.node_b, node[k]);
-                s[k] = row_dot<BF16, LPT, NV, TIGHT>(xv[k], sub, nvec, [&](int v) { return row[v]; });
-            }
+            for (int k = 0; k < TPG; ++k) bias[k] = Elem<BF16>::load(a.node_b, node[k]);
+            row_dots<BF16, LPT, NV, TPG, TIGHT, GROUPED>(xv, sub, nvec, node, [&](int k) { return a.node_w + (int64_t)node[k] * nvec; }, s);
 #pragma unroll
             for (int k = 0; k < TPG; ++k) {
                 const float logit = group_sum<LPT>(s[k]) + bias[k];
                 node[k] = 2 * node[k] + 1 + (logit >= 0.0f ? 1 : 0);
+                if (GROUPED && LPT == kWave) node[k] = __builtin_amdgcn_readfirstlane(node[k]);
             }
         }
         int64_t leaf[TPG];
@@ -203,11 +234,8 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
             if (r < a.L) {
                 float s[TPG], bias[TPG];
 #pragma unroll
-                for (int k = 0; k < TPG; ++k) {
-                    const uint4* row = a.w1 + (leaf[k] * a.L + r) * nvec;
-                    bias[k] = Elem<BF16>::load(a.b1, leaf[k] * a.L + r);
-                    s[k] = row_dot<BF16, LPT, NV, TIGHT>(xv[k], sub, nvec, [&](int v) { return row[v]; });
-                }
+                for (int k = 0; k < TPG; ++k) bias[k] = Elem<BF16>::load(a.b1, leaf[k] * a.L + r);
+                row_dots<BF16, LPT, NV, TPG, TIGHT, GROUPED>(xv, sub, nvec, node, [&](int k) { return a.w1 + (leaf[k] * a.L + r) * nvec; }, s);
 #pragma unroll
                 for (int k = 0; k < TPG; ++k) h[k][r] = activate(group_sum<LPT>(s[k]) + bias[k], a.act);
             } else {
@@ -465,6 +493,50 @@ hipError_t run_walk(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
                  : run_walk_t<BF16, LPT, NV, TPG, kWalkBlock, MODE, false>(p, leaf_idx, s);
 }
 
+// The grouped launch: a block takes one tile of slots.
+template <bool BF16, int LPT, int NV, int TPG>
+hipError_t run_grouped(const Problem& p, int base_level, const int32_t* perm, const int32_t* start, int32_t* leaf_idx, hipStream_t s) {
+    constexpr int kBlock = 256, kTile = kBlock / LPT * TPG;
+    WalkArgs a = {};
+    a.x = (const uint4*)p.x;
+    a.node_w = (const uint4*)p.node_w;
+    a.node_b = p.node_b;
+    a.w1 = (const uint4*)p.leaf_w1;
+    a.b1 = p.leaf_b1;
+    a.w2 = p.leaf_w2;
+    a.b2 = p.leaf_b2;
+    a.out = p.out;
+    a.leaf_idx = leaf_idx;
+    a.T = p.T;
+    a.O = p.O;
+    a.share = a.chunk = kTile;
+    a.depth = p.depth;
+    a.nvec = (int)(p.D / Elem<BF16>::kPerVec);
+    a.L = p.L;
+    a.act = p.act;
+    a.out_vec = vec_ok(p.out, p.O, BF16) && vec_ok(p.leaf_w2, p.O, BF16) && vec_ok(p.leaf_b2, p.O, BF16);
+    a.perm = perm;
+    a.start = start;
+    a.base_level = base_level;
+    const int64_t blocks = ((p.T + kTile - 1) / kTile + kXcds - 1) / kXcds * kXcds;
+    const bool tight = p.D == Elem<BF16>::kPerVec * LPT * NV && (!a.out_vec || p.O == p.D);
+    note_launch("walk_kernel<%s,%d,%d,%d,%d,grouped,%s> from=%d", BF16 ? "bf16" : "f32", LPT, NV, TPG, kBlock, tight ? "tight" : "checked", base_level);
+    if (tight) walk_kernel<BF16, LPT, NV, TPG, kBlock, kWalkGrouped, true, false><<<dim3((unsigned)blocks), dim3(kBlock), 0, s>>>(a);
+    else walk_kernel<BF16, LPT, NV, TPG, kBlock, kWalkGrouped, false, false><<<dim3((unsigned)blocks), dim3(kBlock), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+template <bool BF16>
+hipError_t dispatch_grouped(const Problem& p, int base_level, const int32_t* perm, const int32_t* start, int32_t* leaf_idx, hipStream_t s) {
+    const int64_t nvec = p.D / Elem<BF16>::kPerVec;
+    if (nvec <= 64) return run_grouped<BF16, 16, 4, 2>(p, base_level, perm, start, leaf_idx, s);
+    if (nvec <= 96) return run_grouped<BF16, 16, 6, 2>(p, base_level, perm, start, leaf_idx, s);
+    if (nvec <= 128) return run_grouped<BF16, 16, 8, 2>(p, base_level, perm, start, leaf_idx, s);
+    if (nvec <= 256) return run_grouped<BF16, 64, 4, 2>(p, base_level, perm, start, leaf_idx, s);
+    if (nvec <= 512) return run_grouped<BF16, 64, 8, 2>(p, base_level, perm, start, leaf_idx, s);
+    return run_grouped<BF16, 64, 16, 1>(p, base_level, perm, start, leaf_idx, s);
+}
+
 template <bool BF16, int MODE>
 hipError_t dispatch_walk(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
     constexpr bool FUSED = MODE == kWalkFused;     // the walk + hidden launch takes the descent's tiles
@@ -576,6 +648,13 @@ hipError_t launch_descend(const Problem& p, int32_t* leaf_idx, hipStream_t s, De
 hipError_t launch_walk_fused(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
     if (p.T == 0) return hipSuccess;
     return p.bf16 ? dispatch_walk<true, kWalkFused>(p, leaf_idx, s) : dispatch_walk<false, kWalkFused>(p, leaf_idx, s);
+}
+
+// The lower part of the tree for tokens grouped by the node of level base_level that they have reached (start), the leaf and the
+// output row: the fused launch from there on, with the same bits.
+hipError_t launch_walk_grouped(const Problem& p, int base_level, const int32_t* perm, const int32_t* start, int32_t* leaf_idx, hipStream_t s) {
+    if (p.T == 0) return hipSuccess;
+    return p.bf16 ? dispatch_grouped<true>(p, base_level, perm, start, leaf_idx, s) : dispatch_grouped<false>(p, base_level, perm, start, leaf_idx, s);
 }
 
 // The same launch stopping after the leaf's hidden neurons: leaf_idx [T] (required) and hidden [T, L]
