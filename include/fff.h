@@ -313,7 +313,8 @@ int fff_release_workspace(void);
  *                    16-byte aligned output rows), 6 = the fused launch with the tokens grouped by the
  *                    node they reach after the top levels (2 <= depth, up to 131072 tokens, leaf_width
  *                    <= 8, 16-byte aligned output rows; the same bits as 1; uses the workspace, and is
- *                    path 1 where there is none to be had); a path the shape does not allow falls back
+ *                    path 1 where there is none to be had), 7 = one wave per token (medium batches;
+ *                    leaf_width <= 64, 16-byte aligned rows of up to 8 KB; "last_path" says 1); a path the shape does not allow falls back
  *                    to one it does
  *   "leaf_path"      staged path only: 0 = choose by shape and bucket size (default),
  *                    1 = always the gather kernel, 2 = the MFMA tile kernels whenever the

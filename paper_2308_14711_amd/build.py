@@ -18,7 +18,7 @@ TORCH_LIB = os.path.join(HERE, "_fff_torch.so")             # the ordinary calls
 PROBE_LIB = os.path.join(HERE, "libfff_bench_probes.so")   # measuring sticks of bench.py, not the product
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["fff_api.hip", "fff_walk.hip", "fff_bucket.hip", "fff_leaf.hip", "fff_leaf_tiles.hip", "fff_leaf_slices.hip", "fff_subtree.hip",
+SOURCES = ["fff_api.hip", "fff_walk.hip", "fff_walk_wave.hip", "fff_bucket.hip", "fff_leaf.hip", "fff_leaf_tiles.hip", "fff_leaf_slices.hip", "fff_subtree.hip",
            "fff_token_block.hip", "fff_token_rows.hip", "fff_moe_gate.hip", "fff_soft.hip", "fff_block.hip"]
 PROBE_SOURCES = ["bench_probes.hip"]
 TORCH_SOURCE = "fff_torch.cpp"

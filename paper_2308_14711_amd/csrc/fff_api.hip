@@ -43,7 +43,7 @@ DeviceWs g_ws[kMaxDevices];
 std::mutex g_mu;
 
 struct Options {
-    int64_t path = 0;            // 0 auto, 1 fused walk, 2 staged, 3 generic one-wave-per-token, ..., 6 grouped walk
+    int64_t path = 0;            // 0 auto, 1 fused walk, 2 staged, 3 generic one-wave-per-token, ..., 6 grouped walk, 7 wave a token
     int64_t leaf_path = 0;       // 0 auto, 1 gather kernel only, 2 MFMA tiles whenever the shape allows
     int64_t bucketing = 1;       // 0: leaf kernel visits tokens in token order
     int64_t stage_timing = 0;    // 1: bracket the stages of fff_forward_hard with events
@@ -258,7 +258,7 @@ bool staged_shape_ok(const Problem& p) {
     return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.L <= 64;
 }
 
-enum { kPathAuto = 0, kPathFused = 1, kPathStaged = 2, kPathGeneric = 3, kPathToken = 4, kPathSplit = 5, kPathGrouped = 6 };
+enum { kPathAuto = 0, kPathFused = 1, kPathStaged = 2, kPathGeneric = 3, kPathToken = 4, kPathSplit = 5, kPathGrouped = 6, kPathWave = 7 };
 
 // One launch that keeps the token row in registers from the root to the output
 // row wins while a leaf is narrow (its weights are a few rows per token, like a
@@ -269,6 +269,7 @@ int choose_path(const Problem& p) {
     const bool split_ok = fused_ok && slices_shape_ok(p);
     if (g_opt.path == kPathToken && token_ok) return kPathToken;
     if (g_opt.path == kPathSplit && split_ok) return kPathSplit;
+    if (g_opt.path == kPathWave && wave_shape_ok(p)) return kPathWave;
     if (g_opt.path == kPathFused && fused_ok) return kPathFused;
     if (g_opt.path == kPathStaged && staged_ok) return kPathStaged;
     if (g_opt.path == kPathGeneric) return kPathGeneric;
@@ -288,6 +289,7 @@ int choose_path(const Problem& p) {
         // (token block / element-wise: 2181 tokens of 9 bf16 features, 168 neurons 94 / 62; 1161 of 11, 116 neurons 39 / 43)
         token_limit = 3 * g_opt.token_max_T;
     }
+    if (g_opt.path == kPathAuto && p.T > g_opt.token_max_T && wave_better(p)) return kPathWave;
     if (g_opt.path == kPathAuto && token_ok && p.T <= token_limit) return kPathToken;
     // Whole rows of leaves wider than the staged path takes go one block a token at any batch size: their alternative is the
     // element-wise kernel (4312 tokens of 464 bf16 features, 240 neurons: 391 us against 168).  Not so rows of other
@@ -791,7 +793,7 @@ int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
 int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch) {
     const bool marks = fixed_scratch == nullptr;
     const int path = choose_path(p);
-    g_opt.last_path = path;
+    g_opt.last_path = path == kPathWave ? (int)kPathFused : path;      // (one fused launch, whichever kernel)
     if (path == kPathGeneric) {
         // rows of at least one piece by 16-byte pieces at any element (20011 tokens of 77 features: 7.5 us against 19.8 element by
         // element); option path = 3 asks for the element-wise kernel
@@ -809,6 +811,12 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
         bool done = false;
         const int rc = run_walk_grouped(p, leaf_idx, s, fixed_scratch, &done);
         if (done) return rc;
+    }
+    if (path == kPathWave) {
+        if (marks) stage_mark(s);
+        hipError_t e = launch_walk_wave(p, leaf_idx, s);
+        for (int k = 0; marks && k < 4; ++k) stage_mark(s);
+        return e == hipSuccess ? FFF_OK : set_device_error(e, "wave kernel launch");
     }
     if (path == kPathFused) {
         if (marks) stage_mark(s);

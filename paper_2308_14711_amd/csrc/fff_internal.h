@@ -81,6 +81,11 @@ bool bucket_fold_ok(int depth, int64_t blocks, int64_t share);
 hipError_t launch_descend(const Problem& p, int32_t* leaf_idx, hipStream_t s, DescentCounts* dc = nullptr);
 // Descent + leaf network + output row in one launch; needs fused_shape_ok(p).
 hipError_t launch_walk_fused(const Problem& p, int32_t* leaf_idx, hipStream_t s);
+// The same for batches of up to 48 tokens a compute unit, a wave a token, leaves of up to 64 neurons (launch_walk_wave needs
+// wave_shape_ok; wave_better: whether it is the faster one).
+bool wave_shape_ok(const Problem& p);
+bool wave_better(const Problem& p);
+hipError_t launch_walk_wave(const Problem& p, int32_t* leaf_idx, hipStream_t s);
 // The fused launch's lower part for tokens grouped (perm) by the node of level base_level they have reached (start [T]); needs
 // fused_shape_ok(p).
 hipError_t launch_walk_grouped(const Problem& p, int base_level, const int32_t* perm, const int32_t* start, int32_t* leaf_idx, hipStream_t s);

@@ -1,0 +1,92 @@
+"""A wave a token (medium batches): every kernel of it against the oracle, at the edges of its rows, trips, blocks and output units."""
+import pytest
+
+import fff_workloads as W
+from fff_testlib import check_against_oracle, run_forward, to_device
+
+pytestmark = pytest.mark.gpu
+
+# T, D, O, depth, L, dtype
+CASES = [
+    (1, 8, 8, 1, 1, W.DTYPE_BF16), (257, 512, 512, 2, 8, W.DTYPE_BF16), (600, 520, 1, 3, 9, W.DTYPE_BF16),          # a piece a lane, one more
+    (1025, 768, 768, 11, 1, W.DTYPE_BF16), (2047, 768, 520, 10, 5, W.DTYPE_BF16), (4097, 1024, 77, 6, 4, W.DTYPE_BF16),
+    (4095, 1032, 513, 5, 3, W.DTYPE_BF16), (2049, 2048, 2048, 7, 17, W.DTYPE_BF16), (300, 2056, 72, 4, 64, W.DTYPE_BF16),
+    (1030, 4096, 4096, 9, 2, W.DTYPE_BF16), (3000, 4088, 10, 6, 7, W.DTYPE_BF16), (8193, 64, 64, 8, 32, W.DTYPE_BF16),
+    (4096, 784, 10, 6, 4, W.DTYPE_F32), (513, 4, 3, 12, 1, W.DTYPE_F32), (2500, 260, 260, 5, 16, W.DTYPE_F32),
+    (700, 2048, 31, 3, 6, W.DTYPE_F32), (12289, 128, 128, 6, 8, W.DTYPE_F32),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["T%d_D%d_O%d_d%d_L%d_%s" % (c[:5] + (("f32", "bf16")[c[5]],)) for c in CASES])
+@pytest.mark.parametrize("act", [W.ACT_RELU, W.ACT_GELU], ids=["relu", "gelu"])
+def test_against_the_oracle(case, act):
+    import torch
+    import paper_2308_14711_amd as F
+    T, D, O, depth, L, dtype = case
+    print("\n[case] wave a token T=%d D=%d O=%d depth=%d L=%d dtype=%d act=%d seed 81" % (case + (act,)), flush=True)
+    w = W.make_layer("wave", T, D, O, depth, L, act, dtype, seed=81)
+    dev = to_device(w)
+    F.fff_set_option("path", 7)
+    try:
+        out, idx = run_forward(w, dev)
+        assert F.fff_get_option("last_path") == 1 and "walk_wave_kernel" in F.fff_last_launch()
+        again, _ = run_forward(w, dev, want_idx=False)
+    finally:
+        F.fff_set_option("path", 0)
+    check_against_oracle(w, out, idx)
+    assert torch.equal(out, again)
+
+
+@pytest.mark.parametrize("where", ["leaf_w1", "node_w"])
+def test_infinite_weights_and_nan_tokens_stay_with_their_tokens(where):
+    """Lanes past a row multiply nothing: an infinite last weight (of one leaf's neuron, or of a node) reaches the tokens that meet it and
+    no other, and is not turned into NaN."""
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] wave a token, infinite weights T=1500 D=72 O=16 depth=5 L=3 fp32 in %s" % where, flush=True)
+    w = W.make_layer("wave_inf", 1500, 72, 16, 5, 3, W.ACT_RELU, W.DTYPE_F32, seed=82)
+    dev = to_device(w)
+    dev["x"][7] = float("nan")
+    F.fff_set_option("path", 7)
+    try:
+        ref, leaf = run_forward(w, dev)
+        if where == "leaf_w1":
+            dev["leaf_w1"][int(leaf[20]), 1, -1] = float("inf")
+            got, now = run_forward(w, dev)
+            assert torch.equal(now, leaf)
+            hit = leaf == leaf[20]
+        else:
+            dev["node_w"][0, -1] = float("inf")
+            got, now = run_forward(w, dev)
+            right = dev["x"][:, -1] > 0
+            assert torch.equal(now[dev["x"][:, -1] != 0] >= 16, right[dev["x"][:, -1] != 0])
+            hit = (now != leaf)
+    finally:
+        F.fff_set_option("path", 0)
+    hit[7] = True
+    assert torch.equal(got[~hit], ref[~hit]) and int((~hit).sum()) > 500
+    if where == "leaf_w1":
+        only = hit.clone()
+        only[7] = False
+        x_last, h = dev["x"][only][:, -1], got[only]
+        assert not bool(torch.isnan(h[x_last > 0]).any()) and not bool(torch.isinf(h[x_last < 0]).any())
+    assert int(leaf[7]) == 0            # NaN logits go left
+
+
+@pytest.mark.parametrize("T, D, O, L, dtype, expect", [
+    (512, 768, 768, 4, W.DTYPE_BF16, False), (513, 768, 768, 8, W.DTYPE_BF16, True), (1024, 768, 768, 9, W.DTYPE_BF16, False),
+    (1024, 4096, 4096, 8, W.DTYPE_BF16, True), (2048, 768, 768, 1, W.DTYPE_BF16, True), (2048, 128, 128, 1, W.DTYPE_BF16, False),
+    (2048, 768, 768, 16, W.DTYPE_BF16, True), (4096, 2048, 2048, 32, W.DTYPE_BF16, True), (4096, 4096, 4096, 8, W.DTYPE_BF16, False),
+    (4096, 784, 10, 4, W.DTYPE_F32, True), (4097, 768, 768, 1, W.DTYPE_BF16, False), (8192, 256, 256, 16, W.DTYPE_BF16, True),
+    (12288, 512, 512, 4, W.DTYPE_BF16, True), (12289, 512, 512, 4, W.DTYPE_BF16, False),
+])
+def test_which_calls_take_it(T, D, O, L, dtype, expect):
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] route T=%d D=%d O=%d depth=6 L=%d dtype=%d" % (T, D, O, L, dtype), flush=True)
+    dt = torch.bfloat16 if dtype == W.DTYPE_BF16 else torch.float32
+    depth, n = 6, 64
+    new = lambda *s: torch.zeros(s, dtype=dt, device="cuda")
+    F.fff_forward_hard(new(T, D), new(n - 1, D), new(n - 1), new(n, L, D), new(n, L), new(n, L, O), new(n, O), depth, L, W.ACT_RELU, new(T, O))
+    torch.cuda.synchronize()
+    assert ("walk_wave_kernel" in F.fff_last_launch()) == expect, F.fff_last_launch()
