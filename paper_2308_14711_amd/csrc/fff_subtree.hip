@@ -20,6 +20,10 @@
 // row arrives) where the two leaf kernels take 18 + 19; fp32, 25216 tokens: 42 us, the gather kernel 65.  Measured and not kept: token
 // rows straight to registers in the instruction's layout (64 bytes of 16 rows a load: 47 us), 96 to 128 tokens a block, output rows 16
 // tokens at a time (more waves, but a chain of loads each: 36 -> 43 us), a deeper ring (no change).
+// Normalised bf16 rows (fff_forward_block; 50432 tokens of 768, 4 neurons a node, 8 a leaf): levels from the root 60 -> 55 us, lower end 84 -> 76
+// with the steps of the contraction interleaved, the statistics without masks and the residual rows requested a range ahead; the vector
+// unit is busy half of the time.  Measured and not kept there: one round of blocks of 5 to 8 waves, or of 13 on a whole compute unit (131.8
+// against 130.6 us for the call), stages in another order in each block (no change).
 #include "fff_device.h"
 #include "fff_internal.h"
 
@@ -127,6 +131,15 @@ __device__ __forceinline__ void load4(const float* p, float* f) {
 }
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+
+// s plus the elements of a piece
+template <bool BF16> __device__ __forceinline__ float piece_sum(const uint4& v, float s) {
+    if (BF16) {
+        constexpr uint32_t ones = 0x3f803f80u;
+        return dot2_bf16(v.w, ones, dot2_bf16(v.z, ones, dot2_bf16(v.y, ones, dot2_bf16(v.x, ones, s))));
+    }
+    return s + __uint_as_float(v.x) + __uint_as_float(v.y) + __uint_as_float(v.z) + __uint_as_float(v.w);
+}
 
 struct Yes { static constexpr bool value = true; };
 struct No { static constexpr bool value = false; };
@@ -268,13 +281,13 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
             float2 st[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+                // (a vector unit busy half of this launch's time: pieces inside the row need no masks, and two bf16 values are added at once)
                 float s = 0.0f, f[E];
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
                     if (16 * i >= a.pieces) continue;
-                    widen<BF16>(v[r][i], f);
-#pragma unroll
-                    for (int e = 0; e < E; ++e) s += j + 16 * i < a.pieces ? f[e] : 0.0f;
+                    if (16 * i + 16 > a.pieces) v[r][i] = keep_if(j + 16 * i < a.pieces, v[r][i]);
+                    s = piece_sum<BF16>(v[r][i], s);
                 }
                 const float mu = group_sum<16>(s) / width;
                 float q = 0.0f;
@@ -282,11 +295,13 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
                 for (int i = 0; i < NV; ++i) {
                     if (16 * i >= a.pieces) continue;
                     widen<BF16>(v[r][i], f);
+                    float p = 0.0f;
 #pragma unroll
                     for (int e = 0; e < E; ++e) {
-                        const float d = j + 16 * i < a.pieces ? f[e] - mu : 0.0f;
-                        q = fmaf(d, d, q);
+                        const float d = f[e] - mu;
+                        p = fmaf(d, d, p);
                     }
+                    q += 16 * i + 16 <= a.pieces || j + 16 * i < a.pieces ? p : 0.0f;
                 }
                 const float var = group_sum<16>(q) / width;
                 st[r] = make_float2(mu, 1.0f / sqrtf(var + a.eps));
@@ -358,16 +373,77 @@ __global__ __launch_bounds__(256, 2) void subtree_kernel(const SubtreeArgs a) {
         }
     };
     for (int kc = 0; kc < kStages - 1 && kc < chunks; ++kc) request(kc);
-    for (int kc = 0; kc < chunks; ++kc) {
-        // stage kc has landed for this wave once no more than the loads requested after it are outstanding, for
-        // the block after the barrier; the barrier also says that everyone has read stage kc - 1, which the
-        // next request overwrites
+    // stage kc has landed for this wave once no more than the loads requested after it are outstanding, for
+    // the block after the barrier; the barrier also says that everyone has read stage kc - 1, which the
+    // next request overwrites
+    const auto next_stage = [&](int kc) {
         const int ahead = chunks - 1 - kc < kStages - 2 ? chunks - 1 - kc : kStages - 2;
         if (ahead >= 2) wait_loads<2 * kLoads>();
         else if (ahead == 1) wait_loads<kLoads>();
         else wait_loads<0>();
         __syncthreads();
         if (kc + kStages - 1 < chunks) request(kc + kStages - 1);
+    };
+    int done = 0;
+    if (BF16 && LN && !THREE) {
+        // Normalising a piece takes the vector unit about as long as the piece's products take the matrix cores, and the waves of a
+        // compute unit leave the barrier in step: one after the other they take the sum of both (2800 cycles a stage for two blocks).  So a
+        // step of 32 elements is normalised between the matrix instructions of the step before it, and read from LDS ahead of them.
+        struct Step {
+            uint4 x, g, b, w[NB], hi, lo;
+        } even, odd;
+        const auto read = [&](int kc, int u, Step& s) {
+            const uint4* xs = ring + (kc % kStages) * kStagePieces;
+            const int piece = 8 * kc + 2 * kg + u;
+            s.x = xs[tile_swz(tok, 2 * kg + u)];
+            s.g = s_gamma[LN ? piece : 0];
+            s.b = s_beta[LN ? piece : 0];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) s.w[b] = xs[kTok * 8 + tile_swz(16 * b + j, 2 * kg + u)];
+        };
+        const auto normalise = [&](Step& s) {
+            uint4 lo2;
+            token_piece<BF16, LN, THREE>(s.x, s.g, s.b, mean, rstd, &s.hi, &s.lo, &lo2);
+        };
+        const auto products = [&](const Step& s) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = mfma_piece<BF16>(s.w[b], s.hi, acc[b]);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = mfma_piece<BF16>(s.w[b], s.lo, acc[b]);
+        };
+        const auto interleave = [&] {
+            __builtin_amdgcn_sched_group_barrier(0x100, 3 + NB, 0);                     // LDS reads
+#pragma unroll
+            for (int i = 0; i < 2 * NB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                        // a matrix instruction
+                __builtin_amdgcn_sched_group_barrier(0x2, (80 + 2 * NB - 1) / (2 * NB), 0);    // its share of the normalisation
+            }
+        };
+        const int full = a.pieces / 8;
+        if (full > 0) {
+            next_stage(0);
+            read(0, 0, even);
+            normalise(even);
+            for (; done < full - 1; ++done) {
+                read(done, 1, odd);
+                products(even);
+                normalise(odd);
+                interleave();
+                next_stage(done + 1);
+                read(done + 1, 0, even);
+                products(odd);
+                normalise(even);
+                interleave();
+            }
+            read(done, 1, odd);
+            products(even);
+            normalise(odd);
+            products(odd);
+            ++done;
+        }
+    }
+    for (int kc = done; kc < chunks; ++kc) {
+        next_stage(kc);
         if (8 * kc + 8 <= a.pieces) multiply(kc, No());
         else multiply(kc, Yes());
     }
@@ -614,10 +690,12 @@ __device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint
             for (int q = 0; q < 4; ++q) x[g][q] = *(const uint2*)((const uint16_t*)a.x + (int64_t)tq[q] * O + oc);
         }
     };
-    if (wv < ranges) request_weights(wv, 0);
+    uint2 x[4][4];
+    if (wv < ranges) {
+        request_weights(wv, 0);
+        request_tokens(wv, x);
+    }
     for (int r = wv; r < ranges; r += 4) {
-        uint2 x[4][4];
-        request_tokens(r, x);
         // largest magnitudes (as bit patterns) of the weights met
         u16x2_t most = {0, 0};
         f32x4_t acc[4][4];
@@ -664,8 +742,23 @@ __device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint
                 }
             }
         }
-        // the next range's weights before this one's rows leave: a wait for a load is a wait for everything before it
-        if (r + 4 < ranges) request_weights(r + 4, 0);
+        if (residual) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[g][0][q] += bf16_lo(x[g][q].x);
+                    acc[g][1][q] += bf16_hi(x[g][q].x);
+                    acc[g][2][q] += bf16_lo(x[g][q].y);
+                    acc[g][3][q] += bf16_hi(x[g][q].y);
+                }
+        }
+        // the next range's weights and tokens before this one's rows leave: a wait for a load is a wait for everything before it
+        // (the leaf launch of 50432 tokens of 768, 8 neurons, with residual: 84 -> 79 us)
+        if (r + 4 < ranges) {
+            request_weights(r + 4, 0);
+            request_tokens(r + 4, x);
+        }
         if (__ballot(most.x >= 0x7f80 || most.y >= 0x7f80)) {
             write_rows_apart(a, hid, pitch, third, third_pitch, s_tok, s_sub, n, first_leaf, r);
             continue;
@@ -679,13 +772,7 @@ __device__ __forceinline__ void write_rows_mfma(const SubtreeArgs& a, const uint
             const int32_t tq[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                float y[4] = {acc[g][0][q], acc[g][1][q], acc[g][2][q], acc[g][3][q]};
-                if (residual) {
-                    y[0] += bf16_lo(x[g][q].x);
-                    y[1] += bf16_hi(x[g][q].x);
-                    y[2] += bf16_lo(x[g][q].y);
-                    y[3] += bf16_hi(x[g][q].y);
-                }
+                const float y[4] = {acc[g][0][q], acc[g][1][q], acc[g][2][q], acc[g][3][q]};
                 const u32x2_t v = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
                 u32x2_t* const to = (u32x2_t*)((uint16_t*)a.out + (int64_t)tq[q] * O + 64 * r + 4 * j);
                 if (whole) __builtin_nontemporal_store(v, to);
