@@ -44,11 +44,11 @@ __device__ __forceinline__ float row_dot(const uint4 (&xv)[NV], int sub, int nve
     return acc0 + acc1;
 }
 
-// The same for the TPG tokens of a lane group, row k at row_of(k).  SHARE: a row that all of the wave's tokens want (their nodes are
-// equal) is fetched once.
-template <bool BF16, int LPT, int NV, int TPG, bool TIGHT, bool SHARE, typename RowOf>
+// The same for the TPG tokens of a lane group, row k at row_of(k); a row that both tokens of a wave want (their nodes are equal) is
+// fetched once.
+template <bool BF16, int LPT, int NV, int TPG, bool TIGHT, typename RowOf>
 __device__ __forceinline__ void row_dots(const uint4 (&xv)[TPG][NV], int sub, int nvec, const int (&node)[TPG], RowOf row_of, float (&s)[TPG]) {
-    if (SHARE && LPT == kWave && TPG == 2 && node[0] == node[TPG - 1]) {
+    if (LPT == kWave && TPG == 2 && node[0] == node[TPG - 1]) {
         const uint4* row = row_of(0);
         uint4 wv[NV];
 #pragma unroll
@@ -179,8 +179,11 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
         int node[TPG];
 #pragma unroll
         for (int k = 0; k < TPG; ++k) {
-            node[k] = GROUPED ? (1 << a.base_level) - 1 + a.start[t[k]] : 0;
-            if (GROUPED && LPT == kWave) node[k] = __builtin_amdgcn_readfirstlane(node[k]);
+            node[k] = 0;
+            if constexpr (GROUPED) {
+                node[k] = (1 << a.base_level) - 1 + a.start[t[k]];
+                if (LPT == kWave) node[k] = __builtin_amdgcn_readfirstlane(node[k]);
+            }
         }
 
         // levels whose rows sit in LDS
@@ -200,9 +203,19 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
         // deeper levels: one row fetch per token per level, TPG of them in flight
         for (int m = GROUPED ? a.base_level : a.top; m < a.depth; ++m) {
             float s[TPG], bias[TPG];
+            // (not row_dots for both: it costs the launches of short rows, four tokens a lane group, up to 70 %: 30819 tokens of 104 9.0 -> 15.3 us)
+            if constexpr (GROUPED) {
 #pragma unroll
-            for (int k = 0; k < TPG; ++k) bias[k] = Elem<BF16>::load(a.node_b, node[k]);
-            row_dots<BF16, LPT, NV, TPG, TIGHT, GROUPED>(xv, sub, nvec, node, [&](int k) { return a.node_w + (int64_t)node[k] * nvec; }, s);
+                for (int k = 0; k < TPG; ++k) bias[k] = Elem<BF16>::load(a.node_b, node[k]);
+                row_dots<BF16, LPT, NV, TPG, TIGHT>(xv, sub, nvec, node, [&](int k) { return a.node_w + (int64_t)node[k] * nvec; }, s);
+            } else {
+#pragma unroll
+                for (int k = 0; k < TPG; ++k) {
+                    const uint4* row = a.node_w + (int64_t)node[k] * nvec;
+                    bias[k] = Elem<BF16>::load(a.node_b, node[k]);
+                    s[k] = row_dot<BF16, LPT, NV, TIGHT>(xv[k], sub, nvec, [&](int v) { return row[v]; });
+                }
+            }
 #pragma unroll
             for (int k = 0; k < TPG; ++k) {
                 const float logit = group_sum<LPT>(s[k]) + bias[k];
@@ -233,9 +246,18 @@ __global__ __launch_bounds__(kWalkBlock) void walk_kernel(const WalkArgs a) {
         for (int r = 0; r < kFusedMaxLeafWidth; ++r) {
             if (r < a.L) {
                 float s[TPG], bias[TPG];
+                if constexpr (GROUPED) {
 #pragma unroll
-                for (int k = 0; k < TPG; ++k) bias[k] = Elem<BF16>::load(a.b1, leaf[k] * a.L + r);
-                row_dots<BF16, LPT, NV, TPG, TIGHT, GROUPED>(xv, sub, nvec, node, [&](int k) { return a.w1 + (leaf[k] * a.L + r) * nvec; }, s);
+                    for (int k = 0; k < TPG; ++k) bias[k] = Elem<BF16>::load(a.b1, leaf[k] * a.L + r);
+                    row_dots<BF16, LPT, NV, TPG, TIGHT>(xv, sub, nvec, node, [&](int k) { return a.w1 + (leaf[k] * a.L + r) * nvec; }, s);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < TPG; ++k) {
+                        const uint4* row = a.w1 + (leaf[k] * a.L + r) * nvec;
+                        bias[k] = Elem<BF16>::load(a.b1, leaf[k] * a.L + r);
+                        s[k] = row_dot<BF16, LPT, NV, TIGHT>(xv[k], sub, nvec, [&](int v) { return row[v]; });
+                    }
+                }
 #pragma unroll
                 for (int k = 0; k < TPG; ++k) h[k][r] = activate(group_sum<LPT>(s[k]) + bias[k], a.act);
             } else {
@@ -532,6 +554,7 @@ hipError_t dispatch_grouped(const Problem& p, int base_level, const int32_t* per
     if (nvec <= 64) return run_grouped<BF16, 16, 4, 2>(p, base_level, perm, start, leaf_idx, s);
     if (nvec <= 96) return run_grouped<BF16, 16, 6, 2>(p, base_level, perm, start, leaf_idx, s);
     if (nvec <= 128) return run_grouped<BF16, 16, 8, 2>(p, base_level, perm, start, leaf_idx, s);
+    if (nvec <= 192) return run_grouped<BF16, 64, 3, 2>(p, base_level, perm, start, leaf_idx, s);
     if (nvec <= 256) return run_grouped<BF16, 64, 4, 2>(p, base_level, perm, start, leaf_idx, s);
     if (nvec <= 512) return run_grouped<BF16, 64, 8, 2>(p, base_level, perm, start, leaf_idx, s);
     return run_grouped<BF16, 64, 16, 1>(p, base_level, perm, start, leaf_idx, s);
@@ -601,6 +624,9 @@ hipError_t dispatch_walk(const Problem& p, int32_t* leaf_idx, hipStream_t s) {
     }
     if (nvec <= 128) return small_batch ? run_walk<BF16, 16, 8, 1, 512, MODE>(p, leaf_idx, s)
                                         : run_walk<BF16, 16, 8, 2, 512, MODE>(p, leaf_idx, s);
+    // (three pieces a lane where they hold the row: with four a quarter of the lanes' requests are masked, and a masked request is four
+    // guarded ones; descent of 25216 fp32 tokens of 768, depth 8: 31.7 -> 25.9 us, of 1536 bf16 features 37.0 -> 28.4)
+    if (nvec <= 192) return run_walk<BF16, 64, 3, 2, 1024, MODE>(p, leaf_idx, s);
     if (nvec <= 256) return run_walk<BF16, 64, 4, 2, 1024, MODE>(p, leaf_idx, s);
     if (nvec <= 512) {
         const int64_t tpg = g_walk_tuning.tpg, blk = g_walk_tuning.block;
