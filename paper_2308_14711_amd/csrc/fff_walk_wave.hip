@@ -8,7 +8,7 @@
 //   - the leaf's first neurons, its biases and its first output weights are requested together.
 // A token's sums are taken over 64 lanes; the activations of a leaf are kept one a lane and evaluated once for all.
 //
-// What bounds it: the trips (2048 bf16 tokens of 768, depth 11, one neuron: 10.4 us in walk_kernel, 8.6 here), and with wider leaves the
+// What bounds it: the trips (2048 bf16 tokens of 768, depth 11, one neuron: 10.4 us in walk_kernel, 8.4 here), and with wider leaves the
 // rows of each token through the L1s (4096 fp32 tokens of 784, depth 6, 4 neurons: 14.7 -> 9.9 us, 0.5 MB of rows a compute unit).
 #include "fff_device.h"
 #include "fff_internal.h"
@@ -255,9 +255,10 @@ hipError_t launch_walk_wave(const Problem& p, int32_t* leaf_idx, hipStream_t s) 
     int64_t waves = (p.T + cus - 1) / cus;
     waves = waves < 4 ? 4 : waves > 16 ? 8 : waves;
     if (waves > max_waves(a.nvec <= 256 ? 4 : 8)) waves = max_waves(a.nvec <= 256 ? 4 : 8);
-    // Levels kept in LDS: a block of few tokens finds the top rows in L1 and L2 as fast (2048 tokens of 768, depth 11: 8.6 us without, 8.7 with
-    // three levels, 9.5 with five); more tokens share more (4096 fp32 ones of 784, depth 6: 12.3 without, 10.4 with four).
-    const int64_t widest = p.T <= 4 * cus ? 0 : p.T <= 8 * cus || row_bytes <= 2048 ? (p.T <= 16 * cus ? 7 : 14) : p.T <= 16 * cus ? 28 : 14;   // KB
+    // Levels kept in LDS: a block of up to eight tokens finds the top rows in L1 and L2 as fast as it would fill LDS with them (5000 random calls
+    // of 1024 to 2048 tokens: without 1.01 to 1.12 times as fast as with three levels; 2048 tokens of 768, depth 11: 8.6 -> 8.4 us); more tokens share
+    // more (4096 fp32 ones of 784, depth 6: 12.3 without, 10.4 with four).
+    const int64_t widest = p.T <= 8 * cus ? 0 : p.T > 16 * cus ? 14 : row_bytes <= 2048 ? 7 : 28;   // KB
     a.top = 0;
     while (a.top < p.depth && (row_bytes << a.top) <= widest * 1024 && (row_bytes + 4) * ((2 << a.top) - 1) <= 64 * 1024) ++a.top;
     const size_t lds_bytes = (size_t)(row_bytes + 4) * (((int64_t)1 << a.top) - 1);
