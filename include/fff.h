@@ -44,6 +44,9 @@
  *     the rule above: hipFree waits for the device.  It cannot happen during
  *     stream capture (such a call returns FFF_ERR_WORKSPACE instead), and not
  *     at all after fff_reserve_workspace* with sizes at least as large.
+ *     A captured graph of calls that use the workspace holds its address: it
+ *     is not to be replayed once the block has been freed -- by growth, by
+ *     fff_release_workspace or by the caller whose memory it was.
  */
 #ifndef FFF_H
 #define FFF_H
@@ -104,6 +107,25 @@ int fff_forward_hard(const void* x, const void* node_w, const void* node_b,
                      int depth, int leaf_width, int act,
                      void* out, int32_t* leaf_idx, void* stream,
                      int64_t T, int64_t D, int64_t O, int dtype);
+
+/*
+ * fff_forward_hard_scratch: the same with scratch of the caller's, in which calls that one fused launch would take -- it uses no memory
+ * of its own, the workspace neither -- run grouped by the node they reach after the top levels where that is faster (three launches, the
+ * same results bit for bit).  Which launches run depends on the sizes, dtype, alignment and options alone.
+ *   scratch        device memory, 256-byte aligned, of one call from its launches until they have run (calls on one
+ *                  stream may share it); needs no initial value; NULL: as fff_forward_hard
+ *   scratch_bytes  at least fff_hard_scratch_bytes of the same sizes (0: these sizes never use scratch, or
+ *                  are out of range)
+ * Errors: as for fff_forward_hard; FFF_ERR_WORKSPACE (scratch misaligned, or too short for a call that uses it),
+ * FFF_ERR_ALIAS (scratch overlaps x, out or leaf_idx).
+ */
+int fff_forward_hard_scratch(const void* x, const void* node_w, const void* node_b,
+                             const void* leaf_w1, const void* leaf_b1,
+                             const void* leaf_w2, const void* leaf_b2,
+                             int depth, int leaf_width, int act,
+                             void* out, int32_t* leaf_idx, void* stream,
+                             int64_t T, int64_t D, int64_t O, int dtype, void* scratch, size_t scratch_bytes);
+size_t fff_hard_scratch_bytes(int64_t T, int64_t D, int64_t O, int depth, int leaf_width, int dtype);
 
 /*
  * fff_forward_hard_static: for callers that cannot allocate device memory -- code under HIP graph

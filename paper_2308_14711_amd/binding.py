@@ -58,6 +58,9 @@ def lib() -> ctypes.CDLL:
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
         L.fff_forward_hard.argtypes = [vp] * 7 + [i32, i32, i32, vp, vp, vp, i64, i64, i64, i32]
         L.fff_forward_hard_static.argtypes = L.fff_forward_hard.argtypes
+        L.fff_forward_hard_scratch.argtypes = L.fff_forward_hard.argtypes + [vp, ctypes.c_size_t]
+        L.fff_hard_scratch_bytes.argtypes = [i64, i64, i64, i32, i32, i32]
+        L.fff_hard_scratch_bytes.restype = ctypes.c_size_t
         L.fff_static_scratch_bytes.argtypes = []
         L.fff_static_scratch_bytes.restype = ctypes.c_size_t
         L.fff_descend.argtypes = [vp, vp, vp, i32, vp, vp, i64, i64, i32]
@@ -193,7 +196,8 @@ def _check_leaves(where, x, T, D, O, depth, leaf_width, leaf_w1, leaf_b1, leaf_w
 def fff_forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, leaf_width, act,
                      out, leaf_idx=None, stream=None, static_scratch=False) -> None:
     """Forward_I for x [T, D] -> out [T, O] (and leaf_idx [T] int32 if given).  static_scratch=True
-    calls fff_forward_hard_static, the variant that allocates nothing."""
+    calls fff_forward_hard_static, the variant that allocates nothing.  Large batches of deep trees may work in
+    scratch of torch's allocator (fff_forward_hard_scratch), captured by torch.cuda.graph or not."""
     rc = (_native_module or _native()).forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth,
                                                     leaf_width, act, out, leaf_idx, stream, static_scratch)
     if rc == 0:
@@ -209,16 +213,26 @@ def fff_forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, dept
             _expect(where, "node_b", node_b, ((1 << depth) - 1,), x.dtype)
         _check_leaves(where, x, T, D, O, depth, leaf_width, leaf_w1, leaf_b1, leaf_w2, leaf_b2, out, leaf_idx, "leaf_idx")
     _check_dense(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, out, leaf_idx)
-    entry = lib().fff_forward_hard_static if static_scratch else lib().fff_forward_hard
-    _check(entry(_ptr(x), _ptr(node_w), _ptr(node_b), _ptr(leaf_w1), _ptr(leaf_b1), _ptr(leaf_w2), _ptr(leaf_b2),
-                 depth, leaf_width, act, _ptr(out), _ptr(leaf_idx), _stream_handle(stream), T, D, O, _dtype_code(x)),
-           where)
+    args = (_ptr(x), _ptr(node_w), _ptr(node_b), _ptr(leaf_w1), _ptr(leaf_b1), _ptr(leaf_w2), _ptr(leaf_b2),
+            depth, leaf_width, act, _ptr(out), _ptr(leaf_idx), _stream_handle(stream), T, D, O, _dtype_code(x))
+    if static_scratch:
+        _check(lib().fff_forward_hard_static(*args), where)
+        return
+    need, scratch = 0, None
+    if _in_range(depth, leaf_width):
+        need = fff_hard_scratch_bytes(T, D, O, depth, leaf_width, _dtype_code(x))
+        scratch = _torch_scratch(need, stream) if need else None
+    _check(lib().fff_forward_hard_scratch(*args, _ptr(scratch), need), where)
 
 
 def fff_forward_hard_static(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, leaf_width, act,
                             out, leaf_idx=None, stream=None) -> None:
     fff_forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, leaf_width, act, out, leaf_idx,
                      stream, static_scratch=True)
+
+
+def fff_hard_scratch_bytes(T: int, D: int, O: int, depth: int, leaf_width: int, dtype: int) -> int:
+    return int(lib().fff_hard_scratch_bytes(T, D, O, depth, leaf_width, dtype))
 
 
 def fff_static_scratch_bytes() -> int:
@@ -406,8 +420,8 @@ def fff_workspace_bytes_soft(T: int, O: int, depth: int, leaf_width: int) -> int
 
 def fff_set_workspace(buf, stream=None) -> None:
     """Every later call on the current device works in `buf` (a dense device tensor the caller keeps
-    alive), or in the library's own workspace again for buf = None.  (fff_forward_block needs no workspace: its scratch is
-    torch's either way.)"""
+    alive), or in the library's own workspace again for buf = None.  (fff_forward_block, and fff_forward_hard where one fused
+    launch would take the call, need no workspace: their scratch is torch's either way.)"""
     if buf is None:
         _check(lib().fff_set_workspace(None, 0, _stream_handle(stream)), "fff_set_workspace")
         return

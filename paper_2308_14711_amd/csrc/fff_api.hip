@@ -612,6 +612,12 @@ bool grouped_shape_ok(const Problem& p) {
            vec_ok(p.leaf_b2, p.O, p.bf16);
 }
 
+// The sizes whose time the estimates below were fitted to.
+bool walk_grouped_range(const Problem& p) {
+    const int64_t row = p.D * (p.bf16 ? 2 : 4);
+    return p.depth >= 8 && p.depth <= 16 && row >= 512 && p.O <= 2 * p.D && 4 * p.O >= p.D && p.T > 32 * (int64_t)device_info().cus && grouped_shape_ok(p);
+}
+
 // Whether a call that `path` would take goes to the grouped walk instead.
 //
 // Below the top levels every token of the fused launch wants rows of its own, and once the tables outgrow an L2 most of them come from
@@ -628,10 +634,8 @@ bool walk_grouped(const Problem& p, int path) {
     if (g_opt.path == kPathGrouped) return grouped_shape_ok(p);
     if (g_opt.path != kPathAuto || g_opt.leaf_path != 0 || g_opt.leaf_split != 0 || !g_opt.bucketing || g_subtree != 0) return false;
     if (path != kPathFused && path != kPathSplit && path != kPathStaged) return false;
+    if (!walk_grouped_range(p) || (path == kPathStaged && subtree_levels(p, false) >= 0)) return false;
     const int64_t es = p.bf16 ? 2 : 4;
-    if (p.T <= 32 * (int64_t)device_info().cus || p.D * es < 512 || p.O > 2 * p.D || 4 * p.O < p.D || p.depth < 8 || p.depth > 16 ||
-        !grouped_shape_ok(p) || (path == kPathStaged && subtree_levels(p, false) >= 0))
-        return false;
     const double T = (double)p.T, node = 1e-6 * (double)(p.D * es), leaf = 1e-6 * (double)((p.L * (p.D + p.O) + p.O) * es);    // MB
     const double leaves = (double)((int64_t)1 << p.depth);
     // rows that some token meets, if all leaves are as likely
@@ -752,45 +756,45 @@ int scratch_on_device(void** ptr) {
     return FFF_OK;
 }
 
+// Scratch of the grouped walk, in words: the node every token reaches, the tokens in their order, the descent's counts.
+int64_t walk_scratch_words(int64_t T) { return 2 * round_up(T, kAlignWords) + kFoldWords; }
+
 // The first kGroupLevel levels for every token, the tokens grouped by the node they reach, then the rest of the fused launch in that
-// order: the same bits as the fused launch.  *done stays false, and nothing is enqueued, where there is no workspace to be had (the fused
-// launch needs none).
-int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch, bool* done) {
+// order: the same bits as the fused launch.
+int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, int32_t* node, int32_t* perm, int32_t* counts, int64_t capacity,
+                     bool marks) {
     const int level = p.depth <= kGroupLevel ? p.depth - 1 : kGroupLevel;
-    const bool marks = fixed_scratch == nullptr;
-    Workspace ws;
-    Layout lay;
-    if (fixed_scratch) {
-        lay = layout_for(p.T, p.depth);
-        carve(fixed_scratch, lay, &ws);
-    } else if (get_workspace(p.T, p.depth, &ws, &lay, s) != FFF_OK) {
-        g_last_error.clear();
-        return FFF_OK;
-    }
-    *done = true;
     g_opt.last_path = kPathGrouped;
     Problem top = p;
     top.depth = level;
     DescentCounts dc;
-    dc.M = ws.hidden;
-    dc.capacity = kTilesMaxLeafWidth / 2 * p.T < kFoldWords ? kTilesMaxLeafWidth / 2 * p.T : kFoldWords;
+    dc.M = counts;
+    dc.capacity = capacity;
     if (marks) stage_mark(s);
-    hipError_t e = launch_descend(top, ws.leaf_idx, s, &dc);
+    hipError_t e = launch_descend(top, node, s, &dc);
     if (e != hipSuccess) return set_device_error(e, "descent kernel launch");
     if (marks) stage_mark(s);
-    const int rc = run_bucket(ws.leaf_idx, p.T, level, ws, nullptr, nullptr, ws.perm, nullptr, s, &dc);
-    if (rc != FFF_OK) return rc;
+    e = dc.blocks > 0 ? launch_bucket_fold(node, p.T, level, dc, nullptr, nullptr, perm, nullptr, s)
+                      : launch_bucket_hist(node, p.T, level, nullptr, nullptr, perm, nullptr, s);
+    if (e != hipSuccess) return set_device_error(e, "bucket kernel launch");
     if (marks) stage_mark(s);
-    e = launch_walk_grouped(p, level, ws.perm, ws.leaf_idx, leaf_idx, s);
+    e = launch_walk_grouped(p, level, perm, node, leaf_idx, s);
     for (int i = 0; marks && i < 2; ++i) stage_mark(s);
     return e == hipSuccess ? FFF_OK : set_device_error(e, "grouped walk kernel launch");
+}
+
+int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, const Workspace& ws, bool marks) {
+    const int64_t words = kTilesMaxLeafWidth / 2 * p.T;
+    return run_walk_grouped(p, leaf_idx, s, ws.leaf_idx, ws.perm, ws.hidden, words < kFoldWords ? words : kFoldWords, marks);
 }
 
 // The launches of Forward_I.  fixed_scratch == nullptr: the staged path works in the device's
 // workspace and the stages are bracketed by events when "stage_timing" is on.  Otherwise that block
 // of device memory (large enough for layout_for(T, depth): the caller has checked) is carved
 // instead, its control words are cleared by a kernel first, and no event is created.
-int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch) {
+// walk_scratch: the grouped walk in this memory (walk_scratch_words) in the place of the fused launch.  Memory of this call alone: the fused
+// launch needs none, and what takes its place may not allocate, fail or leave an address in a captured graph where that did not.
+int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch, void* walk_scratch = nullptr) {
     const bool marks = fixed_scratch == nullptr;
     const int path = choose_path(p);
     g_opt.last_path = path == kPathWave ? (int)kPathFused : path;      // (one fused launch, whichever kernel)
@@ -807,16 +811,22 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
         for (int k = 0; marks && k < 4; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "token-block kernel launch");
     }
-    if (walk_grouped(p, path)) {
-        bool done = false;
-        const int rc = run_walk_grouped(p, leaf_idx, s, fixed_scratch, &done);
-        if (done) return rc;
+    if (walk_scratch) {
+        int32_t *const node = (int32_t*)walk_scratch, *const perm = node + round_up(p.T, kAlignWords);
+        return run_walk_grouped(p, leaf_idx, s, node, perm, perm + round_up(p.T, kAlignWords), kFoldWords, marks);
     }
     if (path == kPathWave) {
         if (marks) stage_mark(s);
         hipError_t e = launch_walk_wave(p, leaf_idx, s);
         for (int k = 0; marks && k < 4; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "wave kernel launch");
+    }
+    if (path == kPathFused && g_opt.path == kPathGrouped && walk_grouped(p, path)) {      // (asked for)
+        Workspace ws;
+        Layout lay;
+        if (fixed_scratch) carve(fixed_scratch, layout_for(p.T, p.depth), &ws);
+        if (fixed_scratch || get_workspace(p.T, p.depth, &ws, &lay, s) == FFF_OK) return run_walk_grouped(p, leaf_idx, s, ws, marks);
+        g_last_error.clear();
     }
     if (path == kPathFused) {
         if (marks) stage_mark(s);
@@ -827,15 +837,17 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
     Workspace ws;
     Layout lay;
     hipError_t e;
+    const bool grouped = walk_grouped(p, path);
     if (fixed_scratch) {
         lay = layout_for(p.T, p.depth);
         carve(fixed_scratch, lay, &ws);
-        if (path == kPathStaged && (e = launch_zero(ws.ctrl, kCtrlWords, s)) != hipSuccess)
+        if (path == kPathStaged && !grouped && (e = launch_zero(ws.ctrl, kCtrlWords, s)) != hipSuccess)
             return set_device_error(e, "zero kernel launch");
     } else {
         const int rc = get_workspace(p.T, p.depth, &ws, &lay, s);
         if (rc != FFF_OK) return rc;
     }
+    if (grouped) return run_walk_grouped(p, leaf_idx, s, ws, marks);
     int32_t* li = leaf_idx ? leaf_idx : ws.leaf_idx;
     if (path == kPathSplit) {
         // walk and hidden neurons per token, then the output rows by column slices; the hidden
@@ -888,18 +900,47 @@ using namespace fff;
 
 extern "C" {
 
-int fff_forward_hard(const void* x, const void* node_w, const void* node_b, const void* leaf_w1,
-                     const void* leaf_b1, const void* leaf_w2, const void* leaf_b2, int depth,
-                     int leaf_width, int act, void* out, int32_t* leaf_idx, void* stream, int64_t T,
-                     int64_t D, int64_t O, int dtype) {
+int fff_forward_hard_scratch(const void* x, const void* node_w, const void* node_b, const void* leaf_w1,
+                             const void* leaf_b1, const void* leaf_w2, const void* leaf_b2, int depth,
+                             int leaf_width, int act, void* out, int32_t* leaf_idx, void* stream, int64_t T,
+                             int64_t D, int64_t O, int dtype, void* scratch, size_t scratch_bytes) {
     bool empty = false;
     const int rc = check_forward_hard(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, leaf_width, act,
                                       out, T, D, O, dtype, &empty);
     if (rc != FFF_OK || empty) return rc;
+    if (scratch) {
+        const int64_t es = dtype == FFF_BF16 ? 2 : 4;
+        if ((reinterpret_cast<uintptr_t>(scratch) & 255u) != 0) return FFF_ERR_WORKSPACE;
+        if (overlaps(scratch, (int64_t)scratch_bytes, x, T * D * es) || overlaps(scratch, (int64_t)scratch_bytes, out, T * O * es) ||
+            (leaf_idx && overlaps(scratch, (int64_t)scratch_bytes, leaf_idx, T * 4)))
+            return FFF_ERR_ALIAS;
+    }
     Problem p{x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, out, leaf_idx,
               T, D, O, depth, leaf_width, act, dtype == FFF_BF16};
+    const bool grouped = scratch && choose_path(p) == kPathFused && g_opt.path == kPathAuto && walk_grouped(p, kPathFused);
+    const size_t need = (size_t)walk_scratch_words(T) * sizeof(int32_t);
+    if (grouped && scratch_bytes < need) {
+        g_last_error = "the scratch holds " + std::to_string(scratch_bytes) + " bytes, this call needs " + std::to_string(need);
+        return FFF_ERR_WORKSPACE;
+    }
     begin_device_call();
-    return run_forward_hard(p, leaf_idx, (hipStream_t)stream, nullptr);
+    return run_forward_hard(p, leaf_idx, (hipStream_t)stream, nullptr, grouped ? scratch : nullptr);
+}
+
+int fff_forward_hard(const void* x, const void* node_w, const void* node_b, const void* leaf_w1,
+                     const void* leaf_b1, const void* leaf_w2, const void* leaf_b2, int depth,
+                     int leaf_width, int act, void* out, int32_t* leaf_idx, void* stream, int64_t T,
+                     int64_t D, int64_t O, int dtype) {
+    return fff_forward_hard_scratch(x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, leaf_width, act, out, leaf_idx, stream, T,
+                                    D, O, dtype, nullptr, 0);
+}
+
+size_t fff_hard_scratch_bytes(int64_t T, int64_t D, int64_t O, int depth, int leaf_width, int dtype) {
+    if (check_common(depth, T, D, dtype) != FFF_OK || check_leaf(depth, leaf_width, 0, T, D, O) != FFF_OK || T == 0) return 0;
+    Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+              T, D, O, depth, leaf_width, 0, dtype == FFF_BF16};
+    return g_opt.path == kPathAuto && walk_grouped_range(p) && choose_path(p) == kPathFused && walk_grouped(p, kPathFused)
+               ? (size_t)walk_scratch_words(T) * sizeof(int32_t) : 0;
 }
 
 int fff_forward_hard_static(const void* x, const void* node_w, const void* node_b, const void* leaf_w1,

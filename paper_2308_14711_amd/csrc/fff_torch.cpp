@@ -126,6 +126,34 @@ Layer layer(Call& c, int leaf, int depth, int width, int act, int out) {
     return a;
 }
 
+// Scratch of one call from torch's allocator, in the order of the call's stream: handed back once the call has enqueued its work.
+// Null where there is none to be had (nothing may throw past the released interpreter lock).
+struct Scratch {
+    void* p = nullptr;
+    Scratch(size_t bytes, hipStream_t s) {
+        // an allocator with nothing left asks the device, which must not spoil what another thread captures just now
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        try {
+            p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, s);
+        } catch (const std::exception&) {
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    ~Scratch() {
+        if (p) c10::hip::HIPCachingAllocator::raw_delete(p);
+    }
+    Scratch(const Scratch&) = delete;
+};
+
+// Whether the call is being captured (it is left to binding.py then, which finds out who captures).
+bool captured(void* s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 // x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, depth, leaf_width, act, out, leaf_idx, stream, static_scratch
 PyObject* forward_hard(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 14) return PyLong_FromLong(-1);
@@ -141,10 +169,16 @@ PyObject* forward_hard(PyObject*, PyObject* const* args, Py_ssize_t n) {
         PyErr_Clear();
         c.ok = false;
     }
-    auto entry = truth == 1 ? fff_forward_hard_static : fff_forward_hard;
     return answer(c, [&] {
-        return entry(a.x, a.node_w, a.node_b, a.w1, a.b1, a.w2, a.b2, a.depth, a.width, a.act, a.out, idx, s, a.T, a.D,
-                     a.O, c.code());
+        const auto call = [&](auto entry, auto... more) {
+            return entry(a.x, a.node_w, a.node_b, a.w1, a.b1, a.w2, a.b2, a.depth, a.width, a.act, a.out, idx, s, a.T, a.D, a.O, c.code(), more...);
+        };
+        if (truth == 1) return call(fff_forward_hard_static);
+        const size_t bytes = fff_hard_scratch_bytes(a.T, a.D, a.O, a.depth, a.width, c.code());
+        if (bytes == 0) return call(fff_forward_hard);
+        if (captured(s)) return -1;
+        const Scratch scratch(bytes, (hipStream_t)s);
+        return call(fff_forward_hard_scratch, scratch.p, bytes);
     });
 }
 
@@ -184,26 +218,6 @@ PyObject* forward_soft(PyObject*, PyObject* const* args, Py_ssize_t n) {
     });
 }
 
-// Scratch of one call from torch's allocator, in the order of the call's stream: handed back once the call has enqueued its work.
-// Null where there is none to be had (nothing may throw past the released interpreter lock).
-struct Scratch {
-    void* p = nullptr;
-    Scratch(size_t bytes, hipStream_t s) {
-        // an allocator with nothing left asks the device, which must not spoil what another thread captures just now
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        try {
-            p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, s);
-        } catch (const std::exception&) {
-        }
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
-    ~Scratch() {
-        if (p) c10::hip::HIPCachingAllocator::raw_delete(p);
-    }
-    Scratch(const Scratch&) = delete;
-};
-
 // x, ln_gamma, ln_beta, ln_eps, node_w1, node_b1, node_w2, node_b2, leaf_w1, leaf_b1, leaf_w2, leaf_b2,
 // depth, node_size, leaf_width, act, residual, out, leaf_idx, stream
 PyObject* forward_block(PyObject*, PyObject* const* args, Py_ssize_t n) {
@@ -229,12 +243,7 @@ PyObject* forward_block(PyObject*, PyObject* const* args, Py_ssize_t n) {
         };
         const size_t bytes = fff_block_scratch_bytes(a.T, a.D, a.O, a.depth, (int)size, a.width, gamma != nullptr, c.code());
         if (bytes == 0) return call(nullptr, 0);
-        // (a captured call is left to binding.py, which finds out who captures)
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing((hipStream_t)s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return -1;
-        }
+        if (captured(s)) return -1;
         const Scratch scratch(bytes, (hipStream_t)s);
         return call(scratch.p, bytes);
     });

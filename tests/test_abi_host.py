@@ -158,6 +158,24 @@ def test_block_scratch_is_checked_on_the_host(L):
     assert call(p(2048), size()) == ALIAS and call(p(1030), size()) == ALIAS
 
 
+def test_hard_scratch_is_checked_on_the_host(L):
+    import paper_2308_14711_amd as F
+    OK, NULL, WORKSPACE, ALIAS = 0, 1, 6, 8
+    size = lambda T=16384, D=4096, O=4096, depth=15, width=4, dtype=1: F.fff_hard_scratch_bytes(T, D, O, depth, width, dtype)
+    assert 8 * 16384 < size() < 9 * 16384 + (1 << 20)
+    assert size(T=8192) == 0 and size(depth=7) == 0 and size(D=77, O=77) == 0 and size(width=9) == 0     # never grouped
+    assert size(D=768, O=768, depth=13, width=1, T=65536) == 0                            # in the place of the split launch: the workspace
+    for bad in (dict(T=-1), dict(T=0), dict(depth=-1), dict(depth=25), dict(width=0), dict(D=0), dict(O=0), dict(dtype=2)):
+        assert size(**bad) == 0, bad
+    p = lambda mb, off=0: ctypes.c_void_p((mb << 20) + off)
+    call = lambda scratch, nbytes, T=16384, x=p(1 << 14): L.fff_forward_hard_scratch(
+        x, p(2 << 14), p(3 << 14), p(4 << 14), p(5 << 14), p(6 << 14), p(7 << 14), 15, 4, 0, p(8 << 14), None, None, T, 4096, 4096, 1, scratch, nbytes)
+    assert call(p(9 << 14), size(), T=0) == OK and call(p(9 << 14), size(), x=None) == NULL
+    assert call(p(9 << 14, 128), size()) == WORKSPACE and call(p(9 << 14), size() - 1) == WORKSPACE
+    assert str(size()) in L.fff_last_device_error().decode()
+    assert call(p(8 << 14), size()) == ALIAS and call(p((1 << 14) + 6), size()) == ALIAS
+
+
 def test_bench_probe_library_is_separate_and_checks_its_arguments():
     """The microbenchmarks of bench.py live in a library of their own: the product ABI exports none
     of them, and the probe library rejects bad arguments on the host."""

@@ -64,48 +64,129 @@ def test_which_calls_take_it(T, D, O, depth, L, dtype, expect):
     assert F.fff_get_option("last_path") == expect, F.fff_last_launch()
 
 
-def test_without_a_workspace_the_fused_launch_runs():
-    """A call whose other route is the fused launch, which needs no workspace, still needs none: captured where the library's would have to
-    grow, or with a caller's that is too short, it is the fused launch, with the same bits."""
+def _deep():
+    """A call that the fused launch would take, and whose tables outgrow the L2s: its arguments and its output."""
     import torch
-    import paper_2308_14711_amd as F
-    print("\n[case] grouped walk without workspace T=16385 D=4096 depth=14 L=3 bf16", flush=True)
     g0 = torch.Generator(device="cuda").manual_seed(73)
     new = lambda *s: torch.empty(s, device="cuda").uniform_(-.05, .05, generator=g0).to(torch.bfloat16)
     T, D, depth, L, n = 16385, 4096, 14, 3, 1 << 14
     args = (new(T, D), new(n - 1, D), new(n - 1), new(n, L, D), new(n, L), new(n, L, D), new(n, D), depth, L, W.ACT_GELU)
-    ref, out = (torch.zeros((T, D), dtype=torch.bfloat16, device="cuda") for _ in range(2))
-    F.fff_forward_hard(*args, ref)
+    return args, torch.full((T, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+
+
+def test_in_the_place_of_the_fused_launch_the_workspace_is_left_alone():
+    """The fused launch needs no memory.  What takes its place neither grows the library's workspace nor works in it or in the caller's, so
+    that a captured graph of such a call holds neither: it has scratch of torch's, and calls through the C ABI that bring none are fused.  The same
+    bits each way."""
+    import ctypes
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] grouped walk without workspace T=16385 D=4096 depth=14 L=3 bf16", flush=True)
+    args, ref = _deep()
+    T, D = ref.shape
+    depth, L = args[7:9]
+    out = torch.full_like(ref, float("nan"))
+    same = lambda: torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    F.fff_set_option("path", 1)
+    try:
+        F.fff_forward_hard(*args, ref)
+    finally:
+        F.fff_set_option("path", 0)
     torch.cuda.synchronize()
-    assert F.fff_get_option("last_path") in (1, 6)
-    taken = F.fff_get_option("last_path") == 6
-    buf = torch.empty(256, dtype=torch.uint8, device="cuda")
-    F.fff_set_workspace(buf)
+    F.fff_release_workspace()
+    F.fff_debug_option("fail_workspace_growth", 1)          # (a call that grows it uses this up)
     try:
         F.fff_forward_hard(*args, out)
         torch.cuda.synchronize()
-        assert F.fff_get_option("last_path") == 1 and torch.equal(out.view(torch.int16), ref.view(torch.int16))
+        assert F.fff_debug_option("fail_workspace_growth") == 1 and F.fff_get_option("last_path") == 6 and same()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            F.fff_forward_hard(*args, out)
+        assert F.fff_get_option("last_path") == 6
+        p = lambda t: ctypes.c_void_p(t.data_ptr())
+        raw = [p(t) for t in args[:7]] + [depth, L, W.ACT_GELU, p(out), None, None, T, D, D, W.DTYPE_BF16]
+        call = lambda entry, *more: (out.fill_(float("nan")), entry(*raw, *more), torch.cuda.synchronize())[1]
+        need = F.fff_hard_scratch_bytes(T, D, D, depth, L, W.DTYPE_BF16)
+        scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
+        lib = F.lib()
+        for entry, more, path in ((lib.fff_forward_hard, (), 1), (lib.fff_forward_hard_scratch, (None, 0), 1),
+                                  (lib.fff_forward_hard_scratch, (p(scratch), need), 6), (lib.fff_forward_hard_static, (), 1)):
+            assert call(entry, *more) == 0 and F.fff_get_option("last_path") == path and same()
+        assert F.fff_debug_option("fail_workspace_growth") == 1
     finally:
-        F.fff_set_workspace(None)
-    F.fff_release_workspace()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
-        F.fff_forward_hard(*args, out)
-    assert F.fff_get_option("last_path") == 1
-    F.fff_reserve_workspace(T, depth)
-    again = torch.cuda.CUDAGraph()
-    out2 = torch.zeros_like(out)
-    with torch.cuda.graph(again):
-        F.fff_forward_hard(*args, out2)
-    assert F.fff_get_option("last_path") == (6 if taken else 1)
-    for _ in range(3):
-        for g, o in ((graph, out), (again, out2)):
-            o.zero_()
-            g.replay()
+        F.fff_debug_option("fail_workspace_growth", 0)
+    buf = torch.full((F.fff_workspace_bytes(T, depth),), 77, dtype=torch.uint8, device="cuda")
+    for b in (buf[:256], buf):                              # too short for a layer that needs it, and large enough
+        F.fff_set_workspace(b)
+        try:
+            out.fill_(float("nan"))
+            F.fff_forward_hard(*args, out)
             torch.cuda.synchronize()
-            assert torch.equal(o.view(torch.int16), ref.view(torch.int16))
-    out.zero_()
-    F.fff_forward_hard_static(*args, out)
+            assert F.fff_get_option("last_path") == 6 and same()
+            with torch.cuda.graph(torch.cuda.CUDAGraph()):
+                F.fff_forward_hard(*args, out)
+            assert F.fff_get_option("last_path") == 6
+        finally:
+            F.fff_set_workspace(None)
+    assert (buf[256:] == 77).all()
+    for _ in range(3):
+        out.fill_(float("nan"))
+        scribble = [torch.full((1 << 20,), 255, dtype=torch.uint8, device="cuda") for _ in range(8)]     # eager work between the replays
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same()
+        del scribble
+
+
+def test_streams_other_captures_and_no_memory():
+    """Overlapping calls on several streams have scratch of their own; a stream that is captured by other means than torch's graphs, whose
+    replays would work in memory of a later owner, and a full device get the fused launch."""
+    import ctypes
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] grouped walk on four streams, captured outside torch, out of memory T=16385 D=4096 depth=14 L=3 bf16", flush=True)
+    args, ref = _deep()
+    F.fff_forward_hard(*args, ref)
+    torch.cuda.synchronize()
+    assert F.fff_get_option("last_path") == 6
+    streams, outs = [torch.cuda.Stream() for _ in range(4)], [torch.full_like(ref, float("nan")) for _ in range(4)]
+    torch.cuda.synchronize()
+    for rep in range(2):
+        for s, o in zip(streams, outs):
+            F.fff_forward_hard(*args, o, None, s)
+            assert F.fff_get_option("last_path") == 6
+    torch.cuda.synchronize()
+    assert all(torch.equal(o.view(torch.int16), ref.view(torch.int16)) for o in outs)
+    out, side = outs[0], streams[0]
+    hip = ctypes.CDLL("libamdhip64.so")
+    s, graph, execution = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(s, 1) == 0                  # thread-local
+    try:
+        F.fff_forward_hard(*args, out, None, side)
+    finally:
+        ended = hip.hipStreamEndCapture(s, ctypes.byref(graph))
+    assert ended == 0 and F.fff_get_option("last_path") == 1
+    assert hip.hipGraphInstantiate(ctypes.byref(execution), graph, None, None, ctypes.c_size_t(0)) == 0
+    for _ in range(3):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(execution, s) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    assert hip.hipGraphExecDestroy(execution) == 0 and hip.hipGraphDestroy(graph) == 0
+    out.fill_(float("nan"))
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    try:
+        keep = []
+        try:                                                     # what the allocator still holds free
+            while True:
+                keep.append(torch.empty(1 << 19, dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            pass
+        F.fff_forward_hard(*args, out)
+        assert F.fff_get_option("last_path") == 1
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
-    assert taken
