@@ -258,6 +258,11 @@ bool staged_shape_ok(const Problem& p) {
     return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.L <= 64;
 }
 
+bool grouped_shape_ok(const Problem& p) {
+    return fused_shape_ok(p) && p.depth >= 2 && p.T >= 1 && p.T <= 131072 && vec_ok(p.out, p.O, p.bf16) && vec_ok(p.leaf_w2, p.O, p.bf16) &&
+           vec_ok(p.leaf_b2, p.O, p.bf16);
+}
+
 enum { kPathAuto = 0, kPathFused = 1, kPathStaged = 2, kPathGeneric = 3, kPathToken = 4, kPathSplit = 5, kPathGrouped = 6, kPathWave = 7 };
 
 // One launch that keeps the token row in registers from the root to the output
@@ -270,6 +275,7 @@ int choose_path(const Problem& p) {
     if (g_opt.path == kPathToken && token_ok) return kPathToken;
     if (g_opt.path == kPathSplit && split_ok) return kPathSplit;
     if (g_opt.path == kPathWave && wave_shape_ok(p)) return kPathWave;
+    if (g_opt.path == kPathGrouped && grouped_shape_ok(p)) return kPathGrouped;
     if (g_opt.path == kPathFused && fused_ok) return kPathFused;
     if (g_opt.path == kPathStaged && staged_ok) return kPathStaged;
     if (g_opt.path == kPathGeneric) return kPathGeneric;
@@ -607,11 +613,6 @@ bool block_cut(const Problem& p, const WideNodes& wide, BlockCut* cut) {
 // How many levels the grouped walk goes through before it groups (of 5 .. 9 the best on average for every row length, +- 1 %).
 constexpr int kGroupLevel = 6;
 
-bool grouped_shape_ok(const Problem& p) {
-    return fused_shape_ok(p) && p.depth >= 2 && p.T >= 1 && p.T <= 131072 && vec_ok(p.out, p.O, p.bf16) && vec_ok(p.leaf_w2, p.O, p.bf16) &&
-           vec_ok(p.leaf_b2, p.O, p.bf16);
-}
-
 // The sizes whose time the estimates below were fitted to.
 bool walk_grouped_range(const Problem& p) {
     const int64_t row = p.D * (p.bf16 ? 2 : 4);
@@ -631,7 +632,6 @@ bool walk_grouped_range(const Problem& p) {
 // 9 % for the grouped walk and 13 % for the others): of the 1591 calls that the line at 1.05 takes 1.16 times as fast on average, 90
 // more than 5 % slower.  Where the subtree launch has the lower end of the tree it stays ahead.
 bool walk_grouped(const Problem& p, int path) {
-    if (g_opt.path == kPathGrouped) return grouped_shape_ok(p);
     if (g_opt.path != kPathAuto || g_opt.leaf_path != 0 || g_opt.leaf_split != 0 || !g_opt.bucketing || g_subtree != 0) return false;
     if (path != kPathFused && path != kPathSplit && path != kPathStaged) return false;
     if (!walk_grouped_range(p) || (path == kPathStaged && subtree_levels(p, false) >= 0)) return false;
@@ -796,7 +796,18 @@ int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, const W
 // launch needs none, and what takes its place may not allocate, fail or leave an address in a captured graph where that did not.
 int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch, void* walk_scratch = nullptr) {
     const bool marks = fixed_scratch == nullptr;
-    const int path = choose_path(p);
+    int path = choose_path(p);
+    if (path == kPathGrouped) {                                        // (asked for: the fused launch where there is no workspace to be had)
+        Workspace ws;
+        Layout lay;
+        int rc = FFF_OK;
+        if (fixed_scratch) carve(fixed_scratch, layout_for(p.T, p.depth), &ws);
+        else rc = get_workspace(p.T, p.depth, &ws, &lay, s);
+        if (rc == FFF_OK) return run_walk_grouped(p, leaf_idx, s, ws, marks);
+        if (rc != FFF_ERR_WORKSPACE) return rc;
+        g_last_error.clear();
+        path = kPathFused;
+    }
     g_opt.last_path = path == kPathWave ? (int)kPathFused : path;      // (one fused launch, whichever kernel)
     if (path == kPathGeneric) {
         // rows of at least one piece by 16-byte pieces at any element (20011 tokens of 77 features: 7.5 us against 19.8 element by
@@ -820,13 +831,6 @@ int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* f
         hipError_t e = launch_walk_wave(p, leaf_idx, s);
         for (int k = 0; marks && k < 4; ++k) stage_mark(s);
         return e == hipSuccess ? FFF_OK : set_device_error(e, "wave kernel launch");
-    }
-    if (path == kPathFused && g_opt.path == kPathGrouped && walk_grouped(p, path)) {      // (asked for)
-        Workspace ws;
-        Layout lay;
-        if (fixed_scratch) carve(fixed_scratch, layout_for(p.T, p.depth), &ws);
-        if (fixed_scratch || get_workspace(p.T, p.depth, &ws, &lay, s) == FFF_OK) return run_walk_grouped(p, leaf_idx, s, ws, marks);
-        g_last_error.clear();
     }
     if (path == kPathFused) {
         if (marks) stage_mark(s);
@@ -917,7 +921,7 @@ int fff_forward_hard_scratch(const void* x, const void* node_w, const void* node
     }
     Problem p{x, node_w, node_b, leaf_w1, leaf_b1, leaf_w2, leaf_b2, out, leaf_idx,
               T, D, O, depth, leaf_width, act, dtype == FFF_BF16};
-    const bool grouped = scratch && choose_path(p) == kPathFused && g_opt.path == kPathAuto && walk_grouped(p, kPathFused);
+    const bool grouped = scratch && choose_path(p) == kPathFused && walk_grouped(p, kPathFused);
     const size_t need = (size_t)walk_scratch_words(T) * sizeof(int32_t);
     if (grouped && scratch_bytes < need) {
         g_last_error = "the scratch holds " + std::to_string(scratch_bytes) + " bytes, this call needs " + std::to_string(need);
@@ -939,7 +943,7 @@ size_t fff_hard_scratch_bytes(int64_t T, int64_t D, int64_t O, int depth, int le
     if (check_common(depth, T, D, dtype) != FFF_OK || check_leaf(depth, leaf_width, 0, T, D, O) != FFF_OK || T == 0) return 0;
     Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
               T, D, O, depth, leaf_width, 0, dtype == FFF_BF16};
-    return g_opt.path == kPathAuto && walk_grouped_range(p) && choose_path(p) == kPathFused && walk_grouped(p, kPathFused)
+    return walk_grouped_range(p) && choose_path(p) == kPathFused && walk_grouped(p, kPathFused)
                ? (size_t)walk_scratch_words(T) * sizeof(int32_t) : 0;
 }
 

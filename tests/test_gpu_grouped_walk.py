@@ -64,6 +64,30 @@ def test_which_calls_take_it(T, D, O, depth, L, dtype, expect):
     assert F.fff_get_option("last_path") == expect, F.fff_last_launch()
 
 
+@pytest.mark.parametrize("T, D, depth, L, other", [(8200, 768, 12, 1, 5), (9000, 768, 8, 8, 2), (700, 256, 6, 4, 1)], ids=["split", "staged", "medium"])
+def test_asked_for_without_a_workspace_it_is_the_fused_launch(T, D, depth, L, other):
+    """Option path = 6 with a caller's workspace that is too short, whatever launch the sizes take by themselves."""
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] path 6 without a workspace T=%d D=O=%d depth=%d L=%d bf16 seed 74" % (T, D, depth, L), flush=True)
+    w = W.make_layer("grouped_no_ws", T, D, D, depth, L, W.ACT_RELU, W.DTYPE_BF16, seed=74)
+    dev = to_device(w)
+    run_forward(w, dev)
+    assert F.fff_get_option("last_path") == other
+    try:
+        F.fff_set_option("path", 1)
+        out, idx = run_forward(w, dev)
+        F.fff_set_option("path", 6)
+        short = torch.empty(256, dtype=torch.uint8, device="cuda")
+        F.fff_set_workspace(short)
+        got, got_idx = run_forward(w, dev)
+        assert F.fff_get_option("last_path") == 1 and "grouped" not in F.fff_last_launch()
+    finally:
+        F.fff_set_workspace(None)
+        F.fff_set_option("path", 0)
+    assert torch.equal(got, out) and torch.equal(got_idx, idx)
+
+
 def _deep():
     """A call that the fused launch would take, and whose tables outgrow the L2s: its arguments and its output."""
     import torch
