@@ -258,6 +258,16 @@ bool staged_shape_ok(const Problem& p) {
     return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.L <= 64;
 }
 
+int64_t g_subtree = 0;   // debug option "subtree"
+
+// Whether no option picks among the launches of the staged path, the walk kernels or the block-a-token kernels: one that does asks for
+// these launches, and what takes calls from them by itself (a wave a token, the grouped walk) stands aside.
+bool launches_by_default() {
+    const WalkTuning& w = g_walk_tuning;
+    return g_opt.path == 0 && g_opt.leaf_path == 0 && g_opt.leaf_split == 0 && g_opt.bucketing && g_opt.bucket_kernel == 0 && g_subtree == 0 &&
+           g_token_kernel == 0 && !w.tpg && !w.block && !w.top && !w.bpc && !w.prefetch && !w.plain_x;
+}
+
 bool grouped_shape_ok(const Problem& p) {
     return fused_shape_ok(p) && p.depth >= 2 && p.T >= 1 && p.T <= 131072 && vec_ok(p.out, p.O, p.bf16) && vec_ok(p.leaf_w2, p.O, p.bf16) &&
            vec_ok(p.leaf_b2, p.O, p.bf16);
@@ -295,7 +305,7 @@ int choose_path(const Problem& p) {
         // (token block / element-wise: 2181 tokens of 9 bf16 features, 168 neurons 94 / 62; 1161 of 11, 116 neurons 39 / 43)
         token_limit = 3 * g_opt.token_max_T;
     }
-    if (g_opt.path == kPathAuto && p.T > g_opt.token_max_T && wave_better(p)) return kPathWave;
+    if (p.T > g_opt.token_max_T && launches_by_default() && wave_better(p)) return kPathWave;
     if (g_opt.path == kPathAuto && token_ok && p.T <= token_limit) return kPathToken;
     // Whole rows of leaves wider than the staged path takes go one block a token at any batch size: their alternative is the
     // element-wise kernel (4312 tokens of 464 bf16 features, 240 neurons: 391 us against 168).  Not so rows of other
@@ -404,8 +414,6 @@ int run_bucket(const int32_t* leaf_idx, int64_t T, int depth, const Workspace& w
         return set_device_error(e, "bucket kernel launch");
     return FFF_OK;
 }
-
-int64_t g_subtree = 0;   // debug option "subtree"
 
 // How many of the last levels the subtree launch takes; -1: whole descent and leaf kernels.
 //
@@ -632,8 +640,7 @@ bool walk_grouped_range(const Problem& p) {
 // 9 % for the grouped walk and 13 % for the others): of the 1591 calls that the line at 1.05 takes 1.16 times as fast on average, 90
 // more than 5 % slower.  Where the subtree launch has the lower end of the tree it stays ahead.
 bool walk_grouped(const Problem& p, int path) {
-    if (g_opt.path != kPathAuto || g_opt.leaf_path != 0 || g_opt.leaf_split != 0 || !g_opt.bucketing || g_subtree != 0) return false;
-    if (path != kPathFused && path != kPathSplit && path != kPathStaged) return false;
+    if (!launches_by_default() || (path != kPathFused && path != kPathSplit && path != kPathStaged)) return false;
     if (!walk_grouped_range(p) || (path == kPathStaged && subtree_levels(p, false) >= 0)) return false;
     const int64_t es = p.bf16 ? 2 : 4;
     const double T = (double)p.T, node = 1e-6 * (double)(p.D * es), leaf = 1e-6 * (double)((p.L * (p.D + p.O) + p.O) * es);    // MB

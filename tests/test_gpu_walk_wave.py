@@ -90,3 +90,31 @@ def test_which_calls_take_it(T, D, O, L, dtype, expect):
     F.fff_forward_hard(new(T, D), new(n - 1, D), new(n - 1), new(n, L, D), new(n, L), new(n, L, O), new(n, O), depth, L, W.ACT_RELU, new(T, O))
     torch.cuda.synchronize()
     assert ("walk_wave_kernel" in F.fff_last_launch()) == expect, F.fff_last_launch()
+
+
+# option, value, T, L: an option that picks among the launches of another path, and what the call's launches are named then
+OTHERS = [
+    ("leaf_path", 1, 4000, 16, "leaf_gather_kernel"), ("leaf_path", 2, 4000, 16, "leaf_hidden_kernel"), ("bucketing", 0, 4000, 16, "leaf_gather_kernel"),
+    ("bucket_kernel", 3, 4000, 16, "bucket_hist_kernel"), ("leaf_split", 4, 4000, 16, "leaf_gather_kernel"), ("subtree", 2, 4000, 16, "subtree_kernel"),
+    ("subtree", 1, 4000, 16, "leaf_hidden_kernel"), ("token_kernel", 2, 2000, 16, "token_rows_kernel"), ("walk_top", 1, 4000, 4, "walk_kernel"),
+    ("walk_bpc", 2, 4000, 4, "walk_kernel"), ("walk_tpg", 1, 4000, 4, "walk_kernel"),
+]
+
+
+@pytest.mark.parametrize("option, value, T, L, name", OTHERS, ids=["%s%d" % o[:2] for o in OTHERS])
+def test_options_of_the_other_launches_reach_them(option, value, T, L, name):
+    import paper_2308_14711_amd as F
+    print("\n[case] wave a token, option %s=%d T=%d D=256 O=128 depth=6 L=%d bf16 seed 83" % (option, value, T, L), flush=True)
+    w = W.make_layer("wave_options", T, 256, 128, 6, L, W.ACT_GELU, W.DTYPE_BF16, seed=83)
+    dev = to_device(w)
+    run_forward(w, dev)
+    assert "walk_wave_kernel" in F.fff_last_launch()
+    public = option in ("leaf_path", "bucketing")
+    (F.fff_set_option if public else F.fff_debug_option)(option, value)
+    try:
+        out, idx = run_forward(w, dev)
+        assert "walk_wave_kernel" not in F.fff_last_launch() and name in F.fff_last_launch(), F.fff_last_launch()
+        assert ("bucket" in F.fff_last_launch()) == (L > 8 and T > 3072 and option != "bucketing")
+    finally:
+        (F.fff_set_option if public else F.fff_debug_option)(option, 1 if option == "bucketing" else 0)
+    check_against_oracle(w, out, idx)
