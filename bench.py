@@ -734,6 +734,7 @@ def hard_bench(name, args, np, torch, W, F, headline=True):
 
     alg = algorithmic_bytes(w, ref_idx)
     path_names = {1: "fused", 2: "staged", 3: "generic", 4: "token_block", 5: "split", 6: "grouped"}
+    one_launch = "token_block" if F.fff_get_option("last_path") == 4 else "walk_wave" if kernels.startswith("walk_wave") else "walk_fused"
 
     # per-stage durations: HIP events recorded by the library on the call's stream
     stages = {}
@@ -751,8 +752,8 @@ def hard_bench(name, args, np, torch, W, F, headline=True):
             alg = dict(alg, descent=w.T * w.D * (2 if w.dtype == 1 else 4) + 4 * w.T, walk_grouped=alg["path"])
             names = (("descent", d_ms), ("bucketing", b_ms), ("walk_grouped", l_ms))
         elif single:     # one launch did the whole path: it carries the whole path's bytes
-            alg = dict(alg, walk_fused=alg["path"], token_block=alg["path"])
-            names = ((("token_block" if F.fff_get_option("last_path") == 4 else "walk_fused"), d_ms),)
+            alg = dict(alg, **{one_launch: alg["path"]})
+            names = ((one_launch, d_ms),)
         elif F.fff_get_option("last_leaf_path") == 2:   # the leaf stage ran as two kernels
             names = (("descent", d_ms), ("bucketing", b_ms), ("leaf_hidden", l_ms), ("leaf_output", l2_ms))
         else:
@@ -868,7 +869,7 @@ def hard_bench(name, args, np, torch, W, F, headline=True):
         "config": {"workload": "%s: %s" % (w.name, w.note), "T": w.T, "D": w.D, "O": w.O, "depth": w.depth,
                    "leaf_width": w.leaf_width, "act": "gelu" if w.act else "relu", "buffer_sets": nsets,
                    "seed": 0, "options": args.opt, "force_top": args.force_top,
-                   "launch_path": path_names.get(F.fff_get_option("last_path"), "?"), "kernels": kernels},
+                   "launch_path": "wave" if one_launch == "walk_wave" else path_names.get(F.fff_get_option("last_path"), "?"), "kernels": kernels},
         "roofline": roofline,
         "path": {"alg_bytes": alg["path"], "GBps": round(path_gbs, 1), "frac": round(path_gbs / HBM_PEAK_GBS, 4),
                  "frac_of_copy_ceiling": round(path_gbs / copy_ceiling_once(torch)["GBps"], 4),

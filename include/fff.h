@@ -349,7 +349,7 @@ int fff_release_workspace(void);
  * Read-only, describing the last call: "last_path" (1..6 as above), "last_leaf_path"
  * (1 = gather kernel, 2 = the two tile kernels, 3 = both, each on its share of the tiles, 4 = the launch that
  * takes the last levels of the walk with the leaf: "leaf_path" 0 only),
- * "last_walk_top" (tree levels the descent or fused launch kept in LDS),
+ * "last_walk_top" (tree levels the descent, fused or wave-a-token launch kept in LDS; 0 after an fff_forward_hard without one),
  * "last_block_kernel" (fff_forward_block: 1 = rows of whole aligned 16-byte pieces, 2 = any other rows),
  * "last_block_top" (node levels fff_forward_block kept in LDS).
  * Unknown names or negative values return FFF_ERR_UNSUPPORTED.

@@ -803,6 +803,7 @@ int run_walk_grouped(const Problem& p, int32_t* leaf_idx, hipStream_t s, const W
 // launch needs none, and what takes its place may not allocate, fail or leave an address in a captured graph where that did not.
 int run_forward_hard(const Problem& p, int32_t* leaf_idx, hipStream_t s, void* fixed_scratch, void* walk_scratch = nullptr) {
     const bool marks = fixed_scratch == nullptr;
+    g_walk_tuning.last_top = 0;         // (of this call; a launch that keeps levels in LDS says so)
     int path = choose_path(p);
     if (path == kPathGrouped) {                                        // (asked for: the fused launch where there is no workspace to be had)
         Workspace ws;

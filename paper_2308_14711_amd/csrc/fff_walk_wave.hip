@@ -261,6 +261,7 @@ hipError_t launch_walk_wave(const Problem& p, int32_t* leaf_idx, hipStream_t s) 
     const int64_t widest = p.T <= 8 * cus ? 0 : p.T > 16 * cus ? 14 : row_bytes <= 2048 ? 7 : 28;   // KB
     a.top = 0;
     while (a.top < p.depth && (row_bytes << a.top) <= widest * 1024 && (row_bytes + 4) * ((2 << a.top) - 1) <= 64 * 1024) ++a.top;
+    g_walk_tuning.last_top = a.top;
     const size_t lds_bytes = (size_t)(row_bytes + 4) * (((int64_t)1 << a.top) - 1);
     const bool pieces = vec_ok(p.out, p.O, p.bf16) && vec_ok(p.leaf_w2, p.O, p.bf16) && vec_ok(p.leaf_b2, p.O, p.bf16);
     if (p.bf16) return pieces ? dispatch<true, true>(a, (int)waves, lds_bytes, s) : dispatch<true, false>(a, (int)waves, lds_bytes, s);

@@ -92,6 +92,27 @@ def test_which_calls_take_it(T, D, O, L, dtype, expect):
     assert ("walk_wave_kernel" in F.fff_last_launch()) == expect, F.fff_last_launch()
 
 
+@pytest.mark.parametrize("T, top", [(2000, 0), (4000, 5), (8000, 6)])
+def test_last_walk_top_is_of_this_call(T, top):
+    """Levels in LDS as the kernel's note has them, after a call that kept other ones; 0 after a call that kept none."""
+    import paper_2308_14711_amd as F
+    print("\n[case] wave a token, last_walk_top T=%d D=128 O=40 depth=7 L=3 bf16 seed 84" % T, flush=True)
+    w = W.make_layer("wave_top", T, 128, 40, 7, 3, W.ACT_RELU, W.DTYPE_BF16, seed=84)
+    dev = to_device(w)
+    try:
+        for path, want in ((1, None), (7, top), (1, None), (4, 0)):
+            F.fff_set_option("path", path)
+            run_forward(w, dev)
+            note = F.fff_last_launch()
+            assert ("walk_wave_kernel" in note) == (path == 7)
+            if want is None:
+                want = int(note.split("top=")[1])
+                assert want not in (0, top)
+            assert F.fff_get_option("last_walk_top") == want and (path != 7 or note.endswith("top=%d" % want)), note
+    finally:
+        F.fff_set_option("path", 0)
+
+
 # option, value, T, L: an option that picks among the launches of another path, and what the call's launches are named then
 OTHERS = [
     ("leaf_path", 1, 4000, 16, "leaf_gather_kernel"), ("leaf_path", 2, 4000, 16, "leaf_hidden_kernel"), ("bucketing", 0, 4000, 16, "leaf_gather_kernel"),
