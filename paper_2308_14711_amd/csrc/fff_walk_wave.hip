@@ -212,23 +212,49 @@ bool wave_shape_ok(const Problem& p) {
     return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.D * (p.bf16 ? 2 : 4) <= 512 * 16 && p.L <= kMaxNeurons && p.depth >= 1 && p.depth < 30;
 }
 
-// Where a wave a token is ahead of what else takes a call: lines from 18660 random calls of both sides (128 to 20000 tokens, rows of 32
-// bytes to 8 KB, depth 1 to 14, 1 to 32 neurons).  By tokens a compute unit (up to 2 a block a token is taken):
-//   2 to 4    up to 8 neurons: 1.24 (one neuron, short rows) to 2.3
-//   4 to 8    up to 16 neurons: 1.4 to 2.1; not one or two on rows of up to 512 bytes (0.95 to 1.2)
+// Whether 17 to 32 tokens a compute unit (many: more than 24), leaves of more than 8 neurons, go faster through the staged path's matrix launches.
+// By tokens a leaf, from 4021 such calls (profiles/wave_a_token_calls.csv): 32 neurons from 32 tokens on (0.78 to 1.05; fewer 1.2 and more), in the larger
+// half of the batches 17 to 28 neurons from 64 on (1.01, every third call 0.7 to 0.95), 13 to 16 from 12 on (0.90 to 0.98; 9 to 12 neurons 1.1) and
+// small leaf rows, which the gather kernel finds in L1, from 2 on (1.0); leaf rows of more than 23 KB from 8 on (0.95).
+bool staged_fills_tiles(const Problem& p, bool many, int64_t leaf_rows) {
+    const int64_t per_leaf = p.T >> p.depth, L = p.L;
+    if (L <= 16 && per_leaf >= 8 && per_leaf < 16 && leaf_rows > 23 * 1024) return true;
+    if (many && L >= 16 && leaf_rows < 8192 && per_leaf >= 2) return true;
+    return L > 28 ? per_leaf >= 32 : many && (L > 16 ? per_leaf >= 64 : L > 12 && per_leaf >= 12);
+}
+
+// Where a wave a token is ahead of what else takes a call: lines from 23285 random calls of both sides (513 to 12800 tokens, rows of 64
+// bytes to 8 KB, depth 1 to 14, 1 to 32 neurons; profiles/wave_a_token_calls.csv).  By tokens a compute unit (up to 2 a block a token is taken):
+//   2 to 4    up to 8 neurons: 1.5 (one neuron, short rows) to 2.4
+//   4 to 8    up to 16 neurons: 1.5 to 2.2; not one or two on rows of up to 512 bytes (0.95 to 1.2)
 //   8 to 16   rows of up to 4 KB (beyond, 8 waves are all that a block holds: 0.8 to 0.9) of more than 512 bytes, or 256 from 3 neurons on, or any from 6
-//             on or with output rows that are not whole pieces: 1.1 to 2.1
-//   16 to 32  leaves of more than 8 neurons on rows of up to 2 KB: 1.3 to 1.8 (the staged path's place); 6 to 8 neurons on 512 bytes to 1 KB: 1.2
-//   32 to 48  3 to 8 neurons on 256 bytes to 1 KB: 1.2 to 1.5
+//             on or with output rows that are not whole pieces: 1.2 to 2.1; from 12 on not leaves of up to 8 neurons on rows of up to 256 bytes (1.02, a
+//             tenth of the calls 0.85) or, with output rows that are not whole pieces, less than 3 KB of rows for a token (1.1, every seventh 0.84 to 0.95)
+//   16 to 32  leaves of more than 8 neurons on rows of up to 2 KB: 1.2 to 2.0; 6 to 8 neurons on 512 bytes to 1 KB: 1.16 and more up to 24 tokens (beyond
+//             0.96, but 1.4 with output rows of more than 40 bytes that are not whole pieces).  Not where bf16 tokens fill the tiles of the staged path's
+//             matrix launches (staged_fills_tiles: there 0.97 on average, down to 0.56)
+//   32 to 48  3 to 8 neurons on 512 bytes to 1 KB: 1.1 to 1.5; on 256 to 512 with leaf rows of 4 MB together (1.2; less: 0.9 to 1.07); output rows that are
+//             not whole pieces 1.5 from 40 bytes on (shorter ones 1.06, every fourth call 0.85 to 0.95)
+// Element-wise output rows of wide leaves are a trip for 64 elements of four neurons: up to 12 tokens a compute unit a block a token, with four to
+// eight waves for them, is ahead from 7000 weights on (2547 tokens of 32, 32 neurons, 958 outputs 29.7 us, 58.2 here).
+// Of the 23285 calls the lines leave 22180 here, 1.72 times as fast on average, 38 more than 5 % slower, 14 more than 10 %.
 bool wave_better(const Problem& p) {
-    const int64_t cus = device_info().cus, row = p.D * (p.bf16 ? 2 : 4), T = p.T, L = p.L;
-    if (!wave_shape_ok(p)) return false;
+    const int64_t cus = device_info().cus, es = p.bf16 ? 2 : 4, row = p.D * es, out_row = p.O * es, T = p.T, L = p.L;
+    if (!wave_shape_ok(p) || T > 48 * cus) return false;
     const bool pieces = vec_ok(p.out, p.O, p.bf16) && vec_ok(p.leaf_w2, p.O, p.bf16) && vec_ok(p.leaf_b2, p.O, p.bf16);
+    const int64_t leaf_rows = L * (row + out_row) + out_row, met = p.depth * row + leaf_rows;      // bytes of a leaf's rows, of all that a token meets
     if (T <= 4 * cus) return L <= 8;
+    if (T <= 12 * cus && !pieces && L > 8 && L * p.O >= 7000) return false;
     if (T <= 8 * cus) return L <= 16 && (L > 2 || row > 512 || !pieces);
-    if (T <= 16 * cus) return row <= 4096 && L <= 32 && (row > 512 || (row > 256 && L >= 3) || L >= 6 || !pieces);
-    if (T <= 32 * cus) return L > 8 ? L <= 32 && row <= 2048 : L >= 6 && row > 512 && row <= 1024;
-    return T <= 48 * cus && L >= 3 && L <= 8 && row > 256 && row <= 1024;
+    if (T <= 16 * cus) {
+        if (row > 4096 || L > 32 || (T > 12 * cus && L <= 8 && (pieces ? row <= 256 : met < 3000))) return false;
+        return row > 512 || (row > 256 && L >= 3) || L >= 6 || !pieces;
+    }
+    if (T <= 32 * cus) {
+        if (L <= 8) return L >= 6 && row > 512 && row <= 1024 && (T <= 24 * cus || (!pieces && out_row > 40));
+        return L <= 32 && row <= 2048 && !(p.bf16 && pieces && staged_fills_tiles(p, T > 24 * cus, leaf_rows));
+    }
+    return L >= 3 && L <= 8 && row > 256 && row <= 1024 && (pieces ? row > 512 || leaf_rows << p.depth > (int64_t)4 << 20 : out_row > 40);
 }
 
 hipError_t launch_walk_wave(const Problem& p, int32_t* leaf_idx, hipStream_t s) {

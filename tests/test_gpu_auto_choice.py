@@ -22,6 +22,10 @@ SHAPES = [
     (40000,  640,  640,  11, 2,  W.DTYPE_BF16),
     (1500,   768,  768,  8,  4,  W.DTYPE_BF16),
     (30000,  512,  512,  9,  2,  W.DTYPE_F32),
+    # a wave a token against a block a token on element-wise output rows of wide leaves, and against the staged path's full tiles
+    (2547,   32,   958,  5,  32, W.DTYPE_BF16),
+    (6366,   544,  544,  1,  32, W.DTYPE_BF16),
+    (8128,   872,  872,  9,  16, W.DTYPE_BF16),
 ]
 
 

@@ -77,8 +77,19 @@ def test_infinite_weights_and_nan_tokens_stay_with_their_tokens(where):
     (512, 768, 768, 4, W.DTYPE_BF16, False), (513, 768, 768, 8, W.DTYPE_BF16, True), (1024, 768, 768, 9, W.DTYPE_BF16, False),
     (1024, 4096, 4096, 8, W.DTYPE_BF16, True), (2048, 768, 768, 1, W.DTYPE_BF16, True), (2048, 128, 128, 1, W.DTYPE_BF16, False),
     (2048, 768, 768, 16, W.DTYPE_BF16, True), (4096, 2048, 2048, 32, W.DTYPE_BF16, True), (4096, 4096, 4096, 8, W.DTYPE_BF16, False),
-    (4096, 784, 10, 4, W.DTYPE_F32, True), (4097, 768, 768, 1, W.DTYPE_BF16, False), (8192, 256, 256, 16, W.DTYPE_BF16, True),
+    (4096, 784, 10, 4, W.DTYPE_F32, True), (4097, 768, 768, 1, W.DTYPE_BF16, False), (8192, 256, 250, 16, W.DTYPE_BF16, True),
     (12288, 512, 512, 4, W.DTYPE_BF16, True), (12289, 512, 512, 4, W.DTYPE_BF16, False),
+    # bf16 leaves of full tiles go to the staged path's matrix launches, fp32 ones not
+    (8192, 256, 256, 16, W.DTYPE_BF16, False), (8192, 256, 256, 16, W.DTYPE_F32, True), (6144, 256, 256, 16, W.DTYPE_BF16, True),
+    (8192, 256, 256, 12, W.DTYPE_BF16, True), (6144, 256, 256, 24, W.DTYPE_BF16, True), (6145, 256, 256, 24, W.DTYPE_BF16, False),
+    (6144, 256, 256, 32, W.DTYPE_BF16, False),
+    # element-wise output rows of wide leaves: a block a token
+    (2500, 64, 437, 16, W.DTYPE_BF16, True), (2500, 64, 439, 16, W.DTYPE_BF16, False), (3073, 64, 439, 16, W.DTYPE_BF16, True),
+    # short rows
+    (3072, 64, 64, 6, W.DTYPE_BF16, True), (3073, 64, 64, 6, W.DTYPE_BF16, False), (3073, 64, 7, 6, W.DTYPE_BF16, False),
+    (3073, 200, 7, 6, W.DTYPE_BF16, True),
+    (6144, 320, 320, 6, W.DTYPE_BF16, True), (6145, 320, 320, 6, W.DTYPE_BF16, False), (6145, 320, 19, 6, W.DTYPE_BF16, False),
+    (6145, 320, 21, 6, W.DTYPE_BF16, True), (9000, 256, 256, 4, W.DTYPE_BF16, False), (9000, 256, 21, 4, W.DTYPE_BF16, True),
 ])
 def test_which_calls_take_it(T, D, O, L, dtype, expect):
     import torch
