@@ -637,8 +637,11 @@ bool walk_grouped_range(const Problem& p) {
 // skewed) 213 -> 100.  Not so while the tables are small against the rows (the split launch at depth 11: 69 and 71).
 // By estimates in us of the grouped walk and of what the call would take, terms and weights below, fitted to 4300 random calls with
 // uniform and with skewed leaves (8200 to 131072 tokens, rows of 512 bytes to 16 KB, depth 8 to 16; half of the estimates are within
-// 9 % for the grouped walk and 13 % for the others): of the 1591 calls that the line at 1.05 takes 1.16 times as fast on average, 90
-// more than 5 % slower.  Where the subtree launch has the lower end of the tree it stays ahead.
+// 9 % for the grouped walk and 13 % for the others).  The lines are from 7759 further calls of both sides (profiles/grouped_walk_calls.csv): where
+// they lie the two take the same time on average (rows that fill their lanes badly: tiles 1.0 below the line, the others 0.97 to 1.08).  The fused launch keeps
+// less than 40 MB of token rows with fewer than 0.8 tokens a leaf (0.97), the gather kernel rows that fill less than 61 % of the lanes (0.96).  Of the
+// 7110 that the lines leave here, 1.17 times as fast, 218 are more than 5 % slower and 62 more than 10 %, most of them with skewed leaves, which
+// spare the others' caches and which sizes do not tell.  Where the subtree launch has the lower end of the tree it stays ahead.
 bool walk_grouped(const Problem& p, int path) {
     if (!launches_by_default() || (path != kPathFused && path != kPathSplit && path != kPathStaged)) return false;
     if (!walk_grouped_range(p) || (path == kPathStaged && subtree_levels(p, false) >= 0)) return false;
@@ -652,21 +655,25 @@ bool walk_grouped(const Problem& p, int path) {
     const bool wide = p.D * es > 2048;
     const double grouped_term[5] = {1, x, out, x * (p.depth - 6) + leaf_rows, met};
     constexpr double grouped_short[5] = {17.1, 0.348, 0.0207, 0.0493, 0.0599}, grouped_wide[5] = {19.9, 0.414, 0.0257, 0.0402, 0.0864};
+    // lanes past the end of a row wait with the others (rows of 2056 bf16 features, 257 of 512 pieces: 1.23 times the fitted time)
+    const int64_t pieces = p.D * es / 16;
+    int64_t held = 1024;
+    for (const int64_t h : {512, 256, 192, 128, 96, 64}) held = pieces <= h ? h : held;
+    const double filled = (double)pieces / (double)held, waiting = 1 + 0.45 * (1 - filled), least = 0.9 * waiting > 1.05 ? 0.9 * waiting : 1.05;
     const double grouped = weighted(wide ? grouped_wide : grouped_short, grouped_term);
-    double now;
     if (path == kPathStaged) {
         const double term[6] = {1, x, out, x * (p.depth - 5), leaf_rows, met};
         constexpr double gather_short[6] = {16.4, 0, 0.0349, 0.143, 0.0257, 0.187}, gather_wide[6] = {14.1, 0.457, 0.0178, 0.0634, 0.0324, 0.163};
         constexpr double tiles_short[6] = {25, 0.146, 0, 0.0608, 0, 1.04}, tiles_wide[6] = {29.8, 0.671, 0.184, 0, 0.0018, 0.599};
-        now = leaf_tiles_pay(p) ? weighted(wide ? tiles_wide : tiles_short, term) : weighted(wide ? gather_wide : gather_short, term);
-    } else {
-        const double rows = x * (p.depth - 5) + leaf_rows, beyond = log2(met / 4);
-        const double term[6] = {1, x, out, rows, rows * (beyond < 0 ? 0 : beyond > 4 ? 4 : beyond), met};
-        constexpr double fused_short[6] = {7.56, 0.176, 0, 0.0615, 0.0037, 0.0551}, fused_wide[6] = {9.35, 0.148, 0.0916, 0.0699, 0.0023, 0.0606};
-        constexpr double split_short[6] = {9.06, 0.159, 0.0822, 0.0589, 0.0029, 0.0503}, split_wide[6] = {14.8, 0.153, 0.0887, 0.0527, 0.0036, 0.0723};
-        now = path == kPathFused ? weighted(wide ? fused_wide : fused_short, term) : weighted(wide ? split_wide : split_short, term);
+        if (leaf_tiles_pay(p)) return weighted(wide ? tiles_wide : tiles_short, term) > (10 * p.O < 7 * p.D ? 1.12 : 1.05) * waiting * grouped;
+        return !(p.depth <= 12 && filled <= 0.61 && p.L > 3) && weighted(wide ? gather_wide : gather_short, term) > least * grouped;
     }
-    return now > 1.05 * grouped;
+    const double rows = x * (p.depth - 5) + leaf_rows, beyond = log2(met / 4);
+    const double term[6] = {1, x, out, rows, rows * (beyond < 0 ? 0 : beyond > 4 ? 4 : beyond), met};
+    constexpr double fused_short[6] = {7.56, 0.176, 0, 0.0615, 0.0037, 0.0551}, fused_wide[6] = {9.35, 0.148, 0.0916, 0.0699, 0.0023, 0.0606};
+    constexpr double split_short[6] = {9.06, 0.159, 0.0822, 0.0589, 0.0029, 0.0503}, split_wide[6] = {14.8, 0.153, 0.0887, 0.0527, 0.0036, 0.0723};
+    if (path == kPathSplit) return weighted(wide ? split_wide : split_short, term) > least * grouped;
+    return !(x < 40 && T < 0.8 * leaves) && weighted(wide ? fused_wide : fused_short, term) > least * grouped;
 }
 
 // Scratch of the grouped launches, in words: node reached (twice), grouped order, mean and deviation of T tokens, group offsets, counts.

@@ -26,6 +26,9 @@ SHAPES = [
     (2547,   32,   958,  5,  32, W.DTYPE_BF16),
     (6366,   544,  544,  1,  32, W.DTYPE_BF16),
     (8128,   872,  872,  9,  16, W.DTYPE_BF16),
+    # the grouped walk against the tile kernels, with rows that fill half of its lanes
+    (12753,  2080, 2080, 8,  6,  W.DTYPE_BF16),
+    (14111,  2272, 2272, 9,  8,  W.DTYPE_BF16),
 ]
 
 

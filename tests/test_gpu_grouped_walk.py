@@ -51,6 +51,10 @@ def test_same_bits_as_the_fused_launch(case, node_b):
     (30000, 360, 360, 13, 4, W.DTYPE_F32, 6),        # of the staged path's gather kernel
     (30000, 768, 768, 8, 8, W.DTYPE_BF16, 2),        # not of its subtree launch
     (8192, 1024, 1024, 13, 4, W.DTYPE_BF16, 1),      # up to 32 tokens a compute unit: fused
+    (12753, 2080, 2080, 8, 6, W.DTYPE_BF16, 2),      # rows that fill half of the lanes stay with the tile kernels,
+    (13000, 2080, 2080, 11, 8, W.DTYPE_BF16, 2),     # with the gather kernel
+    (13000, 2104, 2104, 11, 2, W.DTYPE_BF16, 5),     # and with the split launch
+    (9000, 2048, 2048, 14, 8, W.DTYPE_BF16, 1),      # few token rows, fewer than leaves: fused
 ])
 def test_which_calls_take_it(T, D, O, depth, L, dtype, expect):
     import torch
