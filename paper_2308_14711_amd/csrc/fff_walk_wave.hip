@@ -207,9 +207,11 @@ template <bool BF16, bool PIECES> hipError_t dispatch(const WaveArgs& a, int wav
 
 }  // namespace
 
-// Whole aligned token, node and input weight rows of up to 512 pieces; output rows may be anything.
+// Whole aligned token, node and input weight rows of up to 512 pieces; output rows of any alignment, of at most 2^30 elements (the kernel's
+// positions in a row are 32 bits, and a wave looks 64 units ahead).
 bool wave_shape_ok(const Problem& p) {
-    return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.D * (p.bf16 ? 2 : 4) <= 512 * 16 && p.L <= kMaxNeurons && p.depth >= 1 && p.depth < 30;
+    return walk_shape_ok(p) && vec_ok(p.leaf_w1, p.D, p.bf16) && p.D * (p.bf16 ? 2 : 4) <= 512 * 16 && p.L <= kMaxNeurons && p.depth >= 1 && p.depth < 30 &&
+           p.O <= (int64_t)1 << 30;
 }
 
 // Whether 17 to 32 tokens a compute unit (many: more than 24), leaves of more than 8 neurons, go faster through the staged path's matrix launches.

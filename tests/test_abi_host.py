@@ -176,6 +176,22 @@ def test_hard_scratch_is_checked_on_the_host(L):
     assert call(p(8 << 14), size()) == ALIAS and call(p((1 << 14) + 6), size()) == ALIAS
 
 
+def test_output_rows_beyond_32_bit_positions_do_not_take_a_wave_a_token(L):
+    """walk_wave_kernel counts a row's positions in 32 bits.  Where there is no device a call ends at its launch, whose name stays."""
+    import torch
+    import paper_2308_14711_amd as F
+    if torch.cuda.is_available():
+        pytest.skip("the addresses are made up: only where nothing can run")
+    p = lambda i: ctypes.c_void_p(i << 41)
+    F.fff_set_option("path", 7)
+    try:
+        for O, wave in ((1 << 30, True), ((1 << 30) + 1, False), ((1 << 31) + 8, False), (1 << 32, False)):
+            assert L.fff_forward_hard(*[p(i) for i in range(1, 8)], 1, 1, 0, p(8), None, None, 1, 8, O, 1) == 7      # FFF_ERR_DEVICE
+            assert ("walk_wave_kernel" in F.fff_last_launch()) == wave, (O, F.fff_last_launch())
+    finally:
+        F.fff_set_option("path", 0)
+
+
 def test_bench_probe_library_is_separate_and_checks_its_arguments():
     """The microbenchmarks of bench.py live in a library of their own: the product ABI exports none
     of them, and the probe library rejects bad arguments on the host."""
