@@ -39,6 +39,8 @@ CASES = [
     ("whole",      1500, 1024, 1040, 9,     1, 5,  GELU, BF16,  True,  False, 2),        # output rows of more than 1024: rows in three parts
     ("whole_two",  1300, 136,  1032, 8,     8, 4,  RELU, BF16,  True,  False, 2),        # the same, levels in two launches, an odd stage
     ("whole_one",  65,   8,    1032, 2,     1, 1,  GELU, BF16,  True,  False, 1),
+    ("stages2",    700,  128,  128,  4,     3, 4,  GELU, BF16,  True,  True,  1),        # two and three whole stages, nothing behind them
+    ("stages3",    700,  192,  192,  5,     2, 6,  RELU, BF16,  True,  True,  2),
     ("plain",      1100, 2056, 40,   5,     3, 6,  RELU, BF16,  False, False, 2),        # no normalisation: rows of any length
     ("f32",        1300, 512,  512,  6,     4, 8,  GELU, F32,   True,  True,  1),
     ("f32_two",    1200, 100,  68,   9,     2, 3,  RELU, F32,   True,  False, 2),        # 100 features: three pieces and a quarter of a stage

@@ -7,7 +7,7 @@ from fff_testlib import check_against_oracle, run_forward, to_device
 
 pytestmark = pytest.mark.gpu
 
-# T, D, O, depth, L, dtype: rows of 1, 4, 6, 8 pieces a lane of 16 and 4, 8, 16 of 64, whole and checked ones; a tile holds 32 tokens
+# T, D, O, depth, L, dtype: rows of 4, 6, 8 pieces a lane of 16 and 3, 4, 8, 16 of 64, whole and checked ones; a tile holds 32 tokens
 # (16 lanes each), 8 or 4: one more, one less, a single token
 CASES = [
     (1, 768, 768, 7, 1, W.DTYPE_BF16), (31, 512, 512, 2, 3, W.DTYPE_BF16), (33, 768, 768, 8, 2, W.DTYPE_BF16),
@@ -15,6 +15,8 @@ CASES = [
     (4097, 1800, 600, 9, 1, W.DTYPE_BF16), (7, 4096, 4096, 8, 4, W.DTYPE_BF16), (3001, 4000, 4000, 9, 3, W.DTYPE_BF16),
     (515, 8192, 2048, 8, 2, W.DTYPE_BF16), (1030, 384, 384, 10, 8, W.DTYPE_F32), (517, 1024, 1000, 8, 1, W.DTYPE_F32),
     (130, 2000, 500, 7, 2, W.DTYPE_F32), (5, 4096, 4096, 7, 1, W.DTYPE_F32),
+    (7, 1032, 1032, 7, 2, W.DTYPE_BF16), (1001, 1528, 768, 9, 1, W.DTYPE_BF16), (9, 1536, 1536, 8, 3, W.DTYPE_BF16),     # 129, 191, 192 pieces
+    (9, 764, 764, 8, 4, W.DTYPE_F32), (1030, 768, 768, 9, 1, W.DTYPE_F32),
 ]
 
 

@@ -363,17 +363,25 @@ def test_descend_and_leaf_stages():
     assert err.max() <= 2e-2
 
 
-@pytest.mark.parametrize("opt", [("bucketing", 0), ("path", 1), ("path", 2), ("path", 3), ("path", 4), ("path", 5),
-                                 ("leaf_path", 1)])
+# an option, and the kernels that a call's launches are named by then (the options of the leaf stage on the staged path)
+ALTERNATIVES = {("bucketing", 0): "descent + leaf_gather", ("path", 1): "fused", ("path", 2): "bucket", ("path", 3): "generic", ("path", 4): "token_",
+                ("path", 5): "leaf_slices", ("path", 6): "grouped", ("path", 7): "walk_wave", ("leaf_path", 1): "bucket + leaf_gather"}
+
+
+@pytest.mark.parametrize("opt", ALTERNATIVES, ids=["%s-%d" % o for o in ALTERNATIVES])
 def test_alternative_paths_agree_with_the_oracle(opt):
     import paper_2308_14711_amd as F
     w = W.make_layer("paths", 2000, 256, 128, 6, 4, W.ACT_GELU, W.DTYPE_BF16, seed=9)
     old = F.fff_get_option(opt[0])
+    F.fff_set_option("path", 2)
     F.fff_set_option(*opt)
     try:
         out, idx = run_forward(w)
     finally:
         F.fff_set_option(opt[0], old)
+        F.fff_set_option("path", 0)
+    launches = F.fff_last_launch()
+    assert all(name in launches for name in ALTERNATIVES[opt].split(" + ")) and ("bucket" in launches) == (opt in (("path", 2), ("path", 6), ("leaf_path", 1)))
     _log("paths %s" % (opt,), check_against_oracle(w, out, idx))
 
 
@@ -393,6 +401,8 @@ TILE_SIZES = [
     ("w768_rounds",    40000, 768,  256, 7,     1, W.DTYPE_BF16),
     ("w1024_small",    5000,  1024, 256, 6,     2, W.DTYPE_BF16),
     ("w1024_large",    9000,  1024, 1024, 6,    2, W.DTYPE_BF16),
+    ("w1536_large",    9000,  1536, 1536, 6,    2, W.DTYPE_BF16),      # three pieces a lane of a wave, several rounds
+    ("f32_w760_large", 9000,  760,  768, 7,     3, W.DTYPE_F32),
     ("f32_w64_large",  17000, 64,   16,  6,     2, W.DTYPE_F32),
     ("f32_w256_small", 4000,  256,  64,  7,     3, W.DTYPE_F32),
 ]

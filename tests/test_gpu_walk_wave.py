@@ -37,6 +37,56 @@ def test_against_the_oracle(case, act):
     assert torch.equal(out, again)
 
 
+@pytest.mark.parametrize("dtype", [W.DTYPE_BF16, W.DTYPE_F32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("moved", ["out", "leaf_w2", "leaf_b2"])
+def test_output_rows_off_a_piece(moved, dtype):
+    """Output rows of whole pieces whose tensors start one element behind a 16-byte boundary: stored and read element by element, and
+    nothing beside them is touched."""
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] wave a token, %s off a boundary T=1500 D=O=256 depth=6 L=3 dtype=%d seed 85" % (moved, dtype), flush=True)
+    w = W.make_layer("wave_off", 1500, 256, 256, 6, 3, W.ACT_GELU, dtype, seed=85)
+    dev = to_device(w)
+    dev["out"] = torch.full((w.T, w.O), 7.0, dtype=dev["x"].dtype, device="cuda")
+    room = torch.full((dev[moved].numel() + 9,), 7.0, dtype=dev["x"].dtype, device="cuda")
+    dev[moved] = room[1:-8].view(dev[moved].shape).copy_(dev[moved])
+    assert dev[moved].data_ptr() % 16 != 0
+    idx = torch.empty((w.T,), dtype=torch.int32, device="cuda")
+    for path in (7, 0):
+        F.fff_set_option("path", path)
+        try:
+            F.fff_forward_hard(dev["x"], dev["node_w"], dev["node_b"], dev["leaf_w1"], dev["leaf_b1"], dev["leaf_w2"], dev["leaf_b2"], w.depth,
+                               w.leaf_width, w.act, dev["out"], idx)
+        finally:
+            F.fff_set_option("path", 0)
+        torch.cuda.synchronize()
+        assert "walk_wave_kernel" in F.fff_last_launch() and "elements" in F.fff_last_launch()
+        check_against_oracle(w, dev["out"], idx)
+        assert (room[:1] == 7).all() and (room[-8:] == 7).all()
+
+
+def test_captured_and_replayed():
+    import torch
+    import paper_2308_14711_amd as F
+    print("\n[case] wave a token, captured T=2048 D=O=768 depth=11 L=1 bf16 seed 86", flush=True)
+    w = W.make_layer("wave_graph", 2048, 768, 768, 11, 1, W.ACT_GELU, W.DTYPE_BF16, seed=86)
+    dev = to_device(w)
+    ref, ref_idx = run_forward(w, dev)
+    assert "walk_wave_kernel" in F.fff_last_launch()
+    out, idx = torch.empty_like(ref), torch.empty_like(ref_idx)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        F.fff_forward_hard(dev["x"], dev["node_w"], dev["node_b"], dev["leaf_w1"], dev["leaf_b1"], dev["leaf_w2"], dev["leaf_b2"], w.depth,
+                           w.leaf_width, w.act, out, idx)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        idx.fill_(-1)
+        again, _ = run_forward(w, dev)                      # eager work between the replays
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(idx, ref_idx) and torch.equal(again, ref)
+
+
 @pytest.mark.parametrize("where", ["leaf_w1", "node_w"])
 def test_infinite_weights_and_nan_tokens_stay_with_their_tokens(where):
     """Lanes past a row multiply nothing: an infinite last weight (of one leaf's neuron, or of a node) reaches the tokens that meet it and

@@ -65,12 +65,13 @@ def test_static_scratch_entry_matches_the_allocating_one():
         finally:
             F.fff_set_option("path", 0)
             F.fff_debug_option("bucket_kernel", 0)
-    # 5. shapes that take one launch and no scratch at all go through the same entry point
-    print("\n[case] static scratch, fused launch: T=3000 D=256 O=128 depth=6 L=4 bf16 seed 45", flush=True)
-    w = W.make_layer("static_e", 3000, 256, 128, 6, 4, W.ACT_GELU, W.DTYPE_BF16, seed=45)
-    out, idx, path, kernels = _both(F, w)
-    assert path == 1
-    check_against_oracle(w, out, idx)
+    # 5. shapes that take one launch and no scratch at all go through the same entry point: a wave a token, fused
+    for T, L, kernel in ((3000, 4, "walk_wave_kernel"), (20011, 2, ",fused,")):
+        print("\n[case] static scratch, one launch: T=%d D=256 O=128 depth=6 L=%d bf16 seed 45" % (T, L), flush=True)
+        w = W.make_layer("static_e", T, 256, 128, 6, L, W.ACT_GELU, W.DTYPE_BF16, seed=45)
+        out, idx, path, kernels = _both(F, w)
+        assert path == 1 and kernel in kernels and "+" not in kernels, kernels
+        check_against_oracle(w, out, idx)
     # 6. beyond the array: an error before anything is enqueued
     T, depth = 600000, 10
     assert F.fff_workspace_bytes(T, depth) > F.fff_static_scratch_bytes()
