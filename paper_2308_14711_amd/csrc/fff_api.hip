@@ -631,7 +631,7 @@ bool walk_grouped_range(const Problem& p) {
 //
 // Below the top levels every token of the fused launch wants rows of its own, and once the tables outgrow an L2 most of them come from
 // memory (16384 tokens, 4096-wide, depth 15, 4 neurons, skewed: 1636 MB moved, 236 us).  Tokens of one subtree that run on one XCD at
-// the same time find them in its L2, and a row that both tokens of a wave want is fetched once (850 MB, 217 us); the price is a second
+// the same time find them in its L2, and a row that both tokens of a wave want is fetched once (861 MB, 217 us); the price is a second
 // read of the token rows and two launches more.  In the place of the split launch (65536 tokens, 768-wide, one neuron, depth 13) 101
 // -> 86 us; of the staged path with more leaves than its fast bucketing takes (58703 fp32 tokens, 360-wide, depth 13, 4 neurons,
 // skewed) 213 -> 100.  Not so while the tables are small against the rows (the split launch at depth 11: 69 and 71).

@@ -126,10 +126,10 @@ __global__ __launch_bounds__(256) void leaf_gather_kernel(
 // 64 pieces, a wave beyond), which hold its row as pieces at any element (load_any), and goes from the root
 // to its output row in one launch.
 //
-// Bound by the chain of trips to the caches, one a level and two in the leaf, and by how many tokens walk at once: with 16 lanes a
-// token four of them share a wave, so that 20000 tokens are resident together, where a wave per token with element-wise loads
-// (fused_generic_kernel) took two and a half rounds of longer trips (20011 tokens of 77 bf16 features, depth 6, 4 neurons, 9 outputs:
-// 19.8 -> 7.5 us a call).  The elements a last window repeats, and whole
+// Bound by the rows through the L1s, at any element: 20011 tokens of 77 bf16 features, depth 6, 4 neurons, 9 outputs are 13200 accesses a
+// compute unit, and the L1s' address units are busy for 10900 of the kernel's 17500 cycles (two levels a trip, a row more for each: 7.5 -> 8.7 us).
+// With 16 lanes a token four of them share a wave, so that 20000 tokens are resident together, where a wave per token with element-wise loads
+// (fused_generic_kernel) took two and a half rounds of longer trips (the same tokens: 19.8 -> 7.5 us a call).  The elements a last window repeats, and whole
 // pieces past the row, are zeros on both sides of a product: an infinite weight or feature counts once.
 template <bool BF16, int LPT, int NV>
 __global__ __launch_bounds__(256) void fused_rows_kernel(const Problem p, int32_t* __restrict__ leaf_out, int out_pieces) {

@@ -1,10 +1,10 @@
-// A wave a token, for batches between the block-a-token launches and the streaming ones (up to 32 tokens a compute unit).
+// A wave a token, for batches between the block-a-token launches and the streaming ones (up to 48 tokens a compute unit).
 //
 // Such a batch is a chain of dependent trips to L2, one a level in walk_kernel, whose tiles of 32 tokens also leave most compute
-// units idle.  Here a block holds few tokens (all compute units have a block as soon as there is a token for each), and a trip
+// units idle.  Here a block holds few tokens (4 at least: a block for every compute unit from four tokens a unit on), and a trip
 // takes as much of the chain as the registers hold:
-//   - the rows of the first levels travel to LDS beside the token's own row, one trip for both;
-//   - below them a trip takes two levels: a node's row and those of both its children, which lie side by side in heap order;
+//   - where more than eight tokens a compute unit share them, the rows of the first levels travel to LDS beside the token's own row, one trip for both;
+//   - below them (or from the root) a trip takes two levels: a node's row and those of both its children, which lie side by side in heap order;
 //   - the leaf's first neurons, its biases and its first output weights are requested together.
 // A token's sums are taken over 64 lanes; the activations of a leaf are kept one a lane and evaluated once for all.
 //
@@ -285,7 +285,7 @@ hipError_t launch_walk_wave(const Problem& p, int32_t* leaf_idx, hipStream_t s) 
     if (waves > max_waves(a.nvec <= 256 ? 4 : 8)) waves = max_waves(a.nvec <= 256 ? 4 : 8);
     // Levels kept in LDS: a block of up to eight tokens finds the top rows in L1 and L2 as fast as it would fill LDS with them (5000 random calls
     // of 1024 to 2048 tokens: without 1.01 to 1.12 times as fast as with three levels; 2048 tokens of 768, depth 11: 8.6 -> 8.4 us); more tokens share
-    // more (4096 fp32 ones of 784, depth 6: 12.3 without, 10.4 with four).
+    // more (4096 fp32 ones of 784, depth 6: 1.18 times the time without as with four).
     const int64_t widest = p.T <= 8 * cus ? 0 : p.T > 16 * cus ? 14 : row_bytes <= 2048 ? 7 : 28;   // KB
     a.top = 0;
     while (a.top < p.depth && (row_bytes << a.top) <= widest * 1024 && (row_bytes + 4) * ((2 << a.top) - 1) <= 64 * 1024) ++a.top;
